@@ -183,14 +183,16 @@ hq_status hq_act_quant_int_linear(const void *x, hq_dtype x_dtype, const uint8_t
                                   uint8_t *xq_out, float *x_scale_out, void *stream);
 
 /*
- * Diagnostic: the kernel family that hq_int_conv2d (static_scale = 0) or hq_int_conv2d_static
- * (static_scale = 1) runs for a convolution of this geometry on the current device, for 4-bit
- * (bits = 4) or 8-bit (bits = 8, hq_int_conv2d_i8) codes.  The choice depends on the geometry
- * only, never on y_dtype: the HQ_I32 outputs (raw integer sums) come from the same kernel as the
- * floating-point outputs.  Host logic only; returns a static string: "tile", "tile (stride 2)",
+ * Diagnostic: the size class of a convolution of this geometry on the current device, for hq_int_conv2d
+ * (static_scale = 0) or hq_int_conv2d_static (static_scale = 1) and 4-bit (bits = 4) or 8-bit (bits = 8,
+ * hq_int_conv2d_i8) codes.  It depends on the geometry only, never on y_dtype (the HQ_I32 outputs come from the same
+ * kernel as the floating-point outputs).  Host logic only; returns a static string: "tile", "tile (stride 2)",
  * "wave-split", "activation-resident", "activation-resident-int8 (P pixels)" with P = 256, 128 or 64
  * (the pixel tile of a workgroup; "128 pixels, 4 waves" for the four-wave form), "small-channel-count"
- * (c_in not a multiple of 64), or "unsupported".
+ * (c_in not a multiple of 64), or "unsupported".  The labels are stable and say how a layer of that size is cut
+ * (whole tiles, K ranges shared by waves, an activation tile per workgroup); several classes may run the same kernel:
+ * stride-1 3x3 layers of 4-bit codes with c_in a multiple of 64 run the one that keeps the expanded activation
+ * tile on chip, except the single-slice (c_in = 192) layers of class "wave-split".
  */
 const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in, int c_out, int r, int s,
                                       int stride, int pad, int static_scale, int bits);

@@ -46,38 +46,22 @@ hq_status check_common(const uint8_t *xq, const float *x_scale, const uint8_t *w
     return HQ_OK;
 }
 
-// Which kernel serves a stride-1 convolution.  The choice depends on the shape only, never on the
-// output type: the integer output (the raw sums) comes from the same kernel as the fp output.
-enum ConvKernel { kConvKernelTile = 0, kConvKernelWave = 1, kConvKernelHalo = 2, kConvKernelRes = 3 };
+// Size class of a stride-1 convolution, the label of hq_int_conv2d_kernel_name.  It depends on the shape only,
+// never on the output type.
+enum ConvClass { kClassTile = 0, kClassWave = 1, kClassResident = 2, kClassResidentInt8 = 3 };
 
-ConvKernel choose_conv_kernel(int64_t pixels, int w, int c_in, int c_out, int r, int sx_static, int bits) {
-    if (bits == 8 || r != 3) return kConvKernelTile;   // the other kernels expand nibbles, 3x3 only
+ConvClass conv_class(int64_t pixels, int w, int c_in, int c_out, int r, int sx_static, int bits) {
+    if (bits == 8 || r != 3) return kClassTile;
     const int64_t cus = hq::compute_units();
-    // At least one 64 x 256 tile per CU and image rows short enough for the packed activation tile of
-    // the four-wave kernel that keeps it in LDS for all nine taps.
-    const int64_t tiles256 = ((pixels + 255) / 256) * ((c_out + 63) / 64);
-    GemmArgs probe{};
-    probe.k = c_in;
-    probe.w = w;
-    probe.pixels = static_cast<uint32_t>(pixels);
-    const bool halo_ok = tiles256 >= cus && hq_conv3x3_halo_fits(probe, HQ_F16);
-    // Per-pixel scales and ONE 192-channel slice: that kernel is still the fastest (measured 30.4 against
-    // 31.9 us on 64 x 64 x 192 at batch 16, buffers rotating through HBM).
-    if (!sx_static && c_in == 192 && halo_ok) return kConvKernelHalo;
-    // Per-pixel scales, 192-channel slices, an activation tile that fits the LDS as int8 and at least
-    // half a tile per CU: the kernel with the expanded activation tile resident, whose workgroup
-    // splits the K range over its waves so that one round of tiles fills the machine.
-    if (!sx_static && hq_conv3x3_res_fits(pixels, w, c_in, c_out)) return kConvKernelRes;
-    // A 3x3 layer with about one 64x64 output tile per CU or fewer cannot fill the machine with
-    // whole tiles: it takes the kernel that also splits a tile's K range over waves.  (With one
-    // scale for the tensor that kernel still combines per-tap sums in fp32, which equals the one
-    // integer sum times one product of scales up to fp32 rounding.)
+    // at least one 64 x 256 tile per CU, and 256 pixels plus the halo within 400 rows
+    const bool wide = ((pixels + 255) / 256) * ((c_out + 63) / 64) >= cus && c_in % 192 == 0 && 256 + 2 * (w + 1) <= 400;
+    if (!sx_static && c_in == 192 && wide) return kClassResident;
+    if (!sx_static && hq_conv3x3_res_fits(pixels, w, c_in, c_out)) return kClassResidentInt8;
+    // about one 64 x 64 output tile per CU or fewer
     const int64_t tiles64 = ((pixels + 63) / 64) * ((c_out + 63) / 64);
-    if (c_in % 192 == 0 && tiles64 * 4 <= 5 * cus) return kConvKernelWave;
-    // One scale for the tensor: no per-tap fold at all, the kernel with the packed activation tile in
-    // LDS at three workgroups per CU.
-    if (sx_static && halo_ok) return kConvKernelHalo;
-    return kConvKernelTile;
+    if (c_in % 192 == 0 && tiles64 * 4 <= 5 * cus) return kClassWave;
+    if (sx_static && wide) return kClassResident;
+    return kClassTile;
 }
 
 }  // namespace
@@ -142,11 +126,15 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
         return hq_gemm_launch_64x64(a, 9, y_dtype, st_);
     }
     if (c_in % 64 != 0) return hq_gemm_launch_anyk(a, r * s, y_dtype, st_);
-    switch (choose_conv_kernel(pixels, w, c_in, c_out, r, sx_static, bits)) {
-        case kConvKernelWave: return hq_conv3x3_wave_launch(a, y_dtype, st_);
-        case kConvKernelHalo: return hq_conv3x3_halo_launch(a, y_dtype, st_);
-        case kConvKernelRes: return hq_conv3x3_res_launch(a, y_dtype, st_);
-        default: break;
+    if (bits == 4 && r == 3) {
+        // One 192-channel slice and so few tiles that the K range is split over waves anyway: the wave-split kernel,
+        // which has no activation tile to expand first (1 x 64 x 64 x 192: 8.4 us against 9.2; 1 x 16 x 16 x 192 -> 100:
+        // 8.6 against 9.4).  From two slices on the resident kernel wins there too (16 x 8 x 8 x 960: 15.4 against 17.8,
+        // 23 x 12 x 12 x 384: 13.6 against 16.8).
+        if (c_in == 192 && conv_class(pixels, w, c_in, c_out, r, 1, bits) == kClassWave)
+            return hq_conv3x3_wave_launch(a, y_dtype, st_);
+        st = hq_resident_launch(a, 9, y_dtype, st_);
+        if (st != HQ_ERR_UNSUPPORTED) return st;
     }
     return launch_gemm(a, r * s, y_dtype, st_);
 }
@@ -250,10 +238,10 @@ extern "C" const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in,
     if (r != s || (r != 1 && r != 3) || stride != 1 || pad != (r - 1) / 2) return "unsupported";
     if (c_in % 8 != 0 || (bits == 8 && c_in % 64 != 0)) return "unsupported";
     if (c_in % 64 != 0) return "small-channel-count";
-    switch (choose_conv_kernel(static_cast<int64_t>(nb) * h * w, w, c_in, c_out, r, static_scale, bits)) {
-        case kConvKernelWave: return "wave-split";
-        case kConvKernelHalo: return "activation-resident";
-        case kConvKernelRes:
+    switch (conv_class(static_cast<int64_t>(nb) * h * w, w, c_in, c_out, r, static_scale, bits)) {
+        case kClassWave: return "wave-split";
+        case kClassResident: return "activation-resident";
+        case kClassResidentInt8:
             switch (hq_conv3x3_res_tile_pixels(static_cast<int64_t>(nb) * h * w, w, c_in, c_out)) {
                 case 256: return "activation-resident-int8 (256 pixels)";
                 case 129: return "activation-resident-int8 (128 pixels, 4 waves)";

@@ -944,10 +944,9 @@ hq_status hq_conv3x3_wave_launch(const GemmArgs &a, hq_dtype y_dtype, hipStream_
 // linear / 1x1 / 3x3 (stride 1) for channel counts that are a multiple of 8 but not of 64 (hq_int_gemm_anyk.hip)
 hq_status hq_gemm_launch_anyk(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream);
 hq_status hq_fill_zero_launch(void *dst, uint64_t ints, hipStream_t stream);
-// 3x3 convolution, per-pixel scales: eight waves per CU, int8 activation tile resident in LDS (hq_conv3x3_res.hip)
+// size classes of the one-launch 3x3 layer (hq_conv3x3_res.hip)
 bool hq_conv3x3_res_fits(int64_t pixels, int w, int c_in, int c_out);
 int hq_conv3x3_res_tile_pixels(int64_t pixels, int w, int c_in, int c_out);
-hq_status hq_conv3x3_res_launch(const GemmArgs &a, hq_dtype y_dtype, hipStream_t stream);
-// 3x3 convolution with the activation tile resident in LDS (hq_conv3x3_halo.hip)
-bool hq_conv3x3_halo_fits(const GemmArgs &a, hq_dtype y_dtype);
-hq_status hq_conv3x3_halo_launch(const GemmArgs &a, hq_dtype y_dtype, hipStream_t stream);
+// stride-1 layers of 4-bit codes, k a multiple of 64, on the 6-bit floating-point matrix instruction
+// (hq_resident.hip); HQ_ERR_UNSUPPORTED, with nothing launched, if a tile does not fit the LDS
+hq_status hq_resident_launch(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream);

@@ -1,0 +1,142 @@
+// Host side of the activation-resident kernel (hq_resident_kernel.h): how a layer is cut into workgroups.
+#include <algorithm>
+#include <atomic>
+
+#include "hq_resident_kernel.h"
+
+const void *hq_resident_pertap(int out, int ks);
+const void *hq_resident_sum(int out, int ks);
+const void *hq_resident_linear(int out, int ks);
+
+namespace {
+
+constexpr int kLdsPerCu = 163840;
+
+struct Plan {
+    int ks, slices, chunk, nw, xw_log2, cb, rows;
+    uint32_t part8, exchange, tables, lds;
+    bool wide, ok;
+};
+
+// LDS layout of a workgroup of nw waves, 1 << xw_log2 pixel groups and cb channel blocks within `budget` bytes.
+Plan lay_out(int kind, int w, int k, int n, int ks, int nw, int xw_log2, int cb, int budget) {
+    const int blocks = (n + 31) / 32;
+    Plan p{};
+    p.ks = ks;
+    p.slices = (k / 64 + ks - 1) / ks;
+    p.nw = nw;
+    p.xw_log2 = xw_log2;
+    p.cb = cb;
+    const int px = 128 << xw_log2;
+    p.rows = (px + (kind == kResLinear ? 0 : 2 * (w + 1)) + 1) | 1;
+    const int tables = resident_table_bytes(kind, px, p.rows, cb);
+    // Sums shared between waves meet in, and fp16 results pass through, 8 KiB per wave.  Where every workgroup has one
+    // phase that area may lie over the activation tile.
+    const int tasks = cb << xw_log2, last = blocks % cb << xw_log2;   // of a workgroup, of the last one of a row
+    auto one_phase_of = [&](int t) { return (t & (t - 1)) == 0 && t < nw; };
+    const bool overlay = one_phase_of(tasks) && one_phase_of(last);
+    const int area = nw * 8192;
+    const int slice_bytes = p.rows * ks * 48;
+    p.chunk = std::min(p.slices, (budget - tables - (overlay ? 0 : area)) / slice_bytes);
+    if (p.chunk < 1 || (p.chunk < p.slices && !overlay)) return p;
+    p.part8 = static_cast<uint32_t>(p.rows) * p.chunk * ks * 32;
+    p.part8 = (p.part8 + 15) & ~15u;
+    const uint32_t act_end = (static_cast<uint32_t>(p.part8) + static_cast<uint32_t>(p.rows) * p.chunk * ks * 16 + 15) & ~15u;
+    // (an area over the tile costs nothing up to the tile's size, or up to the budget of the only workgroup of a CU)
+    p.wide = overlay && nw * 16384 + tables <= budget;
+    p.exchange = overlay ? 0 : act_end;
+    p.tables = overlay ? std::max(act_end, static_cast<uint32_t>(p.wide ? 2 * area : area)) : act_end + area;
+    p.lds = p.tables + tables;
+    p.ok = static_cast<int>(p.lds) <= budget + 32 && p.lds <= kLdsPerCu;
+    return p;
+}
+
+// Clocks of a workgroup, fitted to time stamps of the kernel on 3x3 layers of 64 to 960 channels (within 15 % of
+// them, and in the measured order of the cuts): start and first loads, filling (rounds of 32-row items over the waves),
+// units (two waves per SIMD share the vector issue), results (each exchange of sums costs two barriers).
+double cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
+    const int px = 128 << p.xw_log2, blocks = (n + 31) / 32, taps = kind == kResLinear ? 1 : 9;
+    const int64_t wgs = (pixels + px - 1) / px * ((blocks + p.cb - 1) / p.cb);
+    const int per_cu = p.nw == 4 && p.lds <= kLdsPerCu / 2 ? 2 : 1;
+    const double rounds = static_cast<double>((wgs + static_cast<int64_t>(cus) * per_cu - 1) / (static_cast<int64_t>(cus) * per_cu));
+    const bool paired = p.nw == 8 || (per_cu == 2 && wgs > cus);
+    const int items = (p.rows - 1 + 31) / 32 * p.slices;
+    double clocks = 6500 + 2000 + (paired ? 700.0 : 450.0) * p.ks * ((items + p.nw - 1) / p.nw);
+    for (int left = std::min(blocks, p.cb) << p.xw_log2; left > 0;) {
+        int kl = 0;
+        while ((p.nw >> kl) > left) ++kl;
+        const int units = (taps * p.slices + (1 << kl) - 1) >> kl;
+        clocks += units * p.ks * (paired ? 575.0 : 330.0) + 3600 + (kl ? 1000 + 1500 * kl : 0);
+        left -= p.nw >> kl;
+    }
+    return rounds * clocks;
+}
+
+Plan choose_plan(int kind, int64_t pixels, int w, int k, int n) {
+    const int steps = k / 64, cus = hq::compute_units();
+    const int ks = steps % 3 == 0 || steps > 4 ? 3 : steps == 1 ? 1 : 2;
+    Plan best{};
+    double best_cost = 0;
+    for (const int nw : {8, 4})
+        for (int xw = 0; xw <= 1; ++xw)
+            for (const int cb : {1, 2, 3, 4, 6, 8, 12}) {
+                if (cb > 1 && cb > 2 * ((n + 31) / 32) - 1) continue;
+                const Plan p = lay_out(kind, w, k, n, ks, nw, xw, cb, nw == 4 ? kLdsPerCu / 2 : kLdsPerCu);
+                if (!p.ok) continue;
+                const double c = cost_of(p, kind, pixels, n, cus);
+                if (!best.ok || c < best_cost) { best = p; best_cost = c; }
+            }
+    return best;
+}
+
+// Dynamic LDS beyond the default limit has to be allowed once per kernel and device.
+hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return HQ_ERR_LAUNCH;
+    if ((done.load(std::memory_order_acquire) >> dev) & 1) return HQ_OK;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu) != hipSuccess) return HQ_ERR_LAUNCH;
+    done.fetch_or(1ull << dev, std::memory_order_release);
+    return HQ_OK;
+}
+
+}  // namespace
+
+// HQ_ERR_UNSUPPORTED, with nothing launched: the image rows are too long for a tile and its halo.
+hq_status hq_resident_launch(const GemmArgs &g, int taps, hq_dtype y_dtype, hipStream_t stream) {
+    const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
+    const int kind = taps == 1 ? kResLinear : g.sx_static ? kResSum : kResPerTap;
+    const Plan p = choose_plan(kind, g.pixels, g.w, g.k, g.n);
+    if (!p.ok) return HQ_ERR_UNSUPPORTED;
+    ResidentArgs a{};
+    a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
+    a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.h = g.h; a.w = g.w; a.sx_static = g.sx_static;
+    const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
+    a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
+    a.slices = p.slices; a.chunk = p.chunk; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
+    a.wide = p.wide; a.part8 = p.part8; a.exchange = p.exchange; a.tables = p.tables;
+    const int px = 128 << p.xw_log2, blocks = (g.n + 31) / 32;
+    const int64_t px_tiles = (static_cast<int64_t>(g.pixels) + px - 1) / px, ch_groups = (blocks + p.cb - 1) / p.cb;
+    const int64_t tiles = px_tiles * ch_groups;
+    if (tiles > 0x7fffffff) return HQ_ERR_SHAPE;
+    a.px_tiles = static_cast<uint32_t>(px_tiles);
+    a.ch_groups = static_cast<uint32_t>(ch_groups);
+    // the larger operand is the one that an XCD's run of tiles shares
+    a.ch_major = static_cast<int64_t>(g.n) * taps > static_cast<int64_t>(g.pixels);
+    const hq::Magic31 md = hq::magic31(a.ch_major ? a.px_tiles : a.ch_groups);
+    a.d_magic = md.m; a.d_shift = md.s;
+    const int out = y_dtype == HQ_F16 ? kOutF16 : y_dtype == HQ_F32 ? kOutF32 : kOutI32;
+    if (out == kOutI32 && kind == kResPerTap) {
+        const hq_status st = hq_fill_zero_launch(g.y, static_cast<uint64_t>(g.pixels) * 9 * g.n, stream);
+        if (st != HQ_OK) return st;
+    }
+    const void *fn = kind == kResLinear ? hq_resident_linear(out, p.ks)
+                     : kind == kResSum  ? hq_resident_sum(out, p.ks)
+                                        : hq_resident_pertap(out, p.ks);
+    static std::atomic<uint64_t> allowed[3][3][3];
+    const hq_status st = allow_lds(fn, allowed[kind][out][p.ks - 1]);
+    if (st != HQ_OK) return st;
+    void *args[] = {&a};
+    if (hipLaunchKernel(fn, dim3(static_cast<unsigned>(tiles)), dim3(64 * p.nw), args, p.lds, stream) != hipSuccess)
+        return HQ_ERR_LAUNCH;
+    return check.status();
+}

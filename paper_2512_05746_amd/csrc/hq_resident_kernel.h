@@ -1,0 +1,568 @@
+// Integer GEMM / NHWC convolution of 4-bit codes on the 6-bit floating-point matrix instruction (hq_fp6.h), with
+// the activation tile expanded once and resident in LDS.
+//
+// A workgroup owns XW groups of 128 consecutive pixels (tokens) and a run of blocks of 32 output channels; a wave's
+// result tile is 32 channels x 128 pixels.  The codes of the pixels - for a 3x3 window with those of W + 1 pixels
+// either side - are fetched once, expanded to 6-bit fields and kept in LDS as planes
+//     [64-channel step][lane half][row] of 16-byte operand parts, then of 8-byte parts,
+// so that a wave's operand read of 32 consecutive rows is two contiguous runs for any row shift: 224 bytes per clock
+// and CU measured, against 126 with the halves of a row next to each other.  Weights go from memory straight into
+// registers, one unit ahead; there is no barrier between the filling of the tile and the end of a phase.
+//
+// A unit is one tap and one slice of KS steps: 7 vector instructions per 16 weight codes to expand them (hq_fp6.h),
+// KS operand reads and KS MFMAs for each of the four 32-pixel tiles, and (per-pixel scales) one fold of 16
+// values into the fp32 sums per tile.  What bounds it: vector issue and matrix pipe together.  A 192-channel unit has
+// 5.3 (fold) + 3.5 (weights) + about 1 vector instructions per MFMA; a loop of such a mix alone takes 30 ns per MFMA
+// and SIMD (21 ns without them: on random codes the chip holds 1.6 .. 2.1 GHz), the kernel's 31 .. 33 ns.  The other half
+// of a launch is what surrounds the loop: start and first loads (2 us), expanding the tile (2 .. 4 us; 24
+// instructions per 16 codes for the signed form), exchange and results (2 .. 5 us).
+//
+// Measured (3x3, 4-bit, us, buffers rotating beyond the last-level cache; before: int8 kernels that expanded nibbles
+// at every use or streamed both operands through LDS), per-pixel scales / one scale:
+//     16 x 64 x 64 x 192   31.1 -> 27.3 / 28.4 -> 27.1      16 x 8 x 8 x 960            17.8 -> 15.4 / 17.8 -> 15.0
+//     16 x 32 x 32 x 384   31.9 -> 25.2 / 30.5 -> 25.1       8 x 16 x 16 x 960          32.6 -> 22.0 / 31.4 -> 21.5
+//     16 x 16 x 16 x 576   24.0 -> 20.1 / 26.8 -> 20.2       3 x 45 x 27 x 320 -> 200   32.7 -> 11.1 / 28.8 -> 10.8
+//
+// Phases.  The tasks (pixel group, channel block) of a workgroup are dealt out to its NW waves in phases: NW at a
+// time, then the remainder in powers of two, the units of a task shared by 2, 4 or 8 waves whose sums meet in
+// LDS in a fixed order.  So all waves multiply about the same number of units whatever the channel count is.
+//
+// Weights carry an offset of 8 (hq_fp6.h): a sum exceeds the wanted one by 8 x (sum of the activation codes it
+// covers), the same for all channels: a per-pixel correction from a table of code sums.
+#pragma once
+#include <type_traits>
+
+#include "hq_fp6.h"
+#include "hq_int_gemm_kernel.h"
+
+struct ResidentArgs {
+    const uint8_t *xq;   // [pixels, k/2]
+    const float *sx;     // [pixels], or one value
+    const uint8_t *wq;   // [n, taps, k/2]
+    const float *sw;     // [n]
+    const void *bias;    // [n] of the output dtype, or null
+    void *y;             // [pixels, n]; per-tap integer output [pixels, 9, n], zero-filled before the launch
+    uint32_t pixels;
+    int n, k, h, w;
+    int sx_static;
+    uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
+    int slices, chunk;             // K slices of KS steps, and how many are resident at a time
+    int xw_log2;                   // pixel groups of 128 per workgroup
+    int cb;                        // channel blocks of 32 per workgroup
+    uint32_t ch_groups, px_tiles;  // workgroups: channel runs x pixel tiles
+    uint32_t d_magic, d_shift;     // exact division of a tile index by the count that runs fastest
+    int ch_major;                  // neighbouring workgroups share the channels (else the pixels)
+    int rows;                      // rows of the LDS image, odd, the last one all zeros
+    int wide;                      // the exchange area has 16 KiB per wave (else 8)
+    uint32_t part8, exchange, tables;   // LDS offsets: 8-byte parts, exchange / staging area, tables
+};
+
+namespace {
+
+constexpr int kResLinear = 0;   // no window: one sum per output, scaled by the pixel's scale (or the one scale)
+constexpr int kResPerTap = 1;   // 3x3, per-pixel scales: one sum per tap, combined in fp32
+constexpr int kResSum = 2;      // 3x3, one scale: one sum over all taps
+
+// Barrier that orders LDS only: __syncthreads() would also wait for the wave's global loads (weights requested
+// ahead) and stores.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Buffer accesses: uniform base and bound in scalar registers, a 32-bit offset per lane; loads beyond the bound
+// return zeros, stores beyond it are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, static_cast<int>(bytes), 0x00027000);
+}
+__device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off) {
+    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(lane_off), static_cast<int>(uniform_off), 0));
+}
+__device__ __forceinline__ void buffer_store16(const v4i &v, __amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off) {
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, static_cast<int>(lane_off), static_cast<int>(uniform_off), 0);
+}
+
+__host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
+    return (kind == kResPerTap ? 9 : 1) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
+}
+
+template <int OUT, int KIND, int KS>
+__global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
+    constexpr bool WINDOW = KIND != kResLinear, FOLD = KIND == kResPerTap;
+    constexpr bool INT_TAPS = OUT == kOutI32 && FOLD;
+    constexpr int TAPS = WINDOW ? 9 : 1, NT = 4;
+    using Out = typename OutT<OUT>::type;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+
+    const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6;
+    const int lane = tid & 63, l = lane & 31, h = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cb = a.k >> 1, steps = a.k >> 6, rows = a.rows;
+    const int px_wg = 128 << a.xw_log2;
+    const int halo = WINDOW ? a.w + 1 : 0;
+
+    // workgroup b runs on XCD b % 8: every XCD gets a contiguous run of tiles
+    const uint32_t nwg = gridDim.x, xcd = blockIdx.x & 7, q8 = nwg >> 3, r8 = nwg & 7;
+    const uint32_t tile = xcd * q8 + (xcd < r8 ? xcd : r8) + (blockIdx.x >> 3);
+    const uint32_t fast = a.ch_major ? a.px_tiles : a.ch_groups;
+    const uint32_t slow_i = hq::div_magic31(tile, fast, a.d_magic, a.d_shift), fast_i = tile - slow_i * fast;
+    const uint32_t p0 = (a.ch_major ? fast_i : slow_i) * px_wg;
+    const int c_wg = static_cast<int>(a.ch_major ? slow_i : fast_i) * a.cb * 32;
+    const int blocks = min(a.cb, (a.n - c_wg + 31) / 32);   // channel blocks of this workgroup
+
+    float *s_sx = reinterpret_cast<float *>(lds + a.tables);
+    float *s_corr = s_sx + (FOLD ? TAPS : 1) * px_wg;
+    int *s_mask = reinterpret_cast<int *>(s_corr + px_wg);
+    float *s_rowscale = reinterpret_cast<float *>(s_mask + px_wg);
+    int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);
+    float *s_sw = reinterpret_cast<float *>(s_sum + rows);
+    float *s_bias = s_sw + a.cb * 32;
+
+    // ---- phases: tasks and shares ---------------------------------------------------------------------------
+    // tasks first .. first + (nw >> kl) - 1, each by 1 << kl waves; wave wv has task first + wv >> kl, share wv mod
+    int left = blocks << a.xw_log2, first = 0, kl = 0;
+    auto shrink = [&]() {
+        kl = 0;
+        while ((nw >> kl) > left) ++kl;
+    };
+    shrink();
+    int c0 = 0, px_l = 0, u = 0, u_end = 0;   // first channel, first pixel (local), units of this wave's task
+    uint32_t w_lane = 0;                      // this lane's weight row
+    const int resident0 = a.chunk < a.slices ? a.chunk : a.slices;
+    int s0 = 0, s1 = resident0;               // resident slices
+    auto begin_task = [&]() {
+        const int task = first + (wv >> kl), share = wv & ((1 << kl) - 1);
+        px_l = (task & ((1 << a.xw_log2) - 1)) * 128;
+        c0 = c_wg + (task >> a.xw_log2) * 32;
+        const int co = c0 + tile_row_to_channel(l);
+        w_lane = static_cast<uint32_t>(co < a.n ? co : a.n - 1) * (TAPS * cb) + h * 16;
+        const int units = TAPS * (s1 - s0);
+        u = share * units >> kl;
+        u_end = (share + 1) * units >> kl;
+    };
+    // unit u of the resident slices: tap u / (s1 - s0), slice s0 + u % (s1 - s0)
+    v4i raw[KS];   // packed weights of the next unit
+    const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
+    auto load_weight = [&](int k, int tap, int slice) {
+        const int step = slice * KS + k < steps ? slice * KS + k : 0;   // (past the channels: activations are zero)
+        raw[k] = buffer_load16(w_buf, w_lane, static_cast<uint32_t>(tap * cb + step * 32));
+    };
+    auto load_weights = [&](int tap, int slice) {
+#pragma unroll
+        for (int k = 0; k < KS; ++k) load_weight(k, tap, slice);
+    };
+
+    // ---- activation tile: packed codes -> signed 6-bit fields ------------------------------------------------
+    // Wave items (32 rows, slice): lane = (row, lane half), KS 16-byte pieces each; the code sum of a row's
+    // slice is that of two neighbouring lanes.
+    const int row_items = (px_wg + 2 * halo + 31) >> 5;
+    const uint32_t last = a.pixels - 1;
+    const int64_t row_pixel0 = static_cast<int64_t>(p0) - halo;
+    const int f_row = lane >> 1, f_half = lane & 1;
+    const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, a.pixels * static_cast<uint32_t>(cb));
+    auto fill_load = [&](v4i (&p)[KS], int item) {
+        const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
+        // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
+        const uint32_t off = (static_cast<uint32_t>(p0) - halo + row) * cb + f_half * 16;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            p[k] = v4i{0, 0, 0, 0};
+            if ((s0 + sl) * KS + k < steps) p[k] = buffer_load16(x_buf, off, ((s0 + sl) * KS + k) * 32);
+        }
+    };
+    auto fill_store = [&](const v4i (&p)[KS], int item) {
+        const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
+        int sum = 0;
+        if (row < rows - 1) {
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                int d[6];
+                fp6_signed16(p[k].x, p[k].y, d[0], d[1], d[2]);
+                fp6_signed16(p[k].z, p[k].w, d[3], d[4], d[5]);
+                const int at = ((sl * KS + k) * 2 + f_half) * rows + row;
+                *reinterpret_cast<v4i *>(lds + at * 16) = v4i{d[0], d[1], d[2], d[3]};
+                *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{d[4], d[5]};
+                sum = sum_codes8(p[k].x, sum_codes8(p[k].y, sum_codes8(p[k].z, sum_codes8(p[k].w, sum))));
+            }
+        }
+        sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
+        if (f_half == 0 && row < rows - 1) atomicAdd(&s_sum[row], sum);
+    };
+
+    // All first loads are requested before any is waited for (a first use costs a trip to HBM).
+    v4i p[2][KS];
+    begin_task();
+    const int first_items = row_items * (s1 - s0);
+    fill_load(p[0], wv < first_items ? wv : 0);
+    load_weights(u / (s1 - s0), u % (s1 - s0));
+    constexpr bool ROW_SCALES = KIND != kResSum && OUT != kOutI32;
+    auto row_scale = [&](int i) {
+        int64_t pix = row_pixel0 + i;
+        pix = pix < 0 ? 0 : (pix > static_cast<int64_t>(last) ? last : pix);
+        return a.sx[a.sx_static ? 0 : pix];
+    };
+    float t_scale[2] = {}, t_sw = 0.f, t_bias = 0.f;
+    if constexpr (ROW_SCALES) {
+        t_scale[0] = row_scale(tid);
+        t_scale[1] = row_scale(tid + nt);
+    }
+    if constexpr (OUT != kOutI32) {
+        const int c = c_wg + tid < a.n ? c_wg + tid : a.n - 1;
+        t_sw = a.sw[c];
+        t_bias = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
+    }
+    for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
+    for (int i = tid; i < resident0 * KS * 2; i += nt) {   // the row of zeros
+        const int at = i * rows + rows - 1;
+        *reinterpret_cast<v4i *>(lds + at * 16) = v4i{0, 0, 0, 0};
+        *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{0, 0};
+    }
+    if constexpr (ROW_SCALES) {
+        if (tid < rows) s_rowscale[tid] = t_scale[0];
+        if (tid + nt < rows) s_rowscale[tid + nt] = t_scale[1];
+        for (int i = tid + 2 * nt; i < rows; i += nt) s_rowscale[i] = row_scale(i);
+    }
+    if constexpr (OUT != kOutI32) {
+        if (tid < blocks * 32) {
+            s_sw[tid] = t_sw;
+            s_bias[tid] = t_bias;
+        }
+        for (int i = tid + nt; i < blocks * 32; i += nt) {
+            const int c = c_wg + i < a.n ? c_wg + i : a.n - 1;
+            s_sw[i] = a.sw[c];
+            s_bias[i] = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
+        }
+    }
+    lds_barrier();   // the code sums are zero before they are added to
+
+    v16f sum[NT] = {};   // the accumulators themselves, or (FOLD) fp32 combinations of per-tap sums
+    for (;;) {           // chunks of resident slices
+        const int items = row_items * (s1 - s0);
+        for (int item = wv; item < items; item += 2 * nw) {
+            if (item + nw < items) fill_load(p[1], item + nw);
+            fill_store(p[0], item);
+            if (item + nw < items) {
+                if (item + 2 * nw < items) fill_load(p[0], item + 2 * nw);
+                fill_store(p[1], item + nw);
+            }
+        }
+        lds_barrier();
+        // tables of the pixels: tap masks, scales under the taps, corrections
+        for (int i = tid; i < px_wg; i += nt) {
+            const uint32_t pix = p0 + i;
+            if constexpr (WINDOW) {
+                const uint32_t q = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
+                const int ow = static_cast<int>(pix - q * a.w);
+                const int oh = static_cast<int>(q - hq::div_magic31(q, a.h, a.h_magic, a.h_shift) * a.h);
+                const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
+                int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
+                if (pix >= a.pixels) mask = 0;
+                s_mask[i] = mask;
+                float corr = 0.f;
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
+                    const bool in = (mask >> t) & 1;
+                    if constexpr (FOLD && !INT_TAPS) {
+                        // (a product of two codes is 1/64 in the matrix instruction's units)
+                        const float s = in ? s_rowscale[row] : 0.f;
+                        s_sx[t * px_wg + i] = s * 64.0f;
+                        corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
+                    } else if (in) {
+                        corr += 8.0f * static_cast<float>(s_sum[row]);
+                    }
+                }
+                s_corr[i] = corr;   // (of all slices once the last chunk is resident)
+            } else {
+                s_corr[i] = 8.0f * static_cast<float>(s_sum[i]);
+                if constexpr (OUT != kOutI32) s_sx[i] = s_rowscale[i];
+            }
+        }
+        lds_barrier();
+
+        for (;;) {   // phases
+            int mask[NT];   // kResSum / INT_TAPS: taps inside the image, for the pixels of the four tiles
+            if constexpr (KIND == kResSum || INT_TAPS) {
+#pragma unroll
+                for (int t = 0; t < NT; ++t) mask[t] = s_mask[px_l + t * 32 + l];
+            }
+            const int lane_row = px_l + l + halo;
+            const int ns = s1 - s0;
+            int tap = u / ns, sl = u - tap * ns;
+            // LDS offsets of this lane's row of tile 0 in the two parts of a unit's first plane; the other tiles and
+            // steps lie at fixed distances
+            const int plane16 = rows * 32, plane8 = rows * 16;   // from step to step
+            struct Base { int b16, b8; };
+            auto base_of = [&](int tap, int sl) {
+                const int shift = WINDOW ? (tap / 3 - 1) * a.w + tap % 3 - 1 : 0;
+                const int at = (sl * KS * 2 + h) * rows + lane_row;
+                return Base{(at + shift) * 16, static_cast<int>(a.part8) + (at + shift) * 8};
+            };
+            auto load_tile = [&](v8i (&b)[KS], const Base &base, int tap, int t) {
+                int b16 = base.b16, b8 = base.b8, imm = t;
+                if constexpr (KIND == kResSum) {   // taps outside the image read the row of zeros
+                    const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1;
+                    const int to = (mask[t] >> tap) & 1 ? t * 32 : rows - 1 - row;
+                    b16 += to * 16;
+                    b8 += to * 8;
+                    imm = 0;
+                }
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    const v4i lo = *reinterpret_cast<const v4i *>(lds + (b16 + k * plane16) + imm * 512);
+                    const int2 hi = *reinterpret_cast<const int2 *>(lds + (b8 + k * plane8) + imm * 256);
+                    b[k] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+                }
+            };
+            // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded;
+            // the next unit's weights are requested as soon as this unit's are expanded.
+            Base base = base_of(tap, sl);
+            v8i w6[KS], b[2][KS];
+            load_tile(b[0], base, tap, 0);
+            for (; u < u_end; ++u) {
+                int tap1 = tap, sl1 = sl;   // the next unit (the last one's operands are requested twice)
+                if (u + 1 < u_end) {
+                    if (++sl1 == ns) { sl1 = 0; ++tap1; }
+                }
+                const Base base1 = base_of(tap1, sl1);
+#pragma unroll
+                for (int k = 0; k < KS; ++k) {
+                    int d[6];
+                    fp6_offset16(raw[k].x, raw[k].y, d[0], d[1], d[2]);
+                    fp6_offset16(raw[k].z, raw[k].w, d[3], d[4], d[5]);
+                    w6[k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+                }
+                load_weights(tap1, s0 + sl1);
+                v16f acc[2];
+                float scale[NT];
+                if constexpr (FOLD && !INT_TAPS) {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
+                }
+                auto fold = [&](int t) {
+                    if constexpr (INT_TAPS) {
+                        const uint32_t pix = p0 + px_l + t * 32 + l;
+                        if ((mask[t] >> tap) & 1) {
+                            const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32;
+                            const int extra = sl == 0 ? 8 * s_sum[row] : 0;
+                            int *dst = static_cast<int *>(a.y) + (static_cast<uint64_t>(pix) * 9 + tap) * a.n;
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) {
+                                const int c = c0 + 16 * h + i;
+                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc[t & 1][i] * 64.0f) - extra);
+                            }
+                        }
+                    } else if constexpr (FOLD) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], acc[t & 1][i], sum[t][i]);
+                    }
+                };
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    if (t + 1 < NT) load_tile(b[(t + 1) & 1], base, tap, t + 1);
+                    else load_tile(b[0], base1, tap1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    v16f c = mfma_fp6(w6[0], b[t & 1][0], FOLD ? v16f{} : sum[t]);
+#pragma unroll
+                    for (int k = 1; k < KS; ++k) c = mfma_fp6(w6[k], b[t & 1][k], c);
+                    if constexpr (FOLD) acc[t & 1] = c;
+                    else sum[t] = c;
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (t > 0) fold(t - 1);
+                }
+                fold(NT - 1);
+                tap = tap1;
+                sl = sl1;
+                base = base1;
+            }
+            if (s1 < a.slices) break;   // the sums go on with the next chunk (one phase: host)
+
+            // ---- results of the phase --------------------------------------------------------------------------
+            if constexpr (!INT_TAPS) {
+                // Tasks shared by 2, 4 or 8 waves: in every round a wave hands half of what it holds to a partner and
+                // adds the partner's sums of the other half, until it holds 4 >> kl pixel tiles (or half a tile).
+                int tile0 = 0, half0 = 0;   // what it holds: tiles tile0 .., or half half0 of tile tile0
+                v4i *const outbox = reinterpret_cast<v4i *>(lds + a.exchange) + wv * 512 + lane;
+                auto exchange = [&](auto KEEP, int distance) {   // KEEP: values per lane that stay
+                    constexpr int keep = decltype(KEEP)::value;
+                    const int upper = wv & distance ? 1 : 0;
+                    const v4i *const inbox = reinterpret_cast<const v4i *>(lds + a.exchange) + (wv ^ distance) * 512 + lane;
+                    lds_barrier();   // the area is free (it may lie over the activation tile)
+#pragma unroll
+                    for (int i = 0; i < keep; i += 4) {
+                        v4i out;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int at = i + e, other = keep + i + e;
+                            const float lo = sum[at >> 4][at & 15], hi = sum[other >> 4][other & 15];
+                            out[e] = __float_as_int(upper ? lo : hi);
+                            sum[at >> 4][at & 15] = upper ? hi : lo;
+                        }
+                        outbox[i * 16] = out;
+                    }
+                    lds_barrier();
+#pragma unroll
+                    for (int i = 0; i < keep; i += 4) {
+                        const v4i in = inbox[i * 16];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sum[(i + e) >> 4][(i + e) & 15] += __int_as_float(in[e]);
+                    }
+                    return upper;
+                };
+                if (kl >= 2 && a.wide) {
+                    // room for everything: every wave writes all its sums and adds up its own 64 >> kl values of all waves
+                    const int kws = 1 << kl, share = wv & (kws - 1);
+                    v4i *const box = reinterpret_cast<v4i *>(lds + a.exchange) + lane;
+                    lds_barrier();
+#pragma unroll
+                    for (int i = 0; i < 64; i += 4)
+                        box[(wv * 16 + i / 4) * 64] = v4i{__float_as_int(sum[i >> 4][i & 15]), __float_as_int(sum[i >> 4][(i + 1) & 15]),
+                                                          __float_as_int(sum[i >> 4][(i + 2) & 15]), __float_as_int(sum[i >> 4][(i + 3) & 15])};
+                    lds_barrier();
+                    sum[0] = v16f{};
+                    for (int j = 0; j < kws; ++j) {
+                        const v4i *const from = box + ((wv - share + j) * 16 + (share * 16 >> kl)) * 64;
+#pragma unroll
+                        for (int i = 0; i < 16; i += 4) {
+                            if (i == 8 && kl == 3) break;
+                            const v4i in = from[i * 16];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) sum[0][i + e] += __int_as_float(in[e]);
+                        }
+                    }
+                    tile0 = share * 4 >> kl;
+                    half0 = kl == 3 ? share & 1 : 0;
+                    lds_barrier();   // (the results go through the area)
+                } else {
+                    if (kl >= 1) tile0 = 2 * exchange(std::integral_constant<int, 32>{}, 1 << (kl - 1));
+                    if (kl >= 2) tile0 += exchange(std::integral_constant<int, 16>{}, 1 << (kl - 2));
+                    if (kl >= 3) half0 = exchange(std::integral_constant<int, 8>{}, 1);
+                }
+
+                const float one_scale = (KIND == kResSum && OUT != kOutI32) ? a.sx[0] : 1.0f;
+                // results of eight sums v of a pixel with correction corr and scale s, channels ct .. ct + 7 (in the workgroup)
+                auto scaled = [&](const float (&v)[8], float corr, float s, const float *sw, const float *bias, Out (&res)[8]) {
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        if constexpr (OUT == kOutI32) {
+                            res[i] = static_cast<int>(v[i] * 64.0f - corr);
+                        } else {
+                            const float r = FOLD ? v[i] - corr : (v[i] * 64.0f - corr) * s;
+                            const float y = fmaf(r, sw[i], bias[i]);
+                            if constexpr (OUT == kOutF16) res[i] = __float2half_rn(y);
+                            else res[i] = y;
+                        }
+                    }
+                };
+                const uint32_t rows_left = min(a.pixels - p0, static_cast<uint32_t>(px_wg));
+                Out *const y_wg = static_cast<Out *>(a.y) + static_cast<uint64_t>(p0) * a.n;
+                const __amdgpu_buffer_rsrc_t y_buf = buffer_of(y_wg, rows_left * static_cast<uint32_t>(a.n * sizeof(Out)));
+                const bool vec = a.n % 8 == 0;   // groups of eight channels are whole and 16-byte aligned
+                auto store8 = [&](const Out (&res)[8], int px, int c) {
+                    if (vec) {
+                        const uint32_t off = c < a.n ? static_cast<uint32_t>(px * a.n + c) * sizeof(Out) : 0x80000000u;   // (beyond the bound: dropped)
+                        buffer_store16(reinterpret_cast<const v4i *>(res)[0], y_buf, off, 0);
+                        if constexpr (sizeof(Out) == 4) buffer_store16(reinterpret_cast<const v4i *>(res)[1], y_buf, off + 16, 0);
+                    } else if (px < static_cast<int>(rows_left)) {
+                        for (int i = 0; i < 8; ++i)
+                            if (c + i < a.n) y_wg[static_cast<uint64_t>(px) * a.n + c + i] = res[i];
+                    }
+                };
+                const int ct = c0 - c_wg + 16 * h;
+                auto pixel_scale = [&](int px) { return KIND == kResLinear && OUT != kOutI32 ? s_sx[px] : one_scale; };
+                if (kl < 3) {
+                    // fp16: through LDS, [pixel][four 16-byte pieces] of 2 KiB per tile, so that four neighbouring lanes
+                    // store the 64 contiguous bytes of a pixel instead of every lane a piece of its own (after an
+                    // exchange in the area of the last partner, which nobody else reads)
+                    uint8_t *const stage = lds + a.exchange + (kl ? wv ^ 1 : wv) * 8192;
+                    float sw[16], bias[16], corr[NT], ps[NT];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        sw[i] = OUT != kOutI32 ? s_sw[ct + i] : 0.f;
+                        bias[i] = OUT != kOutI32 ? s_bias[ct + i] : 0.f;
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const int px = px_l + ((tile0 + t) & (NT - 1)) * 32 + l;
+                        corr[t] = s_corr[px];
+                        ps[t] = pixel_scale(px);
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        if (t >= NT >> kl) break;
+                        const int px = px_l + (tile0 + t) * 32;
+                        Out res[2][8];
+#pragma unroll
+                        for (int half = 0; half < 2; ++half) {
+                            float v[8];
+#pragma unroll
+                            for (int i = 0; i < 8; ++i) v[i] = sum[t][8 * half + i];
+                            scaled(v, corr[t], ps[t], sw + 8 * half, bias + 8 * half, res[half]);
+                        }
+                        if constexpr (OUT == kOutF16) {
+#pragma unroll
+                            for (int half = 0; half < 2; ++half)
+                                *reinterpret_cast<v4i *>(stage + t * 2048 + l * 64 + (((2 * h + half) ^ ((l >> 2) & 3)) * 16)) =
+                                    *reinterpret_cast<const v4i *>(res[half]);
+                        } else {
+                            store8(res[0], px + l, c0 + 16 * h);
+                            store8(res[1], px + l, c0 + 16 * h + 8);
+                        }
+                    }
+                    if constexpr (OUT == kOutF16) {
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        __builtin_amdgcn_wave_barrier();
+                        const int q = lane >> 2, piece = lane & 3;
+                        const uint8_t *const from = stage + q * 64 + ((piece ^ ((q >> 2) & 3)) * 16);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            if (t >= NT >> kl) break;
+#pragma unroll
+                            for (int half = 0; half < 2; ++half) {
+                                Out out[8];
+                                *reinterpret_cast<v4i *>(out) = *reinterpret_cast<const v4i *>(from + t * 2048 + half * 1024);
+                                store8(out, px_l + (tile0 + t) * 32 + 16 * half + q, c0 + 8 * piece);
+                            }
+                        }
+                    }
+                } else {
+                    const int px = px_l + tile0 * 32 + l;
+                    float v[8], sw[8], bias[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        v[i] = sum[0][i];
+                        sw[i] = OUT != kOutI32 ? s_sw[ct + 8 * half0 + i] : 0.f;
+                        bias[i] = OUT != kOutI32 ? s_bias[ct + 8 * half0 + i] : 0.f;
+                    }
+                    Out res[8];
+                    scaled(v, s_corr[px], pixel_scale(px), sw, bias, res);
+                    store8(res, px, c0 + 16 * h + 8 * half0);
+                }
+            }
+            first += nw >> kl;
+            left -= nw >> kl;
+            if (left == 0) return;
+            shrink();
+            begin_task();
+            load_weights(u / ns, s0 + u % ns);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) sum[t] = v16f{};
+        }
+
+        // ---- next chunk -----------------------------------------------------------------------------------------
+        s0 = s1;
+        s1 = s0 + a.chunk < a.slices ? s0 + a.chunk : a.slices;
+        begin_task();
+        fill_load(p[0], wv < row_items * (s1 - s0) ? wv : 0);
+        load_weights(u / (s1 - s0), s0 + u % (s1 - s0));
+        lds_barrier();   // every wave is done with the resident slices
+        if constexpr (INT_TAPS) {   // per-tap sums are corrected with the code sums of their own slices
+            for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
+            lds_barrier();
+        }
+    }
+}
+
+}  // namespace

@@ -1,0 +1,58 @@
+"""Parity of the activation-resident kernel (4-bit codes, stride 1) at the sizes where its cuts can go wrong."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle
+from parity_util import check_y, pack_codes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hq():
+    import paper_2512_05746_amd as mod
+    return mod
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (1, 1, 1, 64, 1),          # one pixel, one channel: a single 64-channel step, every tap but one outside
+    (1, 5, 127, 128, 33),      # two steps per slice; one pixel short of a tile; one channel in the second block
+    (2, 8, 8, 320, 96),        # five steps in slices of three: the last slice is padded
+    (3, 43, 1, 192, 160),      # images one pixel wide; one pixel more than a tile; five blocks in three phases
+    (1, 6, 200, 960, 40),      # rows so long that only some slices are resident at a time
+    (2, 33, 60, 448, 72),      # two pixel groups or one, padded slice, ragged channels
+    (5, 40, 40, 256, 200),     # seven channel blocks
+])
+def test_conv3x3(hq, nb, h, w, cin, cout):
+    """Per-tap sums and the sum over all taps bit for bit (the fp32 sums of the 6-bit instruction are exact below 2^24);
+    fp32 results to 1e-5: nine folds and at most two roundings more, each 6e-8 of sums below 8 x the result's."""
+    rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
+    xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
+    xq[0, 0, 0, :], wq[0, :, :, :] = -8, -8
+    sx = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
+    sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
+    bias = rng.standard_normal(cout).astype(np.float32)
+    xq_d, wq_d = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
+    acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
+    acc = host(hq.hq_int_conv2d(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o), "per-tap sums"
+    acc = host(hq.hq_int_conv2d_static(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o.sum(axis=3)), "one sum"
+    y = host(hq.hq_int_conv2d(xq_d, dev(sx), wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
+    check_y("y", y, y_o, rtol=1e-5)
+    s1 = torch.tensor([0.37], dtype=torch.float32, device="cuda")
+    _, y_o = oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1, want_acc=False)
+    y = host(hq.hq_int_conv2d_static(xq_d, s1, wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
+    check_y("y (static)", y, y_o, rtol=1e-5)
