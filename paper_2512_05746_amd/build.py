@@ -1,14 +1,18 @@
-"""Builds libhq.so (the C-ABI HIP library) in-tree for gfx950 with hipcc."""
+"""Builds libhq.so (the C-ABI HIP library) in-tree for gfx950 with hipcc, and the native part of its Python face
+(_marshal.so, host code only) with g++."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libhq.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
+MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = ["hq_hadamard_quant.hip", "hq_int_gemm.hip", "hq_int_gemm_128x128.hip",
            "hq_int_gemm_64x128.hip", "hq_int_gemm_64x64.hip", "hq_conv3x3_wave.hip", "hq_conv3x3_res.hip", "hq_conv3x3_fused.hip", "hq_resident.hip", "hq_resident_pertap.hip", "hq_resident_sum.hip", "hq_resident_linear.hip", "hq_linear_fused.hip", "hq_int_gemm_anyk.hip",
            "hq_single_weights.hip", "hq_width_quant.hip"]
@@ -29,11 +33,10 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
-        return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, h) for h in HEADERS] + [os.path.join(ROOT, "include", "hq.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
+    abi = os.path.join(ROOT, "include", "hq.h")
+    deps = {LIB: sources() + [os.path.join(CSRC, h) for h in HEADERS] + [abi], MARSHAL: [MARSHAL_SOURCE, abi]}
+    return any(not os.path.exists(out) or any(os.path.getmtime(d) > os.path.getmtime(out) for d in ds)
+               for out, ds in deps.items())
 
 
 def _run(cmd, verbose):
@@ -42,13 +45,27 @@ def _run(cmd, verbose):
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (os.path.basename(cmd[0]), out))
     if verbose and out.strip():
         print(out)
 
 
+def marshal_command(out: str):
+    """The g++ command of _marshal.so: PyTorch's headers and libraries, no device code."""
+    import torch
+    torch_dir = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include")]
+    for d in (os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+              os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem", d]
+    cmd += [MARSHAL_SOURCE, "-o", out, "-L", os.path.join(torch_dir, "lib")]
+    return cmd + ["-l" + lib for lib in ("torch_python", "torch", "torch_cpu", "torch_hip", "c10", "c10_hip")]
+
+
 def build_lib(verbose: bool = False) -> str:
-    """Compiles every source to an object (in parallel) and links libhq.so."""
+    """Compiles every source to an object (in parallel), links libhq.so and builds _marshal.so."""
     from concurrent.futures import ThreadPoolExecutor
 
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -57,6 +74,8 @@ def build_lib(verbose: bool = False) -> str:
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     objs = [os.path.join(objdir, os.path.basename(s) + ".%d.o" % os.getpid()) for s in sources()]
     jobs = [[hipcc] + HIPCC_FLAGS + inc + ["-c", src, "-o", obj] for src, obj in zip(sources(), objs)]
+    marshal_tmp = MARSHAL + ".tmp%d" % os.getpid()
+    jobs.insert(0, marshal_command(marshal_tmp))
     with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     tmp = LIB + ".tmp%d" % os.getpid()
@@ -64,6 +83,7 @@ def build_lib(verbose: bool = False) -> str:
     for o in objs:
         os.remove(o)
     os.replace(tmp, LIB)
+    os.replace(marshal_tmp, MARSHAL)
     return LIB
 
 
