@@ -31,6 +31,10 @@ constexpr uint32_t fp6_bits(uint32_t field, int a, int b, int c = -1) {
 __device__ __forceinline__ v16f mfma_fp6(const v8i &a, const v8i &b, const v16f &c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 0, 0, 0);
 }
+// the same product times 16 (block exponents 2^0 and 2^4)
+__device__ __forceinline__ v16f mfma_fp6_times16(const v8i &a, const v8i &b, const v16f &c) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 127, 0, 131);
+}
 
 // Two packed dwords -> three dwords of fields holding code + 8 (0..15, sign bit 0): the offset turns two's
 // complement into a magnitude by flipping one bit, which the masks do on the way (7 instructions for 16 codes).
@@ -64,6 +68,35 @@ __device__ __forceinline__ void fp6_signed16(uint32_t wa, uint32_t wb, int &d0, 
     d0 = static_cast<int>((ma & a0) | (r & b0) | (t & sa0) | (wb & sb0));
     d1 = static_cast<int>((ma & a1) | (r & b1) | (t & sa1) | (wb & sb1));
     d2 = static_cast<int>((ma & a2) | (r & b2) | (t & sa2) | (wb & sb2));
+}
+
+// Digits 1 and 2 of eight numbers in signed base 16 (w1, w2 one digit a nibble), taken together as d1 + 16 d2 for sums
+// in -16 .. 16: the low four bits of the magnitudes and, in bits 3 and 2 of each nibble, sign and sixteens bit.
+struct Fp6Parts { uint32_t low, top; };
+__device__ __forceinline__ Fp6Parts fp6_upper8(uint32_t w1, uint32_t w2) {
+    constexpr uint32_t ones = 0x11111111u;
+    const uint32_t n2 = w2 & ones;                                         // d2 is 1 or -1
+    const uint32_t sign = ((w1 >> 3) & ones & ~n2) | ((w2 >> 3) & ones);   // of d2, or of d1 where d2 is 0
+    uint32_t any = w1 | (w1 >> 1);
+    any = (any | (any >> 2)) & ones;                                       // d1 is not 0
+    const uint32_t neg = sign & any;
+    return {(w1 ^ ((neg << 4) - neg)) + neg, (sign << 3) | ((n2 & ~any) << 2)};
+}
+
+// Two such eights -> three dwords of signed fields of magnitude 0..16 (16 is E2M3's 10000b, again the number itself).
+__device__ __forceinline__ void fp6_upper16(uint32_t wa1, uint32_t wa2, uint32_t wb1, uint32_t wb2, int &d0, int &d1, int &d2) {
+    const Fp6Parts a = fp6_upper8(wa1, wa2), b = fp6_upper8(wb1, wb2);
+    const uint32_t r = __builtin_amdgcn_alignbit(b.low, b.low, 2);
+    const uint32_t t = __builtin_amdgcn_alignbit(a.top, a.top, 30);   // top bits of a's nibbles, two places up
+    constexpr uint32_t a0 = fp6_bits(15, 0, 12, 24), b0 = fp6_bits(15, 6, 18) | (3u << 30);
+    constexpr uint32_t a1 = fp6_bits(15, 4, 16, 28), b1 = fp6_bits(15, 10, 22) | 3u;
+    constexpr uint32_t a2 = fp6_bits(15, 8, 20), b2 = fp6_bits(15, 2, 14, 26);
+    constexpr uint32_t ta0 = fp6_bits(3, 4, 16, 28), tb0 = fp6_bits(3, 10, 22);
+    constexpr uint32_t ta1 = fp6_bits(3, 8, 20), tb1 = fp6_bits(3, 2, 14, 26);
+    constexpr uint32_t ta2 = fp6_bits(3, 0, 12, 24), tb2 = fp6_bits(3, 6, 18, 30);
+    d0 = static_cast<int>((a.low & a0) | (r & b0) | (t & ta0) | (b.top & tb0));
+    d1 = static_cast<int>((a.low & a1) | (r & b1) | (t & ta1) | (b.top & tb1));
+    d2 = static_cast<int>((a.low & a2) | (r & b2) | (t & ta2) | (b.top & tb2));
 }
 
 // Sum of the 8 codes of a packed dword, added to acc.

@@ -133,7 +133,7 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
         // 23 x 12 x 12 x 384: 13.6 against 16.8).
         if (c_in == 192 && conv_class(pixels, w, c_in, c_out, r, 1, bits) == kClassWave)
             return hq_conv3x3_wave_launch(a, y_dtype, st_);
-        st = hq_resident_launch(a, 9, y_dtype, st_);
+        st = hq_resident_launch(a, 0, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
     return launch_gemm(a, r * s, y_dtype, st_);
@@ -167,6 +167,12 @@ hq_status int_conv2d_width(const uint8_t *xu3, const float *x_scale, const uint8
         a.in_pixels = static_cast<uint32_t>(pixels);
         a.pixels = static_cast<uint32_t>(static_cast<int64_t>(nb) * a.h_out * a.w_out);
         return hq_gemm_launch_64x64(a, had_block <= 8 ? 18 : 27, y_dtype, static_cast<hipStream_t>(stream));
+    }
+    // The resident kernel adds all products in fp32, weights as 0..15: exact while 15 x (8 x block) x 9 c_in stays within
+    // 2^24.  (Its two operand planes hold digits 1 and 2 together up to block 32.)
+    if (had_block <= 32 && 15LL * 8 * had_block * 9 * c_in <= 1 << 24) {
+        st = hq_resident_launch(a, had_block, y_dtype, static_cast<hipStream_t>(stream));
+        if (st != HQ_ERR_UNSUPPORTED) return st;
     }
     // |q H_raw| <= 8 x block: up to block 8 the third digit plane is zero and its nine steps are skipped
     return launch_gemm(a, had_block <= 8 ? 18 : 27, y_dtype, static_cast<hipStream_t>(stream));

@@ -1,9 +1,8 @@
-// Integer GEMM / NHWC convolution of 4-bit codes on the 6-bit floating-point matrix instruction (hq_fp6.h), with
+// NHWC 3x3 convolution of 4-bit codes on the 6-bit floating-point matrix instruction (hq_fp6.h), with
 // the activation tile expanded once and resident in LDS.
 //
-// A workgroup owns XW groups of 128 consecutive pixels (tokens) and a run of blocks of 32 output channels; a wave's
-// result tile is 32 channels x 128 pixels.  The codes of the pixels - for a 3x3 window with those of W + 1 pixels
-// either side - are fetched once, expanded to 6-bit fields and kept in LDS as planes
+// A workgroup owns XW groups of 128 consecutive pixels and a run of blocks of 32 output channels; a wave's
+// result tile is 32 channels x 128 pixels.  The codes of the pixels, and those of W + 1 pixels either side, are fetched once, expanded to 6-bit fields and kept in LDS as planes
 //     [64-channel step][lane half][row] of 16-byte operand parts, then of 8-byte parts,
 // so that a wave's operand read of 32 consecutive rows is two contiguous runs for any row shift: 224 bytes per clock
 // and CU measured, against 126 with the halves of a row next to each other.  Weights go from memory straight into
@@ -27,6 +26,12 @@
 // time, then the remainder in powers of two, the units of a task shared by 2, 4 or 8 waves whose sums meet in
 // LDS in a fixed order.  So all waves multiply about the same number of units whatever the channel count is.
 //
+// Digit planes (the width-axis form).  The activations are numbers u = d0 + 16 d1 + 256 d2 in three planes of base-16
+// digits; d1 + 16 d2 lies in -16..16 up to transform block 32, which E2M3 still holds, so two operand planes are enough:
+// the fill combines the upper two, and their products are multiplied by 16 by the block exponent of the matrix
+// instruction.  A unit expands its weights once for both planes.  16 x 16 x 16 x 576, block 16: 33.8 us against 76.7 on the
+// tile kernel, which streams weights and all three planes through LDS.
+//
 // Weights carry an offset of 8 (hq_fp6.h): a sum exceeds the wanted one by 8 x (sum of the activation codes it
 // covers), the same for all channels: a per-pixel correction from a table of code sums.
 #pragma once
@@ -44,7 +49,8 @@ struct ResidentArgs {
     void *y;             // [pixels, n]; per-tap integer output [pixels, 9, n], zero-filled before the launch
     uint32_t pixels;
     int n, k, h, w;
-    int sx_static;
+    int in_planes;       // kResPlanes: planes that are not all zeros (2 or 3)
+    float out_scale;     // times the one scale
     uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
     int slices, chunk;             // K slices of KS steps, and how many are resident at a time
     int xw_log2;                   // pixel groups of 128 per workgroup
@@ -59,9 +65,9 @@ struct ResidentArgs {
 
 namespace {
 
-constexpr int kResLinear = 0;   // no window: one sum per output, scaled by the pixel's scale (or the one scale)
-constexpr int kResPerTap = 1;   // 3x3, per-pixel scales: one sum per tap, combined in fp32
-constexpr int kResSum = 2;      // 3x3, one scale: one sum over all taps
+constexpr int kResPerTap = 0;   // 3x3, per-pixel scales: one sum per tap, combined in fp32
+constexpr int kResSum = 1;      // 3x3, one scale: one sum over all taps
+constexpr int kResPlanes = 2;   // the same with activations u = d0 + 16 (d1 + 16 d2) in three digit planes, |d1 + 16 d2| <= 16
 
 // Barrier that orders LDS only: __syncthreads() would also wait for the wave's global loads (weights requested
 // ahead) and stores.
@@ -85,14 +91,14 @@ __device__ __forceinline__ void buffer_store16(const v4i &v, __amdgpu_buffer_rsr
 }
 
 __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
-    return (kind == kResPerTap ? 9 : 1) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
+    return (kind == kResPerTap ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
 }
 
 template <int OUT, int KIND, int KS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
-    constexpr bool WINDOW = KIND != kResLinear, FOLD = KIND == kResPerTap;
-    constexpr bool INT_TAPS = OUT == kOutI32 && FOLD;
-    constexpr int TAPS = WINDOW ? 9 : 1, NT = 4;
+    constexpr bool FOLD = KIND == kResPerTap, INT_TAPS = OUT == kOutI32 && FOLD;
+    constexpr int TAPS = 9, NT = 4;
+    constexpr int IN = KIND == kResPlanes ? 3 : 1, PL = KIND == kResPlanes ? 2 : 1;   // planes in memory, operand planes in LDS
     using Out = typename OutT<OUT>::type;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
@@ -101,7 +107,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cb = a.k >> 1, steps = a.k >> 6, rows = a.rows;
     const int px_wg = 128 << a.xw_log2;
-    const int halo = WINDOW ? a.w + 1 : 0;
+    const int halo = a.w + 1;
 
     // workgroup b runs on XCD b % 8: every XCD gets a contiguous run of tiles
     const uint32_t nwg = gridDim.x, xcd = blockIdx.x & 7, q8 = nwg >> 3, r8 = nwg & 7;
@@ -113,7 +119,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     const int blocks = min(a.cb, (a.n - c_wg + 31) / 32);   // channel blocks of this workgroup
 
     float *s_sx = reinterpret_cast<float *>(lds + a.tables);
-    float *s_corr = s_sx + (FOLD ? TAPS : 1) * px_wg;
+    float *s_corr = s_sx + (FOLD ? TAPS : 0) * px_wg;
     int *s_mask = reinterpret_cast<int *>(s_corr + px_wg);
     float *s_rowscale = reinterpret_cast<float *>(s_mask + px_wg);
     int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);
@@ -161,30 +167,44 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     const uint32_t last = a.pixels - 1;
     const int64_t row_pixel0 = static_cast<int64_t>(p0) - halo;
     const int f_row = lane >> 1, f_half = lane & 1;
-    const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, a.pixels * static_cast<uint32_t>(cb));
-    auto fill_load = [&](v4i (&p)[KS], int item) {
+    const uint32_t plane_bytes = a.pixels * static_cast<uint32_t>(cb);
+    const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, IN * plane_bytes);
+    auto fill_load = [&](v4i (&p)[IN][KS], int item) {
         const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
         // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
         const uint32_t off = (static_cast<uint32_t>(p0) - halo + row) * cb + f_half * 16;
 #pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            p[k] = v4i{0, 0, 0, 0};
-            if ((s0 + sl) * KS + k < steps) p[k] = buffer_load16(x_buf, off, ((s0 + sl) * KS + k) * 32);
-        }
+        for (int i = 0; i < IN; ++i)
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                p[i][k] = v4i{0, 0, 0, 0};
+                if ((s0 + sl) * KS + k < steps && i < a.in_planes)
+                    p[i][k] = buffer_load16(x_buf, off, i * plane_bytes + ((s0 + sl) * KS + k) * 32);
+            }
     };
-    auto fill_store = [&](const v4i (&p)[KS], int item) {
+    auto fill_store = [&](const v4i (&p)[IN][KS], int item) {
         const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
         int sum = 0;
         if (row < rows - 1) {
 #pragma unroll
             for (int k = 0; k < KS; ++k) {
+                auto codes = [&](const v4i &v, int s) { return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s)))); };
+                auto put = [&](int plane, const int (&d)[6]) {
+                    const int at = (((sl * PL + plane) * KS + k) * 2 + f_half) * rows + row;
+                    *reinterpret_cast<v4i *>(lds + at * 16) = v4i{d[0], d[1], d[2], d[3]};
+                    *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{d[4], d[5]};
+                };
                 int d[6];
-                fp6_signed16(p[k].x, p[k].y, d[0], d[1], d[2]);
-                fp6_signed16(p[k].z, p[k].w, d[3], d[4], d[5]);
-                const int at = ((sl * KS + k) * 2 + f_half) * rows + row;
-                *reinterpret_cast<v4i *>(lds + at * 16) = v4i{d[0], d[1], d[2], d[3]};
-                *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{d[4], d[5]};
-                sum = sum_codes8(p[k].x, sum_codes8(p[k].y, sum_codes8(p[k].z, sum_codes8(p[k].w, sum))));
+                fp6_signed16(p[0][k].x, p[0][k].y, d[0], d[1], d[2]);
+                fp6_signed16(p[0][k].z, p[0][k].w, d[3], d[4], d[5]);
+                put(0, d);
+                sum = codes(p[0][k], sum);
+                if constexpr (KIND == kResPlanes) {
+                    fp6_upper16(p[1][k].x, p[2][k].x, p[1][k].y, p[2][k].y, d[0], d[1], d[2]);
+                    fp6_upper16(p[1][k].z, p[2][k].z, p[1][k].w, p[2][k].w, d[3], d[4], d[5]);
+                    put(1, d);
+                    sum += 16 * codes(p[1][k], 0) + 256 * codes(p[2][k], 0);
+                }
             }
         }
         sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
@@ -192,16 +212,16 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     };
 
     // All first loads are requested before any is waited for (a first use costs a trip to HBM).
-    v4i p[2][KS];
+    v4i p[2][IN][KS];
     begin_task();
     const int first_items = row_items * (s1 - s0);
     fill_load(p[0], wv < first_items ? wv : 0);
     load_weights(u / (s1 - s0), u % (s1 - s0));
-    constexpr bool ROW_SCALES = KIND != kResSum && OUT != kOutI32;
+    constexpr bool ROW_SCALES = FOLD && !INT_TAPS;
     auto row_scale = [&](int i) {
         int64_t pix = row_pixel0 + i;
         pix = pix < 0 ? 0 : (pix > static_cast<int64_t>(last) ? last : pix);
-        return a.sx[a.sx_static ? 0 : pix];
+        return a.sx[pix];
     };
     float t_scale[2] = {}, t_sw = 0.f, t_bias = 0.f;
     if constexpr (ROW_SCALES) {
@@ -214,7 +234,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         t_bias = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
     }
     for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
-    for (int i = tid; i < resident0 * KS * 2; i += nt) {   // the row of zeros
+    for (int i = tid; i < resident0 * PL * KS * 2; i += nt) {   // the row of zeros
         const int at = i * rows + rows - 1;
         *reinterpret_cast<v4i *>(lds + at * 16) = v4i{0, 0, 0, 0};
         *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{0, 0};
@@ -252,39 +272,34 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         // tables of the pixels: tap masks, scales under the taps, corrections
         for (int i = tid; i < px_wg; i += nt) {
             const uint32_t pix = p0 + i;
-            if constexpr (WINDOW) {
-                const uint32_t q = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
-                const int ow = static_cast<int>(pix - q * a.w);
-                const int oh = static_cast<int>(q - hq::div_magic31(q, a.h, a.h_magic, a.h_shift) * a.h);
-                const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
-                int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
-                if (pix >= a.pixels) mask = 0;
-                s_mask[i] = mask;
-                float corr = 0.f;
+            const uint32_t q = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
+            const int ow = static_cast<int>(pix - q * a.w);
+            const int oh = static_cast<int>(q - hq::div_magic31(q, a.h, a.h_magic, a.h_shift) * a.h);
+            const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
+            int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
+            if (pix >= a.pixels) mask = 0;
+            s_mask[i] = mask;
+            float corr = 0.f;
 #pragma unroll
-                for (int t = 0; t < 9; ++t) {
-                    const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
-                    const bool in = (mask >> t) & 1;
-                    if constexpr (FOLD && !INT_TAPS) {
-                        // (a product of two codes is 1/64 in the matrix instruction's units)
-                        const float s = in ? s_rowscale[row] : 0.f;
-                        s_sx[t * px_wg + i] = s * 64.0f;
-                        corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
-                    } else if (in) {
-                        corr += 8.0f * static_cast<float>(s_sum[row]);
-                    }
+            for (int t = 0; t < 9; ++t) {
+                const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
+                const bool in = (mask >> t) & 1;
+                if constexpr (FOLD && !INT_TAPS) {
+                    // (a product of two codes is 1/64 in the matrix instruction's units)
+                    const float s = in ? s_rowscale[row] : 0.f;
+                    s_sx[t * px_wg + i] = s * 64.0f;
+                    corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
+                } else if (in) {
+                    corr += 8.0f * static_cast<float>(s_sum[row]);
                 }
-                s_corr[i] = corr;   // (of all slices once the last chunk is resident)
-            } else {
-                s_corr[i] = 8.0f * static_cast<float>(s_sum[i]);
-                if constexpr (OUT != kOutI32) s_sx[i] = s_rowscale[i];
             }
+            s_corr[i] = corr;   // (of all slices once the last chunk is resident)
         }
         lds_barrier();
 
         for (;;) {   // phases
             int mask[NT];   // kResSum / INT_TAPS: taps inside the image, for the pixels of the four tiles
-            if constexpr (KIND == kResSum || INT_TAPS) {
+            if constexpr (!FOLD || INT_TAPS) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) mask[t] = s_mask[px_l + t * 32 + l];
             }
@@ -296,13 +311,13 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             const int plane16 = rows * 32, plane8 = rows * 16;   // from step to step
             struct Base { int b16, b8; };
             auto base_of = [&](int tap, int sl) {
-                const int shift = WINDOW ? (tap / 3 - 1) * a.w + tap % 3 - 1 : 0;
-                const int at = (sl * KS * 2 + h) * rows + lane_row;
+                const int shift = (tap / 3 - 1) * a.w + tap % 3 - 1;
+                const int at = (sl * PL * KS * 2 + h) * rows + lane_row;
                 return Base{(at + shift) * 16, static_cast<int>(a.part8) + (at + shift) * 8};
             };
-            auto load_tile = [&](v8i (&b)[KS], const Base &base, int tap, int t) {
-                int b16 = base.b16, b8 = base.b8, imm = t;
-                if constexpr (KIND == kResSum) {   // taps outside the image read the row of zeros
+            auto load_tile = [&](v8i (&b)[KS], const Base &base, int tap, int t, int plane) {
+                int b16 = base.b16 + plane * KS * plane16, b8 = base.b8 + plane * KS * plane8, imm = t;
+                if constexpr (!FOLD) {   // taps outside the image read the row of zeros
                     const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1;
                     const int to = (mask[t] >> tap) & 1 ? t * 32 : rows - 1 - row;
                     b16 += to * 16;
@@ -320,7 +335,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             // the next unit's weights are requested as soon as this unit's are expanded.
             Base base = base_of(tap, sl);
             v8i w6[KS], b[2][KS];
-            load_tile(b[0], base, tap, 0);
+            load_tile(b[0], base, tap, 0, 0);
             for (; u < u_end; ++u) {
                 int tap1 = tap, sl1 = sl;   // the next unit (the last one's operands are requested twice)
                 if (u + 1 < u_end) {
@@ -361,16 +376,21 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 };
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    if (t + 1 < NT) load_tile(b[(t + 1) & 1], base, tap, t + 1);
-                    else load_tile(b[0], base1, tap1, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    v16f c = mfma_fp6(w6[0], b[t & 1][0], FOLD ? v16f{} : sum[t]);
 #pragma unroll
-                    for (int k = 1; k < KS; ++k) c = mfma_fp6(w6[k], b[t & 1][k], c);
-                    if constexpr (FOLD) acc[t & 1] = c;
-                    else sum[t] = c;
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (t > 0) fold(t - 1);
+                    for (int plane = 0; plane < PL; ++plane) {
+                        const int now = t * PL + plane, next = now + 1;
+                        if (next < NT * PL) load_tile(b[next & 1], base, tap, next / PL, next % PL);
+                        else load_tile(b[0], base1, tap1, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        v16f c = FOLD ? v16f{} : sum[t];
+#pragma unroll
+                        for (int k = 0; k < KS; ++k)
+                            c = plane ? mfma_fp6_times16(w6[k], b[now & 1][k], c) : mfma_fp6(w6[k], b[now & 1][k], c);
+                        if constexpr (FOLD) acc[t & 1] = c;
+                        else sum[t] = c;
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (t > 0 && plane == 0) fold(t - 1);
+                    }
                 }
                 fold(NT - 1);
                 tap = tap1;
@@ -441,15 +461,15 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     if (kl >= 3) half0 = exchange(std::integral_constant<int, 8>{}, 1);
                 }
 
-                const float one_scale = (KIND == kResSum && OUT != kOutI32) ? a.sx[0] : 1.0f;
-                // results of eight sums v of a pixel with correction corr and scale s, channels ct .. ct + 7 (in the workgroup)
-                auto scaled = [&](const float (&v)[8], float corr, float s, const float *sw, const float *bias, Out (&res)[8]) {
+                const float one_scale = !FOLD && OUT != kOutI32 ? a.sx[0] * a.out_scale : 1.0f;
+                // results of eight sums v of a pixel with correction corr, channels ct .. ct + 7 (in the workgroup)
+                auto scaled = [&](const float (&v)[8], float corr, const float *sw, const float *bias, Out (&res)[8]) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         if constexpr (OUT == kOutI32) {
                             res[i] = static_cast<int>(v[i] * 64.0f - corr);
                         } else {
-                            const float r = FOLD ? v[i] - corr : (v[i] * 64.0f - corr) * s;
+                            const float r = FOLD ? v[i] - corr : (v[i] * 64.0f - corr) * one_scale;
                             const float y = fmaf(r, sw[i], bias[i]);
                             if constexpr (OUT == kOutF16) res[i] = __float2half_rn(y);
                             else res[i] = y;
@@ -471,13 +491,12 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     }
                 };
                 const int ct = c0 - c_wg + 16 * h;
-                auto pixel_scale = [&](int px) { return KIND == kResLinear && OUT != kOutI32 ? s_sx[px] : one_scale; };
                 if (kl < 3) {
                     // fp16: through LDS, [pixel][four 16-byte pieces] of 2 KiB per tile, so that four neighbouring lanes
                     // store the 64 contiguous bytes of a pixel instead of every lane a piece of its own (after an
                     // exchange in the area of the last partner, which nobody else reads)
                     uint8_t *const stage = lds + a.exchange + (kl ? wv ^ 1 : wv) * 8192;
-                    float sw[16], bias[16], corr[NT], ps[NT];
+                    float sw[16], bias[16], corr[NT];
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         sw[i] = OUT != kOutI32 ? s_sw[ct + i] : 0.f;
@@ -487,7 +506,6 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     for (int t = 0; t < NT; ++t) {
                         const int px = px_l + ((tile0 + t) & (NT - 1)) * 32 + l;
                         corr[t] = s_corr[px];
-                        ps[t] = pixel_scale(px);
                     }
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -499,7 +517,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                             float v[8];
 #pragma unroll
                             for (int i = 0; i < 8; ++i) v[i] = sum[t][8 * half + i];
-                            scaled(v, corr[t], ps[t], sw + 8 * half, bias + 8 * half, res[half]);
+                            scaled(v, corr[t], sw + 8 * half, bias + 8 * half, res[half]);
                         }
                         if constexpr (OUT == kOutF16) {
 #pragma unroll
@@ -537,7 +555,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         bias[i] = OUT != kOutI32 ? s_bias[ct + 8 * half0 + i] : 0.f;
                     }
                     Out res[8];
-                    scaled(v, s_corr[px], pixel_scale(px), sw, bias, res);
+                    scaled(v, s_corr[px], sw, bias, res);
                     store8(res, px, c0 + 16 * h + 8 * half0);
                 }
             }

@@ -1,8 +1,8 @@
-// Activation-resident kernel: linear and 1x1 layers (hq_resident_kernel.h).
+// Activation-resident kernel: 3x3 windows with one scale, activations as three digit planes (hq_resident_kernel.h).
 #include "hq_resident_kernel.h"
 
-const void *hq_resident_linear(int out, int ks) {
-    constexpr int KIND = kResLinear;
+const void *hq_resident_planes(int out, int ks) {
+    constexpr int KIND = kResPlanes;
 #define HQ_RES(O) \
     if (out == O) return ks == 1 ? reinterpret_cast<const void *>(resident_kernel<O, KIND, 1>) \
                        : ks == 2 ? reinterpret_cast<const void *>(resident_kernel<O, KIND, 2>) \

@@ -56,3 +56,38 @@ def test_conv3x3(hq, nb, h, w, cin, cout):
     _, y_o = oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1, want_acc=False)
     y = host(hq.hq_int_conv2d_static(xq_d, s1, wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
     check_y("y (static)", y, y_o, rtol=1e-5)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout,block", [
+    (1, 3, 8, 64, 1, 8),         # two planes; one channel
+    (2, 5, 16, 128, 40, 16),     # two steps per slice
+    (1, 7, 64, 320, 96, 32),     # upper digits up to +-16, padded slice
+    (2, 9, 48, 960, 72, 16),     # the largest sums that go this way; some slices resident at a time
+    (1, 3, 48, 192, 33, 1),      # no transform
+    (1, 2, 64, 512, 40, 32),     # sums beyond 2^24: the tile kernel
+])
+def test_conv_width(hq, nb, h, w, cin, cout, block):
+    """Integer sums bit for bit, extreme numbers (+-8 x block) among them; fp32 results to 1e-6 (three roundings)."""
+    rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout + block)
+    q = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
+    q[0, 0, :, : cin // 2], wq[0] = -8, 7   # a flat line: one number of -8 x block
+    signs = np.ones(block)
+    for b in range(block.bit_length() - 1):
+        signs *= np.where(np.arange(block) >> b & 1, -1, 1)
+    q[-1, -1, :, cin // 2:] = np.tile(np.where(signs < 0, -8, 7), w // block)[:, None]   # nearly +8 x block
+    hb = np.array([[(-1) ** bin(i & j).count("1") for j in range(block)] for i in range(block)])
+    u = np.einsum("nhbic,ij->nhbjc", q.astype(np.int64).reshape(nb, h, w // block, block, cin), hb).reshape(nb, h, w, cin)
+    d0 = (u + 8) % 16 - 8
+    r1 = (u - d0) // 16
+    d1 = (r1 + 8) % 16 - 8
+    planes = dev(pack_codes(np.stack([d0, d1, (r1 - d1) // 16]).astype(np.int8)))
+    sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
+    bias = rng.standard_normal(cout).astype(np.float32)
+    wq_d = dev(pack_codes(wq.reshape(cout, 9, cin)))
+    s1 = torch.tensor([0.37], dtype=torch.float32, device="cuda")
+    acc_o, y_o = oracle.int_conv2d_width(q, 0.37, wq, sw, block, bias, stride=1, pad=1)
+    acc = host(hq.hq_int_conv2d_width(planes, None, wq_d, None, None, block, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o)
+    y = host(hq.hq_int_conv2d_width(planes, s1, wq_d, dev(sw), dev(bias), block, y_dtype=torch.float32))
+    check_y("y", y, y_o, rtol=1e-6)
