@@ -5,7 +5,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle
-from parity_util import check_y, pack_codes
+from parity_util import check_codes, check_y, pack_codes, unpack_codes
 
 pytestmark = pytest.mark.gpu
 
@@ -91,3 +91,52 @@ def test_conv_width(hq, nb, h, w, cin, cout, block):
     assert np.array_equal(acc, acc_o)
     y = host(hq.hq_int_conv2d_width(planes, s1, wq_d, dev(sw), dev(bias), block, y_dtype=torch.float32))
     check_y("y", y, y_o, rtol=1e-6)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (1, 1, 1, 64, 1),          # one pixel, one channel: a single 64-channel step
+    (1, 5, 127, 128, 33),      # two steps per slice; one pixel short of a tile; one channel in the second block
+    (3, 43, 1, 320, 160),      # images one pixel wide; the last slice is padded; five blocks
+    (1, 6, 200, 960, 40),      # rows so long that only some slices are resident at a time
+    (2, 33, 60, 448, 72),      # padded slice, ragged channels
+])
+def test_conv3x3_8bit(hq, nb, h, w, cin, cout):
+    """8-bit codes, extreme ones among them: per-tap sums bit for bit (within 192 channels they stay below 2^24); fp32
+    results to 1e-5: at most nine folds a slice and two roundings more, each 6e-8 of sums below 8 x the result's."""
+    rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
+    xq = rng.integers(-128, 128, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-128, 128, (cout, 3, 3, cin)).astype(np.int8)
+    xq[0, 0, 0, :], wq[0, :, :, :] = -128, -128
+    sx = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
+    sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
+    bias = rng.standard_normal(cout).astype(np.float32)
+    xq_d, wq_d = dev(xq), dev(wq.reshape(cout, 9, cin))
+    acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
+    acc = host(hq.hq_int_conv2d_i8(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o), "per-tap sums"
+    y = host(hq.hq_int_conv2d_i8(xq_d, dev(sx), wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
+    check_y("y", y, y_o, rtol=1e-5)
+
+
+@pytest.mark.parametrize("dtype", [np.float16, np.float32])
+@pytest.mark.parametrize("w,c,block", [
+    (6, 2, 2),        # one channel pair
+    (8, 6, 8),        # no whole quad of pairs: bytes
+    (12, 8, 4),       # one quad, one pixel group
+    (64, 24, 64),     # the largest block; three quads
+    (16, 1032, 16),   # more pairs than a workgroup's threads, the second pass nearly empty
+    (5, 520, 1),      # no transform
+])
+def test_width_quant(hq, dtype, w, c, block):
+    """The planes hold q H_raw exactly for codes q that are the oracle's (but for values on a rounding tie)."""
+    rng = np.random.default_rng(w + c + block)
+    x = rng.standard_normal((2, 3, w, c)).astype(dtype)
+    scale = 0.3   # clamps at both ends
+    q_o, t = oracle.act_width_quant_static(x, block, 4, float(np.float32(scale)))
+    xu3 = host(hq.hq_act_hadamard_quant_width(dev(x), torch.tensor([scale], device="cuda"), block, 4))
+    d = unpack_codes(xu3).astype(np.int64)
+    hb = np.array([[(-1) ** bin(i & j).count("1") for j in range(block)] for i in range(block)])
+    u = (d[0] + 16 * d[1] + 256 * d[2]).reshape(2, 3, w // block, block, c)
+    back = np.einsum("nhbic,ij->nhbjc", u, hb).reshape(x.shape)
+    assert (back % block == 0).all()
+    check_codes("codes", (back // block).astype(np.int8), q_o, t, 4)
