@@ -126,12 +126,12 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
         return hq_gemm_launch_64x64(a, 9, y_dtype, st_);
     }
     if (c_in % 64 != 0) return hq_gemm_launch_anyk(a, r * s, y_dtype, st_);
-    if (bits == 4 && r == 3) {
+    if (r == 3) {
         // One 192-channel slice and so few tiles that the K range is split over waves anyway: the wave-split kernel,
         // which has no activation tile to expand first (1 x 64 x 64 x 192: 8.4 us against 9.2; 1 x 16 x 16 x 192 -> 100:
         // 8.6 against 9.4).  From two slices on the resident kernel wins there too (16 x 8 x 8 x 960: 15.4 against 17.8,
-        // 23 x 12 x 12 x 384: 13.6 against 16.8).
-        if (c_in == 192 && conv_class(pixels, w, c_in, c_out, r, 1, bits) == kClassWave)
+        // 23 x 12 x 12 x 384: 13.6 against 16.8).  8-bit codes go there at all sizes (hq_resident_kernel.h).
+        if (bits == 4 && c_in == 192 && conv_class(pixels, w, c_in, c_out, r, 1, bits) == kClassWave)
             return hq_conv3x3_wave_launch(a, y_dtype, st_);
         st = hq_resident_launch(a, 0, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;

@@ -947,7 +947,7 @@ hq_status hq_fill_zero_launch(void *dst, uint64_t ints, hipStream_t stream);
 // size classes of the one-launch 3x3 layer (hq_conv3x3_res.hip)
 bool hq_conv3x3_res_fits(int64_t pixels, int w, int c_in, int c_out);
 int hq_conv3x3_res_tile_pixels(int64_t pixels, int w, int c_in, int c_out);
-// 3x3 layers of stride 1 and 4-bit codes, k a multiple of 64, on the 6-bit floating-point matrix instruction
+// 3x3 layers of stride 1, k a multiple of 64: 4-bit codes on the 6-bit floating-point matrix instruction, 8-bit on int8
 // (hq_resident.hip); had_block != 0: the activations are digit planes of a transform of that block, at most 32;
 // HQ_ERR_UNSUPPORTED, with nothing launched, if a tile does not fit the LDS
 hq_status hq_resident_launch(const GemmArgs &a, int had_block, hq_dtype y_dtype, hipStream_t stream);

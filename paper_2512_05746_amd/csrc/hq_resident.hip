@@ -7,6 +7,7 @@
 const void *hq_resident_pertap(int out, int ks);
 const void *hq_resident_sum(int out, int ks);
 const void *hq_resident_planes(int out, int ks);
+const void *hq_resident_bytes(int out, int ks);
 
 namespace {
 
@@ -36,13 +37,14 @@ Plan lay_out(int kind, int w, int k, int n, int ks, int nw, int xw_log2, int cb,
     auto one_phase_of = [&](int t) { return (t & (t - 1)) == 0 && t < nw; };
     const bool overlay = one_phase_of(tasks) && one_phase_of(last);
     const int area = nw * 8192;
-    const int ops = ks * (kind == kResPlanes ? 2 : 1);   // operands of a row, lane half and slice
-    const int slice_bytes = p.rows * ops * 48;
+    const int ops = ks * (kind >= kResPlanes ? 2 : 1);   // operands of a row, lane half and slice
+    const int part8_bytes = kind == kResBytes ? 0 : 16;   // (8-bit codes are 16-byte operands)
+    const int slice_bytes = p.rows * ops * (32 + part8_bytes);
     p.chunk = std::min(p.slices, (budget - tables - (overlay ? 0 : area)) / slice_bytes);
     if (p.chunk < 1 || (p.chunk < p.slices && !overlay)) return p;
     p.part8 = static_cast<uint32_t>(p.rows) * p.chunk * ops * 32;
     p.part8 = (p.part8 + 15) & ~15u;
-    const uint32_t act_end = (static_cast<uint32_t>(p.part8) + static_cast<uint32_t>(p.rows) * p.chunk * ops * 16 + 15) & ~15u;
+    const uint32_t act_end = (static_cast<uint32_t>(p.part8) + static_cast<uint32_t>(p.rows) * p.chunk * ops * part8_bytes + 15) & ~15u;
     // (an area over the tile costs nothing up to the tile's size, or up to the budget of the only workgroup of a CU)
     p.wide = overlay && nw * 16384 + tables <= budget;
     p.exchange = overlay ? 0 : act_end;
@@ -56,13 +58,13 @@ Plan lay_out(int kind, int w, int k, int n, int ks, int nw, int xw_log2, int cb,
 // them, and in the measured order of the cuts): start and first loads, filling (rounds of 32-row items over the waves),
 // units (two waves per SIMD share the vector issue), results (each exchange of sums costs two barriers).
 double cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
-    const int px = 128 << p.xw_log2, blocks = (n + 31) / 32, planes = kind == kResPlanes ? 2 : 1;
+    const int px = 128 << p.xw_log2, blocks = (n + 31) / 32, planes = kind >= kResPlanes ? 2 : 1;
     const int64_t wgs = (pixels + px - 1) / px * ((blocks + p.cb - 1) / p.cb);
     const int per_cu = p.nw == 4 && p.lds <= kLdsPerCu / 2 ? 2 : 1;
     const double rounds = static_cast<double>((wgs + static_cast<int64_t>(cus) * per_cu - 1) / (static_cast<int64_t>(cus) * per_cu));
     const bool paired = p.nw == 8 || (per_cu == 2 && wgs > cus);
     const int items = (p.rows - 1 + 31) / 32 * p.slices;
-    double clocks = 6500 + 2000 + (paired ? 700.0 : 450.0) * (2 * planes - 1) * p.ks * ((items + p.nw - 1) / p.nw);
+    double clocks = 6500 + 2000 + (paired ? 700.0 : 450.0) * (kind == kResBytes ? 0.5 : 2 * planes - 1) * p.ks * ((items + p.nw - 1) / p.nw);
     for (int left = std::min(blocks, p.cb) << p.xw_log2; left > 0;) {
         int kl = 0;
         while ((p.nw >> kl) > left) ++kl;
@@ -105,14 +107,14 @@ hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
 // HQ_ERR_UNSUPPORTED, with nothing launched: the image rows are too long for a tile and its halo.
 hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
-    const int kind = had_block ? kResPlanes : g.sx_static ? kResSum : kResPerTap;
+    const int kind = g.bits == 8 ? kResBytes : had_block ? kResPlanes : g.sx_static ? kResSum : kResPerTap;
     if (g.n >= 1 << 21) return HQ_ERR_UNSUPPORTED;   // (a tile's results lie within 2 GiB of their first)
     const Plan p = choose_plan(kind, g.pixels, g.w, g.k, g.n);
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
     ResidentArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
     a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.h = g.h; a.w = g.w;
-    a.in_planes = !had_block ? 1 : had_block <= 8 ? 2 : 3;   // |u| <= 8 x block
+    a.in_planes = kind == kResBytes ? 2 : !had_block ? 1 : had_block <= 8 ? 2 : 3;   // |u| <= 8 x block
     a.out_scale = g.out_scale;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
@@ -129,14 +131,15 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     const hq::Magic31 md = hq::magic31(a.ch_major ? a.px_tiles : a.ch_groups);
     a.d_magic = md.m; a.d_shift = md.s;
     const int out = y_dtype == HQ_F16 ? kOutF16 : y_dtype == HQ_F32 ? kOutF32 : kOutI32;
-    if (out == kOutI32 && kind == kResPerTap) {
+    if (out == kOutI32 && (kind == kResPerTap || kind == kResBytes)) {
         const hq_status st = hq_fill_zero_launch(g.y, static_cast<uint64_t>(g.pixels) * 9 * g.n, stream);
         if (st != HQ_OK) return st;
     }
-    const void *fn = kind == kResPlanes ? hq_resident_planes(out, p.ks)
+    const void *fn = kind == kResBytes    ? hq_resident_bytes(out, p.ks)
+                     : kind == kResPlanes ? hq_resident_planes(out, p.ks)
                      : kind == kResSum  ? hq_resident_sum(out, p.ks)
                                         : hq_resident_pertap(out, p.ks);
-    static std::atomic<uint64_t> allowed[3][3][3];
+    static std::atomic<uint64_t> allowed[4][3][3];
     const hq_status st = allow_lds(fn, allowed[kind][out][p.ks - 1]);
     if (st != HQ_OK) return st;
     void *args[] = {&a};

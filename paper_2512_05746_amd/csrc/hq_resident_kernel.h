@@ -32,7 +32,14 @@
 // instruction.  A unit expands its weights once for both planes.  16 x 16 x 16 x 576, block 16: 33.8 us against 76.7 on the
 // tile kernel, which streams weights and all three planes through LDS.
 //
-// Weights carry an offset of 8 (hq_fp6.h): a sum exceeds the wanted one by 8 x (sum of the activation codes it
+// 8-bit codes (the form of 16-byte operands on v_mfma_i32_32x32x32_i8, nothing to expand on either side; the two
+// 32-channel halves of a step take the places of two operand planes, each with weights of its own).  Matrix time is twice
+// that of 4-bit codes and the fold converts 16 values more per tile; matrix and vector time add up almost fully here as
+// there.  us per pass with the quantiser, tile kernel -> this one: 16 x 32 x 32 x 384 51.5 -> 44.1, 16 x 64 x 64 x 192
+// 63.7 -> 45.1, 16 x 16 x 16 x 576 44.0 -> 32.1, 16 x 8 x 8 x 960 48.2 -> 22.5, 3 x 45 x 27 x 320 -> 200 51.3 -> 15.9,
+// 1 x 8 x 8 x 64 (launch) 26.7 -> 11.2: faster at every size tried.
+//
+// Weights carry an offset of 8 (hq_fp6.h; not those of 8 bits): a sum exceeds the wanted one by 8 x (sum of the activation codes it
 // covers), the same for all channels: a per-pixel correction from a table of code sums.
 #pragma once
 #include <type_traits>
@@ -67,6 +74,7 @@ namespace {
 
 constexpr int kResPerTap = 0;   // 3x3, per-pixel scales: one sum per tap, combined in fp32
 constexpr int kResSum = 1;      // 3x3, one scale: one sum over all taps
+constexpr int kResBytes = 3;    // as kResPerTap, with 8-bit codes on the int8 instruction
 constexpr int kResPlanes = 2;   // the same with activations u = d0 + 16 (d1 + 16 d2) in three digit planes, |d1 + 16 d2| <= 16
 
 // Barrier that orders LDS only: __syncthreads() would also wait for the wave's global loads (weights requested
@@ -91,21 +99,26 @@ __device__ __forceinline__ void buffer_store16(const v4i &v, __amdgpu_buffer_rsr
 }
 
 __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
-    return (kind == kResPerTap ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
+    return (kind == kResPerTap || kind == kResBytes ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
 }
 
 template <int OUT, int KIND, int KS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
-    constexpr bool FOLD = KIND == kResPerTap, INT_TAPS = OUT == kOutI32 && FOLD;
+    constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
     constexpr int TAPS = 9, NT = 4;
-    constexpr int IN = KIND == kResPlanes ? 3 : 1, PL = KIND == kResPlanes ? 2 : 1;   // planes in memory, operand planes in LDS
+    // planes in memory, operand planes in LDS (BYTES: the two 32-channel halves of a step) and of the weights
+    constexpr int IN = KIND == kResPlanes ? 3 : BYTES ? 2 : 1, PL = KIND == kResPlanes || BYTES ? 2 : 1, WP = BYTES ? 2 : 1;
+    constexpr int STEP = BYTES ? 64 : 32;   // bytes of a step of 64 codes
     using Out = typename OutT<OUT>::type;
+    using Operand = std::conditional_t<BYTES, v4i, v8i>;
+    using Acc = std::conditional_t<BYTES, v16i, v16f>;
+    constexpr float UNIT = BYTES ? 1.0f : 64.0f;   // a product of two codes is 1 / UNIT in the accumulators
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
     const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6;
     const int lane = tid & 63, l = lane & 31, h = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cb = a.k >> 1, steps = a.k >> 6, rows = a.rows;
+    const int cb = BYTES ? a.k : a.k >> 1, steps = a.k >> 6, rows = a.rows;
     const int px_wg = 128 << a.xw_log2;
     const int halo = a.w + 1;
 
@@ -149,11 +162,13 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         u_end = (share + 1) * units >> kl;
     };
     // unit u of the resident slices: tap u / (s1 - s0), slice s0 + u % (s1 - s0)
-    v4i raw[KS];   // packed weights of the next unit
+    v4i raw[WP][KS];   // weights of the next unit as they lie in memory
     const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
     auto load_weight = [&](int k, int tap, int slice) {
         const int step = slice * KS + k < steps ? slice * KS + k : 0;   // (past the channels: activations are zero)
-        raw[k] = buffer_load16(w_buf, w_lane, static_cast<uint32_t>(tap * cb + step * 32));
+#pragma unroll
+        for (int i = 0; i < WP; ++i)
+            raw[i][k] = buffer_load16(w_buf, w_lane, static_cast<uint32_t>(tap * cb + step * STEP + i * 32));
     };
     auto load_weights = [&](int tap, int slice) {
 #pragma unroll
@@ -168,7 +183,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     const int64_t row_pixel0 = static_cast<int64_t>(p0) - halo;
     const int f_row = lane >> 1, f_half = lane & 1;
     const uint32_t plane_bytes = a.pixels * static_cast<uint32_t>(cb);
-    const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, IN * plane_bytes);
+    const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, BYTES ? plane_bytes : IN * plane_bytes);
     auto fill_load = [&](v4i (&p)[IN][KS], int item) {
         const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
         // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
@@ -179,7 +194,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             for (int k = 0; k < KS; ++k) {
                 p[i][k] = v4i{0, 0, 0, 0};
                 if ((s0 + sl) * KS + k < steps && i < a.in_planes)
-                    p[i][k] = buffer_load16(x_buf, off, i * plane_bytes + ((s0 + sl) * KS + k) * 32);
+                    p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + ((s0 + sl) * KS + k) * STEP);
             }
     };
     auto fill_store = [&](const v4i (&p)[IN][KS], int item) {
@@ -188,6 +203,12 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         if (row < rows - 1) {
 #pragma unroll
             for (int k = 0; k < KS; ++k) {
+                if constexpr (BYTES) {
+#pragma unroll
+                    for (int i = 0; i < PL; ++i)
+                        *reinterpret_cast<v4i *>(lds + ((((sl * PL + i) * KS + k) * 2 + f_half) * rows + row) * 16) = p[i][k];
+                    continue;
+                }
                 auto codes = [&](const v4i &v, int s) { return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s)))); };
                 auto put = [&](int plane, const int (&d)[6]) {
                     const int at = (((sl * PL + plane) * KS + k) * 2 + f_half) * rows + row;
@@ -207,8 +228,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 }
             }
         }
-        sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
-        if (f_half == 0 && row < rows - 1) atomicAdd(&s_sum[row], sum);
+        if constexpr (!BYTES) {
+            sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
+            if (f_half == 0 && row < rows - 1) atomicAdd(&s_sum[row], sum);
+        }
     };
 
     // All first loads are requested before any is waited for (a first use costs a trip to HBM).
@@ -237,7 +260,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     for (int i = tid; i < resident0 * PL * KS * 2; i += nt) {   // the row of zeros
         const int at = i * rows + rows - 1;
         *reinterpret_cast<v4i *>(lds + at * 16) = v4i{0, 0, 0, 0};
-        *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{0, 0};
+        if constexpr (!BYTES) *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{0, 0};
     }
     if constexpr (ROW_SCALES) {
         if (tid < rows) s_rowscale[tid] = t_scale[0];
@@ -285,11 +308,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
                 const bool in = (mask >> t) & 1;
                 if constexpr (FOLD && !INT_TAPS) {
-                    // (a product of two codes is 1/64 in the matrix instruction's units)
                     const float s = in ? s_rowscale[row] : 0.f;
-                    s_sx[t * px_wg + i] = s * 64.0f;
-                    corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
-                } else if (in) {
+                    s_sx[t * px_wg + i] = s * UNIT;
+                    if constexpr (!BYTES) corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
+                } else if (!BYTES && in) {
                     corr += 8.0f * static_cast<float>(s_sum[row]);
                 }
             }
@@ -315,7 +337,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const int at = (sl * PL * KS * 2 + h) * rows + lane_row;
                 return Base{(at + shift) * 16, static_cast<int>(a.part8) + (at + shift) * 8};
             };
-            auto load_tile = [&](v8i (&b)[KS], const Base &base, int tap, int t, int plane) {
+            auto load_tile = [&](Operand (&b)[KS], const Base &base, int tap, int t, int plane) {
                 int b16 = base.b16 + plane * KS * plane16, b8 = base.b8 + plane * KS * plane8, imm = t;
                 if constexpr (!FOLD) {   // taps outside the image read the row of zeros
                     const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1;
@@ -327,14 +349,18 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                 for (int k = 0; k < KS; ++k) {
                     const v4i lo = *reinterpret_cast<const v4i *>(lds + (b16 + k * plane16) + imm * 512);
-                    const int2 hi = *reinterpret_cast<const int2 *>(lds + (b8 + k * plane8) + imm * 256);
-                    b[k] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+                    if constexpr (BYTES) {
+                        b[k] = lo;
+                    } else {
+                        const int2 hi = *reinterpret_cast<const int2 *>(lds + (b8 + k * plane8) + imm * 256);
+                        b[k] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+                    }
                 }
             };
             // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded;
             // the next unit's weights are requested as soon as this unit's are expanded.
             Base base = base_of(tap, sl);
-            v8i w6[KS], b[2][KS];
+            Operand wop[WP][KS], b[2][KS];
             load_tile(b[0], base, tap, 0, 0);
             for (; u < u_end; ++u) {
                 int tap1 = tap, sl1 = sl;   // the next unit (the last one's operands are requested twice)
@@ -344,13 +370,18 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const Base base1 = base_of(tap1, sl1);
 #pragma unroll
                 for (int k = 0; k < KS; ++k) {
-                    int d[6];
-                    fp6_offset16(raw[k].x, raw[k].y, d[0], d[1], d[2]);
-                    fp6_offset16(raw[k].z, raw[k].w, d[3], d[4], d[5]);
-                    w6[k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+                    if constexpr (BYTES) {
+#pragma unroll
+                        for (int i = 0; i < WP; ++i) wop[i][k] = raw[i][k];
+                    } else {
+                        int d[6];
+                        fp6_offset16(raw[0][k].x, raw[0][k].y, d[0], d[1], d[2]);
+                        fp6_offset16(raw[0][k].z, raw[0][k].w, d[3], d[4], d[5]);
+                        wop[0][k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+                    }
                 }
                 load_weights(tap1, s0 + sl1);
-                v16f acc[2];
+                Acc acc[2];
                 float scale[NT];
                 if constexpr (FOLD && !INT_TAPS) {
 #pragma unroll
@@ -361,17 +392,17 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         const uint32_t pix = p0 + px_l + t * 32 + l;
                         if ((mask[t] >> tap) & 1) {
                             const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32;
-                            const int extra = sl == 0 ? 8 * s_sum[row] : 0;
+                            const int extra = !BYTES && sl == 0 ? 8 * s_sum[row] : 0;
                             int *dst = static_cast<int *>(a.y) + (static_cast<uint64_t>(pix) * 9 + tap) * a.n;
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
                                 const int c = c0 + 16 * h + i;
-                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc[t & 1][i] * 64.0f) - extra);
+                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc[t & 1][i] * static_cast<decltype(acc[0][0] + 0)>(UNIT)) - extra);
                             }
                         }
                     } else if constexpr (FOLD) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], acc[t & 1][i], sum[t][i]);
+                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], static_cast<float>(acc[t & 1][i]), sum[t][i]);
                     }
                 };
 #pragma unroll
@@ -382,12 +413,20 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         if (next < NT * PL) load_tile(b[next & 1], base, tap, next / PL, next % PL);
                         else load_tile(b[0], base1, tap1, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
-                        v16f c = FOLD ? v16f{} : sum[t];
+                        if constexpr (BYTES) {
+                            Acc c = plane ? acc[t & 1] : Acc{};
 #pragma unroll
-                        for (int k = 0; k < KS; ++k)
-                            c = plane ? mfma_fp6_times16(w6[k], b[now & 1][k], c) : mfma_fp6(w6[k], b[now & 1][k], c);
-                        if constexpr (FOLD) acc[t & 1] = c;
-                        else sum[t] = c;
+                            for (int k = 0; k < KS; ++k)
+                                c = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop[plane][k], b[now & 1][k], c, 0, 0, 0);
+                            acc[t & 1] = c;
+                        } else {
+                            v16f c = FOLD ? v16f{} : sum[t];
+#pragma unroll
+                            for (int k = 0; k < KS; ++k)
+                                c = plane ? mfma_fp6_times16(wop[0][k], b[now & 1][k], c) : mfma_fp6(wop[0][k], b[now & 1][k], c);
+                            if constexpr (FOLD) acc[t & 1] = c;
+                            else sum[t] = c;
+                        }
                         __builtin_amdgcn_sched_barrier(0);
                         if (t > 0 && plane == 0) fold(t - 1);
                     }
