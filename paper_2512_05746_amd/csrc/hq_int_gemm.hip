@@ -10,14 +10,22 @@ namespace {
 //   - with at least two 64 x 128 tiles per CU, 64-channel tiles at three workgroups per CU win
 //     even where 128-channel tiles waste nothing: three waves per SIMD hide the latencies of
 //     the chunk loop better than two, which outweighs the extra nibble expansion;
+//   - but where those are more than one round (three per CU) and 128 x 128 tiles are not (two per CU), a second, nearly
+//     empty round costs as much as the larger tile, which reads fewer operand bytes per product.  us per layer with the
+//     quantiser, 64 x 128 -> 128 x 128: 4096 x 576 -> 1984 15.4 -> 14.2, 2048 x 960 -> 3840 18.95 -> 18.4, 16384 x 960 -> 512
+//     27.1 -> 26.2, three weight planes 4096 x 576 -> 1728 24.2 -> 22.3.  Not for short K (4096 x 192 -> 1600 10.25 -> 10.4,
+//     6200 x 384 -> 1280 13.7 -> 13.85): there the results are most of the time and the third workgroup hides them;
 //   - otherwise 128 x 128 tiles if there is at least one per CU;
 //   - a layer with fewer tiles takes 64 x 64 tiles at four workgroups per CU.
 hq_status launch_gemm(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream) {
     if ((a.bits == 8 ? a.k : a.k / 2) % 96 != 0) return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
     const int64_t cus = hq::compute_units();
     const int64_t pix128 = (static_cast<int64_t>(a.pixels) + 127) / 128;
+    const int64_t tiles64 = pix128 * ((a.n + 63) / 64), tiles128 = pix128 * ((a.n + 127) / 128);
+    if (a.bits == 4 && taps <= 3 && taps * a.k >= 576 && tiles64 > 3 * cus && tiles128 <= 2 * cus)
+        return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
     if (a.n % 64 == 0 && pix128 * (a.n / 64) >= 2 * cus) return hq_gemm_launch_64x128(a, taps, y_dtype, stream);
-    if (pix128 * ((a.n + 127) / 128) >= cus) return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
+    if (tiles128 >= cus) return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
     return hq_gemm_launch_64x64(a, taps, y_dtype, stream);
 }
 
