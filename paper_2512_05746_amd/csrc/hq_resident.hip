@@ -19,8 +19,9 @@ struct Plan {
     bool wide, ok;
 };
 
-// LDS layout of a workgroup of nw waves, 1 << xw_log2 pixel groups and cb channel blocks within `budget` bytes.
-Plan lay_out(int kind, int w, int k, int n, int ks, int nw, int xw_log2, int cb, int budget) {
+// LDS layout of a workgroup of nw waves, 1 << xw_log2 pixel groups and cb channel blocks within `budget` bytes.  by_slice: with a
+// table of 16-bit code sums by row and slice behind the others (fp32 results of per-pixel scales).
+Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int xw_log2, int cb, int budget) {
     const int blocks = (n + 31) / 32;
     Plan p{};
     p.ks = ks;
@@ -30,7 +31,6 @@ Plan lay_out(int kind, int w, int k, int n, int ks, int nw, int xw_log2, int cb,
     p.cb = cb;
     const int px = 128 << xw_log2;
     p.rows = (px + 2 * (w + 1) + 1) | 1;
-    const int tables = resident_table_bytes(kind, px, p.rows, cb);
     // Sums shared between waves meet in, and fp16 results pass through, 8 KiB per wave.  Where every workgroup has one
     // phase that area may lie over the activation tile.
     const int tasks = cb << xw_log2, last = blocks % cb << xw_log2;   // of a workgroup, of the last one of a row
@@ -40,7 +40,10 @@ Plan lay_out(int kind, int w, int k, int n, int ks, int nw, int xw_log2, int cb,
     const int ops = ks * (kind >= kResPlanes ? 2 : 1);   // operands of a row, lane half and slice
     const int part8_bytes = kind == kResBytes ? 0 : 16;   // (8-bit codes are 16-byte operands)
     const int slice_bytes = p.rows * ops * (32 + part8_bytes);
-    p.chunk = std::min(p.slices, (budget - tables - (overlay ? 0 : area)) / slice_bytes);
+    const int sums = by_slice ? p.rows * 2 : 0;
+    int tables = resident_table_bytes(kind, px, p.rows, cb);
+    p.chunk = std::min(p.slices, (budget - tables - (overlay ? 0 : area)) / (slice_bytes + sums));
+    tables += (p.chunk * sums + 3) & ~3;
     if (p.chunk < 1 || (p.chunk < p.slices && !overlay)) return p;
     p.part8 = static_cast<uint32_t>(p.rows) * p.chunk * ops * 32;
     p.part8 = (p.part8 + 15) & ~15u;
@@ -75,7 +78,7 @@ double cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
     return rounds * clocks;
 }
 
-Plan choose_plan(int kind, int64_t pixels, int w, int k, int n) {
+Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n) {
     const int steps = k / 64, cus = hq::compute_units();
     const int ks = steps % 3 == 0 || steps > 4 ? 3 : steps == 1 ? 1 : 2;
     Plan best{};
@@ -84,7 +87,7 @@ Plan choose_plan(int kind, int64_t pixels, int w, int k, int n) {
         for (int xw = 0; xw <= 1; ++xw)
             for (const int cb : {1, 2, 3, 4, 6, 8, 12}) {
                 if (cb > 1 && cb > 2 * ((n + 31) / 32) - 1) continue;
-                const Plan p = lay_out(kind, w, k, n, ks, nw, xw, cb, nw == 4 ? kLdsPerCu / 2 : kLdsPerCu);
+                const Plan p = lay_out(kind, by_slice, w, k, n, ks, nw, xw, cb, nw == 4 ? kLdsPerCu / 2 : kLdsPerCu);
                 if (!p.ok) continue;
                 const double c = cost_of(p, kind, pixels, n, cus);
                 if (!best.ok || c < best_cost) { best = p; best_cost = c; }
@@ -109,7 +112,7 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     const int kind = g.bits == 8 ? kResBytes : had_block ? kResPlanes : g.sx_static ? kResSum : kResPerTap;
     if (g.n >= 1 << 21) return HQ_ERR_UNSUPPORTED;   // (a tile's results lie within 2 GiB of their first)
-    const Plan p = choose_plan(kind, g.pixels, g.w, g.k, g.n);
+    const Plan p = choose_plan(kind, kind == kResPerTap && y_dtype == HQ_F32, g.pixels, g.w, g.k, g.n);
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
     ResidentArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;

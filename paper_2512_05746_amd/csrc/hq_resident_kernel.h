@@ -40,7 +40,13 @@
 // 1 x 8 x 8 x 64 (launch) 26.7 -> 11.2: faster at every size tried.
 //
 // Weights carry an offset of 8 (hq_fp6.h; not those of 8 bits): a sum exceeds the wanted one by 8 x (sum of the activation codes it
-// covers), the same for all channels: a per-pixel correction from a table of code sums.
+// covers), the same for all channels: a per-pixel correction from a table of code sums.  With one scale all of it is exact.
+// With per-pixel scales the correction is subtracted at the end from sums in fp32 that hold it, one fold per tap and slice,
+// which costs digits: the 2-norm error is 2e-7 .. 3e-7 where code sums are small, up to 1.5e-5 where the codes of a pixel
+// have one sign (64 .. 960 channels), below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).
+// fp32 results would lose digits, so their sums start at minus the correction (one fp16 matrix step per tap and tile), run
+// over all slices of a tap, and are folded once: 6e-8 for both, as with sums in integers.  That form is slower (us, fp32
+// results: 16 x 32 x 32 x 384 28.1 -> 30.7, 16 x 64 x 64 x 192 34.9 -> 39.2) and would cost fp16 results 2 us as well.
 #pragma once
 #include <type_traits>
 
@@ -102,9 +108,19 @@ __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int row
     return (kind == kResPerTap || kind == kResBytes ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
 }
 
+// -sum / 8 in every value of the lane's pixel, that is -8 x the sum of its activation codes in the unit (1/64) of the
+// products: a matrix step of K = 8 in fp16 of which one lane half uses two places (sum = lo + 1024 hi; every part and product
+// is exact).
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
+    const v4h b = {static_cast<_Float16>(static_cast<short>(sum & 1023)), static_cast<_Float16>(static_cast<short>(sum >> 10)), 0, 0};
+    return __builtin_amdgcn_mfma_f32_32x32x8f16(weights, b, v16f{}, 0, 0, 0);
+}
+
 template <int OUT, int KIND, int KS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
+    constexpr bool WHOLE_TAPS = KIND == kResPerTap && OUT == kOutF32;   // (see the offset of the weights above)
     constexpr int TAPS = 9, NT = 4;
     // planes in memory, operand planes in LDS (BYTES: the two 32-channel halves of a step) and of the weights
     constexpr int IN = KIND == kResPlanes ? 3 : BYTES ? 2 : 1, PL = KIND == kResPlanes || BYTES ? 2 : 1, WP = BYTES ? 2 : 1;
@@ -135,9 +151,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     float *s_corr = s_sx + (FOLD ? TAPS : 0) * px_wg;
     int *s_mask = reinterpret_cast<int *>(s_corr + px_wg);
     float *s_rowscale = reinterpret_cast<float *>(s_mask + px_wg);
-    int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);
+    int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);   // code sums [row] of the slices so far
     float *s_sw = reinterpret_cast<float *>(s_sum + rows);
     float *s_bias = s_sw + a.cb * 32;
+    short *s_part = reinterpret_cast<short *>(s_bias + a.cb * 32);   // WHOLE_TAPS: code sums [resident slice][row]
 
     // ---- phases: tasks and shares ---------------------------------------------------------------------------
     // tasks first .. first + (nw >> kl) - 1, each by 1 << kl waves; wave wv has task first + wv >> kl, share wv mod
@@ -230,7 +247,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         }
         if constexpr (!BYTES) {
             sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
-            if (f_half == 0 && row < rows - 1) atomicAdd(&s_sum[row], sum);
+            if (f_half == 0 && row < rows - 1) {
+                if constexpr (WHOLE_TAPS) s_part[sl * rows + row] = static_cast<short>(sum);
+                else atomicAdd(&s_sum[row], sum);
+            }
         }
     };
 
@@ -256,7 +276,9 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         t_sw = a.sw[c];
         t_bias = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
     }
-    for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
+    if constexpr (!WHOLE_TAPS) {
+        for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
+    }
     for (int i = tid; i < resident0 * PL * KS * 2; i += nt) {   // the row of zeros
         const int at = i * rows + rows - 1;
         *reinterpret_cast<v4i *>(lds + at * 16) = v4i{0, 0, 0, 0};
@@ -310,12 +332,21 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 if constexpr (FOLD && !INT_TAPS) {
                     const float s = in ? s_rowscale[row] : 0.f;
                     s_sx[t * px_wg + i] = s * UNIT;
-                    if constexpr (!BYTES) corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
+                    if constexpr (!BYTES && !WHOLE_TAPS) corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
                 } else if (!BYTES && in) {
                     corr += 8.0f * static_cast<float>(s_sum[row]);
                 }
             }
-            s_corr[i] = corr;   // (of all slices once the last chunk is resident)
+            if constexpr (!WHOLE_TAPS) s_corr[i] = corr;   // (of all slices once the last chunk is resident)
+        }
+        if constexpr (WHOLE_TAPS) {   // code sums of a slice -> of all resident slices up to it
+            for (int i = tid; i < px_wg + 2 * halo; i += nt) {
+                int of = s_part[i];
+                for (int sl = 1; sl < s1 - s0; ++sl) {
+                    of += s_part[sl * rows + i];
+                    s_part[sl * rows + i] = static_cast<short>(of);
+                }
+            }
         }
         lds_barrier();
 
@@ -357,11 +388,22 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     }
                 }
             };
-            // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded;
-            // the next unit's weights are requested as soon as this unit's are expanded.
+            // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded (of
+            // WHOLE_TAPS only where the unit ends the slices of its tap); the next unit's weights are requested as soon as
+            // this unit's are expanded.
             Base base = base_of(tap, sl);
             Operand wop[WP][KS], b[2][KS];
             load_tile(b[0], base, tap, 0, 0);
+            Acc tap_acc[WHOLE_TAPS ? NT : 1];
+            const v4h minus = h ? v4h{} : v4h{-0.125f16, -128.0f16, 0, 0};
+            auto codes_upto = [&](int tap, int sl, int t) {
+                return static_cast<int>(s_part[sl * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
+            };
+            if constexpr (WHOLE_TAPS) {   // the sums of a tap start with the offset of the slices that this wave will add
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    tap_acc[t] = minus_eighth_of(minus, codes_upto(tap, min(ns, sl + u_end - u) - 1, t) - (sl ? codes_upto(tap, sl - 1, t) : 0));
+            }
             for (; u < u_end; ++u) {
                 int tap1 = tap, sl1 = sl;   // the next unit (the last one's operands are requested twice)
                 if (u + 1 < u_end) {
@@ -381,11 +423,20 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     }
                 }
                 load_weights(tap1, s0 + sl1);
-                Acc acc[2];
+                Acc unit_acc[WHOLE_TAPS ? 1 : 2];
+                auto acc_of = [&](int t) -> Acc & {
+                    if constexpr (WHOLE_TAPS) return tap_acc[t];
+                    else return unit_acc[t & 1];
+                };
+                const bool ends = !WHOLE_TAPS || u + 1 == u_end || tap1 != tap;
                 float scale[NT];
-                if constexpr (FOLD && !INT_TAPS) {
+                int codes[NT] = {};   // WHOLE_TAPS: of the next tap
+                if (FOLD && !INT_TAPS && ends) {
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
+                    for (int t = 0; t < NT; ++t) {
+                        scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
+                        if constexpr (WHOLE_TAPS) codes[t] = codes_upto(tap1, max(min(ns, u_end - u - 1), 1) - 1, t);
+                    }
                 }
                 auto fold = [&](int t) {
                     if constexpr (INT_TAPS) {
@@ -397,12 +448,13 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
                                 const int c = c0 + 16 * h + i;
-                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc[t & 1][i] * static_cast<decltype(acc[0][0] + 0)>(UNIT)) - extra);
+                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc_of(t)[i] * static_cast<decltype(acc_of(t)[i] + 0)>(UNIT)) - extra);
                             }
                         }
                     } else if constexpr (FOLD) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], static_cast<float>(acc[t & 1][i]), sum[t][i]);
+                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], static_cast<float>(acc_of(t)[i]), sum[t][i]);
+                        if constexpr (WHOLE_TAPS) tap_acc[t] = minus_eighth_of(minus, codes[t]);
                     }
                 };
 #pragma unroll
@@ -414,24 +466,24 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         else load_tile(b[0], base1, tap1, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
                         if constexpr (BYTES) {
-                            Acc c = plane ? acc[t & 1] : Acc{};
+                            Acc c = plane ? acc_of(t) : Acc{};
 #pragma unroll
                             for (int k = 0; k < KS; ++k)
                                 c = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop[plane][k], b[now & 1][k], c, 0, 0, 0);
-                            acc[t & 1] = c;
+                            acc_of(t) = c;
                         } else {
-                            v16f c = FOLD ? v16f{} : sum[t];
+                            v16f c = WHOLE_TAPS ? acc_of(t) : FOLD ? v16f{} : sum[t];
 #pragma unroll
                             for (int k = 0; k < KS; ++k)
                                 c = plane ? mfma_fp6_times16(wop[0][k], b[now & 1][k], c) : mfma_fp6(wop[0][k], b[now & 1][k], c);
-                            if constexpr (FOLD) acc[t & 1] = c;
+                            if constexpr (FOLD) acc_of(t) = c;
                             else sum[t] = c;
                         }
                         __builtin_amdgcn_sched_barrier(0);
-                        if (t > 0 && plane == 0) fold(t - 1);
+                        if (t > 0 && plane == 0 && ends) fold(t - 1);
                     }
                 }
-                fold(NT - 1);
+                if (ends) fold(NT - 1);
                 tap = tap1;
                 sl = sl1;
                 base = base1;
@@ -544,7 +596,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         const int px = px_l + ((tile0 + t) & (NT - 1)) * 32 + l;
-                        corr[t] = s_corr[px];
+                        corr[t] = WHOLE_TAPS ? 0.f : s_corr[px];
                     }
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -594,7 +646,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         bias[i] = OUT != kOutI32 ? s_bias[ct + 8 * half0 + i] : 0.f;
                     }
                     Out res[8];
-                    scaled(v, s_corr[px], sw, bias, res);
+                    scaled(v, WHOLE_TAPS ? 0.f : s_corr[px], sw, bias, res);
                     store8(res, px, c0 + 16 * h + 8 * half0);
                 }
             }

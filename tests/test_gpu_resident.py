@@ -36,7 +36,8 @@ def host(t):
 ])
 def test_conv3x3(hq, nb, h, w, cin, cout):
     """Per-tap sums and the sum over all taps bit for bit (the fp32 sums of the 6-bit instruction are exact below 2^24);
-    fp32 results to 1e-5: nine folds and at most two roundings more, each 6e-8 of sums below 8 x the result's."""
+    fp32 results to 1e-5 of the largest (nine folds, or eighteen where only some slices are resident at a time, and few
+    roundings more, each 6e-8 of partial sums, which with codes of both signs may be some times larger than it)."""
     rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
     xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
     wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
@@ -56,6 +57,29 @@ def test_conv3x3(hq, nb, h, w, cin, cout):
     _, y_o = oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1, want_acc=False)
     y = host(hq.hq_int_conv2d_static(xq_d, s1, wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
     check_y("y (static)", y, y_o, rtol=1e-5)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (2, 16, 16, 64, 64),         # one slice: one unit a tap
+    (1, 20, 13, 128, 33),        # two steps in one slice
+    (2, 9, 9, 960, 200),         # five slices, taps cut between the waves that share a task
+    (4, 16, 16, 576, 576),       # three slices
+    (1, 6, 200, 960, 40),        # some slices resident at a time
+    (3, 45, 27, 320, 200),       # a padded slice, seven channel blocks
+])
+def test_conv3x3_fp32_codes_of_one_sign(hq, nb, h, w, cin, cout):
+    """fp32 results with per-pixel scales where the weights' offset of 8 times the sum of the activation codes is far larger
+    than the result: no digits may be lost to it.  No partial sum exceeds the result's size by more than a tap's, so the bound
+    is 20 roundings of 2^-24 (nine folds, or eighteen where the tile holds only part of the slices; scale and bias)."""
+    rng = np.random.default_rng(cin + cout)
+    xq = rng.integers(3, 8, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-1, 3, (cout, 3, 3, cin)).astype(np.int8)
+    sx = rng.uniform(0.1, 1.0, (nb, h, w)).astype(np.float32)
+    sw = rng.uniform(0.05, 0.1, cout).astype(np.float32)
+    _, y_o = oracle.int_conv2d(xq, sx, wq, sw, None, stride=1, pad=1, want_acc=False)
+    y = host(hq.hq_int_conv2d(dev(pack_codes(xq)), dev(sx), dev(pack_codes(wq.reshape(cout, 9, cin))), dev(sw), None, ksize=3,
+                              y_dtype=torch.float32))
+    check_y("y", y, y_o, rtol=20 * 2.0 ** -24)
 
 
 @pytest.mark.parametrize("nb,h,w,cin,cout,block", [
