@@ -54,14 +54,16 @@ void check(const char *fn, hq_status st) {
     throw PythonError();
 }
 
-// The library only enqueues work; other threads may run meanwhile.
-template <class F>
-hq_status call(F &&f) {
-    hq_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return st;
+// The library only enqueues work; other threads may run meanwhile.  Its arguments are values: all that can fail (sizes that do
+// not fit, storage without memory, the stream) is evaluated by the caller, with the interpreter's lock held.
+struct Unlocked {
+    PyThreadState *const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+template <class... Parameters, class... Values>
+hq_status call(hq_status (*f)(Parameters...), Values... values) {
+    const Unlocked unlocked;
+    return f(values...);
 }
 
 // ---- arguments --------------------------------------------------------------------------------------------
@@ -203,10 +205,12 @@ PyObject *wrap(const at::Tensor &a, const at::Tensor &b) {
     return p;
 }
 
-int narrow(int64_t v) {
-    if (v > 0x7FFFFFFFLL) refuse("a size does not fit 32 bits");
-    return static_cast<int>(v);
+// The library takes sizes of 32 bits (but for the rows of a matrix).
+void expect_32bit(std::initializer_list<int64_t> sizes) {
+    for (const int64_t v : sizes)
+        if (v > 0x7FFFFFFFLL) refuse("a size does not fit 32 bits");
 }
+int narrow(int64_t v) { return static_cast<int>(v); }
 
 void expect_dims(const at::Tensor &t, int64_t dims, const char *text) {
     if (t.dim() != dims) refuse(text);
@@ -241,13 +245,13 @@ PyObject *quantize_weights(Args a) {
     const int block = a.integer(), bits = a.integer();
     expect_dims(w, 3, "w must be [n_out, taps, k_in]");
     const int64_t n = w.size(0), taps = w.size(1), k = w.size(2);
+    expect_32bit({n, taps, k});
     const at::Tensor wq = empty({n, taps, bits == 8 ? k : k / 2}, bits == 8 ? at::kChar : at::kByte, w);
     const at::Tensor ws = empty({n}, at::kFloat, w);
     const hq_dtype dt = hq_type(w.scalar_type());
-    check("hq_quantize_weights", call([&] {
-              return lib.hq_quantize_weights(w.const_data_ptr(), dt, narrow(n), narrow(taps), narrow(k), block, bits,
-                                             static_cast<uint8_t *>(wq.data_ptr()), static_cast<float *>(ws.data_ptr()), stream());
-          }));
+    check("hq_quantize_weights", call(lib.hq_quantize_weights, w.const_data_ptr(), dt, narrow(n), narrow(taps),
+                                      narrow(k), block, bits, static_cast<uint8_t *>(wq.data_ptr()),
+                                      static_cast<float *>(ws.data_ptr()), stream()));
     return wrap(wq, ws);
 }
 
@@ -258,13 +262,13 @@ PyObject *act_hadamard_quant(Args a) {
     pair_of(a.next(), oq, os);
     if (x.dim() < 1) refuse("x must have a channel axis");
     const int64_t k = x.size(-1), m = k ? x.numel() / k : 0;
+    expect_32bit({k});
     const at::Tensor xq = result(oq, with_last(x, bits == 8 ? k : k / 2), bits == 8 ? at::kChar : at::kByte, x);
     const at::Tensor xs = result(os, without_last(x), at::kFloat, x);
     const hq_dtype dt = hq_type(x.scalar_type());
-    check("hq_act_hadamard_quant", call([&] {
-              return lib.hq_act_hadamard_quant(x.const_data_ptr(), dt, m, narrow(k), block, bits,
-                                               static_cast<uint8_t *>(xq.data_ptr()), static_cast<float *>(xs.data_ptr()), stream());
-          }));
+    check("hq_act_hadamard_quant", call(lib.hq_act_hadamard_quant, x.const_data_ptr(), dt, m, narrow(k), block, bits,
+                                        static_cast<uint8_t *>(xq.data_ptr()), static_cast<float *>(xs.data_ptr()),
+                                        stream()));
     return wrap(xq, xs);
 }
 
@@ -273,13 +277,13 @@ PyObject *act_hadamard_quant_i8(Args a) {
     const int block = a.integer(), bits = a.integer();
     if (x.dim() < 1) refuse("x must have a channel axis");
     const int64_t k = x.size(-1), m = k ? x.numel() / k : 0;
+    expect_32bit({k});
     const at::Tensor xq = empty(x.sizes(), at::kChar, x);
     const at::Tensor xs = empty(without_last(x), at::kFloat, x);
     const hq_dtype dt = hq_type(x.scalar_type());
-    check("hq_act_hadamard_quant_i8", call([&] {
-              return lib.hq_act_hadamard_quant_i8(x.const_data_ptr(), dt, m, narrow(k), block, bits,
-                                                  static_cast<int8_t *>(xq.data_ptr()), static_cast<float *>(xs.data_ptr()), stream());
-          }));
+    check("hq_act_hadamard_quant_i8", call(lib.hq_act_hadamard_quant_i8, x.const_data_ptr(), dt, m, narrow(k), block,
+                                           bits, static_cast<int8_t *>(xq.data_ptr()),
+                                           static_cast<float *>(xs.data_ptr()), stream()));
     return wrap(xq, xs);
 }
 
@@ -289,14 +293,13 @@ PyObject *act_hadamard_quant_static(Args a) {
     const int block = a.integer(), bits = a.integer();
     if (x.dim() < 1) refuse("x must have a channel axis");
     const int64_t k = x.size(-1), m = k ? x.numel() / k : 0;
+    expect_32bit({k});
     const at::Tensor xq = result(a.next(), with_last(x, k / 2), at::kByte, x);
     Args one{&scale, 1};
     const float *s = one.scalar();
     const hq_dtype dt = hq_type(x.scalar_type());
-    check("hq_act_hadamard_quant_static", call([&] {
-              return lib.hq_act_hadamard_quant_static(x.const_data_ptr(), dt, m, narrow(k), block, bits, s,
-                                                      static_cast<uint8_t *>(xq.data_ptr()), stream());
-          }));
+    check("hq_act_hadamard_quant_static", call(lib.hq_act_hadamard_quant_static, x.const_data_ptr(), dt, m, narrow(k),
+                                               block, bits, s, static_cast<uint8_t *>(xq.data_ptr()), stream()));
     return wrap(xq);
 }
 
@@ -315,16 +318,16 @@ PyObject *int_linear(Args &a, const char *fn, hq_status (*f)(const Code *, const
     const at::ScalarType ydt = a.dtype();
     expect_dims(xq, 2, "xq must be [m, k]");
     const int64_t m = xq.size(0), kb = xq.size(1), n = wq.dim() ? wq.size(0) : 0;
+    expect_32bit({n, bytes ? kb : kb * 2});
     if (wq.numel() != n * kb) refuse("wq does not match xq in k");
     const void *sx = Args{&x_scale, 1}.vec(scales == Scales::fixed ? 1 : m, at::kFloat, "x_scale");
     const void *sw = Args{&w_scale, 1}.vec(n, at::kFloat, "w_scale");
     const void *b = Args{&bias, 1}.vec(n, ydt, "bias");
     const at::Tensor y = result(a.next(), {m, n}, ydt, xq);
     const hq_dtype dt = hq_type(ydt);
-    check(fn, call([&] {
-              return f(static_cast<const Code *>(xq.const_data_ptr()), f32(sx), static_cast<const Code *>(wq.const_data_ptr()), f32(sw), b,
-                       m, narrow(n), narrow(bytes ? kb : kb * 2), y.data_ptr(), dt, stream());
-          }));
+    check(fn, call(f, static_cast<const Code *>(xq.const_data_ptr()), f32(sx),
+                   static_cast<const Code *>(wq.const_data_ptr()), f32(sw), b, m, narrow(n),
+                   narrow(bytes ? kb : kb * 2), y.data_ptr(), dt, stream()));
     return wrap(y);
 }
 PyObject *linear(Args a) { return int_linear<uint8_t>(a, "hq_int_linear", lib.hq_int_linear, Scales::dynamic); }
@@ -346,6 +349,7 @@ PyObject *int_conv2d(Args &a, const char *fn, hq_status (*f)(const Code *, const
     expect_dims(xq, 4, "xq must be [nb, h, w, c]");
     const int64_t nb = xq.size(0), h = xq.size(1), w = xq.size(2), cb = xq.size(3), n = wq.dim() ? wq.size(0) : 0;
     const int64_t taps = static_cast<int64_t>(ksize) * ksize;
+    expect_32bit({nb, h, w, bytes ? cb : cb * 2, n});
     if (wq.numel() != n * taps * cb) refuse("wq does not match xq / ksize");
     const void *sx = Args{&x_scale, 1}.vec(scales == Scales::fixed ? 1 : nb * h * w, at::kFloat, "x_scale");
     const void *sw = Args{&w_scale, 1}.vec(n, at::kFloat, "w_scale");
@@ -357,11 +361,9 @@ PyObject *int_conv2d(Args &a, const char *fn, hq_status (*f)(const Code *, const
     shape.push_back(n);
     const at::Tensor y = result(a.next(), shape, ydt, xq);
     const hq_dtype dt = hq_type(ydt);
-    check(fn, call([&] {
-              return f(static_cast<const Code *>(xq.const_data_ptr()), f32(sx), static_cast<const Code *>(wq.const_data_ptr()), f32(sw), b,
-                       narrow(nb), narrow(h), narrow(w), narrow(bytes ? cb : cb * 2), narrow(n), ksize, ksize, stride, pad,
-                       y.data_ptr(), dt, stream());
-          }));
+    check(fn, call(f, static_cast<const Code *>(xq.const_data_ptr()), f32(sx),
+                   static_cast<const Code *>(wq.const_data_ptr()), f32(sw), b, narrow(nb), narrow(h), narrow(w),
+                   narrow(bytes ? cb : cb * 2), narrow(n), ksize, ksize, stride, pad, y.data_ptr(), dt, stream()));
     return wrap(y);
 }
 PyObject *conv2d(Args a) { return int_conv2d<uint8_t>(a, "hq_int_conv2d", lib.hq_int_conv2d, Scales::dynamic); }
@@ -378,6 +380,7 @@ PyObject *act_quant_conv2d(Args a) {
     expect_dims(x, 4, "x must be [nb, h, w, c]");
     const int64_t nb = x.size(0), h = x.size(1), w = x.size(2), cin = x.size(3), n = wq.dim() ? wq.size(0) : 0;
     const int64_t taps = static_cast<int64_t>(ksize) * ksize;
+    expect_32bit({nb, h, w, cin, n});
     if (wq.numel() != n * taps * (cin / 2)) refuse("wq does not match x / ksize");
     const void *sw = Args{&w_scale, 1}.vec(n, at::kFloat, "w_scale");
     const void *b = Args{&bias, 1}.vec(n, ydt, "bias");
@@ -393,12 +396,11 @@ PyObject *act_quant_conv2d(Args a) {
         sx = result(os, {nb, h, w}, at::kFloat, x);
     }
     const hq_dtype xdt = hq_type(x.scalar_type()), dt = hq_type(ydt);
-    check("hq_act_quant_int_conv2d", call([&] {
-              return lib.hq_act_quant_int_conv2d(x.const_data_ptr(), xdt, u8(wq), f32(sw), b, narrow(nb), narrow(h), narrow(w), narrow(cin),
-                                                 narrow(n), ksize, ksize, stride, pad, block, bits, y.data_ptr(), dt,
-                                                 xq.defined() ? static_cast<uint8_t *>(xq.data_ptr()) : nullptr,
-                                                 sx.defined() ? static_cast<float *>(sx.data_ptr()) : nullptr, stream());
-          }));
+    check("hq_act_quant_int_conv2d", call(lib.hq_act_quant_int_conv2d, x.const_data_ptr(), xdt, u8(wq), f32(sw), b,
+                                          narrow(nb), narrow(h), narrow(w), narrow(cin), narrow(n), ksize, ksize,
+                                          stride, pad, block, bits, y.data_ptr(), dt,
+                                          xq.defined() ? static_cast<uint8_t *>(xq.data_ptr()) : nullptr,
+                                          sx.defined() ? static_cast<float *>(sx.data_ptr()) : nullptr, stream()));
     return wrap(y);
 }
 
@@ -411,6 +413,7 @@ PyObject *act_quant_linear(Args a) {
     pair_of(codes_out, oq, os);
     if (x.dim() < 1) refuse("x must have a channel axis");
     const int64_t k = x.size(-1), m = k ? x.numel() / k : 0, n = wq.dim() ? wq.size(0) : 0;
+    expect_32bit({n, k});
     if (wq.numel() != n * (k / 2)) refuse("wq does not match x");
     const void *sw = Args{&w_scale, 1}.vec(n, at::kFloat, "w_scale");
     const void *b = Args{&bias, 1}.vec(n, ydt, "bias");
@@ -421,11 +424,10 @@ PyObject *act_quant_linear(Args a) {
         sx = result(os, without_last(x), at::kFloat, x);
     }
     const hq_dtype xdt = hq_type(x.scalar_type()), dt = hq_type(ydt);
-    check("hq_act_quant_int_linear", call([&] {
-              return lib.hq_act_quant_int_linear(x.const_data_ptr(), xdt, u8(wq), f32(sw), b, m, narrow(n), narrow(k), block, bits,
-                                                 y.data_ptr(), dt, xq.defined() ? static_cast<uint8_t *>(xq.data_ptr()) : nullptr,
-                                                 sx.defined() ? static_cast<float *>(sx.data_ptr()) : nullptr, stream());
-          }));
+    check("hq_act_quant_int_linear", call(lib.hq_act_quant_int_linear, x.const_data_ptr(), xdt, u8(wq), f32(sw), b, m,
+                                          narrow(n), narrow(k), block, bits, y.data_ptr(), dt,
+                                          xq.defined() ? static_cast<uint8_t *>(xq.data_ptr()) : nullptr,
+                                          sx.defined() ? static_cast<float *>(sx.data_ptr()) : nullptr, stream()));
     return wrap(y);
 }
 
@@ -434,13 +436,13 @@ PyObject *quantize_weights_single(Args a) {
     const int block = a.integer(), bits = a.integer();
     expect_dims(w, 2, "w must be [n_out, k_in]");
     const int64_t n = w.size(0), k = w.size(1);
+    expect_32bit({n, k});
     const at::Tensor wq3 = empty({n, 3, k / 2}, at::kByte, w);
     const at::Tensor ws = empty({n}, at::kFloat, w);
     const hq_dtype dt = hq_type(w.scalar_type());
-    check("hq_quantize_weights_single", call([&] {
-              return lib.hq_quantize_weights_single(w.const_data_ptr(), dt, narrow(n), narrow(k), block, bits,
-                                                    static_cast<uint8_t *>(wq3.data_ptr()), static_cast<float *>(ws.data_ptr()), stream());
-          }));
+    check("hq_quantize_weights_single", call(lib.hq_quantize_weights_single, w.const_data_ptr(), dt, narrow(n),
+                                             narrow(k), block, bits, static_cast<uint8_t *>(wq3.data_ptr()),
+                                             static_cast<float *>(ws.data_ptr()), stream()));
     return wrap(wq3, ws);
 }
 
@@ -453,6 +455,7 @@ PyObject *linear_single(Args a) {
     const at::ScalarType ydt = a.dtype();
     expect_dims(xq, 2, "xq must be [m, k]");
     const int64_t m = xq.size(0), kb = xq.size(1), n = wq3.dim() ? wq3.size(0) : 0;
+    expect_32bit({n, kb * 2});
     if (wq3.numel() != n * 3 * kb) refuse("wq3 does not match xq in k");
     const void *sx = Args{&x_scale, 1}.vec(m, at::kFloat, "x_scale");
     const void *sw = Args{&w_scale, 1}.vec(n, at::kFloat, "w_scale");
@@ -461,10 +464,8 @@ PyObject *linear_single(Args a) {
     if (ydt == at::kInt) shape = {m, 3, n};
     const at::Tensor y = result(a.next(), shape, ydt, xq);
     const hq_dtype dt = hq_type(ydt);
-    check("hq_int_linear_single", call([&] {
-              return lib.hq_int_linear_single(u8(xq), f32(sx), u8(wq3), f32(sw), b, m, narrow(n), narrow(kb * 2), block, y.data_ptr(), dt,
-                                              stream());
-          }));
+    check("hq_int_linear_single", call(lib.hq_int_linear_single, u8(xq), f32(sx), u8(wq3), f32(sw), b, m, narrow(n),
+                                       narrow(kb * 2), block, y.data_ptr(), dt, stream()));
     return wrap(y);
 }
 
@@ -474,12 +475,12 @@ PyObject *act_hadamard_quant_width(Args a) {
     const int block = a.integer(), bits = a.integer();
     expect_dims(x, 4, "x must be [N, H, W, C]");
     const int64_t nb = x.size(0), h = x.size(1), w = x.size(2), c = x.size(3);
+    expect_32bit({nb, h, w, c});
     const at::Tensor xu3 = result(a.next(), {3, nb, h, w, c / 2}, at::kByte, x);
     const hq_dtype dt = hq_type(x.scalar_type());
-    check("hq_act_hadamard_quant_width", call([&] {
-              return lib.hq_act_hadamard_quant_width(x.const_data_ptr(), dt, narrow(nb), narrow(h), narrow(w), narrow(c), block, bits, scale,
-                                                     static_cast<uint8_t *>(xu3.data_ptr()), stream());
-          }));
+    check("hq_act_hadamard_quant_width", call(lib.hq_act_hadamard_quant_width, x.const_data_ptr(), dt, narrow(nb),
+                                              narrow(h), narrow(w), narrow(c), block, bits, scale,
+                                              static_cast<uint8_t *>(xu3.data_ptr()), stream()));
     return wrap(xu3);
 }
 
@@ -494,6 +495,7 @@ PyObject *conv2d_width(Args a) {
     const int stride = a.integer();
     if (xu3.dim() != 5 || xu3.size(0) != 3) refuse("xu3 must be [3, N, H, W, Cin/2]");
     const int64_t nb = xu3.size(1), h = xu3.size(2), w = xu3.size(3), kb = xu3.size(4), n = wq.dim() ? wq.size(0) : 0;
+    expect_32bit({nb, h, w, kb * 2, n});
     if (wq.numel() != n * 9 * kb) refuse("wq does not match xu3 in Cin or is not a 3x3 kernel");
     const void *sx = Args{&x_scale, 1}.vec(1, at::kFloat, "x_scale");
     const void *sw = Args{&w_scale, 1}.vec(n, at::kFloat, "w_scale");
@@ -502,10 +504,9 @@ PyObject *conv2d_width(Args a) {
     expect_result(o);
     const at::Tensor y = result(out, {nb, o.h, o.w, n}, ydt, xu3);
     const hq_dtype dt = hq_type(ydt);
-    check("hq_int_conv2d_width", call([&] {
-              return lib.hq_int_conv2d_width(u8(xu3), f32(sx), u8(wq), f32(sw), b, narrow(nb), narrow(h), narrow(w), narrow(kb * 2),
-                                             narrow(n), 3, 3, stride, 1, block, y.data_ptr(), dt, stream());
-          }));
+    check("hq_int_conv2d_width", call(lib.hq_int_conv2d_width, u8(xu3), f32(sx), u8(wq), f32(sw), b, narrow(nb),
+                                      narrow(h), narrow(w), narrow(kb * 2), narrow(n), 3, 3, stride, 1, block,
+                                      y.data_ptr(), dt, stream()));
     return wrap(y);
 }
 
