@@ -319,8 +319,10 @@ hq_status hq_act_hadamard_quant_width(const void *x, hq_dtype x_dtype, int nb, i
  *   acc[b, p, q, co] = sum_{r, s, ci} u[b, p + r - pad, q + s - pad, ci] * wq[co, r, s, ci]   (int32, exact)
  *   y[b, p, q, co]   = acc * x_scale[0] * w_scale[co] / sqrt(had_block) + bias[co]
  *
- * with u the integers held by the three planes of xu3 (one integer sum per plane, combined
- * as acc_0 + 16 acc_1 + 256 acc_2).  A tap outside the image contributes 0.
+ * with u = d0 + 16 d1 + 256 d2 the integers held by the three planes of xu3, which must lie in
+ * -8 had_block .. 8 had_block, the range of what hq_act_hadamard_quant_width writes with the same
+ * had_block; sums over larger integers are unspecified (two matrix operands hold d0 and d1 + 16 d2, and
+ * fp32 sums of that range are exact).  A tap outside the image contributes 0.
  *   xu3 [3, nb, h, w, c_in/2], wq [c_out, 3, 3, c_in/2] (codes of the un-transformed weights),
  *   w_scale [c_out], bias [c_out] of y_dtype or NULL, y [nb, h, w, c_out].
  * Built: R = S = 3, pad 1, stride 1 (y [nb, h, w, c_out]) or stride 2 (y [nb, (h-1)/2 + 1, (w-1)/2 + 1, c_out],

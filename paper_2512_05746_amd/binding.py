@@ -203,7 +203,8 @@ def hq_int_conv2d_width(xu3: torch.Tensor, x_scale: Optional[torch.Tensor], wq: 
                         had_block: int = 64, y_dtype: torch.dtype = torch.float16,
                         out: Optional[torch.Tensor] = None, stride: int = 1) -> torch.Tensor:
     """xu3 [3, N, H, W, Cin/2], wq [Cout, 9, Cin/2] (or [Cout, 3, 3, Cin/2]) -> y [N, Ho, Wo, Cout]
-    (same size for stride 1; stride 2 halves it, rounding up); y_dtype int32 returns the exact integer sums."""
+    (same size for stride 1; stride 2 halves it, rounding up); y_dtype int32 returns the exact integer sums.  The
+    integers in the planes must lie within 8 * had_block, as those of hq_act_hadamard_quant_width do."""
     return _native().conv2d_width(xu3, x_scale, wq, w_scale, bias, had_block, y_dtype, out, stride)
 
 

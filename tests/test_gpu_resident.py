@@ -117,6 +117,25 @@ def test_conv_width(hq, nb, h, w, cin, cout, block):
     check_y("y", y, y_o, rtol=1e-6)
 
 
+@pytest.mark.parametrize("block", [1, 8, 16, 32])
+def test_conv_width_whole_range(hq, block):
+    """Every integer of -8 x block .. 8 x block in the planes, wherever it comes from: integer sums bit for bit."""
+    rng = np.random.default_rng(block)
+    nb, h, w, cin, cout = 1, 3, 64, 128, 40
+    top = 8 * block
+    u = rng.integers(-top, top + 1, (nb, h, w, cin))
+    u.reshape(-1)[: 2 * top + 1] = np.arange(-top, top + 1)
+    d0 = (u + 8) % 16 - 8
+    r1 = (u - d0) // 16
+    d1 = (r1 + 8) % 16 - 8
+    planes = dev(pack_codes(np.stack([d0, d1, (r1 - d1) // 16]).astype(np.int8)))
+    wq = rng.integers(-8, 8, (cout, 9, cin)).astype(np.int8)
+    up = np.pad(u, ((0, 0), (1, 1), (1, 1), (0, 0)))
+    want = sum(up[:, t // 3:t // 3 + h, t % 3:t % 3 + w] @ wq[:, t].astype(np.int64).T for t in range(9))
+    acc = host(hq.hq_int_conv2d_width(planes, None, dev(pack_codes(wq)), None, None, block, y_dtype=torch.int32))
+    assert np.array_equal(acc, want)
+
+
 @pytest.mark.parametrize("nb,h,w,cin,cout", [
     (1, 1, 1, 64, 1),          # one pixel, one channel: a single 64-channel step
     (1, 5, 127, 128, 33),      # two steps per slice; one pixel short of a tile; one channel in the second block
