@@ -183,16 +183,19 @@ hq_status hq_act_quant_int_linear(const void *x, hq_dtype x_dtype, const uint8_t
                                   uint8_t *xq_out, float *x_scale_out, void *stream);
 
 /*
- * Diagnostic: the size class of a convolution of this geometry on the current device, for hq_int_conv2d
- * (static_scale = 0) or hq_int_conv2d_static (static_scale = 1) and 4-bit (bits = 4) or 8-bit (bits = 8,
- * hq_int_conv2d_i8) codes.  It depends on the geometry only, never on y_dtype (the HQ_I32 outputs come from the same
- * kernel as the floating-point outputs).  Host logic only; returns a static string: "tile", "tile (stride 2)",
- * "wave-split", "activation-resident", "activation-resident-int8 (P pixels)" with P = 256, 128 or 64
- * (the pixel tile of a workgroup; "128 pixels, 4 waves" for the four-wave form), "small-channel-count"
- * (c_in not a multiple of 64), or "unsupported".  The labels are stable and say how a layer of that size is cut
- * (whole tiles, K ranges shared by waves, an activation tile per workgroup); several classes may run the same kernel:
- * stride-1 3x3 layers of 4-bit codes with c_in a multiple of 64 run the one that keeps the expanded activation
- * tile on chip, except the single-slice (c_in = 192) layers of class "wave-split".
+ * Diagnostic: the kernel that a convolution of this geometry runs on the current device, for hq_int_conv2d
+ * (static_scale = 0) or hq_int_conv2d_static (static_scale = 1) and 4-bit codes (bits = 4), or for hq_int_conv2d_i8
+ * (bits = 8).  Host logic only, the same that the calls use; returns a static string:
+ *   "activation-resident (P pixels, W waves)"   3x3, activation tile of P pixels (128 or 256) on chip, W = 4 or 8 waves a
+ *                       workgroup; with ", slices in turn" before the bracket if only some channel slices are resident
+ *                       at a time
+ *   "wave-split"        3x3, 192 channels, few tiles: K ranges shared by waves
+ *   "tile"              1x1, and 3x3 with image rows too long for the activation tile
+ *   "tile (stride 2)"
+ *   "small-channel-count"   c_in not a multiple of 64
+ *   "unsupported"
+ * It depends on the geometry only, never on y_dtype, but that fp32 results with per-pixel scales need more room on chip: their
+ * tile may be another one, and at the longest image rows that fit they run "tile".
  */
 const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in, int c_out, int r, int s,
                                       int stride, int pad, int static_scale, int bits);

@@ -84,7 +84,7 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
 
 def hq_int_conv2d_kernel_name(nb: int, h: int, w: int, c_in: int, c_out: int, ksize: int = 3, stride: int = 1,
                               pad: Optional[int] = None, static_scale: bool = False, bits: int = 4) -> str:
-    """Name of the kernel family the convolution calls run for this geometry (host logic only)."""
+    """Name of the kernel the convolution calls run for this geometry, and its tile (host logic only)."""
     pad = (ksize - 1) // 2 if pad is None else pad
     return load_library().hq_int_conv2d_kernel_name(nb, h, w, c_in, c_out, ksize, ksize, stride, pad,
                                                     1 if static_scale else 0, bits).decode()

@@ -54,22 +54,11 @@ hq_status check_common(const uint8_t *xq, const float *x_scale, const uint8_t *w
     return HQ_OK;
 }
 
-// Size class of a stride-1 convolution, the label of hq_int_conv2d_kernel_name.  It depends on the shape only,
-// never on the output type.
-enum ConvClass { kClassTile = 0, kClassWave = 1, kClassResident = 2, kClassResidentInt8 = 3 };
-
-ConvClass conv_class(int64_t pixels, int w, int c_in, int c_out, int r, int sx_static, int bits) {
-    if (bits == 8 || r != 3) return kClassTile;
-    const int64_t cus = hq::compute_units();
-    // at least one 64 x 256 tile per CU, and 256 pixels plus the halo within 400 rows
-    const bool wide = ((pixels + 255) / 256) * ((c_out + 63) / 64) >= cus && c_in % 192 == 0 && 256 + 2 * (w + 1) <= 400;
-    if (!sx_static && c_in == 192 && wide) return kClassResident;
-    if (!sx_static && hq_conv3x3_res_fits(pixels, w, c_in, c_out)) return kClassResidentInt8;
-    // about one 64 x 64 output tile per CU or fewer
-    const int64_t tiles64 = ((pixels + 63) / 64) * ((c_out + 63) / 64);
-    if (c_in % 192 == 0 && tiles64 * 4 <= 5 * cus) return kClassWave;
-    if (sx_static && wide) return kClassResident;
-    return kClassTile;
+// One 192-channel slice of 4-bit codes and about one 64 x 64 output tile per CU or fewer: the wave-split kernel, which has no
+// activation tile to expand first (1 x 64 x 64 x 192: 8.4 us against 9.2; 1 x 16 x 16 x 192 -> 100: 8.6 against 9.4).  From two
+// slices on the resident kernel wins there too (16 x 8 x 8 x 960: 15.4 against 17.8, 23 x 12 x 12 x 384: 13.6 against 16.8).
+bool takes_wave_split(int64_t pixels, int c_in, int c_out, int bits) {
+    return bits == 4 && c_in == 192 && ((pixels + 63) / 64) * ((c_out + 63) / 64) * 4 <= 5 * hq::compute_units();
 }
 
 }  // namespace
@@ -135,12 +124,7 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
     }
     if (c_in % 64 != 0) return hq_gemm_launch_anyk(a, r * s, y_dtype, st_);
     if (r == 3) {
-        // One 192-channel slice and so few tiles that the K range is split over waves anyway: the wave-split kernel,
-        // which has no activation tile to expand first (1 x 64 x 64 x 192: 8.4 us against 9.2; 1 x 16 x 16 x 192 -> 100:
-        // 8.6 against 9.4).  From two slices on the resident kernel wins there too (16 x 8 x 8 x 960: 15.4 against 17.8,
-        // 23 x 12 x 12 x 384: 13.6 against 16.8).  8-bit codes go there at all sizes (hq_resident_kernel.h).
-        if (bits == 4 && c_in == 192 && conv_class(pixels, w, c_in, c_out, r, 1, bits) == kClassWave)
-            return hq_conv3x3_wave_launch(a, y_dtype, st_);
+        if (takes_wave_split(pixels, c_in, c_out, bits)) return hq_conv3x3_wave_launch(a, y_dtype, st_);
         st = hq_resident_launch(a, 0, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
@@ -252,16 +236,10 @@ extern "C" const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in,
     if (r != s || (r != 1 && r != 3) || stride != 1 || pad != (r - 1) / 2) return "unsupported";
     if (c_in % 8 != 0 || (bits == 8 && c_in % 64 != 0)) return "unsupported";
     if (c_in % 64 != 0) return "small-channel-count";
-    switch (conv_class(static_cast<int64_t>(nb) * h * w, w, c_in, c_out, r, static_scale, bits)) {
-        case kClassWave: return "wave-split";
-        case kClassResident: return "activation-resident";
-        case kClassResidentInt8:
-            switch (hq_conv3x3_res_tile_pixels(static_cast<int64_t>(nb) * h * w, w, c_in, c_out)) {
-                case 256: return "activation-resident-int8 (256 pixels)";
-                case 129: return "activation-resident-int8 (128 pixels, 4 waves)";
-                case 128: return "activation-resident-int8 (128 pixels)";
-                default: return "activation-resident-int8 (64 pixels)";
-            }
-        default: return "tile";
+    if (r == 3) {   // (as in int_conv2d)
+        const int64_t pixels = static_cast<int64_t>(nb) * h * w;
+        if (takes_wave_split(pixels, c_in, c_out, bits)) return "wave-split";
+        if (const char *cut = hq_resident_cut_name(pixels, w, c_in, c_out, bits, static_scale)) return cut;
     }
+    return "tile";
 }

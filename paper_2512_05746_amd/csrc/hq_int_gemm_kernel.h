@@ -944,10 +944,9 @@ hq_status hq_conv3x3_wave_launch(const GemmArgs &a, hq_dtype y_dtype, hipStream_
 // linear / 1x1 / 3x3 (stride 1) for channel counts that are a multiple of 8 but not of 64 (hq_int_gemm_anyk.hip)
 hq_status hq_gemm_launch_anyk(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream);
 hq_status hq_fill_zero_launch(void *dst, uint64_t ints, hipStream_t stream);
-// size classes of the one-launch 3x3 layer (hq_conv3x3_res.hip)
-bool hq_conv3x3_res_fits(int64_t pixels, int w, int c_in, int c_out);
-int hq_conv3x3_res_tile_pixels(int64_t pixels, int w, int c_in, int c_out);
 // 3x3 layers of stride 1, k a multiple of 64: 4-bit codes on the 6-bit floating-point matrix instruction, 8-bit on int8
 // (hq_resident.hip); had_block != 0: the activations are digit planes of a transform of that block, at most 32;
 // HQ_ERR_UNSUPPORTED, with nothing launched, if a tile does not fit the LDS
 hq_status hq_resident_launch(const GemmArgs &a, int had_block, hq_dtype y_dtype, hipStream_t stream);
+// how that kernel cuts a layer of codes (not planes), a static string, or null where it does not take the layer
+const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, int sx_static);

@@ -82,6 +82,7 @@ Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n) {
     const int steps = k / 64, cus = hq::compute_units();
     const int ks = steps % 3 == 0 || steps > 4 ? 3 : steps == 1 ? 1 : 2;
     Plan best{};
+    if (n >= 1 << 21) return best;   // (a tile's results lie within 2 GiB of their first)
     double best_cost = 0;
     for (const int nw : {8, 4})
         for (int xw = 0; xw <= 1; ++xw)
@@ -95,6 +96,8 @@ Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n) {
     return best;
 }
 
+int kind_of(int bits, int sx_static) { return bits == 8 ? kResBytes : sx_static ? kResSum : kResPerTap; }
+
 // Dynamic LDS beyond the default limit has to be allowed once per kernel and device.
 hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
     int dev = 0;
@@ -107,11 +110,21 @@ hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
 
 }  // namespace
 
+const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, int sx_static) {
+    const Plan p = choose_plan(kind_of(bits, sx_static), false, pixels, w, k, n);
+    if (!p.ok) return nullptr;
+    static const char *const names[2][2][2] = {   // [pixels][waves][slices resident at a time]
+        {{"activation-resident (128 pixels, 4 waves)", "activation-resident (128 pixels, 4 waves, slices in turn)"},
+         {"activation-resident (128 pixels, 8 waves)", "activation-resident (128 pixels, 8 waves, slices in turn)"}},
+        {{"activation-resident (256 pixels, 4 waves)", "activation-resident (256 pixels, 4 waves, slices in turn)"},
+         {"activation-resident (256 pixels, 8 waves)", "activation-resident (256 pixels, 8 waves, slices in turn)"}}};
+    return names[p.xw_log2][p.nw == 8][p.chunk < p.slices];
+}
+
 // HQ_ERR_UNSUPPORTED, with nothing launched: the image rows are too long for a tile and its halo.
 hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
-    const int kind = g.bits == 8 ? kResBytes : had_block ? kResPlanes : g.sx_static ? kResSum : kResPerTap;
-    if (g.n >= 1 << 21) return HQ_ERR_UNSUPPORTED;   // (a tile's results lie within 2 GiB of their first)
+    const int kind = had_block ? kResPlanes : kind_of(g.bits, g.sx_static);
     const Plan p = choose_plan(kind, kind == kResPerTap && y_dtype == HQ_F32, g.pixels, g.w, g.k, g.n);
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
     ResidentArgs a{};

@@ -32,22 +32,25 @@ def test_every_declared_symbol_is_exported(lib):
 
 
 def test_conv_kernel_choice_is_a_function_of_the_geometry(lib):
-    """The kernel family is reported per geometry (no output type among the arguments): the three
-    3x3 families are each reachable, and geometries that are not built say so."""
+    """The kernel and its cut are reported per geometry (no output type among the arguments): every 3x3 kernel
+    is reachable, and geometries that are not built say so."""
     name = hq.hq_int_conv2d_kernel_name
-    assert name(16, 64, 64, 192, 192) == "activation-resident"
-    assert name(20, 50, 50, 192, 64) == "activation-resident-int8 (128 pixels, 4 waves)"
-    assert name(6, 70, 75, 192, 330) == "activation-resident-int8 (256 pixels)"
-    assert name(16, 32, 32, 384, 384) == "activation-resident-int8 (128 pixels)"
-    assert name(16, 16, 16, 576, 576) == "activation-resident-int8 (64 pixels)"
-    assert name(16, 8, 8, 960, 960) == "wave-split"
-    assert name(16, 64, 64, 192, 192, static_scale=True) == "activation-resident"
-    assert name(16, 32, 32, 384, 384, static_scale=True) == "activation-resident"
-    assert name(2, 9, 9, 64, 8) == "tile"
+    for static_scale in (False, True):
+        assert name(16, 64, 64, 192, 192, static_scale=static_scale) == "activation-resident (256 pixels, 8 waves)"
+        assert name(16, 32, 32, 384, 384, static_scale=static_scale) == "activation-resident (128 pixels, 8 waves)"
+        assert name(33, 16, 16, 192, 200, static_scale=static_scale) == "activation-resident (256 pixels, 4 waves)"
+        assert name(3, 9, 6, 384, 24, static_scale=static_scale) == "activation-resident (128 pixels, 4 waves)"
+        assert name(1, 6, 200, 960, 40, static_scale=static_scale) == "activation-resident (128 pixels, 8 waves, slices in turn)"
+        assert name(1, 16, 16, 192, 100, static_scale=static_scale) == "wave-split"
+        assert name(4, 8, 1500, 192, 192, static_scale=static_scale) == "tile"   # no activation tile holds such a row
+    assert name(16, 8, 8, 960, 960) == "activation-resident (128 pixels, 8 waves)"
     assert name(2, 9, 9, 64, 8, ksize=1) == "tile"
     assert name(2, 9, 9, 64, 8, stride=2) == "tile (stride 2)"
     assert name(2, 9, 9, 64, 8, ksize=5) == "unsupported"
-    assert name(16, 64, 64, 192, 192, bits=8) == "tile"
+    assert name(16, 64, 64, 192, 192, bits=8) == "activation-resident (256 pixels, 8 waves)"
+    assert name(1, 16, 16, 192, 100, bits=8).startswith("activation-resident")
+    assert name(4, 8, 1500, 192, 192, bits=8) == "tile"
+    assert name(16, 64, 64, 192, 192, ksize=1, bits=8) == "tile"
     assert name(2, 32, 32, 8, 320) == "small-channel-count"
     assert name(2, 32, 32, 200, 64, ksize=1) == "small-channel-count"
     assert name(2, 32, 32, 12, 64) == "unsupported"

@@ -583,8 +583,8 @@ def test_int_conv_geometry(hq, nb, h, w, cin, cout, ks):
 
 @pytest.mark.parametrize("nb,h,w,cin,cout", [(8, 41, 50, 192, 250), (5, 60, 71, 384, 200), (3, 79, 70, 192, 330)])
 def test_activation_resident_conv_odd_geometry(hq, nb, h, w, cin, cout):
-    """Shapes that take the kernel with the activation tile resident in LDS (at least one 64 x 256
-    tile per CU), with image sizes that are not powers of two, tiles that span image rows and
+    """Shapes that take the kernel with the activation tile resident in LDS, with image sizes that are
+    not powers of two, tiles that span image rows and
     images, a ragged last pixel tile and a ragged last channel tile; per-pixel scales (one or two
     192-channel slices) and one scale for the tensor (zeros must be loaded outside the image)."""
     rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
@@ -594,9 +594,8 @@ def test_activation_resident_conv_odd_geometry(hq, nb, h, w, cin, cout):
     sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
     bias = rng.standard_normal(cout).astype(np.float32)
     xq_d, wq_d = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
-    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout, static_scale=True) == "activation-resident"
-    if cin == 192:
-        assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout) == "activation-resident"
+    for static_scale in (False, True):
+        assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout, static_scale=static_scale).startswith("activation-resident (")
     acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
     acc_g = host(hq.hq_int_conv2d(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
     assert np.array_equal(acc_g, acc_o), "per-tap int32 sums"
@@ -612,18 +611,16 @@ def test_activation_resident_conv_odd_geometry(hq, nb, h, w, cin, cout):
     check_y("y (static)", y_g, y_o, rtol=1e-5)
 
 
-@pytest.mark.parametrize("nb,h,w,cin,cout,px", [(20, 50, 50, 192, 64, "128 pixels, 4 waves"), (6, 70, 75, 192, 330, 256),
-                                                (4, 80, 60, 192, 100, 128),
-                                                (3, 40, 40, 192, 500, 64), (20, 30, 33, 384, 150, 128),
-                                                (17, 32, 20, 384, 390, 128), (33, 16, 16, 192, 200, 128),
-                                                (19, 15, 15, 576, 300, 64), (8, 32, 32, 384, 384, 64)])
-def test_int8_resident_conv_odd_geometry(hq, nb, h, w, cin, cout, px):
-    """Shapes that take the kernel with the int8 activation tile resident in LDS, for each of its
-    three pixel-tile sizes with eight waves (K ranges split over 1+2, 2+4 and 4+8 waves, partial sums
-    exchanged through LDS) and for its four-wave form, one to three 192-channel slices, image sizes that are not powers of
-    two, tiles that span image rows and images, ragged last pixel and channel tiles.  Per-tap int32
-    sums bit for bit (twice: the call zeroes its output), fp32 output to 2e-4 (sums are folded per
-    slice and tap from a biased accumulator)."""
+@pytest.mark.parametrize("nb,h,w,cin,cout,px,waves", [(20, 50, 50, 192, 64, 256, 8), (6, 70, 75, 192, 330, 256, 8),
+                                                      (4, 80, 60, 192, 100, 128, 4),
+                                                      (3, 40, 40, 192, 500, 128, 4), (20, 30, 33, 384, 150, 256, 8),
+                                                      (17, 32, 20, 384, 390, 128, 8), (33, 16, 16, 192, 200, 256, 4),
+                                                      (19, 15, 15, 576, 300, 128, 8), (8, 32, 32, 384, 384, 128, 8)])
+def test_activation_resident_conv_cuts(hq, nb, h, w, cin, cout, px, waves):
+    """Every cut of the kernel with the activation tile resident in LDS (one or two groups of 128 pixels, four or
+    eight waves; K ranges split over waves, partial sums exchanged through LDS), one to three 192-channel slices,
+    image sizes that are not powers of two, tiles that span image rows and images, ragged last pixel and channel
+    tiles.  Per-tap int32 sums bit for bit (twice: the call zeroes its output), fp32 output to 2e-4, fp16 output."""
     rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
     xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
     wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
@@ -632,8 +629,7 @@ def test_int8_resident_conv_odd_geometry(hq, nb, h, w, cin, cout, px):
     sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
     bias = rng.standard_normal(cout).astype(np.float32)
     xq_d, wq_d = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
-    want = "activation-resident-int8 (%s)" % (px if isinstance(px, str) else "%d pixels" % px)
-    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout) == want
+    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout) == "activation-resident (%d pixels, %d waves)" % (px, waves)
     acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
     for rep in range(2):
         acc_g = host(hq.hq_int_conv2d(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
@@ -650,11 +646,11 @@ def test_int8_resident_conv_odd_geometry(hq, nb, h, w, cin, cout, px):
 
 @pytest.mark.parametrize("nb,h,w,cin,cout", [(1, 16, 16, 192, 100), (3, 9, 6, 384, 24), (5, 7, 9, 576, 130),
                                              (2, 8, 8, 960, 960), (1, 1, 1, 192, 8), (4, 16, 16, 192, 320)])
-def test_wave_split_conv_odd_geometry(hq, nb, h, w, cin, cout):
-    """Shapes that take the kernel which splits a tile's K range over the waves of a workgroup
-    (few 64 x 64 tiles): 1, 2 and 4 waves per tile, ragged pixel and channel tiles, tiles spanning
-    images.  Per-tap int32 sums and the one sum over all taps bit for bit (every wave adds its
-    share with integer atomics), fp32 outputs of both scale modes to 1e-5."""
+def test_few_tiles_conv_odd_geometry(hq, nb, h, w, cin, cout):
+    """Few 64 x 64 tiles: with one 192-channel slice the kernel which splits a tile's K range over the
+    waves of a workgroup (1, 2 and 4 waves per tile), with more the activation-resident one; ragged pixel
+    and channel tiles, tiles spanning images.  Per-tap int32 sums and the one sum over all taps bit for bit
+    (added with integer atomics), fp32 outputs of both scale modes to 1e-5."""
     rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
     xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
     wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
@@ -663,8 +659,9 @@ def test_wave_split_conv_odd_geometry(hq, nb, h, w, cin, cout):
     sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
     bias = rng.standard_normal(cout).astype(np.float32)
     xq_d, wq_d = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
-    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout) == "wave-split"
-    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout, static_scale=True) == "wave-split"
+    for static_scale in (False, True):
+        name = hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout, static_scale=static_scale)
+        assert name == "wave-split" if cin == 192 else name.startswith("activation-resident (")
     acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
     for rep in range(2):     # twice: the output buffer is zeroed by the call itself
         acc_g = host(hq.hq_int_conv2d(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
@@ -1225,7 +1222,7 @@ def test_hip_graph_replay_of_the_other_schemes(hq):
 
 
 def test_hip_graph_replay_of_the_one_launch_layers_and_integer_outputs(hq):
-    """The one-launch 3x3 and linear layers, the int8-resident convolution and the integer outputs that
+    """The one-launch 3x3 and linear layers, the activation-resident convolution and the integer outputs that
     are accumulated with atomics (their output is zeroed by a kernel inside the call, not by a memset
     node) captured into one HIP graph: every replay must reproduce the eager results bit for bit."""
     rng = np.random.default_rng(11)
@@ -1244,7 +1241,7 @@ def test_hip_graph_replay_of_the_one_launch_layers_and_integer_outputs(hq):
     yi = torch.empty((nb, h, w, 9, cout), dtype=torch.int32, device="cuda")
     yw = torch.empty((1, 16, 16, 9, 100), dtype=torch.int32, device="cuda")
     del wc
-    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout) == "activation-resident"
+    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout).startswith("activation-resident (")
     assert hq.hq_int_conv2d_kernel_name(1, 16, 16, 192, 100) == "wave-split"
 
     def run():
