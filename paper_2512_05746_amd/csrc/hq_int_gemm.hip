@@ -17,17 +17,56 @@ namespace {
 //     6200 x 384 -> 1280 13.7 -> 13.85): there the results are most of the time and the third workgroup hides them;
 //   - otherwise 128 x 128 tiles if there is at least one per CU;
 //   - a layer with fewer tiles takes 64 x 64 tiles at four workgroups per CU.
-hq_status launch_gemm(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream) {
-    if ((a.bits == 8 ? a.k : a.k / 2) % 96 != 0) return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
+enum class Tile { t128x128, t64x128, t64x64 };
+
+Tile choose_tile(int64_t pixels, int n, int k, int bits, int taps) {
+    if ((bits == 8 ? k : k / 2) % 96 != 0) return Tile::t128x128;
     const int64_t cus = hq::compute_units();
-    const int64_t pix128 = (static_cast<int64_t>(a.pixels) + 127) / 128;
-    const int64_t tiles64 = pix128 * ((a.n + 63) / 64), tiles128 = pix128 * ((a.n + 127) / 128);
-    if (a.bits == 4 && taps <= 3 && taps * a.k >= 576 && tiles64 > 3 * cus && tiles128 <= 2 * cus)
-        return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
-    if (a.n % 64 == 0 && pix128 * (a.n / 64) >= 2 * cus) return hq_gemm_launch_64x128(a, taps, y_dtype, stream);
-    if (tiles128 >= cus) return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
-    return hq_gemm_launch_64x64(a, taps, y_dtype, stream);
+    const int64_t pix128 = (pixels + 127) / 128, tiles64 = pix128 * ((n + 63) / 64), tiles128 = pix128 * ((n + 127) / 128);
+    if (bits == 4 && taps <= 3 && taps * k >= 576 && tiles64 > 3 * cus && tiles128 <= 2 * cus) return Tile::t128x128;
+    if (n % 64 == 0 && pix128 * (n / 64) >= 2 * cus) return Tile::t64x128;
+    return tiles128 >= cus ? Tile::t128x128 : Tile::t64x64;
 }
+
+hq_status launch_gemm(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream) {
+    switch (choose_tile(a.pixels, a.n, a.k, a.bits, taps)) {
+        case Tile::t128x128: return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
+        case Tile::t64x128: return hq_gemm_launch_64x128(a, taps, y_dtype, stream);
+        default: return hq_gemm_launch_64x64(a, taps, y_dtype, stream);
+    }
+}
+
+}  // namespace
+
+// Estimated us of a call: its start, the results (per MB of fp16), and for every 64 input channels (nine taps) what a round of
+// a CU's tiles costs plus what each of its tiles costs.  Fitted to 1448 calls of 3x3 layers of 64 to 960 channels, 64 to
+// 170000 pixels, rows of 8 to 448: 4 .. 10 % rms.
+double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had_block) {
+    struct Costs {
+        double start, result_mb;
+        struct { double round, tile; } short_chunks, t64x128, t128x128, t64x64;   // short: K in chunks of 64 codes
+    };
+    constexpr Costs per_tap{5.6, 0.36, {3.84, 0.38}, {0, 1.18}, {0, 2.90}, {0.90, 0.42}};
+    constexpr Costs one_sum{3.7, 0.23, {2.85, 0.98}, {0, 1.26}, {0, 3.10}, {0.90, 0.62}};
+    constexpr Costs bytes{5.1, 0.24, {5.67, 1.67}, {0, 2.00}, {0, 4.40}, {1.66, 0.71}};
+    constexpr Costs planes{6.4, 0.51, {11.6, 1.31}, {0, 3.44}, {4.00, 7.00}, {3.30, 1.22}};
+    const Costs &c = had_block ? planes : bits == 8 ? bytes : sx_static ? one_sum : per_tap;
+    const Tile tile = choose_tile(pixels, n, k, bits, 9);
+    const int pt = tile == Tile::t64x64 ? 64 : 128, ct = tile == Tile::t128x128 ? 128 : 64;
+    const int per_round = tile == Tile::t64x64 ? 4 : tile == Tile::t64x128 ? 3 : 2;   // (workgroups of a CU)
+    const double tiles = static_cast<double>((pixels + pt - 1) / pt * ((n + ct - 1) / ct)) / hq::compute_units();
+    const double rounds = ceil(tiles / per_round), used = (rounds - 1) * per_round + ceil(tiles - (rounds - 1) * per_round);
+    const auto &cost = (bits == 8 ? k : k / 2) % 96 != 0 ? c.short_chunks
+                       : tile == Tile::t64x128           ? c.t64x128
+                       : tile == Tile::t128x128          ? c.t128x128
+                                                         : c.t64x64;
+    // (groups of 16 channels are stored at once where all are whole, value by value otherwise)
+    const double start = c.start + (n % 16 ? 2 : 0), result_mb = c.result_mb + (n % 16 ? 1.2 : 0);
+    const double planes_read = had_block && had_block <= 8 ? 2.0 / 3.0 : 1.0;
+    return start + static_cast<double>(pixels) * n * 2e-6 * result_mb + k / 64 * (cost.round * rounds + cost.tile * used) * planes_read;
+}
+
+namespace {
 
 // The kernels index pixels with 32 bits and address the packed operands with
 // 32-bit byte offsets; a 3x3 tap shifts an activation offset by up to w + 1 pixels

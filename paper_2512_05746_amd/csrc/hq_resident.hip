@@ -60,7 +60,8 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
 // Clocks of a workgroup, fitted to time stamps of the kernel on 3x3 layers of 64 to 960 channels (within 15 % of
 // them, and in the measured order of the cuts): start and first loads, filling (rounds of 32-row items over the waves),
 // units (two waves per SIMD share the vector issue), results (each exchange of sums costs two barriers).
-double cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
+struct Cost { double clocks, rounds; };
+Cost cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
     const int px = 128 << p.xw_log2, blocks = (n + 31) / 32, planes = kind >= kResPlanes ? 2 : 1;
     const int64_t wgs = (pixels + px - 1) / px * ((blocks + p.cb - 1) / p.cb);
     const int per_cu = p.nw == 4 && p.lds <= kLdsPerCu / 2 ? 2 : 1;
@@ -75,25 +76,41 @@ double cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
         clocks += units * p.ks * planes * (paired ? 575.0 : 330.0) + 3600 + (kl ? 1000 + 1500 * kl : 0);
         left -= p.nw >> kl;
     }
-    return rounds * clocks;
+    return {rounds * clocks, rounds};
 }
 
-Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n) {
+// The best cut, not ok if none fits the LDS.
+Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n, Cost &cost) {
     const int steps = k / 64, cus = hq::compute_units();
     const int ks = steps % 3 == 0 || steps > 4 ? 3 : steps == 1 ? 1 : 2;
     Plan best{};
     if (n >= 1 << 21) return best;   // (a tile's results lie within 2 GiB of their first)
-    double best_cost = 0;
     for (const int nw : {8, 4})
         for (int xw = 0; xw <= 1; ++xw)
             for (const int cb : {1, 2, 3, 4, 6, 8, 12}) {
                 if (cb > 1 && cb > 2 * ((n + 31) / 32) - 1) continue;
                 const Plan p = lay_out(kind, by_slice, w, k, n, ks, nw, xw, cb, nw == 4 ? kLdsPerCu / 2 : kLdsPerCu);
                 if (!p.ok) continue;
-                const double c = cost_of(p, kind, pixels, n, cus);
-                if (!best.ok || c < best_cost) { best = p; best_cost = c; }
+                const Cost c = cost_of(p, kind, pixels, n, cus);
+                if (!best.ok || c.clocks < cost.clocks) { best = p; cost = c; }
             }
     return best;
+}
+
+// The cut, not ok where the tile kernel is estimated to be the faster one by more than the estimates are off.  That is so for
+// images so wide that a tile's rows and those above and below fill the LDS (the tile is expanded again for every 128 channels,
+// or some slices at a time), and for some layers of few channels or of a few more tiles than CUs.  us, resident kernel against
+// tile kernel: 1 x 128 x 256 x 192 26.3 / 19.9, 1 x 128 x 256 x 576 144 / 116, 1 x 73 x 448 x 960 419 / 302; but
+// 1 x 256 x 128 x 384 49.3 / 57.6, 3 x 45 x 27 x 320 -> 200 11.6 / 34.
+Plan choose_kernel(int kind, int had_block, int64_t pixels, int w, int k, int n) {
+    Cost cost{};
+    Plan p = choose_plan(kind, false, pixels, w, k, n, cost);
+    if (!p.ok) return p;
+    struct Us { double kclock, chunk; };   // of a thousand clocks, and of making a set of slices resident
+    constexpr Us us[4] = {{0.42, 1.6}, {0.42, 1.6}, {0.34, 2.2}, {0.42, 1.3}};   // by kind; fitted as hq_tile_us, 7 .. 11 % rms
+    const double resident = us[kind].kclock * cost.clocks * 1e-3 + us[kind].chunk * cost.rounds * ((p.slices + p.chunk - 1) / p.chunk);
+    p.ok = hq_tile_us(pixels, n, k, kind == kResBytes ? 8 : 4, kind == kResSum, had_block) >= 0.92 * resident;
+    return p;
 }
 
 int kind_of(int bits, int sx_static) { return bits == 8 ? kResBytes : sx_static ? kResSum : kResPerTap; }
@@ -111,7 +128,7 @@ hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
 }  // namespace
 
 const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, int sx_static) {
-    const Plan p = choose_plan(kind_of(bits, sx_static), false, pixels, w, k, n);
+    const Plan p = choose_kernel(kind_of(bits, sx_static), 0, pixels, w, k, n);
     if (!p.ok) return nullptr;
     static const char *const names[2][2][2] = {   // [pixels][waves][slices resident at a time]
         {{"activation-resident (128 pixels, 4 waves)", "activation-resident (128 pixels, 4 waves, slices in turn)"},
@@ -121,11 +138,15 @@ const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, 
     return names[p.xw_log2][p.nw == 8][p.chunk < p.slices];
 }
 
-// HQ_ERR_UNSUPPORTED, with nothing launched: the image rows are too long for a tile and its halo.
+// HQ_ERR_UNSUPPORTED, with nothing launched: the layer is one for the tile kernel.
 hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     const int kind = had_block ? kResPlanes : kind_of(g.bits, g.sx_static);
-    const Plan p = choose_plan(kind, kind == kResPerTap && y_dtype == HQ_F32, g.pixels, g.w, g.k, g.n);
+    Plan p = choose_kernel(kind, had_block, g.pixels, g.w, g.k, g.n);
+    if (p.ok && kind == kResPerTap && y_dtype == HQ_F32) {
+        Cost cost{};
+        p = choose_plan(kind, true, g.pixels, g.w, g.k, g.n, cost);
+    }
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
     ResidentArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;

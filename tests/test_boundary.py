@@ -43,6 +43,8 @@ def test_conv_kernel_choice_is_a_function_of_the_geometry(lib):
         assert name(1, 6, 200, 960, 40, static_scale=static_scale) == "activation-resident (128 pixels, 8 waves, slices in turn)"
         assert name(1, 16, 16, 192, 100, static_scale=static_scale) == "wave-split"
         assert name(4, 8, 1500, 192, 192, static_scale=static_scale) == "tile"   # no activation tile holds such a row
+        assert name(1, 128, 256, 576, 576, static_scale=static_scale) == "tile"   # it fits, and costs more than it saves
+        assert name(1, 256, 128, 384, 384, static_scale=static_scale).startswith("activation-resident")
     assert name(16, 8, 8, 960, 960) == "activation-resident (128 pixels, 8 waves)"
     assert name(2, 9, 9, 64, 8, ksize=1) == "tile"
     assert name(2, 9, 9, 64, 8, stride=2) == "tile (stride 2)"

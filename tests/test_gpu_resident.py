@@ -89,6 +89,9 @@ def test_conv3x3_fp32_codes_of_one_sign(hq, nb, h, w, cin, cout):
     (2, 9, 48, 960, 72, 16),     # the largest sums that go this way; some slices resident at a time
     (1, 3, 48, 192, 33, 1),      # no transform
     (1, 2, 64, 512, 40, 32),     # sums beyond 2^24: the tile kernel
+    (1, 3, 208, 192, 40, 16),    # the longest rows that fit beside 16-pixel blocks
+    (1, 3, 224, 192, 40, 16),    # rows too long: the tile kernel, three planes
+    (1, 3, 216, 192, 40, 8),     # and two
 ])
 def test_conv_width(hq, nb, h, w, cin, cout, block):
     """Integer sums bit for bit, extreme numbers (+-8 x block) among them; fp32 results to 1e-6 (three roundings)."""
@@ -159,6 +162,60 @@ def test_conv3x3_8bit(hq, nb, h, w, cin, cout):
     assert np.array_equal(acc, acc_o), "per-tap sums"
     y = host(hq.hq_int_conv2d_i8(xq_d, dev(sx), wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
     check_y("y", y, y_o, rtol=1e-5)
+
+
+@pytest.mark.parametrize("h,w,cin,cout,kernel", [
+    (4, 1344, 64, 40, "resident"), (4, 1345, 64, 40, "tile"),     # the longest image row whose tile fits, and one more
+    (4, 454, 320, 72, "resident"), (4, 455, 320, 72, "tile"),     # (slices in turn; fp32 results: tile on both sides)
+    (4, 207, 960, 40, "resident"), (4, 208, 960, 40, "tile"),     # estimated to be faster on the tile kernel
+    (24, 320, 576, 72, "tile"), (32, 256, 384, 208, "tile"),      # K chunks of 192 codes, ragged channels
+    (90, 256, 192, 192, "tile"),                                  # 64 x 128 tiles
+])
+def test_conv3x3_long_rows(hq, h, w, cin, cout, kernel):
+    """Both sides of the rule between the resident and the tile kernel: per-tap sums and one sum bit for bit, fp32 and fp16
+    results (1e-5: eighteen folds at most and few roundings more, partial sums up to some times the result; 1e-3: fp16)."""
+    rng = np.random.default_rng(h + w + cin + cout)
+    name = hq.hq_int_conv2d_kernel_name(1, h, w, cin, cout)
+    assert name == "tile" if kernel == "tile" else name.startswith("activation-resident"), name
+    xq = rng.integers(-8, 8, (1, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
+    sx = rng.uniform(0.01, 1.0, (1, h, w)).astype(np.float32)
+    sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
+    bias = rng.standard_normal(cout).astype(np.float16)
+    xq_d, wq_d = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
+    acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
+    acc = host(hq.hq_int_conv2d(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o), "per-tap sums"
+    acc = host(hq.hq_int_conv2d_static(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o.sum(axis=3)), "one sum"
+    for ydt, rtol in ((torch.float32, 1e-5), (torch.float16, 1e-3)):
+        b = dev(bias).to(ydt)
+        check_y("y", host(hq.hq_int_conv2d(xq_d, dev(sx), wq_d, dev(sw), b, ksize=3, y_dtype=ydt)), y_o, rtol=rtol)
+    s1 = torch.tensor([0.37], dtype=torch.float32, device="cuda")
+    _, y_o = oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1, want_acc=False)
+    y = host(hq.hq_int_conv2d_static(xq_d, s1, wq_d, dev(sw), dev(bias), ksize=3, y_dtype=torch.float16))
+    check_y("y (static)", y, y_o, rtol=1e-3)
+
+
+@pytest.mark.parametrize("h,w,cin,cout,kernel", [
+    (4, 329, 192, 40, "resident"), (4, 330, 192, 40, "tile"), (4, 1031, 64, 40, "resident"), (4, 1032, 64, 40, "tile"),
+    (4, 329, 960, 40, "resident"), (90, 256, 192, 192, "tile"),
+])
+def test_conv3x3_8bit_long_rows(hq, h, w, cin, cout, kernel):
+    """As test_conv3x3_long_rows."""
+    rng = np.random.default_rng(h + w + cin + cout)
+    name = hq.hq_int_conv2d_kernel_name(1, h, w, cin, cout, bits=8)
+    assert name == "tile" if kernel == "tile" else name.startswith("activation-resident"), name
+    xq = rng.integers(-128, 128, (1, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-128, 128, (cout, 3, 3, cin)).astype(np.int8)
+    sx = rng.uniform(0.01, 1.0, (1, h, w)).astype(np.float32)
+    sw = rng.uniform(1e-5, 1e-3, cout).astype(np.float32)   # (fp16 results stay in range)
+    xq_d, wq_d = dev(xq), dev(wq.reshape(cout, 9, cin))
+    acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, None, stride=1, pad=1)
+    acc = host(hq.hq_int_conv2d_i8(xq_d, None, wq_d, None, None, ksize=3, y_dtype=torch.int32))
+    assert np.array_equal(acc, acc_o), "per-tap sums"
+    for ydt, rtol in ((torch.float32, 1e-5), (torch.float16, 1e-3)):
+        check_y("y", host(hq.hq_int_conv2d_i8(xq_d, dev(sx), wq_d, dev(sw), None, ksize=3, y_dtype=ydt)), y_o, rtol=rtol)
 
 
 @pytest.mark.parametrize("dtype", [np.float16, np.float32])
