@@ -32,7 +32,7 @@ extern "C" hq_status hq_act_quant_int_conv2d(const void *x, hq_dtype x_dtype, co
     if (pixels >= 0x7FFFFFFFLL || static_cast<int64_t>(c_out) * 9 * (c_in / 2) > 0xFFFFFFFFLL) return HQ_ERR_UNSUPPORTED;
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     ResPlan p;
-    if (!res_choose(pixels, w, c_in, c_out, hq::compute_units(), true, p)) return HQ_ERR_UNSUPPORTED;
+    if (!res_choose(pixels, w, c_in, c_out, hq::compute_units(), p)) return HQ_ERR_UNSUPPORTED;
     if (p.tiles > 0x7fffffffLL) return HQ_ERR_SHAPE;
     GemmArgs g{};
     g.wq = wq; g.sw = w_scale; g.bias = bias; g.y = y;
@@ -48,6 +48,6 @@ extern "C" hq_status hq_act_quant_int_conv2d(const void *x, hq_dtype x_dtype, co
         const hq_status zs = hq_fill_zero_launch(y, static_cast<uint64_t>(pixels) * 9 * c_out, st);
         if (zs != HQ_OK) return zs;
     }
-    res_launch_plan<true>(a, p, y_dtype, st);
+    res_launch_plan(a, p, y_dtype, st);
     return check.status();
 }

@@ -48,8 +48,6 @@ constexpr int kResBlock = 64 * 96;   // weight rows of one 64-channel block of o
 constexpr int kRes4WaveCost = 85;    // percent: time of the four-wave form relative to the eight-wave form
 
 struct ResArgs {
-    const uint8_t *xq;   // [pixels, k/2]
-    const float *sx;     // [pixels]
     const uint8_t *wq;   // [n, 9, k/2]
     const float *sw;     // [n]
     const void *bias;    // [n] of the output dtype, or null
@@ -58,12 +56,11 @@ struct ResArgs {
     int n, k, h, w;
     uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
     uint32_t s_magic, s_shift;                     // ... of a unit index by the number of slices
-    uint32_t p_magic, p_shift;                     // ... of a piece index by the 16-byte pieces per activation row
     int pg_log2;         // PX = 64 << pg_log2
     int slices;          // k / 192
     uint32_t n_co_tiles, n_tiles;
     uint32_t stage_base, stage_bytes, tab_base;    // LDS layout: activations at 0, then stages, then tables
-    // transform and quantisation done here (FUSED): the fp16 activations [pixels, k], qmax of the codes, and
+    // the fp16 activations [pixels, k], qmax of the codes, and
     // optional outputs of the codes [pixels, k/2] and scales [pixels] the kernel used (null: not written)
     const __half *x;
     float qmax;
@@ -88,12 +85,12 @@ constexpr int res_stages(int pgl, int nwl) { return nwl == 3 ? (pgl == 0 ? 2 : 3
 
 // NWL: log2 of the waves per workgroup (3 or 2).  The K ranges are split (waves / 2) / pgn ways in
 // phase A and waves / pgn ways in phase B.
-// FUSED: the activations arrive as fp16 and the kernel itself applies the block-64 Hadamard
+// The activations arrive as fp16 and the kernel itself applies the block-64 Hadamard
 // transform (on the matrix cores, as the stand-alone transform-quantise kernel does, with the same
 // arithmetic and so the same codes) and the per-pixel quantisation to the rows of its tile and
 // halo: the codes go straight into the LDS image as int8 and never reach memory, the scales into
 // a table (Method, "Matrix Multiplication": X H is only ever consumed by the integer product).
-template <int OUT, int PGL, int NWL, bool FUSED>
+template <int OUT, int PGL, int NWL>
 __global__ __launch_bounds__(64 << NWL, NWL == 3 ? 1 : 2) void conv3x3_res_kernel(ResArgs a) {
     constexpr int NT = 64 << NWL;
     constexpr int kResLds = res_lds(NWL);
@@ -126,7 +123,7 @@ __global__ __launch_bounds__(64 << NWL, NWL == 3 ? 1 : 2) void conv3x3_res_kerne
     int *s_mask = reinterpret_cast<int *>(s_sx + TAPS * PX);              // [PX]
     float *s_sw = reinterpret_cast<float *>(s_mask + PX);                 // [192]
     float *s_bias = s_sw + 192;                                           // [192]
-    float *s_rowscale = s_bias + 192;                                     // [rows] (FUSED): scale of every row of the image
+    float *s_rowscale = s_bias + 192;                                     // [rows]: scale of every row of the image
 
     // ---- tile of this workgroup (XCD-contiguous: workgroup b runs on XCD b % 8) ------------------
     uint32_t tile = blockIdx.x;
@@ -203,7 +200,6 @@ __global__ __launch_bounds__(64 << NWL, NWL == 3 ? 1 : 2) void conv3x3_res_kerne
     // ---- table entries are requested first, so that their latency and that of the activation rows
     //      below pass together -------------------------------------------------------------------------------
     int t_mask = 0;
-    float t_sx[TAPS];
     float t_sw = 0.f, t_bias = 0.f;
     const int t_chan = NT - 1 - tid;   // (the last threads first: they have no pixel to look up)
     if (tid < PX) {
@@ -214,14 +210,6 @@ __global__ __launch_bounds__(64 << NWL, NWL == 3 ? 1 : 2) void conv3x3_res_kerne
         const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
         t_mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
         if (pix >= a.pixels) t_mask = 0;
-        if constexpr (!INT_OUT && !FUSED) {
-#pragma unroll
-            for (int t = 0; t < TAPS; ++t) {
-                uint32_t ip = pix + static_cast<uint32_t>((t / 3 - 1) * a.w + (t % 3 - 1));   // wraps below 0
-                ip = ip < last ? ip : last;
-                t_sx[t] = a.sx[ip];
-            }
-        }
     }
     if constexpr (!INT_OUT) {
         if (t_chan < 192 && co0 + t_chan < a.n) {
@@ -237,7 +225,7 @@ __global__ __launch_bounds__(64 << NWL, NWL == 3 ? 1 : 2) void conv3x3_res_kerne
     // is three 64-byte K steps of four 16-byte pieces [MFMA 0 / lane half 0, 0 / 1, 1 / 0, 1 / 1], the
     // piece index xor-ed with (row / 4) % 4 so that the operand reads of 16 consecutive rows hit 16
     // different bank groups (row stride 192 bytes = 12 groups).
-    if constexpr (FUSED) {
+    {
         // One wave transforms and quantises 16 rows at a time: lane l owns row l % 16 of the group and
         // K slice q = l / 16; its operands of 64-channel block b are the two 16-byte pieces at channels
         // 64 b + 32 h + 8 q, its 16 results are channels 64 b + 16 q .. + 15.  First pass: the row's
@@ -330,52 +318,13 @@ __global__ __launch_bounds__(64 << NWL, NWL == 3 ? 1 : 2) void conv3x3_res_kerne
                 }
             }
         }
-    } else
-    {
-        const uint32_t pieces_per_row = 6u * S;
-        const uint32_t total = static_cast<uint32_t>(rows) * pieces_per_row;
-        const int64_t first = static_cast<int64_t>(p0) - halo;
-        constexpr int BATCH = NWL == 3 ? 5 : 7;   // pieces per thread in flight: one batch covers a tile
-        for (uint32_t base = tid; base < total; base += NT * BATCH) {
-            v4i p[BATCH];
-            uint32_t dst[BATCH];
-#pragma unroll
-            for (int e = 0; e < BATCH; ++e) {
-                const uint32_t q = base + NT * e;
-                if (q < total) {
-                    const uint32_t row = hq::div_magic31(q, pieces_per_row, a.p_magic, a.p_shift);
-                    const uint32_t rem = q - row * pieces_per_row;
-                    int64_t pix = first + row;
-                    pix = pix < 0 ? 0 : (pix > static_cast<int64_t>(last) ? last : pix);
-                    p[e] = *reinterpret_cast<const v4i *>(a.xq + static_cast<uint64_t>(pix) * kbytes + rem * 16);
-                    const uint32_t slice = rem / 6, pc = rem - slice * 6;
-                    const uint32_t sw = (row >> 2) & 3;
-                    // piece index of (MFMA 0, lane half pc & 1); MFMA 1 is that index xor 2
-                    dst[e] = (slice * rows + row) * 192 + (pc >> 1) * 64 + (((pc & 1) ^ sw) * 16);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < BATCH; ++e) {
-                const uint32_t q = base + NT * e;
-                if (q < total) {
-                    v4i first_half, second_half;
-                    expand(p[e], first_half, second_half);
-                    *reinterpret_cast<v4i *>(lds + dst[e]) = first_half;
-                    *reinterpret_cast<v4i *>(lds + (dst[e] ^ 32)) = second_half;
-                }
-            }
-        }
     }
 
     // ---- tables ------------------------------------------------------------------------------------------
     if (tid < PX) {
         s_mask[tid] = t_mask;
-        if constexpr (!INT_OUT && !FUSED) {
-#pragma unroll
-            for (int t = 0; t < TAPS; ++t) s_sx[t * PX + tid] = ((t_mask >> t) & 1) ? t_sx[t] * (1.0f / 256.0f) : 0.f;
-        }
     }
-    if constexpr (!INT_OUT && FUSED) {
+    if constexpr (!INT_OUT) {
         __syncthreads();   // the scales of all rows are in the table
         if (tid < PX) {
             const int mask = s_mask[tid];
@@ -794,14 +743,14 @@ struct ResPlan {
 
 // LDS layout of a tile of 64 << pg_log2 pixels for a workgroup of 1 << nw_log2 waves, or false if it
 // does not fit.
-bool res_plan(int64_t pixels, int w, int c_in, int c_out, int pg_log2, int nw_log2, bool fused, ResPlan &p) {
+bool res_plan(int64_t pixels, int w, int c_in, int c_out, int pg_log2, int nw_log2, ResPlan &p) {
     if (nw_log2 - 1 - pg_log2 < 0) return false;
     const int px = 64 << pg_log2, nw = 1 << nw_log2;
     const int lds = res_lds(nw_log2);
     const int slices = c_in / 192;
     const int64_t rows = px + 2 * (static_cast<int64_t>(w) + 1);
     const int64_t act = rows * slices * 192;
-    const int64_t tab = ((9 * px + px + 2 * 192 + (fused ? rows : 0)) * 4 + 15) & ~static_cast<int64_t>(15);
+    const int64_t tab = ((9 * px + px + 2 * 192 + rows) * 4 + 15) & ~static_cast<int64_t>(15);
     const int64_t stage = static_cast<int64_t>(nw >> pg_log2) * kResBlock;
     const int64_t nstage = res_stages(pg_log2, nw_log2);
     if (act + nstage * stage + tab > lds) return false;
@@ -825,19 +774,19 @@ bool res_plan(int64_t pixels, int w, int c_in, int c_out, int pg_log2, int nw_lo
 // one tile per CU at a time.  Four waves and 128 pixels: two tiles per CU at a time, each at half
 // the rate, but the two workgroups of a CU are not in step with each other (measured faster
 // wherever the layer fills the CUs twice over).
-bool res_choose(int64_t pixels, int w, int c_in, int c_out, int cus, bool fused, ResPlan &best) {
+bool res_choose(int64_t pixels, int w, int c_in, int c_out, int cus, ResPlan &best) {
     if (c_in % 192 != 0 || c_in <= 0 || c_in > 192 * 16) return false;
     bool found = false;
     int64_t best_cost = 0;
     for (int l = 2; l >= 0; --l) {
         ResPlan p;
-        if (!res_plan(pixels, w, c_in, c_out, l, 3, fused, p)) continue;
+        if (!res_plan(pixels, w, c_in, c_out, l, 3, p)) continue;
         const int64_t rounds = (p.tiles + cus - 1) / cus;
         const int64_t cost = rounds * ((64 << l) + 48);
         if (!found || cost < best_cost) { best = p; best_cost = cost; found = true; }
     }
     ResPlan p4;
-    if (res_plan(pixels, w, c_in, c_out, 1, 2, fused, p4)) {
+    if (res_plan(pixels, w, c_in, c_out, 1, 2, p4)) {
         const int64_t rounds = (p4.tiles + 2 * cus - 1) / (2 * cus);
         const int64_t cost = rounds * (2 * 128 + 48) * kRes4WaveCost / 100;
         if (!found || cost < best_cost) { best = p4; best_cost = cost; found = true; }
@@ -848,15 +797,13 @@ bool res_choose(int64_t pixels, int w, int c_in, int c_out, int cus, bool fused,
 
 // Fills the geometry, divisions and LDS layout of a launch.
 inline void res_fill_args(ResArgs &a, const GemmArgs &g, const ResPlan &p) {
-    a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
+    a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
     a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.h = g.h; a.w = g.w;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
     a.slices = g.k / 192;
     const hq::Magic31 ms = hq::magic31(static_cast<uint32_t>(a.slices));
     a.s_magic = ms.m; a.s_shift = ms.s;
-    const hq::Magic31 mp = hq::magic31(static_cast<uint32_t>(6 * a.slices));
-    a.p_magic = mp.m; a.p_shift = mp.s;
     a.pg_log2 = p.pg_log2;
     a.n_co_tiles = static_cast<uint32_t>((g.n + 191) / 192);
     a.n_tiles = static_cast<uint32_t>(p.tiles);
@@ -864,13 +811,12 @@ inline void res_fill_args(ResArgs &a, const GemmArgs &g, const ResPlan &p) {
 }
 
 // Launches the configuration of the plan (integer output: the caller has zero-filled it).
-template <bool FUSED>
 void res_launch_plan(const ResArgs &a, const ResPlan &p, hq_dtype y_dtype, hipStream_t stream) {
     const dim3 grid(a.n_tiles), block(64 << p.nw_log2);
 #define HQ_RES_CASE(PGL, NWL)                                                                                      \
-    if (y_dtype == HQ_I32) hipLaunchKernelGGL((conv3x3_res_kernel<kOutI32, PGL, NWL, FUSED>), grid, block, 0, stream, a);      \
-    else if (y_dtype == HQ_F16) hipLaunchKernelGGL((conv3x3_res_kernel<kOutF16, PGL, NWL, FUSED>), grid, block, 0, stream, a); \
-    else hipLaunchKernelGGL((conv3x3_res_kernel<kOutF32, PGL, NWL, FUSED>), grid, block, 0, stream, a);
+    if (y_dtype == HQ_I32) hipLaunchKernelGGL((conv3x3_res_kernel<kOutI32, PGL, NWL>), grid, block, 0, stream, a);      \
+    else if (y_dtype == HQ_F16) hipLaunchKernelGGL((conv3x3_res_kernel<kOutF16, PGL, NWL>), grid, block, 0, stream, a); \
+    else hipLaunchKernelGGL((conv3x3_res_kernel<kOutF32, PGL, NWL>), grid, block, 0, stream, a);
     if (p.nw_log2 == 2) { HQ_RES_CASE(1, 2) }
     else if (p.pg_log2 == 2) { HQ_RES_CASE(2, 3) }
     else if (p.pg_log2 == 1) { HQ_RES_CASE(1, 3) }

@@ -1,11 +1,11 @@
-// 3x3 / stride 1 / pad 1 NHWC convolution on int8 MFMA for layers with few output tiles:
+// 3x3 / stride 1 / pad 1 NHWC convolution of 192 channels on int8 MFMA for layers with few output tiles:
 // every WAVE works alone on one 64-channel x 64-pixel output tile (2 x 2 MFMA tiles of
 // 32x32) and on one contiguous share of that tile's K range (Method, "Convolution":
 // one integer sum per tap, taps combined in fp32 with the scale of the input pixel
 // under the tap).
 //
-// Why.  With 64x64 output tiles a layer of 1024 pixels x 960 channels has 240 tiles for
-// 1024 SIMDs.  Splitting every tile's 9 * C_in / 192 chunks over KG = 1, 2 or 4 waves of
+// Why.  With 64x64 output tiles a layer of 4096 pixels x 192 channels has 192 tiles for
+// 1024 SIMDs.  Splitting every tile's nine chunks (one tap each) over KG = 1, 2 or 4 waves of
 // one workgroup fills the machine, keeps the efficient 2 x 2 register tile (six vector
 // instructions of nibble expansion per MFMA instead of twelve for a 32x32 wave tile) and
 // needs no exchange through global memory: the KG partial fp32 results of a tile meet in
@@ -27,14 +27,14 @@
 namespace {
 
 struct WaveConvArgs {
-    const uint8_t *xq;   // [pixels, k/2]
+    const uint8_t *xq;   // [pixels, 96]
     const float *sx;     // [pixels], or one value for the whole tensor (sx_static)
-    const uint8_t *wq;   // [n, 9, k/2]
+    const uint8_t *wq;   // [n, 9, 96]
     const float *sw;     // [n]
     const void *bias;    // [n] of the output dtype, or null
     void *y;             // [pixels, n]
     uint32_t pixels;
-    int n, k, h, w;
+    int n, h, w;
     uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
     uint32_t n_px_tiles, n_tiles;
     int kg_log2;         // waves per tile: 1 << kg_log2 (1, 2 or 4)
@@ -60,9 +60,6 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lrow = lane & 31, lhalf = lane >> 5;
-    const int kbytes = a.k >> 1;
-    const int cpt = kbytes / ROWB;               // chunks per tap (host guarantees divisibility)
-    const int chunks = TAPS * cpt;
     const uint32_t last = a.pixels - 1;
 
     // ---- this wave's unit: tile and chunk range ---------------------------------------------
@@ -77,8 +74,8 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
     uint32_t tile = unit >> a.kg_log2;
     const bool active = tile < a.n_tiles;        // the same for all waves of a tile
     if (!active) tile = a.n_tiles - 1;
-    const int c0 = active ? (g * chunks) >> a.kg_log2 : 0;
-    const int c1 = active ? ((g + 1) * chunks) >> a.kg_log2 : 0;
+    const int c0 = active ? (g * TAPS) >> a.kg_log2 : 0;
+    const int c1 = active ? ((g + 1) * TAPS) >> a.kg_log2 : 0;
     const int co0 = static_cast<int>(tile / a.n_px_tiles) * 64;
     const uint32_t p0 = (tile % a.n_px_tiles) * 64;
 
@@ -92,25 +89,25 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
         const int q = 64 * r + lane, row = q / KCH, piece = (q % KCH) ^ ((row >> 3) & 1);
-        pat_a[r] = static_cast<uint32_t>(tile_row_to_channel(row)) * TAPS * kbytes + piece * 16;
-        pat_b[r] = static_cast<uint32_t>(row) * kbytes + piece * 16;
+        pat_a[r] = static_cast<uint32_t>(tile_row_to_channel(row)) * TAPS * ROWB + piece * 16;
+        pat_b[r] = static_cast<uint32_t>(row) * ROWB + piece * 16;
     }
     const bool rows_inside = co0 + 64 <= a.n && p0 + 64 <= a.pixels;
-    int ftap = c0 / cpt, fch = c0 - ftap * cpt;   // chunk being fetched
+    int ftap = c0;   // chunk (tap) being fetched
     auto issue_loads = [&](int stage) {
         const int dpix = (ftap / 3 - 1) * a.w + (ftap % 3 - 1);
         uint8_t *image = lds + wave * WAVE_BYTES + stage * STAGE_BYTES;
         const int64_t first = static_cast<int64_t>(p0) + dpix;
         if (rows_inside && first >= 0 && first + 63 <= static_cast<int64_t>(last)) {
-            const uint8_t *base_a = a.wq + (static_cast<uint64_t>(co0) * TAPS + ftap) * kbytes + fch * ROWB;
-            const uint8_t *base_b = a.xq + static_cast<uint64_t>(first) * kbytes + fch * ROWB;
+            const uint8_t *base_a = a.wq + (static_cast<uint64_t>(co0) * TAPS + ftap) * ROWB;
+            const uint8_t *base_b = a.xq + static_cast<uint64_t>(first) * ROWB;
 #pragma unroll
             for (int i = 0; i < 6; ++i)
-                load_to_lds16(base_a + (i >= 3 ? static_cast<uint64_t>(32) * TAPS * kbytes : 0) + pat_a[i % 3],
+                load_to_lds16(base_a + (i >= 3 ? static_cast<uint64_t>(32) * TAPS * ROWB : 0) + pat_a[i % 3],
                               image + i * 1024);
 #pragma unroll
             for (int i = 0; i < 6; ++i)
-                load_to_lds16(base_b + (i >= 3 ? static_cast<uint64_t>(32) * kbytes : 0) + pat_b[i % 3],
+                load_to_lds16(base_b + (i >= 3 ? static_cast<uint64_t>(32) * ROWB : 0) + pat_b[i % 3],
                               image + OP_BYTES + i * 1024);
         } else {
 #pragma unroll
@@ -118,7 +115,7 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
                 const int q = 64 * i + lane, row = q / KCH, piece = (q % KCH) ^ ((row >> 3) & 1);
                 int co = co0 + (row & ~31) + tile_row_to_channel(row & 31);
                 co = co < a.n ? co : a.n - 1;
-                const uint32_t off = (static_cast<uint32_t>(co) * TAPS + ftap) * kbytes + fch * ROWB + piece * 16;
+                const uint32_t off = (static_cast<uint32_t>(co) * TAPS + ftap) * ROWB + piece * 16;
                 load_to_lds16(a.wq + off, image + i * 1024);
             }
 #pragma unroll
@@ -126,11 +123,11 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
                 const int q = 64 * i + lane, row = q / KCH, piece = (q % KCH) ^ ((row >> 3) & 1);
                 uint32_t pix = p0 + row + static_cast<uint32_t>(dpix);   // wraps below pixel 0
                 pix = pix < last ? pix : last;
-                const uint32_t off = pix * kbytes + fch * ROWB + piece * 16;
+                const uint32_t off = pix * ROWB + piece * 16;
                 load_to_lds16(a.xq + off, image + OP_BYTES + i * 1024);
             }
         }
-        if (++fch == cpt) { fch = 0; ++ftap; }
+        ++ftap;
     };
 
     constexpr bool INT_OUT = OUT == kOutI32;
@@ -206,7 +203,6 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
                     acc[tm][tn] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a1[tm], b1[tn], acc[tm][tn], 0, 0, 0);
         };
 
-        int tap = c0 / cpt, ch = c0 - tap * cpt;
         int stage = 0;
         for (int c = c0; c < c1; ++c) {
             // chunk c has landed once only the loads of the later chunks in flight are pending
@@ -217,43 +213,39 @@ __global__ __launch_bounds__(256, 1) void conv3x3_wave_kernel(WaveConvArgs a) {
             const uint32_t sa = lds_a + stage * STAGE_BYTES, sb = lds_b + stage * STAGE_BYTES;
             Ops op[2];
             read_packed<TM, TN, ROWB, 0>(op[0], sa, sb);
-            chunk_steps<0, KS, TM, TN, ROWB>(op, sa, sb, ch == 0 || c == c0, multiply);
+            chunk_steps<0, KS, TM, TN, ROWB>(op, sa, sb, true, multiply);
 
-            const bool tap_ends = ch + 1 == cpt;
-            if (tap_ends || c + 1 == c1) {
-                if constexpr (INT_OUT) {
-                    // This wave's share of the tap's sum, added to the zero-filled output: integer
-                    // additions are exact, so the order in which the waves of a tile arrive does not
-                    // matter.  Per-tap sums [pixel, tap, n]; one sum over all taps [pixel, n] when the
-                    // tensor has one scale (then taps outside the image must not count either).
-                    int *yi = static_cast<int *>(a.y);
+            if constexpr (INT_OUT) {
+                // This wave's share of the tap's sum, added to the zero-filled output: integer
+                // additions are exact, so the order in which the waves of a tile arrive does not
+                // matter.  Per-tap sums [pixel, tap, n]; one sum over all taps [pixel, n] when the
+                // tensor has one scale (then taps outside the image must not count either).
+                int *yi = static_cast<int *>(a.y);
 #pragma unroll
-                    for (int tn = 0; tn < TN; ++tn) {
-                        const uint32_t pix = p0 + tn * 32 + lrow;
-                        if (pix >= a.pixels || !((my_mask[tn] >> tap) & 1)) continue;
+                for (int tn = 0; tn < TN; ++tn) {
+                    const uint32_t pix = p0 + tn * 32 + lrow;
+                    if (pix >= a.pixels || !((my_mask[tn] >> c) & 1)) continue;
 #pragma unroll
-                        for (int tm = 0; tm < TM; ++tm) {
-                            const int cbase = co0 + tm * 32 + 16 * lhalf;
-                            int *dst = yi + (a.sx_static ? static_cast<int64_t>(pix)
-                                                         : static_cast<int64_t>(pix) * TAPS + tap) * a.n + cbase;
+                    for (int tm = 0; tm < TM; ++tm) {
+                        const int cbase = co0 + tm * 32 + 16 * lhalf;
+                        int *dst = yi + (a.sx_static ? static_cast<int64_t>(pix)
+                                                     : static_cast<int64_t>(pix) * TAPS + c) * a.n + cbase;
 #pragma unroll
-                            for (int r = 0; r < 16; ++r)
-                                if (cbase + r < a.n) atomicAdd(dst + r, acc[tm][tn][r] >> 8);
-                        }
+                        for (int r = 0; r < 16; ++r)
+                            if (cbase + r < a.n) atomicAdd(dst + r, acc[tm][tn][r] >> 8);
                     }
-                } else {
-                    float s[TN];
-                    read_tap_scales<TN>(s, lds_sx + tap * (TN * 32 * 4));
-#pragma unroll
-                    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-                        for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r)
-                                facc[tm][tn][r] += s[tn] * static_cast<float>(acc[tm][tn][r]);
                 }
+            } else {
+                float s[TN];
+                read_tap_scales<TN>(s, lds_sx + c * (TN * 32 * 4));
+#pragma unroll
+                for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+                    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            facc[tm][tn][r] += s[tn] * static_cast<float>(acc[tm][tn][r]);
             }
-            if (tap_ends) { ch = 0; ++tap; } else { ++ch; }
             stage = stage + 1 == NSTAGE ? 0 : stage + 1;
         }
     }
@@ -340,13 +332,13 @@ __global__ void fill_zero_kernel(int4 *dst, uint64_t n16, int *tail, int n_tail)
 }  // namespace
 
 // Waves per tile that minimise rounds * (chunks per wave + fixed cost) on `cus` CUs of four SIMDs.
-int hq_conv3x3_wave_split(int64_t tiles, int chunks, int cus) {
+static int waves_per_tile_log2(int64_t tiles, int cus) {
     int best = 0;
     int64_t best_cost = -1;
     for (int l = 0; l <= 2; ++l) {
         const int64_t waves = tiles << l;
         const int64_t rounds = (waves + 4 * cus - 1) / (4 * cus);
-        const int64_t cost = rounds * ((chunks + (1 << l) - 1) / (1 << l) + 3);
+        const int64_t cost = rounds * ((9 + (1 << l) - 1) / (1 << l) + 3);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; best = l; }
     }
     return best;
@@ -365,17 +357,17 @@ hq_status hq_fill_zero_launch(void *dst, uint64_t ints, hipStream_t stream) {
 
 hq_status hq_conv3x3_wave_launch(const GemmArgs &g, hq_dtype y_dtype, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
-    if (g.k % 192 != 0 || (y_dtype != HQ_F16 && y_dtype != HQ_F32 && y_dtype != HQ_I32)) return HQ_ERR_UNSUPPORTED;
+    if (g.k != 192 || (y_dtype != HQ_F16 && y_dtype != HQ_F32 && y_dtype != HQ_I32)) return HQ_ERR_UNSUPPORTED;
     WaveConvArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
-    a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.h = g.h; a.w = g.w; a.sx_static = g.sx_static;
+    a.pixels = g.pixels; a.n = g.n; a.h = g.h; a.w = g.w; a.sx_static = g.sx_static;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
     a.n_px_tiles = static_cast<uint32_t>((static_cast<int64_t>(g.pixels) + 63) / 64);
     const int64_t tiles = static_cast<int64_t>(a.n_px_tiles) * ((g.n + 63) / 64);
     if (tiles > 0x1fffffff) return HQ_ERR_SHAPE;
     a.n_tiles = static_cast<uint32_t>(tiles);
-    a.kg_log2 = hq_conv3x3_wave_split(tiles, 9 * (g.k / 192), hq::compute_units());
+    a.kg_log2 = waves_per_tile_log2(tiles, hq::compute_units());
     const unsigned grid = static_cast<unsigned>(((tiles << a.kg_log2) + 3) / 4);
     if (y_dtype == HQ_I32) {
         // integer output [pixels, 9, n] (per-tap sums) or [pixels, n] (one scale: one sum): zero it, then

@@ -675,3 +675,14 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 }
 
 }  // namespace
+
+// One form's kernels by output type and steps per slice (a file each, so that they compile in parallel).
+#define HQ_RESIDENT_FORM(NAME, KIND)                                                                            \
+    const void *NAME(int out, int ks) {                                                                         \
+        static const void *const kernels[3][3] = {                                                              \
+            HQ_RESIDENT_FORM_OUT(kOutF16, KIND), HQ_RESIDENT_FORM_OUT(kOutF32, KIND), HQ_RESIDENT_FORM_OUT(kOutI32, KIND)}; \
+        return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][ks - 1];                                    \
+    }
+#define HQ_RESIDENT_FORM_OUT(OUT, KIND)                                                                         \
+    {reinterpret_cast<const void *>(resident_kernel<OUT, KIND, 1>), reinterpret_cast<const void *>(resident_kernel<OUT, KIND, 2>), \
+     reinterpret_cast<const void *>(resident_kernel<OUT, KIND, 3>)}
