@@ -35,11 +35,22 @@ def sources():
     return [os.path.join(CSRC, s) for s in SOURCES]
 
 
+def built_for() -> str:
+    """The interpreter and the PyTorch whose interfaces _marshal.so is compiled against; the file holds this text."""
+    import torch
+    return "built for Python %s, PyTorch %s" % (sys.version.split()[0], torch.__version__)
+
+
+def _marshal_matches() -> bool:
+    with open(MARSHAL, "rb") as f:
+        return built_for().encode() in f.read()
+
+
 def is_stale() -> bool:
     abi = os.path.join(ROOT, "include", "hq.h")
     deps = {LIB: sources() + [os.path.join(CSRC, h) for h in HEADERS] + [abi], MARSHAL: [MARSHAL_SOURCE, abi]}
     return any(not os.path.exists(out) or any(os.path.getmtime(d) > os.path.getmtime(out) for d in ds)
-               for out, ds in deps.items())
+               for out, ds in deps.items()) or not _marshal_matches()
 
 
 def _run(cmd, verbose):
@@ -59,7 +70,7 @@ def marshal_command(out: str):
     torch_dir = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I", os.path.join(ROOT, "include")]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DHQ_BUILT_FOR="%s"' % built_for(), "-I", os.path.join(ROOT, "include")]
     for d in (os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
         cmd += ["-isystem", d]

@@ -20,6 +20,9 @@
 
 #include "hq.h"
 
+// (build.py looks for this text in the file)
+extern "C" __attribute__((used, visibility("default"))) const char hq_marshal_built_for[] = HQ_BUILT_FOR;
+
 namespace {
 
 // ---- the library ------------------------------------------------------------------------------------------

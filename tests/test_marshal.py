@@ -46,3 +46,12 @@ def test_late_errors_are_raised():
                          timeout=300)
     assert res.returncode == 0 and res.stdout.endswith("done\n"), res.stdout
     assert res.stdout.count("raised ValueError") == res.stdout.count("raised RuntimeError") == 6, res.stdout
+
+
+def test_a_library_of_another_pytorch_is_stale(monkeypatch):
+    from paper_2512_05746_amd import build
+    if build.is_stale():
+        build.build_lib()
+    assert not build.is_stale()
+    monkeypatch.setattr(build, "built_for", lambda: "built for Python 0.0, PyTorch 0.0")
+    assert build.is_stale()
