@@ -173,22 +173,29 @@ at::Tensor result(PyObject *o, at::IntArrayRef shape, at::ScalarType dt, const a
     return t;
 }
 
-// out = None or a pair of buffers
-void pair_of(PyObject *o, PyObject *&a, PyObject *&b) {
-    a = b = Py_None;
-    if (o == Py_None) return;
-    // (borrowed references: the caller's pair outlives the call)
-    if (PyTuple_Check(o) && PyTuple_GET_SIZE(o) >= 2) {
-        a = PyTuple_GET_ITEM(o, 0);
-        b = PyTuple_GET_ITEM(o, 1);
-    } else if (PyList_Check(o) && PyList_GET_SIZE(o) >= 2) {
-        a = PyList_GET_ITEM(o, 0);
-        b = PyList_GET_ITEM(o, 1);
-    } else {
-        PyErr_SetString(PyExc_TypeError, "expected a pair of tensors");
-        throw PythonError();
+// out = None or a pair of buffers (any sequence of them)
+struct Pair {
+    PyObject *a = Py_None, *b = Py_None;
+    explicit Pair(PyObject *o) {
+        if (o == Py_None) return;
+        owned = true;
+        a = PySequence_GetItem(o, 0);
+        b = a ? PySequence_GetItem(o, 1) : nullptr;
+        if (!b) {
+            Py_XDECREF(a);
+            throw PythonError();
+        }
     }
-}
+    ~Pair() {
+        if (!owned) return;
+        Py_DECREF(a);
+        Py_DECREF(b);
+    }
+    Pair(const Pair &) = delete;
+
+private:
+    bool owned = false;
+};
 
 using Shape = c10::SmallVector<int64_t, 6>;
 
@@ -226,7 +233,7 @@ ConvOut conv_out(int64_t h, int64_t w, int ksize, int stride, int pad) {
     if (stride < 1 || pad < 0 || ksize < 1) refuse("bad convolution geometry");
     // (rounded down, as for positive sizes; a window larger than the padded image is refused by the library)
     auto out = [&](int64_t n) {
-        const int64_t d = n + 2 * pad - ksize;
+        const int64_t d = n + int64_t{2} * pad - ksize;
         return (d >= 0 ? d / stride : -((-d + stride - 1) / stride)) + 1;
     };
     return {out(h), out(w)};
@@ -261,13 +268,12 @@ PyObject *quantize_weights(Args a) {
 PyObject *act_hadamard_quant(Args a) {
     const at::Tensor &x = a.device("x");
     const int block = a.integer(), bits = a.integer();
-    PyObject *oq, *os;
-    pair_of(a.next(), oq, os);
+    const Pair out(a.next());
     if (x.dim() < 1) refuse("x must have a channel axis");
     const int64_t k = x.size(-1), m = k ? x.numel() / k : 0;
     expect_32bit({k});
-    const at::Tensor xq = result(oq, with_last(x, bits == 8 ? k : k / 2), bits == 8 ? at::kChar : at::kByte, x);
-    const at::Tensor xs = result(os, without_last(x), at::kFloat, x);
+    const at::Tensor xq = result(out.a, with_last(x, bits == 8 ? k : k / 2), bits == 8 ? at::kChar : at::kByte, x);
+    const at::Tensor xs = result(out.b, without_last(x), at::kFloat, x);
     const hq_dtype dt = hq_type(x.scalar_type());
     check("hq_act_hadamard_quant", call(lib.hq_act_hadamard_quant, x.const_data_ptr(), dt, m, narrow(k), block, bits,
                                         static_cast<uint8_t *>(xq.data_ptr()), static_cast<float *>(xs.data_ptr()),
@@ -378,8 +384,8 @@ PyObject *act_quant_conv2d(Args a) {
     PyObject *w_scale = a.next(), *bias = a.next();
     const int block = a.integer(), bits = a.integer(), ksize = a.integer(), stride = a.integer(), pad = padding(a, ksize);
     const at::ScalarType ydt = a.dtype();
-    PyObject *out = a.next(), *oq, *os, *codes_out = a.next();
-    pair_of(codes_out, oq, os);
+    PyObject *out = a.next(), *codes = a.next();
+    const Pair codes_out(codes);
     expect_dims(x, 4, "x must be [nb, h, w, c]");
     const int64_t nb = x.size(0), h = x.size(1), w = x.size(2), cin = x.size(3), n = wq.dim() ? wq.size(0) : 0;
     const int64_t taps = static_cast<int64_t>(ksize) * ksize;
@@ -394,9 +400,9 @@ PyObject *act_quant_conv2d(Args a) {
     shape.push_back(n);
     const at::Tensor y = result(out, shape, ydt, x);
     at::Tensor xq, sx;
-    if (codes_out != Py_None) {
-        xq = result(oq, {nb, h, w, cin / 2}, at::kByte, x);
-        sx = result(os, {nb, h, w}, at::kFloat, x);
+    if (codes != Py_None) {
+        xq = result(codes_out.a, {nb, h, w, cin / 2}, at::kByte, x);
+        sx = result(codes_out.b, {nb, h, w}, at::kFloat, x);
     }
     const hq_dtype xdt = hq_type(x.scalar_type()), dt = hq_type(ydt);
     check("hq_act_quant_int_conv2d", call(lib.hq_act_quant_int_conv2d, x.const_data_ptr(), xdt, u8(wq), f32(sw), b,
@@ -412,8 +418,8 @@ PyObject *act_quant_linear(Args a) {
     PyObject *w_scale = a.next(), *bias = a.next();
     const int block = a.integer(), bits = a.integer();
     const at::ScalarType ydt = a.dtype();
-    PyObject *out = a.next(), *oq, *os, *codes_out = a.next();
-    pair_of(codes_out, oq, os);
+    PyObject *out = a.next(), *codes = a.next();
+    const Pair codes_out(codes);
     if (x.dim() < 1) refuse("x must have a channel axis");
     const int64_t k = x.size(-1), m = k ? x.numel() / k : 0, n = wq.dim() ? wq.size(0) : 0;
     expect_32bit({n, k});
@@ -422,9 +428,9 @@ PyObject *act_quant_linear(Args a) {
     const void *b = Args{&bias, 1}.vec(n, ydt, "bias");
     const at::Tensor y = result(out, with_last(x, n), ydt, x);
     at::Tensor xq, sx;
-    if (codes_out != Py_None) {
-        xq = result(oq, with_last(x, k / 2), at::kByte, x);
-        sx = result(os, without_last(x), at::kFloat, x);
+    if (codes != Py_None) {
+        xq = result(codes_out.a, with_last(x, k / 2), at::kByte, x);
+        sx = result(codes_out.b, without_last(x), at::kFloat, x);
     }
     const hq_dtype xdt = hq_type(x.scalar_type()), dt = hq_type(ydt);
     check("hq_act_quant_int_linear", call(lib.hq_act_quant_int_linear, x.const_data_ptr(), xdt, u8(wq), f32(sw), b, m,

@@ -12,6 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = """
 import sys
 sys.path.insert(0, %r)
+from collections import deque
 import torch
 from torch._subclasses.fake_tensor import FakeTensor, FakeTensorMode
 import paper_2512_05746_amd as hq
@@ -30,6 +31,8 @@ for k, error in ((1 << 31, ValueError), (64, RuntimeError)):   # a size beyond 3
         ("conv2d_width", lambda: hq.hq_int_conv2d_width(d(3, 1, 1, 1, k // 2), None, d(1, 9, k // 2), None, y_dtype=i32,
                                                         out=d(1, dtype=i32))),
         ("quant", lambda: hq.hq_act_hadamard_quant(d(1, k, dtype=f16), out=(d(1, k // 2), d(1, dtype=f32)))),
+        ("quant, pair of another type", lambda: hq.hq_act_hadamard_quant(d(1, k, dtype=f16),
+                                                                         out=deque([d(1, k // 2), d(1, dtype=f32)]))),
     ):
         print(name, k, flush=True)
         try:
@@ -45,7 +48,7 @@ def test_late_errors_are_raised():
     res = subprocess.run([sys.executable, "-c", PROGRAM % ROOT], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
                          timeout=300)
     assert res.returncode == 0 and res.stdout.endswith("done\n"), res.stdout
-    assert res.stdout.count("raised ValueError") == res.stdout.count("raised RuntimeError") == 6, res.stdout
+    assert res.stdout.count("raised ValueError") == res.stdout.count("raised RuntimeError") == 7, res.stdout
 
 
 def test_a_library_of_another_pytorch_is_stale(monkeypatch):
