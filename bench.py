@@ -31,6 +31,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 INT8_MFMA_PEAK_TOPS = 256 * 8192 * 2.4e9 / 1e12      # 5033 TOP/s dense int8, 256 CUs at 2.4 GHz
+E2M3_MFMA_PEAK_TOPS = 2 * INT8_MFMA_PEAK_TOPS        # the 6-bit floating-point instruction: 64 codes where int8 has 32
 HBM_PEAK_GBS = 8000.0
 CONFIG = 5
 
@@ -194,8 +195,19 @@ def main():
         del rot
     torch.cuda.synchronize()
 
+    def instruction(layer, x, static_scale=False):
+        """The matrix instruction of a 4-bit layer's integer stage, and its peak."""
+        e2m3 = layer.ksize == 3 and hq.hq_int_conv2d_kernel_name(
+            *x.shape, layer.n_out, static_scale=static_scale).startswith("activation-resident")
+        return ("e2m3", E2M3_MFMA_PEAK_TOPS) if e2m3 else ("int8", INT8_MFMA_PEAK_TOPS)
+
+    def mixed_peak(layers_x, static_scale=False):
+        """The rate of these layers if each ran at the peak of its instruction."""
+        return sum(l.ops for l, _ in layers_x) / sum(l.ops / instruction(l, x, static_scale)[1] for l, x in layers_x)
+
     per_layer = []
-    for i, (layer, *_r) in enumerate(state):
+    for i, (layer, x_i, *_r) in enumerate(state):
+        mfma_name, mfma_peak = instruction(layer, x_i)
         out_bytes = layer.m * layer.n_out * 2
         in_bytes = layer.m * layer.k_in // 2 + layer.m * 4
         w_bytes = layer.n_out * layer.taps * layer.k_in // 2
@@ -204,15 +216,15 @@ def main():
         int_gbs = (out_bytes + in_bytes + w_bytes) / int_us[i] / 1e3
         # the roof that binds the integer stage of this layer: the matrix cores when its arithmetic
         # intensity is above the machine balance (peak op/s over peak bytes/s), else the output write
-        mfma_bound = layer.ops / (out_bytes + in_bytes + w_bytes) > INT8_MFMA_PEAK_TOPS * 1e3 / HBM_PEAK_GBS
+        mfma_bound = layer.ops / (out_bytes + in_bytes + w_bytes) > mfma_peak * 1e3 / HBM_PEAK_GBS
         per_layer.append({
             "layer": layer.name, "gop": round(layer.ops / 1e9, 3),
             "int_us": round(float(int_us[i]), 2),
             "int_tops": round(int_tops, 1),
-            "int_frac_mfma_peak": round(int_tops / INT8_MFMA_PEAK_TOPS, 4),
+            "int_instruction": mfma_name, "int_frac_mfma_peak": round(int_tops / mfma_peak, 4),
             "int_gbs": round(int_gbs, 1),
             "int_binding_roof": "mfma" if mfma_bound else "hbm",
-            "int_frac_of_binding_roof": round(int_tops / INT8_MFMA_PEAK_TOPS if mfma_bound
+            "int_frac_of_binding_roof": round(int_tops / mfma_peak if mfma_bound
                                               else int_gbs / HBM_PEAK_GBS, 4),
             "quant_us": round(float(quant_us[i]), 2),
             "quant_gbs": round(q_bytes / quant_us[i] / 1e3, 1),
@@ -325,7 +337,7 @@ def main():
         i_us = batched_us(run_conv_width, s)
         width_layers.append({"layer": layer.name, "block": block, "quant_us": round(q_us, 2), "int_us": round(i_us, 2),
                              "int_tops_useful": round(layer.ops / i_us / 1e6, 1),
-                             "int_tops_issued": round(3 * layer.ops / i_us / 1e6, 1)})
+                             "int_tops_issued": round((2 if block <= 32 else 3) * layer.ops / i_us / 1e6, 1)})
     torch.cuda.synchronize()
 
     # ---- the same sweep with 8-bit codes for both operands (one int8 code per byte) ---------------
@@ -378,6 +390,8 @@ def main():
     conv3_us = float(sum(int_us[i] for i in conv3))
     achieved = conv3_ops / conv3_us / 1e6
     int_all_tops = total_ops / float(int_us.sum()) / 1e6
+    conv3_peak = mixed_peak([state[i][:2] for i in conv3])
+    static_conv3_tops = conv3_ops / sum(static_layers[i]["int_us"] for i in conv3) / 1e6
 
     # ---- standalone transform+quantise on the largest activation, cache-defeating rotation --
     big = max(state, key=lambda s: s[1].numel())
@@ -454,9 +468,9 @@ def main():
         "metric": "w4a4_gemm_conv_tops", "value": round(value, 2), "unit": "TOP/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": "int8", "data": "synthetic",
+        "vs_baseline": None, "dtype": "int4 codes, exact integer sums (3x3: E2M3 products; linear, 1x1: int8)", "data": "synthetic",
         "config": {
-            "workload": "configs[4]: LDM-4-shaped UNet layer sweep, batch 16, W4A4, fp16 I/O, "
+            "workload": "configuration 5: LDM-4-shaped UNet layer sweep, batch 16, W4A4, fp16 I/O, "
                         "block-64 Hadamard; 9 layers, act-quant + integer conv/linear each",
             "total_gop": round(total_ops / 1e9, 2), "launches_per_step": 2 * len(state),
             "launch": "hipgraph replay" if graph is not None else "eager",
@@ -469,13 +483,16 @@ def main():
                                 "at_queried_clock": round(props.multi_processor_count * 8192 * clock_khz * 1e3 / 1e12, 1),
                                 "queried_clock_mhz": round(clock_khz / 1e3), "compute_units": props.multi_processor_count,
                                 "fractions_use": "nominal"},
+        "e2m3_mfma_peak_tops": round(E2M3_MFMA_PEAK_TOPS, 1),
         "int_stage_tops_kernel_time": round(int_all_tops, 1),
         "frac_int8_mfma_peak_kernel_time": round(int_all_tops / INT8_MFMA_PEAK_TOPS, 4),
         "roofline": {
             "kernel": "the four 3x3 implicit-GEMM convolution launches of the sweep: " + ", ".join(
                 hq.hq_int_conv2d_kernel_name(*state[i][1].shape, state[i][0].n_out) for i in conv3),
-            "bound": "mfma", "achieved": round(achieved, 1), "peak": round(INT8_MFMA_PEAK_TOPS, 1),
-            "unit": "TOP/s", "frac": round(achieved / INT8_MFMA_PEAK_TOPS, 4),
+            "bound": "mfma", "achieved": round(achieved, 1), "peak": round(conv3_peak, 1),
+            "peak_of": ", ".join(instruction(*state[i][:2])[0] for i in conv3),
+            "unit": "TOP/s", "frac": round(achieved / conv3_peak, 4),
+            "frac_int8_mfma_peak": round(achieved / INT8_MFMA_PEAK_TOPS, 4),
             "traffic": measured_traffic(),
             "traffic_unit": "HBM bytes per launch, mean over the four 3x3 launches; read from the committed "
                             "rocprofv3 FETCH_SIZE / WRITE_SIZE summary of this command "
@@ -510,9 +527,9 @@ def main():
         "static_scale_mode": {
             "what": "the same sweep through hq_*_static (one caller-supplied activation scale per tensor); "
                     "not part of `value`",
-            "conv3x3_tops_kernel_time": round(conv3_ops / sum(static_layers[i]["int_us"] for i in conv3) / 1e6, 1),
-            "frac_int8_mfma_peak": round(conv3_ops / sum(static_layers[i]["int_us"] for i in conv3) / 1e6
-                                         / INT8_MFMA_PEAK_TOPS, 4),
+            "conv3x3_tops_kernel_time": round(static_conv3_tops, 1),
+            "frac_mfma_peak": round(static_conv3_tops / mixed_peak([state[i][:2] for i in conv3], True), 4),
+            "frac_int8_mfma_peak": round(static_conv3_tops / INT8_MFMA_PEAK_TOPS, 4),
             "sum_kernel_us": round(sum(l["int_us"] + l["quant_us"] for l in static_layers), 1),
             "layers": static_layers,
         },
@@ -525,7 +542,8 @@ def main():
         "width_axis_mode": {
             "what": "the 3x3 layers through hq_act_hadamard_quant_width + hq_int_conv2d_width (the paper's own "
                     "convolution: transform along the width axis, one scale, integer H_raw on the codes, "
-                    "un-transformed weights); useful = 2*M*N*K, issued = three integer passes; not part of `value`",
+                    "un-transformed weights); useful = 2*M*N*K, issued = two operand planes up to block 32, three above; "
+                    "not part of `value`",
             "layers": width_layers,
         },
         "stride2_downsampling": {
