@@ -54,7 +54,9 @@ double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had
     const Tile tile = choose_tile(pixels, n, k, bits, 9);
     const int pt = tile == Tile::t64x64 ? 64 : 128, ct = tile == Tile::t128x128 ? 128 : 64;
     const int per_round = tile == Tile::t64x64 ? 4 : tile == Tile::t64x128 ? 3 : 2;   // (workgroups of a CU)
-    const double tiles = static_cast<double>((pixels + pt - 1) / pt * ((n + ct - 1) / ct)) / hq::compute_units();
+    const int64_t total = (pixels + pt - 1) / pt * ((n + ct - 1) / ct);
+    if (static_cast<double>(total) * ((bits == 8 ? k : k / 2) / 32) * (had_block ? 27 : 9) > 0x7fffffff) return HUGE_VAL;   // (refused)
+    const double tiles = static_cast<double>(total) / hq::compute_units();
     const double rounds = ceil(tiles / per_round), used = (rounds - 1) * per_round + ceil(tiles - (rounds - 1) * per_round);
     const auto &cost = (bits == 8 ? k : k / 2) % 96 != 0 ? c.short_chunks
                        : tile == Tile::t64x128           ? c.t64x128
@@ -63,7 +65,8 @@ double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had
     // (groups of 16 channels are stored at once where all are whole, value by value otherwise)
     const double start = c.start + (n % 16 ? 2 : 0), result_mb = c.result_mb + (n % 16 ? 1.2 : 0);
     const double planes_read = had_block && had_block <= 8 ? 2.0 / 3.0 : 1.0;
-    return start + static_cast<double>(pixels) * n * 2e-6 * result_mb + k / 64 * (cost.round * rounds + cost.tile * used) * planes_read;
+    return start + static_cast<double>(pixels) * n * 2e-6 * result_mb +
+           k / 64 * (cost.round * rounds + cost.tile * used) * planes_read;
 }
 
 namespace {
