@@ -70,7 +70,8 @@ def marshal_command(out: str):
     torch_dir = os.path.dirname(torch.__file__)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DHQ_BUILT_FOR="%s"' % built_for(), "-I", os.path.join(ROOT, "include")]
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DHQ_BUILT_FOR="%s"' % built_for(),
+           "-I", os.path.join(ROOT, "include")]
     for d in (os.path.join(torch_dir, "include"), os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
         cmd += ["-isystem", d]

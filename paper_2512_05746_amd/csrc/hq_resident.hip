@@ -47,7 +47,7 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     if (p.chunk < 1 || (p.chunk < p.slices && !overlay)) return p;
     p.part8 = static_cast<uint32_t>(p.rows) * p.chunk * ops * 32;
     p.part8 = (p.part8 + 15) & ~15u;
-    const uint32_t act_end = (static_cast<uint32_t>(p.part8) + static_cast<uint32_t>(p.rows) * p.chunk * ops * part8_bytes + 15) & ~15u;
+    const uint32_t act_end = (p.part8 + static_cast<uint32_t>(p.rows) * p.chunk * ops * part8_bytes + 15) & ~15u;
     // (an area over the tile costs nothing up to the tile's size, or up to the budget of the only workgroup of a CU)
     p.wide = overlay && nw * 16384 + tables <= budget;
     p.exchange = overlay ? 0 : act_end;
@@ -65,10 +65,12 @@ Cost cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
     const int px = 128 << p.xw_log2, blocks = (n + 31) / 32, planes = kind >= kResPlanes ? 2 : 1;
     const int64_t wgs = (pixels + px - 1) / px * ((blocks + p.cb - 1) / p.cb);
     const int per_cu = p.nw == 4 && p.lds <= kLdsPerCu / 2 ? 2 : 1;
-    const double rounds = static_cast<double>((wgs + static_cast<int64_t>(cus) * per_cu - 1) / (static_cast<int64_t>(cus) * per_cu));
+    const int64_t per_round = static_cast<int64_t>(cus) * per_cu;
+    const double rounds = static_cast<double>((wgs + per_round - 1) / per_round);
     const bool paired = p.nw == 8 || (per_cu == 2 && wgs > cus);
     const int items = (p.rows - 1 + 31) / 32 * p.slices;
-    double clocks = 6500 + 2000 + (paired ? 700.0 : 450.0) * (kind == kResBytes ? 0.5 : 2 * planes - 1) * p.ks * ((items + p.nw - 1) / p.nw);
+    const double fill = (paired ? 700.0 : 450.0) * (kind == kResBytes ? 0.5 : 2 * planes - 1) * p.ks;
+    double clocks = 6500 + 2000 + fill * ((items + p.nw - 1) / p.nw);
     for (int left = std::min(blocks, p.cb) << p.xw_log2; left > 0;) {
         int kl = 0;
         while ((p.nw >> kl) > left) ++kl;
@@ -108,7 +110,8 @@ Plan choose_kernel(int kind, int had_block, int64_t pixels, int w, int k, int n)
     if (!p.ok) return p;
     struct Us { double kclock, chunk; };   // of a thousand clocks, and of making a set of slices resident
     constexpr Us us[4] = {{0.42, 1.6}, {0.42, 1.6}, {0.34, 2.2}, {0.42, 1.3}};   // by kind; fitted as hq_tile_us, 7 .. 11 % rms
-    const double resident = us[kind].kclock * cost.clocks * 1e-3 + us[kind].chunk * cost.rounds * ((p.slices + p.chunk - 1) / p.chunk);
+    const int chunks = (p.slices + p.chunk - 1) / p.chunk;
+    const double resident = us[kind].kclock * cost.clocks * 1e-3 + us[kind].chunk * cost.rounds * chunks;
     p.ok = hq_tile_us(pixels, n, k, kind == kResBytes ? 8 : 4, kind == kResSum, had_block) >= 0.92 * resident;
     return p;
 }

@@ -2,7 +2,8 @@
 // the activation tile expanded once and resident in LDS.
 //
 // A workgroup owns XW groups of 128 consecutive pixels and a run of blocks of 32 output channels; a wave's
-// result tile is 32 channels x 128 pixels.  The codes of the pixels, and those of W + 1 pixels either side, are fetched once, expanded to 6-bit fields and kept in LDS as planes
+// result tile is 32 channels x 128 pixels.  The codes of the pixels, and those of W + 1 pixels either side, are fetched
+// once, expanded to 6-bit fields and kept in LDS as planes
 //     [64-channel step][lane half][row] of 16-byte operand parts, then of 8-byte parts,
 // so that a wave's operand read of 32 consecutive rows is two contiguous runs for any row shift: 224 bytes per clock
 // and CU measured, against 126 with the halves of a row next to each other.  Weights go from memory straight into
@@ -37,10 +38,13 @@
 // that of 4-bit codes and the fold converts 16 values more per tile; matrix and vector time add up almost fully here as
 // there.  us per pass with the quantiser, tile kernel -> this one: 16 x 32 x 32 x 384 51.5 -> 44.1, 16 x 64 x 64 x 192
 // 63.7 -> 45.1, 16 x 16 x 16 x 576 44.0 -> 32.1, 16 x 8 x 8 x 960 48.2 -> 22.5, 3 x 45 x 27 x 320 -> 200 51.3 -> 15.9,
-// 1 x 8 x 8 x 64 (launch) 26.7 -> 11.2: faster at every size tried.
+// 1 x 8 x 8 x 64 (launch) 26.7 -> 11.2.
 //
-// Weights carry an offset of 8 (hq_fp6.h; not those of 8 bits): a sum exceeds the wanted one by 8 x (sum of the activation codes it
-// covers), the same for all channels: a per-pixel correction from a table of code sums.  With one scale all of it is exact.
+// Which layers come here and which stay on the tile kernel: choose_kernel in hq_resident.hip.
+//
+// Weights carry an offset of 8 (hq_fp6.h; not those of 8 bits): a sum exceeds the wanted one by 8 x (sum of the activation
+// codes it covers), the same for all channels: a per-pixel correction from a table of code sums.  With one scale all of it
+// is exact.
 // With per-pixel scales the correction is subtracted at the end from sums in fp32 that hold it, one fold per tap and slice,
 // which costs digits: the 2-norm error is 2e-7 .. 3e-7 where code sums are small, up to 1.5e-5 where the codes of a pixel
 // have one sign (64 .. 960 channels), below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).
@@ -80,8 +84,8 @@ namespace {
 
 constexpr int kResPerTap = 0;   // 3x3, per-pixel scales: one sum per tap, combined in fp32
 constexpr int kResSum = 1;      // 3x3, one scale: one sum over all taps
+constexpr int kResPlanes = 2;   // as kResSum, with activations u = d0 + 16 (d1 + 16 d2) in three digit planes, |d1 + 16 d2| <= 16
 constexpr int kResBytes = 3;    // as kResPerTap, with 8-bit codes on the int8 instruction
-constexpr int kResPlanes = 2;   // the same with activations u = d0 + 16 (d1 + 16 d2) in three digit planes, |d1 + 16 d2| <= 16
 
 // Barrier that orders LDS only: __syncthreads() would also wait for the wave's global loads (weights requested
 // ahead) and stores.
@@ -97,11 +101,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint3
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, static_cast<int>(bytes), 0x00027000);
 }
 __device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off) {
-    return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(lane_off), static_cast<int>(uniform_off), 0));
+    return __builtin_bit_cast(
+        v4i, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(lane_off), static_cast<int>(uniform_off), 0));
 }
 __device__ __forceinline__ void buffer_store16(const v4i &v, __amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off) {
     typedef unsigned v4u __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, static_cast<int>(lane_off), static_cast<int>(uniform_off), 0);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, static_cast<int>(lane_off),
+                                           static_cast<int>(uniform_off), 0);
 }
 
 __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
@@ -113,7 +119,8 @@ __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int row
 // is exact).
 typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
-    const v4h b = {static_cast<_Float16>(static_cast<short>(sum & 1023)), static_cast<_Float16>(static_cast<short>(sum >> 10)), 0, 0};
+    const v4h b = {static_cast<_Float16>(static_cast<short>(sum & 1023)),
+                   static_cast<_Float16>(static_cast<short>(sum >> 10)), 0, 0};
     return __builtin_amdgcn_mfma_f32_32x32x8f16(weights, b, v16f{}, 0, 0, 0);
 }
 
@@ -226,7 +233,9 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         *reinterpret_cast<v4i *>(lds + ((((sl * PL + i) * KS + k) * 2 + f_half) * rows + row) * 16) = p[i][k];
                     continue;
                 }
-                auto codes = [&](const v4i &v, int s) { return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s)))); };
+                auto codes = [&](const v4i &v, int s) {
+                    return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s))));
+                };
                 auto put = [&](int plane, const int (&d)[6]) {
                     const int at = (((sl * PL + plane) * KS + k) * 2 + f_half) * rows + row;
                     *reinterpret_cast<v4i *>(lds + at * 16) = v4i{d[0], d[1], d[2], d[3]};
@@ -402,7 +411,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             if constexpr (WHOLE_TAPS) {   // the sums of a tap start with the offset of the slices that this wave will add
 #pragma unroll
                 for (int t = 0; t < NT; ++t)
-                    tap_acc[t] = minus_eighth_of(minus, codes_upto(tap, min(ns, sl + u_end - u) - 1, t) - (sl ? codes_upto(tap, sl - 1, t) : 0));
+                    tap_acc[t] = minus_eighth_of(minus, codes_upto(tap, min(ns, sl + u_end - u) - 1, t) -
+                                                            (sl ? codes_upto(tap, sl - 1, t) : 0));
             }
             for (; u < u_end; ++u) {
                 int tap1 = tap, sl1 = sl;   // the next unit (the last one's operands are requested twice)
@@ -448,7 +458,9 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
                                 const int c = c0 + 16 * h + i;
-                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc_of(t)[i] * static_cast<decltype(acc_of(t)[i] + 0)>(UNIT)) - extra);
+                                if (c < a.n)
+                                    atomicAdd(dst + c,
+                                              static_cast<int>(acc_of(t)[i] * static_cast<decltype(acc_of(t)[i] + 0)>(UNIT)) - extra);
                             }
                         }
                     } else if constexpr (FOLD) {
@@ -529,8 +541,9 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     lds_barrier();
 #pragma unroll
                     for (int i = 0; i < 64; i += 4)
-                        box[(wv * 16 + i / 4) * 64] = v4i{__float_as_int(sum[i >> 4][i & 15]), __float_as_int(sum[i >> 4][(i + 1) & 15]),
-                                                          __float_as_int(sum[i >> 4][(i + 2) & 15]), __float_as_int(sum[i >> 4][(i + 3) & 15])};
+                        box[(wv * 16 + i / 4) * 64] =
+                            v4i{__float_as_int(sum[i >> 4][i & 15]), __float_as_int(sum[i >> 4][(i + 1) & 15]),
+                                __float_as_int(sum[i >> 4][(i + 2) & 15]), __float_as_int(sum[i >> 4][(i + 3) & 15])};
                     lds_barrier();
                     sum[0] = v16f{};
                     for (int j = 0; j < kws; ++j) {
@@ -573,7 +586,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const bool vec = a.n % 8 == 0;   // groups of eight channels are whole and 16-byte aligned
                 auto store8 = [&](const Out (&res)[8], int px, int c) {
                     if (vec) {
-                        const uint32_t off = c < a.n ? static_cast<uint32_t>(px * a.n + c) * sizeof(Out) : 0x80000000u;   // (beyond the bound: dropped)
+                        // (beyond the bound: dropped)
+                        const uint32_t off = c < a.n ? static_cast<uint32_t>(px * a.n + c) * sizeof(Out) : 0x80000000u;
                         buffer_store16(reinterpret_cast<const v4i *>(res)[0], y_buf, off, 0);
                         if constexpr (sizeof(Out) == 4) buffer_store16(reinterpret_cast<const v4i *>(res)[1], y_buf, off + 16, 0);
                     } else if (px < static_cast<int>(rows_left)) {

@@ -2,8 +2,9 @@
 // results, PyTorch's current stream.  No arithmetic and no device code.
 //
 // Why native: interpreted, a call spent about 11 us on attribute look-ups, checks and the foreign-function layer
-// before its kernel was launched - more than most of the kernels take; here it is about 4 us, most of it the launch.  (Two calls back to back on small
-// layers: 23 .. 24 us a layer before, 9.8 .. 10.4 us with this; linear 8192 x 384 -> 1152: 23.4 -> 15.1 us, bound by its kernels.)
+// before its kernel was launched - more than most of the kernels take; here it is about 4 us, most of it the launch.
+// (Two calls back to back on small layers: 23 .. 24 us a layer before, 9.8 .. 10.4 us with this; linear
+// 8192 x 384 -> 1152: 23.4 -> 15.1 us, bound by its kernels.)
 //
 // The entry points of the library are handed over as addresses (bind), so that the library is loaded in one place.
 #include <Python.h>
@@ -112,7 +113,8 @@ struct Args {
     }
     const at::Tensor &codes(at::ScalarType dt, const char *name) {
         const at::Tensor &t = device(name);
-        if (t.scalar_type() != dt) refuse(std::string(name) + " must hold " + (dt == at::kByte ? "torch.uint8" : "torch.int8") + " codes");
+        if (t.scalar_type() != dt)
+            refuse(std::string(name) + " must hold " + (dt == at::kByte ? "torch.uint8" : "torch.int8") + " codes");
         return t;
     }
     // an optional vector: exactly n elements of dt; the pointer, or null for None
@@ -345,8 +347,10 @@ PyObject *linear_i8(Args a) { return int_linear<int8_t>(a, "hq_int_linear_i8", l
 
 // hq_int_conv2d, hq_int_conv2d_static, hq_int_conv2d_i8
 template <class Code>
-PyObject *int_conv2d(Args &a, const char *fn, hq_status (*f)(const Code *, const float *, const Code *, const float *, const void *, int, int,
-                                                              int, int, int, int, int, int, int, void *, hq_dtype, void *), Scales scales) {
+PyObject *int_conv2d(Args &a, const char *fn,
+                     hq_status (*f)(const Code *, const float *, const Code *, const float *, const void *, int, int, int, int,
+                                    int, int, int, int, int, void *, hq_dtype, void *),
+                     Scales scales) {
     constexpr bool bytes = std::is_same<Code, int8_t>::value;
     constexpr at::ScalarType code = bytes ? at::kChar : at::kByte;
     const at::Tensor &xq = a.codes(code, "xq");
@@ -560,8 +564,9 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
 
 #define HQ_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(entry<f>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    HQ_METHOD(quantize_weights), HQ_METHOD(act_hadamard_quant), HQ_METHOD(act_hadamard_quant_i8), HQ_METHOD(act_hadamard_quant_static),
-    HQ_METHOD(linear), HQ_METHOD(linear_static), HQ_METHOD(linear_i8), HQ_METHOD(conv2d), HQ_METHOD(conv2d_static), HQ_METHOD(conv2d_i8),
+    HQ_METHOD(quantize_weights), HQ_METHOD(act_hadamard_quant), HQ_METHOD(act_hadamard_quant_i8),
+    HQ_METHOD(act_hadamard_quant_static), HQ_METHOD(linear), HQ_METHOD(linear_static), HQ_METHOD(linear_i8),
+    HQ_METHOD(conv2d), HQ_METHOD(conv2d_static), HQ_METHOD(conv2d_i8),
     HQ_METHOD(act_quant_conv2d), HQ_METHOD(act_quant_linear), HQ_METHOD(quantize_weights_single), HQ_METHOD(linear_single),
     HQ_METHOD(act_hadamard_quant_width), HQ_METHOD(conv2d_width),
     {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(bind)), METH_FASTCALL, nullptr},
