@@ -340,8 +340,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const bool in = (mask >> t) & 1;
                 if constexpr (FOLD && !INT_TAPS) {
                     const float s = in ? s_rowscale[row] : 0.f;
-                    s_sx[t * px_wg + i] = s * UNIT;
-                    if constexpr (!BYTES && !WHOLE_TAPS) corr = fmaf(s * 8.0f, static_cast<float>(s_sum[row]), corr);
+                    s_sx[t * px_wg + i] = s;
+                    if constexpr (!BYTES && !WHOLE_TAPS) corr = fmaf(s * (8.0f / UNIT), static_cast<float>(s_sum[row]), corr);
                 } else if (!BYTES && in) {
                     corr += 8.0f * static_cast<float>(s_sum[row]);
                 }
@@ -573,7 +573,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         if constexpr (OUT == kOutI32) {
                             res[i] = static_cast<int>(v[i] * 64.0f - corr);
                         } else {
-                            const float r = FOLD ? v[i] - corr : (v[i] * 64.0f - corr) * one_scale;
+                            // (scales of up to the largest float: they are not multiplied by the unit before their codes)
+                            const float r = FOLD ? (v[i] - corr) * UNIT : (v[i] * 64.0f - corr) * one_scale;
                             const float y = fmaf(r, sw[i], bias[i]);
                             if constexpr (OUT == kOutF16) res[i] = __float2half_rn(y);
                             else res[i] = y;

@@ -82,6 +82,22 @@ def test_conv3x3_fp32_codes_of_one_sign(hq, nb, h, w, cin, cout):
     check_y("y", y, y_o, rtol=20 * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("scale", [1e37, 1e-30])
+def test_conv3x3_extreme_scales(hq, scale):
+    """Scales near the ends of fp32's range whose products with the weights' are ordinary numbers."""
+    rng = np.random.default_rng(5)
+    nb, h, w, cin, cout = 2, 9, 9, 384, 40
+    xq = np.zeros((nb, h, w, cin), np.int8)
+    xq[..., :3] = rng.integers(-1, 2, (nb, h, w, 3))     # (sums of up to 27 codes: no product of scale and sum overflows)
+    wq = rng.integers(-1, 2, (cout, 3, 3, cin)).astype(np.int8)
+    sx = (rng.uniform(0.5, 1.0, (nb, h, w)) * scale).astype(np.float32)
+    sw = (rng.uniform(0.5, 1.0, cout) / scale).astype(np.float32)
+    _, y_o = oracle.int_conv2d(xq, sx, wq, sw, None, stride=1, pad=1, want_acc=False)
+    for ydt, rtol in ((torch.float32, 1e-5), (torch.float16, 1e-3)):
+        y = hq.hq_int_conv2d(dev(pack_codes(xq)), dev(sx), dev(pack_codes(wq.reshape(cout, 9, cin))), dev(sw), None, ksize=3, y_dtype=ydt)
+        check_y("y", host(y), y_o, rtol=rtol)
+
+
 @pytest.mark.parametrize("nb,h,w,cin,cout,block", [
     (1, 3, 8, 64, 1, 8),         # two planes; one channel
     (2, 5, 16, 128, 40, 16),     # two steps per slice
