@@ -31,25 +31,33 @@ constexpr uint32_t fp6_bits(uint32_t field, int a, int b, int c = -1) {
 __device__ __forceinline__ v16f mfma_fp6(const v8i &a, const v8i &b, const v16f &c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 0, 0, 0);
 }
-// the same product times 16 (block exponents 2^0 and 2^4)
-__device__ __forceinline__ v16f mfma_fp6_times16(const v8i &a, const v8i &b, const v16f &c) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 127, 0, 131);
+// the same with the products of a lane's column times 2^(exponent - 127)
+__device__ __forceinline__ v16f mfma_fp6_scaled(const v8i &a, const v8i &b, const v16f &c, int exponent) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 127, 0, exponent);
 }
 
 // Two packed dwords -> three dwords of fields holding code + 8 (0..15, sign bit 0): the offset turns two's
-// complement into a magnitude by flipping one bit, which the masks do on the way (7 instructions for 16 codes).
+// complement into a magnitude by flipping one bit, which the merging does on the way (7 instructions for 16 codes).
 // A sum of products with such an operand exceeds the wanted one by 8 x (sum of the other operand).
-__device__ __forceinline__ void fp6_offset16(uint32_t wa, uint32_t wb, int &d0, int &d1, int &d2) {
+// An instruction reads one constant from scalar registers: the masks of the first dword are held in vector registers (the empty
+// statements keep the compiler from taking them for constants, which would cost three instructions more).
+struct Fp6Masks {
+    uint32_t a0 = fp6_bits(15, 0, 12, 24), a1 = fp6_bits(15, 4, 16, 28), a2 = fp6_bits(15, 8, 20);
+    __device__ __forceinline__ Fp6Masks() { asm("" : "+v"(a0), "+v"(a1), "+v"(a2)); }
+};
+// (p & mask) ^ q
+__device__ __forceinline__ uint32_t and_xor(uint32_t p, uint32_t mask, uint32_t q) {
+    return __builtin_amdgcn_bitop3_b32(p, mask, q, 0x6A);
+}
+__device__ __forceinline__ void fp6_offset16(const Fp6Masks &m, uint32_t wa, uint32_t wb, int &d0, int &d1, int &d2) {
     const uint32_t r = __builtin_amdgcn_alignbit(wb, wb, 2);   // rotate right by two
-    constexpr uint32_t a0 = fp6_bits(15, 0, 12, 24), b0 = fp6_bits(15, 6, 18) | (3u << 30);
-    constexpr uint32_t a1 = fp6_bits(15, 4, 16, 28), b1 = fp6_bits(15, 10, 22) | 3u;
-    constexpr uint32_t a2 = fp6_bits(15, 8, 20), b2 = fp6_bits(15, 2, 14, 26);
+    constexpr uint32_t b0 = fp6_bits(15, 6, 18) | (3u << 30), b1 = fp6_bits(15, 10, 22) | 3u, b2 = fp6_bits(15, 2, 14, 26);
     constexpr uint32_t x0 = fp6_bits(8, 0, 12, 24) | fp6_bits(8, 6, 18);
     constexpr uint32_t x1 = fp6_bits(8, 4, 16, 28) | fp6_bits(8, 10, 22) | 2u;
     constexpr uint32_t x2 = fp6_bits(8, 8, 20) | fp6_bits(8, 2, 14, 26);
-    d0 = static_cast<int>(((wa & a0) ^ x0) ^ (r & b0));
-    d1 = static_cast<int>(((wa & a1) ^ x1) ^ (r & b1));
-    d2 = static_cast<int>(((wa & a2) ^ x2) ^ (r & b2));
+    d0 = static_cast<int>(and_xor(r, b0, and_xor(wa, m.a0, x0)));
+    d1 = static_cast<int>(and_xor(r, b1, and_xor(wa, m.a1, x1)));
+    d2 = static_cast<int>(and_xor(r, b2, and_xor(wa, m.a2, x2)));
 }
 
 // Two packed dwords -> three dwords of signed fields (sign and magnitude), same order.

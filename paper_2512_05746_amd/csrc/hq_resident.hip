@@ -4,10 +4,10 @@
 
 #include "hq_resident_kernel.h"
 
-const void *hq_resident_pertap(int out, int ks);
-const void *hq_resident_sum(int out, int ks);
-const void *hq_resident_planes(int out, int ks);
-const void *hq_resident_bytes(int out, int ks);
+const void *hq_resident_pertap(int out, bool ring, int ns);
+const void *hq_resident_sum(int out, bool ring, int ns);
+const void *hq_resident_planes(int out, bool ring, int ns);
+const void *hq_resident_bytes(int out, bool ring, int ns);
 
 namespace {
 
@@ -15,12 +15,12 @@ constexpr int kLdsPerCu = 163840;
 
 struct Plan {
     int ks, slices, chunk, nw, xw_log2, cb, rows;
-    uint32_t part8, exchange, tables, lds;
-    bool wide, ok;
+    uint32_t part8, exchange, ring, ring_stride, tables, lds;
+    bool wide, has_ring, ring_shared, ok;
 };
 
 // LDS layout of a workgroup of nw waves, 1 << xw_log2 pixel groups and cb channel blocks within `budget` bytes.  by_slice: with a
-// table of 16-bit code sums by row and slice behind the others (fp32 results of per-pixel scales).
+// table of 16-bit code sums by row and step behind the others (fp32 results of per-pixel scales).
 Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int xw_log2, int cb, int budget) {
     const int blocks = (n + 31) / 32;
     Plan p{};
@@ -40,7 +40,7 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     const int ops = ks * (kind >= kResPlanes ? 2 : 1);   // operands of a row, lane half and slice
     const int part8_bytes = kind == kResBytes ? 0 : 16;   // (8-bit codes are 16-byte operands)
     const int slice_bytes = p.rows * ops * (32 + part8_bytes);
-    const int sums = by_slice ? p.rows * 2 : 0;
+    const int sums = by_slice ? p.rows * 2 * ks : 0;   // (a sum for every step)
     int tables = resident_table_bytes(kind, px, p.rows, cb);
     p.chunk = std::min(p.slices, (budget - tables - (overlay ? 0 : area)) / (slice_bytes + sums));
     tables += (p.chunk * sums + 3) & ~3;
@@ -54,6 +54,23 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     p.tables = overlay ? std::max(act_end, static_cast<uint32_t>(p.wide ? 2 * area : area)) : act_end + area;
     p.lds = p.tables + tables;
     p.ok = static_cast<int>(p.lds) <= budget + 32 && p.lds <= kLdsPerCu;
+    // The rings of weights: behind the tile (and the exchange area of its own, if it has one) where that leaves room for them, with
+    // the tables behind them; else in the exchange area, which costs a barrier from phase to phase; else (one phase, and a tile that
+    // fills the LDS) there are none.
+    const uint32_t ring_bytes = resident_ring_slots(kind) * resident_slot_bytes(kind), free_at = overlay ? act_end : act_end + area;
+    p.has_ring = true;
+    p.ring = p.exchange;
+    p.ring_stride = 8192;
+    p.ring_shared = !overlay;
+    if (static_cast<int>(free_at + nw * ring_bytes) + tables <= budget) {
+        p.ring = free_at;
+        p.ring_stride = ring_bytes;
+        p.ring_shared = false;
+        p.tables = std::max<uint32_t>(p.tables, free_at + nw * ring_bytes);
+        p.lds = p.tables + tables;
+    } else if (overlay) {
+        p.has_ring = false;
+    }
     return p;
 }
 
@@ -158,7 +175,7 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     a.out_scale = g.out_scale;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
-    a.slices = p.slices; a.chunk = p.chunk; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
+    a.chunk = p.chunk * p.ks; a.grain = p.ks; a.ring = p.ring; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
     a.wide = p.wide; a.part8 = p.part8; a.exchange = p.exchange; a.tables = p.tables;
     const int px = 128 << p.xw_log2, blocks = (g.n + 31) / 32;
     const int64_t px_tiles = (static_cast<int64_t>(g.pixels) + px - 1) / px, ch_groups = (blocks + p.cb - 1) / p.cb;
@@ -175,12 +192,13 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
         const hq_status st = hq_fill_zero_launch(g.y, static_cast<uint64_t>(g.pixels) * 9 * g.n, stream);
         if (st != HQ_OK) return st;
     }
-    const void *fn = kind == kResBytes    ? hq_resident_bytes(out, p.ks)
-                     : kind == kResPlanes ? hq_resident_planes(out, p.ks)
-                     : kind == kResSum  ? hq_resident_sum(out, p.ks)
-                                        : hq_resident_pertap(out, p.ks);
-    static std::atomic<uint64_t> allowed[4][3][3];
-    const hq_status st = allow_lds(fn, allowed[kind][out][p.ks - 1]);
+    const int ns = p.chunk == p.slices ? resident_unrolled(kind, out, g.k / 64) : 0;
+    const void *fn = kind == kResBytes    ? hq_resident_bytes(out, p.has_ring, ns)
+                     : kind == kResPlanes ? hq_resident_planes(out, p.has_ring, ns)
+                     : kind == kResSum  ? hq_resident_sum(out, p.has_ring, ns)
+                                        : hq_resident_pertap(out, p.has_ring, ns);
+    static std::atomic<uint64_t> allowed[4][3][5];
+    const hq_status st = allow_lds(fn, allowed[kind][out][ns ? 1 + ns : p.has_ring]);
     if (st != HQ_OK) return st;
     void *args[] = {&a};
     if (hipLaunchKernel(fn, dim3(static_cast<unsigned>(tiles)), dim3(64 * p.nw), args, p.lds, stream) != hipSuccess)

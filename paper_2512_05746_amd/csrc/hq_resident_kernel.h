@@ -5,23 +5,23 @@
 // result tile is 32 channels x 128 pixels.  The codes of the pixels, and those of W + 1 pixels either side, are fetched
 // once, expanded to 6-bit fields and kept in LDS as planes
 //     [64-channel step][lane half][row] of 16-byte operand parts, then of 8-byte parts,
-// so that a wave's operand read of 32 consecutive rows is two contiguous runs for any row shift: 224 bytes per clock
-// and CU measured, against 126 with the halves of a row next to each other.  Weights go from memory straight into
-// registers, one unit ahead; there is no barrier between the filling of the tile and the end of a phase.
+// so that a wave's operand read of 32 consecutive rows is two contiguous runs for any row shift (4 clocks a KiB, without
+// conflicts).  Weights pass through a ring in LDS of the wave's own; there is no barrier between the filling of the tile and the
+// end of a phase.
 //
-// A unit is one tap and one slice of KS steps: 7 vector instructions per 16 weight codes to expand them (hq_fp6.h),
-// KS operand reads and KS MFMAs for each of the four 32-pixel tiles, and (per-pixel scales) one fold of 16
-// values into the fp32 sums per tile.  What bounds it: vector issue and matrix pipe together.  A 192-channel unit has
-// 5.3 (fold) + 3.5 (weights) + about 1 vector instructions per MFMA; a loop of such a mix alone takes 30 ns per MFMA
-// and SIMD (21 ns without them: on random codes the chip holds 1.6 .. 2.1 GHz), the kernel's 31 .. 33 ns.  The other half
-// of a launch is what surrounds the loop: start and first loads (2 us), expanding the tile (2 .. 4 us; 24
-// instructions per 16 codes for the signed form), exchange and results (2 .. 5 us).
+// A step is 64 channels of one tap: 14 vector instructions to expand the weights (hq_fp6.h), one operand read and one MFMA for
+// each of the four 32-pixel tiles; per-pixel scales: one fold of 16 values a tile into the fp32 sums for every tap.  What bounds
+// it: a loop of such MFMAs alone takes 23 ns each (the chip holds 1.7 GHz under them), the kernel's 32 .. 34.  The rest is
+// the wave's own instructions (14 an MFMA, issued in order, two waves a SIMD), LDS (34 clocks of its time an MFMA and CU: operands,
+// ring) and the address path (22 clocks an MFMA).  Taking the weights' requests out of the loop makes it 1.3 us faster on
+// 16 x 32 x 32 x 384, the operand reads 3, the expansion 3, the folds 1.  Before, weights were loaded straight into the operand's
+// lanes (37 clocks of address path an MFMA), folds were per 192 channels, expansion took 20 instructions and addresses 25.
+// The other half of a launch is what surrounds the loop: start and first loads (2 us), expanding the tile (2 .. 4 us;
+// 24 instructions per 16 codes for the signed form), exchange and results (2 .. 5 us).
 //
-// Measured (3x3, 4-bit, us, buffers rotating beyond the last-level cache; before: int8 kernels that expanded nibbles
-// at every use or streamed both operands through LDS), per-pixel scales / one scale:
-//     16 x 64 x 64 x 192   31.1 -> 27.3 / 28.4 -> 27.1      16 x 8 x 8 x 960            17.8 -> 15.4 / 17.8 -> 15.0
-//     16 x 32 x 32 x 384   31.9 -> 25.2 / 30.5 -> 25.1       8 x 16 x 16 x 960          32.6 -> 22.0 / 31.4 -> 21.5
-//     16 x 16 x 16 x 576   24.0 -> 20.1 / 26.8 -> 20.2       3 x 45 x 27 x 320 -> 200   32.7 -> 11.1 / 28.8 -> 10.8
+// Measured (3x3, 4-bit, us per pass with the quantiser, weights in L2; kernel with weights in registers -> this one):
+//     per-pixel scales: 8 x 16 x 16 x 960 25.3 -> 24.3, 3 x 45 x 27 x 320 -> 200 14.2 -> 13.8, 3 x 44 x 44 x 576 -> 152 17.2 -> 16.9
+//     one scale:       16 x 32 x 32 x 384 28.5 -> 28.0, 4 x 46 x 46 x 960 -> 488 68.7 -> 66.8
 //
 // Phases.  The tasks (pixel group, channel block) of a workgroup are dealt out to its NW waves in phases: NW at a
 // time, then the remainder in powers of two, the units of a task shared by 2, 4 or 8 waves whose sums meet in
@@ -35,22 +35,23 @@
 //
 // 8-bit codes (the form of 16-byte operands on v_mfma_i32_32x32x32_i8, nothing to expand on either side; the two
 // 32-channel halves of a step take the places of two operand planes, each with weights of its own).  Matrix time is twice
-// that of 4-bit codes and the fold converts 16 values more per tile; matrix and vector time add up almost fully here as
-// there.  us per pass with the quantiser, tile kernel -> this one: 16 x 32 x 32 x 384 51.5 -> 44.1, 16 x 64 x 64 x 192
-// 63.7 -> 45.1, 16 x 16 x 16 x 576 44.0 -> 32.1, 16 x 8 x 8 x 960 48.2 -> 22.5, 3 x 45 x 27 x 320 -> 200 51.3 -> 15.9,
-// 1 x 8 x 8 x 64 (launch) 26.7 -> 11.2.
+// that of 4-bit codes and bounds it: 42 clocks an MFMA of 32, at the 1.5 GHz that the chip holds under them.  us per pass with
+// the quantiser, weights in registers and a fold of twice the instructions for every 192 channels -> this form: 16 x 32 x 32 x 384
+// 43.7 -> 39.1, 2 x 24 x 40 x 640 31.3 -> 27.4.
+//
+// One scale: taps outside the image must add nothing.  Their products are multiplied by 2^-127 (the block exponent that the matrix
+// instruction takes for every column) instead of reading a row of zeros, which would cost every tile an address of its own
+// in every step (16 x 32 x 32 x 384: 31.2 -> 26.2 us); what they leave, below 1e-35, is rounded away before the sums are scaled.
 //
 // Which layers come here and which stay on the tile kernel: choose_kernel in hq_resident.hip.
 //
 // Weights carry an offset of 8 (hq_fp6.h; not those of 8 bits): a sum exceeds the wanted one by 8 x (sum of the activation
 // codes it covers), the same for all channels: a per-pixel correction from a table of code sums.  With one scale all of it
 // is exact.
-// With per-pixel scales the correction is subtracted at the end from sums in fp32 that hold it, one fold per tap and slice,
-// which costs digits: the 2-norm error is 2e-7 .. 3e-7 where code sums are small, up to 1.5e-5 where the codes of a pixel
-// have one sign (64 .. 960 channels), below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).
-// fp32 results would lose digits, so their sums start at minus the correction (one fp16 matrix step per tap and tile), run
-// over all slices of a tap, and are folded once: 6e-8 for both, as with sums in integers.  That form is slower (us, fp32
-// results: 16 x 32 x 32 x 384 28.1 -> 30.7, 16 x 64 x 64 x 192 34.9 -> 39.2) and would cost fp16 results 2 us as well.
+// With per-pixel scales the fp32 sums start from minus the correction and then hold it in part, which costs digits: the 2-norm
+// error is 2e-7 .. 3e-7 where code sums are small, up to 1.5e-5 where the codes of a pixel have one sign (64 .. 960 channels),
+// below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).  fp32 results would lose digits, so there
+// the sums of a tap start at minus its correction (one fp16 matrix step per tap and tile): 6e-8, as with sums in integers.
 #pragma once
 #include <type_traits>
 
@@ -69,15 +70,18 @@ struct ResidentArgs {
     int in_planes;       // kResPlanes: planes that are not all zeros (2 or 3)
     float out_scale;     // times the one scale
     uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
-    int slices, chunk;             // K slices of KS steps, and how many are resident at a time
+    int chunk;                     // steps of 64 channels that are resident at a time
+    int grain;                     // fp32 results: steps of a tap that stay together
     int xw_log2;                   // pixel groups of 128 per workgroup
     int cb;                        // channel blocks of 32 per workgroup
     uint32_t ch_groups, px_tiles;  // workgroups: channel runs x pixel tiles
     uint32_t d_magic, d_shift;     // exact division of a tile index by the count that runs fastest
     int ch_major;                  // neighbouring workgroups share the channels (else the pixels)
-    int rows;                      // rows of the LDS image, odd, the last one all zeros
+    int rows;                      // rows of the LDS image and one more, odd
     int wide;                      // the exchange area has 16 KiB per wave (else 8)
-    uint32_t part8, exchange, tables;   // LDS offsets: 8-byte parts, exchange / staging area, tables
+    uint32_t ring_stride;          // LDS from wave to wave's ring
+    int ring_shared;               // the rings lie in the exchange area
+    uint32_t part8, exchange, ring, tables;   // LDS offsets: 8-byte parts, exchange / staging area, rings, tables
 };
 
 namespace {
@@ -110,6 +114,36 @@ __device__ __forceinline__ void buffer_store16(const v4i &v, __amdgpu_buffer_rsr
                                            static_cast<int>(uniform_off), 0);
 }
 
+// Direct-to-LDS load of 16 bytes a lane: lane i's land at lds_base + 16 i.  Inline assembly, because the compiler cannot tell which
+// slot of a ring such a load fills and would wait for all of them before every LDS read; the waits (wait_vmem) are placed by
+// hand.  (Its own counted waits stay right: they only wait for more.)
+__device__ __forceinline__ v4i buffer_words(const void *p, uint32_t bytes) {   // a buffer as four scalar registers
+    const uint64_t at = reinterpret_cast<uint64_t>(p);
+    return v4i{static_cast<int>(at), static_cast<int>(at >> 32 & 0xFFFF), static_cast<int>(bytes), 0x00027000};
+}
+__device__ __forceinline__ void load_to_ring(const v4i &r, uint32_t lane_off, uint32_t uniform_off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :
+                 : "s"(lds_base), "v"(lane_off), "s"(r), "s"(uniform_off)
+                 : "memory");
+}
+// steps of a tap that a form is built for (0: any number)
+__host__ __device__ constexpr int resident_unrolled(int kind, int out, int ns) {
+    return kind == kResPerTap && out == kOutF16 && ns <= 3 ? ns : 0;
+}
+// bytes of a step's weights for 32 channels, a slot of a ring
+__host__ __device__ constexpr int resident_slot_bytes(int kind) { return kind == kResBytes ? 2048 : 1024; }
+constexpr int resident_ring_slots(int) { return 3; }
+
+// LDS reads at an address that is already one of LDS (no base to add)
+typedef int v2i __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ v4i lds_v4i(int address, int offset = 0) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) v4i *>(static_cast<uint32_t>(address) + offset);
+}
+__device__ __forceinline__ v2i lds_v2i(int address, int offset = 0) {
+    return *reinterpret_cast<const __attribute__((address_space(3))) v2i *>(static_cast<uint32_t>(address) + offset);
+}
+
 __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
     return (kind == kResPerTap || kind == kResBytes ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
 }
@@ -124,7 +158,12 @@ __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
     return __builtin_amdgcn_mfma_f32_32x32x8f16(weights, b, v16f{}, 0, 0, 0);
 }
 
-template <int OUT, int KIND, int KS>
+// RING: weights pass through a ring in LDS (else, where no room is left for it, straight from memory).
+// NS: 0, or the 1 .. 3 steps of a tap (fp16 results with per-pixel scales, up to 192 channels): a tap is unrolled, with its weights
+// straight from memory and one tap ahead in registers, tile by tile, the folds between the tiles.  A tap so short has a fold for
+// every 4 to 12 matrix instructions, and this order hides them best: us a pass with the quantiser, steps in a loop with a ring -> this:
+// 1 x 62 x 62 x 128 12.3 -> 11.8, 16 x 64 x 64 x 192 (the kernel alone) 24.7 -> 23.4; with more steps the ring wins (below).
+template <int OUT, int KIND, bool RING, int NS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
     constexpr bool WHOLE_TAPS = KIND == kResPerTap && OUT == kOutF32;   // (see the offset of the weights above)
@@ -132,6 +171,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     // planes in memory, operand planes in LDS (BYTES: the two 32-channel halves of a step) and of the weights
     constexpr int IN = KIND == kResPlanes ? 3 : BYTES ? 2 : 1, PL = KIND == kResPlanes || BYTES ? 2 : 1, WP = BYTES ? 2 : 1;
     constexpr int STEP = BYTES ? 64 : 32;   // bytes of a step of 64 codes
+    constexpr int AHEAD = IN == 1 ? 4 : 2;                // items of the fill whose loads are in flight
     using Out = typename OutT<OUT>::type;
     using Operand = std::conditional_t<BYTES, v4i, v8i>;
     using Acc = std::conditional_t<BYTES, v16i, v16f>;
@@ -150,7 +190,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     const uint32_t tile = xcd * q8 + (xcd < r8 ? xcd : r8) + (blockIdx.x >> 3);
     const uint32_t fast = a.ch_major ? a.px_tiles : a.ch_groups;
     const uint32_t slow_i = hq::div_magic31(tile, fast, a.d_magic, a.d_shift), fast_i = tile - slow_i * fast;
-    const uint32_t p0 = (a.ch_major ? fast_i : slow_i) * px_wg;
+    const uint32_t px_tile = a.ch_major ? fast_i : slow_i, p0 = px_tile * px_wg;
     const int c_wg = static_cast<int>(a.ch_major ? slow_i : fast_i) * a.cb * 32;
     const int blocks = min(a.cb, (a.n - c_wg + 31) / 32);   // channel blocks of this workgroup
 
@@ -158,10 +198,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     float *s_corr = s_sx + (FOLD ? TAPS : 0) * px_wg;
     int *s_mask = reinterpret_cast<int *>(s_corr + px_wg);
     float *s_rowscale = reinterpret_cast<float *>(s_mask + px_wg);
-    int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);   // code sums [row] of the slices so far
+    int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);   // code sums [row] of the resident steps
     float *s_sw = reinterpret_cast<float *>(s_sum + rows);
     float *s_bias = s_sw + a.cb * 32;
-    short *s_part = reinterpret_cast<short *>(s_bias + a.cb * 32);   // WHOLE_TAPS: code sums [resident slice][row]
+    short *s_part = reinterpret_cast<short *>(s_bias + a.cb * 32);   // WHOLE_TAPS: code sums [resident step][row]
 
     // ---- phases: tasks and shares ---------------------------------------------------------------------------
     // tasks first .. first + (nw >> kl) - 1, each by 1 << kl waves; wave wv has task first + wv >> kl, share wv mod
@@ -171,104 +211,181 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         while ((nw >> kl) > left) ++kl;
     };
     shrink();
-    int c0 = 0, px_l = 0, u = 0, u_end = 0;   // first channel, first pixel (local), units of this wave's task
-    uint32_t w_lane = 0;                      // this lane's weight row
-    const int resident0 = a.chunk < a.slices ? a.chunk : a.slices;
-    int s0 = 0, s1 = resident0;               // resident slices
+    int c0 = 0, px_l = 0;    // first channel, first pixel (local)
+    int s0 = 0, ns = a.chunk < steps ? a.chunk : steps;   // resident steps s0 .. s0 + ns - 1
+    int q = 0, q_end = 0;    // steps of this wave's share: tap q / ns, resident step q % ns
+
+    // ---- weights: from memory into the wave's ring in LDS, R steps ahead --------------------------------------
+    // A step's 32 rows of 32 bytes (BYTES: 64) are fetched by neighbouring lanes piece by piece, which takes the address
+    // path 22 clocks a KiB; loads straight into the operand's lanes (16 rows in every 16 lanes) take 37, more than the matrix
+    // instructions that the KiB feeds.  In rows 8..15 mod 16 (BYTES: 4..7, 8..11, 12..15) the pieces change places, so that
+    // the operand reads meet no bank conflict.  Every step requests one (past the share's end its last one again), so the
+    // number of requests in flight is always the same.
+    constexpr int R = resident_ring_slots(KIND), SLOT = resident_slot_bytes(KIND), DMAS = SLOT / 1024;
+    const v4i w_buf = buffer_words(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
+    const uint32_t ring_at = a.ring + wv * a.ring_stride;   // (uniform)
+    const uint32_t ring = lds_address(lds) + ring_at;
+    uint32_t w_row[DMAS];    // this lane's pieces: offset of the weight row and piece (without a ring: [0] its operand's row)
+    // where this lane's operand pieces lie in a slot
+    int r_piece[WP];
+#pragma unroll
+    for (int i = 0; i < WP; ++i)
+        r_piece[i] = static_cast<int>(ring) + (BYTES ? l * 64 + ((2 * i + h) ^ ((l >> 2) & 3)) * 16 : l * 32 + (h ^ ((l >> 3) & 1)) * 16);
+    uint32_t f_off = 0, f_tap_last = 0, f_last = 0;   // position requested next, the last of its tap and of the share
+    uint32_t slot = 0;       // slot read last and filled next
+    auto advance = [&]() {
+        if (f_off == f_tap_last) {
+            f_off += cb - ns * STEP;
+            f_tap_last += cb;
+        }
+        f_off = min(f_off + STEP, f_last);
+    };
+    v4i raw[WP];             // weights of the next step (BYTES: of this step) as they lie in memory
+    auto request = [&]() {   // the next position into its slot
+        if constexpr (RING) {
+#pragma unroll
+            for (int j = 0; j < DMAS; ++j) load_to_ring(w_buf, w_row[j], f_off, ring + slot + j * 1024);
+            advance();
+        }
+    };
+    auto take = [&]() {      // raw <- the next slot; R - 1 steps were requested after it
+        if constexpr (RING) {
+            wait_vmem<(R - 1) * DMAS>();
+            asm volatile("" ::: "memory");
+            slot = slot == (R - 1) * SLOT ? 0 : slot + SLOT;
+#pragma unroll
+            for (int i = 0; i < WP; ++i) raw[i] = lds_v4i(r_piece[i] + slot);
+        } else {
+            const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
+#pragma unroll
+            for (int i = 0; i < WP; ++i) raw[i] = buffer_load16(buf, w_row[0] + i * 32, f_off);
+            advance();
+        }
+    };
+    v4i raw_tap[NS ? NS : 1];   // NS: weights of the next tap
+    auto take_tap = [&](int tap) {
+        const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
+#pragma unroll
+        for (int k = 0; k < NS; ++k) raw_tap[k] = buffer_load16(buf, w_row[0], static_cast<uint32_t>(tap * cb + k * STEP));
+    };
     auto begin_task = [&]() {
         const int task = first + (wv >> kl), share = wv & ((1 << kl) - 1);
         px_l = (task & ((1 << a.xw_log2) - 1)) * 128;
         c0 = c_wg + (task >> a.xw_log2) * 32;
-        const int co = c0 + tile_row_to_channel(l);
-        w_lane = static_cast<uint32_t>(co < a.n ? co : a.n - 1) * (TAPS * cb) + h * 16;
-        const int units = TAPS * (s1 - s0);
-        u = share * units >> kl;
-        u_end = (share + 1) * units >> kl;
-    };
-    // unit u of the resident slices: tap u / (s1 - s0), slice s0 + u % (s1 - s0)
-    v4i raw[WP][KS];   // weights of the next unit as they lie in memory
-    const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
-    auto load_weight = [&](int k, int tap, int slice) {
-        const int step = slice * KS + k < steps ? slice * KS + k : 0;   // (past the channels: activations are zero)
+        auto row_of = [&](int i) {
+            const int co = c0 + tile_row_to_channel(i);
+            return static_cast<uint32_t>(co < a.n ? co : a.n - 1) * (TAPS * cb);
+        };
 #pragma unroll
-        for (int i = 0; i < WP; ++i)
-            raw[i][k] = buffer_load16(w_buf, w_lane, static_cast<uint32_t>(tap * cb + step * STEP + i * 32));
-    };
-    auto load_weights = [&](int tap, int slice) {
+        for (int j = 0; j < DMAS; ++j) {
+            const int row = BYTES ? j * 16 + (lane >> 2) : lane >> 1;
+            w_row[j] = row_of(row) + (BYTES ? (lane & 3) ^ ((row >> 2) & 3) : (lane & 1) ^ ((row >> 3) & 1)) * 16;
+        }
+        if constexpr (!RING) w_row[0] = row_of(l) + h * 16;
+        // (a tap that two waves share is folded twice: fp32 results are cut at every a.grain-th step of a tap only)
+        const int grain = NS ? NS : OUT == kOutF32 ? a.grain : 1, grains = (ns + grain - 1) / grain;
+        auto cut = [&](int of) {
+            const int at = of * (TAPS * grains) >> kl, tap = at / grains;
+            return tap * ns + (at - tap * grains) * grain;
+        };
+        q = cut(share);
+        q_end = cut(share + 1);
+        const int tap = q / ns, last_tap = (q_end - 1) / ns;
+        f_off = tap * cb + (s0 + q - tap * ns) * STEP;
+        f_tap_last = tap * cb + (s0 + ns - 1) * STEP;
+        f_last = last_tap * cb + (s0 + q_end - 1 - last_tap * ns) * STEP;
+        if constexpr (NS > 0) take_tap(tap);
+        if constexpr (RING) {
 #pragma unroll
-        for (int k = 0; k < KS; ++k) load_weight(k, tap, slice);
+            for (int i = 0; i < R; ++i) {
+                slot = i * SLOT;
+                request();
+            }
+        }
     };
 
     // ---- activation tile: packed codes -> signed 6-bit fields ------------------------------------------------
-    // Wave items (32 rows, slice): lane = (row, lane half), KS 16-byte pieces each; the code sum of a row's
-    // slice is that of two neighbouring lanes.
-    const int row_items = (px_wg + 2 * halo + 31) >> 5;
+    // Wave items (32 rows, step): lane = (row, lane half), one 16-byte piece each; the code sum of a row's step is that of
+    // two neighbouring lanes.  Neighbouring waves take the steps of the same rows.
+    const int row_span = (px_wg + 2 * halo + 31) & ~31;
     const uint32_t last = a.pixels - 1;
     const int64_t row_pixel0 = static_cast<int64_t>(p0) - halo;
     const int f_row = lane >> 1, f_half = lane & 1;
     const uint32_t plane_bytes = a.pixels * static_cast<uint32_t>(cb);
     const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, BYTES ? plane_bytes : IN * plane_bytes);
-    auto fill_load = [&](v4i (&p)[IN][KS], int item) {
-        const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
-        // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
-        const uint32_t off = (static_cast<uint32_t>(p0) - halo + row) * cb + f_half * 16;
-#pragma unroll
-        for (int i = 0; i < IN; ++i)
-#pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                p[i][k] = v4i{0, 0, 0, 0};
-                if ((s0 + sl) * KS + k < steps && i < a.in_planes)
-                    p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + ((s0 + sl) * KS + k) * STEP);
-            }
+    struct Item { int step, row; };
+    int nw_step = 0, nw_row = 0;   // nw items on
+    auto next = [&](Item &i) {
+        i.step += nw_step;
+        i.row += nw_row;
+        if (i.step >= ns) {
+            i.step -= ns;
+            i.row += 32;
+        }
     };
-    auto fill_store = [&](const v4i (&p)[IN][KS], int item) {
-        const int sl = item / row_items, row = (item - sl * row_items) * 32 + f_row;
+    auto fill_load = [&](v4i (&p)[IN], const Item &item) {
+        if (item.row >= row_span) return;
+        // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
+        const uint32_t off = (static_cast<uint32_t>(p0) - halo + item.row + f_row) * cb + f_half * 16;
+#pragma unroll
+        for (int i = 0; i < IN; ++i) {
+            if (i < a.in_planes) p[i] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step) * STEP);
+            else p[i] = v4i{0, 0, 0, 0};
+        }
+    };
+    auto fill_store = [&](const v4i (&p)[IN], const Item &item) {
+        const int row = item.row + f_row;
         int sum = 0;
         if (row < rows - 1) {
+            auto at = [&](int plane) { return ((item.step * PL + plane) * 2 + f_half) * rows + row; };
+            if constexpr (BYTES) {
 #pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                if constexpr (BYTES) {
-#pragma unroll
-                    for (int i = 0; i < PL; ++i)
-                        *reinterpret_cast<v4i *>(lds + ((((sl * PL + i) * KS + k) * 2 + f_half) * rows + row) * 16) = p[i][k];
-                    continue;
-                }
+                for (int i = 0; i < PL; ++i) *reinterpret_cast<v4i *>(lds + at(i) * 16) = p[i];
+            } else {
                 auto codes = [&](const v4i &v, int s) {
                     return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s))));
                 };
                 auto put = [&](int plane, const int (&d)[6]) {
-                    const int at = (((sl * PL + plane) * KS + k) * 2 + f_half) * rows + row;
-                    *reinterpret_cast<v4i *>(lds + at * 16) = v4i{d[0], d[1], d[2], d[3]};
-                    *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{d[4], d[5]};
+                    *reinterpret_cast<v4i *>(lds + at(plane) * 16) = v4i{d[0], d[1], d[2], d[3]};
+                    *reinterpret_cast<int2 *>(lds + a.part8 + at(plane) * 8) = int2{d[4], d[5]};
                 };
                 int d[6];
-                fp6_signed16(p[0][k].x, p[0][k].y, d[0], d[1], d[2]);
-                fp6_signed16(p[0][k].z, p[0][k].w, d[3], d[4], d[5]);
+                fp6_signed16(p[0].x, p[0].y, d[0], d[1], d[2]);
+                fp6_signed16(p[0].z, p[0].w, d[3], d[4], d[5]);
                 put(0, d);
-                sum = codes(p[0][k], sum);
+                sum = codes(p[0], 0);
                 if constexpr (KIND == kResPlanes) {
-                    fp6_upper16(p[1][k].x, p[2][k].x, p[1][k].y, p[2][k].y, d[0], d[1], d[2]);
-                    fp6_upper16(p[1][k].z, p[2][k].z, p[1][k].w, p[2][k].w, d[3], d[4], d[5]);
+                    fp6_upper16(p[1].x, p[2].x, p[1].y, p[2].y, d[0], d[1], d[2]);
+                    fp6_upper16(p[1].z, p[2].z, p[1].w, p[2].w, d[3], d[4], d[5]);
                     put(1, d);
-                    sum += 16 * codes(p[1][k], 0) + 256 * codes(p[2][k], 0);
+                    sum += 16 * codes(p[1], 0) + 256 * codes(p[2], 0);
                 }
             }
         }
         if constexpr (!BYTES) {
             sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
             if (f_half == 0 && row < rows - 1) {
-                if constexpr (WHOLE_TAPS) s_part[sl * rows + row] = static_cast<short>(sum);
+                if constexpr (WHOLE_TAPS) s_part[item.step * rows + row] = static_cast<short>(sum);
                 else atomicAdd(&s_sum[row], sum);
             }
         }
     };
 
     // All first loads are requested before any is waited for (a first use costs a trip to HBM).
-    v4i p[2][IN][KS];
+    v4i p[AHEAD][IN];
+    Item load_item{}, store_item{};
+    auto begin_fill = [&]() {
+        nw_row = nw / ns * 32;
+        nw_step = nw % ns;
+        load_item = store_item = Item{wv % ns, wv / ns * 32};
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            fill_load(p[i], load_item);
+            next(load_item);
+        }
+    };
+    begin_fill();
     begin_task();
-    const int first_items = row_items * (s1 - s0);
-    fill_load(p[0], wv < first_items ? wv : 0);
-    load_weights(u / (s1 - s0), u % (s1 - s0));
     constexpr bool ROW_SCALES = FOLD && !INT_TAPS;
     auto row_scale = [&](int i) {
         int64_t pix = row_pixel0 + i;
@@ -285,75 +402,83 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         t_sw = a.sw[c];
         t_bias = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
     }
-    if constexpr (!WHOLE_TAPS) {
+    constexpr bool SUMS = !BYTES && !WHOLE_TAPS;
+    if constexpr (SUMS) {
         for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
+        lds_barrier();   // the code sums are zero before they are added to
     }
-    for (int i = tid; i < resident0 * PL * KS * 2; i += nt) {   // the row of zeros
-        const int at = i * rows + rows - 1;
-        *reinterpret_cast<v4i *>(lds + at * 16) = v4i{0, 0, 0, 0};
-        if constexpr (!BYTES) *reinterpret_cast<int2 *>(lds + a.part8 + at * 8) = int2{0, 0};
-    }
-    if constexpr (ROW_SCALES) {
-        if (tid < rows) s_rowscale[tid] = t_scale[0];
-        if (tid + nt < rows) s_rowscale[tid + nt] = t_scale[1];
-        for (int i = tid + 2 * nt; i < rows; i += nt) s_rowscale[i] = row_scale(i);
-    }
-    if constexpr (OUT != kOutI32) {
-        if (tid < blocks * 32) {
-            s_sw[tid] = t_sw;
-            s_bias[tid] = t_bias;
-        }
-        for (int i = tid + nt; i < blocks * 32; i += nt) {
-            const int c = c_wg + i < a.n ? c_wg + i : a.n - 1;
-            s_sw[i] = a.sw[c];
-            s_bias[i] = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
-        }
-    }
-    lds_barrier();   // the code sums are zero before they are added to
 
-    v16f sum[NT] = {};   // the accumulators themselves, or (FOLD) fp32 combinations of per-tap sums
-    for (;;) {           // chunks of resident slices
-        const int items = row_items * (s1 - s0);
-        for (int item = wv; item < items; item += 2 * nw) {
-            if (item + nw < items) fill_load(p[1], item + nw);
-            fill_store(p[0], item);
-            if (item + nw < items) {
-                if (item + 2 * nw < items) fill_load(p[0], item + 2 * nw);
-                fill_store(p[1], item + nw);
+    int touched = 0;     // (see below)
+    v16f sum[NT];        // the accumulators themselves, or (FOLD) fp32 combinations of per-tap sums
+    for (;;) {           // chunks of resident steps
+        while (store_item.row < row_span) {
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (store_item.row >= row_span) break;
+                fill_store(p[i], store_item);
+                next(store_item);
+                fill_load(p[i], load_item);
+                next(load_item);
+            }
+        }
+        if (s0 == 0) {
+            // The weights of the workgroup's channels start their way into the L2: from HBM they would take longer than the ring
+            // looks ahead.  A word of every line, which nobody waits for; workgroups that share the channels take an eighth each.
+            const uint32_t line = ((px_tile & 7) * nt + tid) * 128u, size = static_cast<uint32_t>(min(blocks * 32, a.n - c_wg)) * (TAPS * cb);
+            if (RING && line < size) touched = *reinterpret_cast<const int *>(a.wq + static_cast<uint32_t>(c_wg) * (TAPS * cb) + line);
+            if constexpr (ROW_SCALES) {
+                if (tid < rows) s_rowscale[tid] = t_scale[0];
+                if (tid + nt < rows) s_rowscale[tid + nt] = t_scale[1];
+                for (int i = tid + 2 * nt; i < rows; i += nt) s_rowscale[i] = row_scale(i);
+            }
+            if constexpr (OUT != kOutI32) {
+                if (tid < blocks * 32) {
+                    s_sw[tid] = t_sw;
+                    s_bias[tid] = t_bias;
+                }
+                for (int i = tid + nt; i < blocks * 32; i += nt) {
+                    const int c = c_wg + i < a.n ? c_wg + i : a.n - 1;
+                    s_sw[i] = a.sw[c];
+                    s_bias[i] = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
+                }
             }
         }
         lds_barrier();
-        // tables of the pixels: tap masks, scales under the taps, corrections
-        for (int i = tid; i < px_wg; i += nt) {
+        // tables of the pixels: tap masks, scales under the taps, corrections; a lane has one row of the window, four lanes a pixel
+        for (int j = tid; j < 4 * px_wg; j += nt) {
+            const int r = j & 3, i = j >> 2;   // (r == 3: nothing)
             const uint32_t pix = p0 + i;
-            const uint32_t q = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
-            const int ow = static_cast<int>(pix - q * a.w);
-            const int oh = static_cast<int>(q - hq::div_magic31(q, a.h, a.h_magic, a.h_shift) * a.h);
+            const uint32_t line = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
+            const int ow = static_cast<int>(pix - line * a.w);
+            const int oh = static_cast<int>(line - hq::div_magic31(line, a.h, a.h_magic, a.h_shift) * a.h);
             const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
             int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
             if (pix >= a.pixels) mask = 0;
-            s_mask[i] = mask;
+            if (r == 0) s_mask[i] = mask;
             float corr = 0.f;
 #pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
+            for (int s = 0; s < 3; ++s) {
+                if (r == 3) break;
+                const int t = 3 * r + s, row = halo + i + (r - 1) * a.w + (s - 1);
                 const bool in = (mask >> t) & 1;
-                if constexpr (FOLD && !INT_TAPS) {
-                    const float s = in ? s_rowscale[row] : 0.f;
-                    s_sx[t * px_wg + i] = s;
-                    if constexpr (!BYTES && !WHOLE_TAPS) corr = fmaf(s * (8.0f / UNIT), static_cast<float>(s_sum[row]), corr);
-                } else if (!BYTES && in) {
-                    corr += 8.0f * static_cast<float>(s_sum[row]);
+                if constexpr (ROW_SCALES) {
+                    const float scale = in ? s_rowscale[row] : 0.f;
+                    s_sx[t * px_wg + i] = scale;
+                    if constexpr (SUMS) corr = fmaf(scale * (8.0f / UNIT), static_cast<float>(s_sum[row]), corr);
+                } else if (SUMS && in) {
+                    corr += (8.0f / UNIT) * static_cast<float>(s_sum[row]);
                 }
             }
-            if constexpr (!WHOLE_TAPS) s_corr[i] = corr;   // (of all slices once the last chunk is resident)
+            corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0xB1, 0xF, 0xF, true));   // lanes 1,0,3,2
+            corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0x4E, 0xF, 0xF, true));   // lanes 2,3,0,1
+            if (r == 0) s_corr[i] = corr;
         }
-        if constexpr (WHOLE_TAPS) {   // code sums of a slice -> of all resident slices up to it
+        if constexpr (WHOLE_TAPS) {   // code sums of a step -> of all resident steps up to it
             for (int i = tid; i < px_wg + 2 * halo; i += nt) {
                 int of = s_part[i];
-                for (int sl = 1; sl < s1 - s0; ++sl) {
-                    of += s_part[sl * rows + i];
-                    s_part[sl * rows + i] = static_cast<short>(of);
+                for (int k = 1; k < ns; ++k) {
+                    of += s_part[k * rows + i];
+                    s_part[k * rows + i] = static_cast<short>(of);
                 }
             }
         }
@@ -365,142 +490,214 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                 for (int t = 0; t < NT; ++t) mask[t] = s_mask[px_l + t * 32 + l];
             }
-            const int lane_row = px_l + l + halo;
-            const int ns = s1 - s0;
-            int tap = u / ns, sl = u - tap * ns;
-            // LDS offsets of this lane's row of tile 0 in the two parts of a unit's first plane; the other tiles and
-            // steps lie at fixed distances
-            const int plane16 = rows * 32, plane8 = rows * 16;   // from step to step
-            struct Base { int b16, b8; };
-            auto base_of = [&](int tap, int sl) {
-                const int shift = (tap / 3 - 1) * a.w + tap % 3 - 1;
-                const int at = (sl * PL * KS * 2 + h) * rows + lane_row;
-                return Base{(at + shift) * 16, static_cast<int>(a.part8) + (at + shift) * 8};
-            };
-            auto load_tile = [&](Operand (&b)[KS], const Base &base, int tap, int t, int plane) {
-                int b16 = base.b16 + plane * KS * plane16, b8 = base.b8 + plane * KS * plane8, imm = t;
-                if constexpr (!FOLD) {   // taps outside the image read the row of zeros
-                    const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1;
-                    const int to = (mask[t] >> tap) & 1 ? t * 32 : rows - 1 - row;
-                    b16 += to * 16;
-                    b8 += to * 8;
-                    imm = 0;
+            // the sums start from minus the correction for the weights' offset
+            const bool corrects = SUMS && !INT_TAPS && (wv & ((1 << kl) - 1)) == 0;
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                float from = 0.f;
+                if (corrects) {
+                    const int i = px_l + t * 32 + l;
+                    from = -s_corr[i];
                 }
 #pragma unroll
-                for (int k = 0; k < KS; ++k) {
-                    const v4i lo = *reinterpret_cast<const v4i *>(lds + (b16 + k * plane16) + imm * 512);
-                    if constexpr (BYTES) {
-                        b[k] = lo;
-                    } else {
-                        const int2 hi = *reinterpret_cast<const int2 *>(lds + (b8 + k * plane8) + imm * 256);
+                for (int i = 0; i < 16; ++i) sum[t][i] = s0 == 0 ? from : sum[t][i] + from;
+            }
+            const int lane_row = px_l + l + halo;
+
+            if constexpr (NS > 0) {
+                // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded; the next
+                // tap's weights are requested as soon as this one's are expanded.
+                const Fp6Masks masks;
+                const int step16 = rows * 32, step8 = rows * 16;
+                int tap = q / NS;
+                const int tap_end = q_end / NS;
+                struct Base { int b16, b8; };
+                auto base_of = [&](int tap) {
+                    const int at = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + h * rows;
+                    return Base{static_cast<int>(lds_address(lds)) + at * 16, static_cast<int>(lds_address(lds) + a.part8) + at * 8};
+                };
+                auto load_tile = [&](v8i (&b)[NS], const Base &base, int t) {
+#pragma unroll
+                    for (int k = 0; k < NS; ++k) {
+                        const v4i lo = lds_v4i(base.b16 + k * step16, t * 512);
+                        const v2i hi = lds_v2i(base.b8 + k * step8, t * 256);
                         b[k] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
                     }
-                }
-            };
-            // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded (of
-            // WHOLE_TAPS only where the unit ends the slices of its tap); the next unit's weights are requested as soon as
-            // this unit's are expanded.
-            Base base = base_of(tap, sl);
-            Operand wop[WP][KS], b[2][KS];
-            load_tile(b[0], base, tap, 0, 0);
-            Acc tap_acc[WHOLE_TAPS ? NT : 1];
-            const v4h minus = h ? v4h{} : v4h{-0.125f16, -128.0f16, 0, 0};
-            auto codes_upto = [&](int tap, int sl, int t) {
-                return static_cast<int>(s_part[sl * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
-            };
-            if constexpr (WHOLE_TAPS) {   // the sums of a tap start with the offset of the slices that this wave will add
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    tap_acc[t] = minus_eighth_of(minus, codes_upto(tap, min(ns, sl + u_end - u) - 1, t) -
-                                                            (sl ? codes_upto(tap, sl - 1, t) : 0));
-            }
-            for (; u < u_end; ++u) {
-                int tap1 = tap, sl1 = sl;   // the next unit (the last one's operands are requested twice)
-                if (u + 1 < u_end) {
-                    if (++sl1 == ns) { sl1 = 0; ++tap1; }
-                }
-                const Base base1 = base_of(tap1, sl1);
-#pragma unroll
-                for (int k = 0; k < KS; ++k) {
-                    if constexpr (BYTES) {
-#pragma unroll
-                        for (int i = 0; i < WP; ++i) wop[i][k] = raw[i][k];
-                    } else {
-                        int d[6];
-                        fp6_offset16(raw[0][k].x, raw[0][k].y, d[0], d[1], d[2]);
-                        fp6_offset16(raw[0][k].z, raw[0][k].w, d[3], d[4], d[5]);
-                        wop[0][k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
-                    }
-                }
-                load_weights(tap1, s0 + sl1);
-                Acc unit_acc[WHOLE_TAPS ? 1 : 2];
-                auto acc_of = [&](int t) -> Acc & {
-                    if constexpr (WHOLE_TAPS) return tap_acc[t];
-                    else return unit_acc[t & 1];
                 };
-                const bool ends = !WHOLE_TAPS || u + 1 == u_end || tap1 != tap;
-                float scale[NT];
-                int codes[NT] = {};   // WHOLE_TAPS: of the next tap
-                if (FOLD && !INT_TAPS && ends) {
+                Base base = base_of(tap);
+                v8i wop[NS], b[2][NS];
+                load_tile(b[0], base, 0);
+                for (; tap < tap_end; ++tap) {
+                    const int tap1 = tap + 1 < tap_end ? tap + 1 : tap;   // (the last one's operands are requested twice)
+                    const Base base1 = base_of(tap1);
+#pragma unroll
+                    for (int k = 0; k < NS; ++k) {
+                        int d[6];
+                        fp6_offset16(masks, raw_tap[k].x, raw_tap[k].y, d[0], d[1], d[2]);
+                        fp6_offset16(masks, raw_tap[k].z, raw_tap[k].w, d[3], d[4], d[5]);
+                        wop[k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+                    }
+                    take_tap(tap1);
+                    float scale[NT];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
+                    v16f acc[2];
+                    auto fold = [&](int t) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], acc[t & 1][i], sum[t][i]);
+                    };
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
-                        scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
-                        if constexpr (WHOLE_TAPS) codes[t] = codes_upto(tap1, max(min(ns, u_end - u - 1), 1) - 1, t);
+                        if (t + 1 < NT) load_tile(b[(t + 1) & 1], base, t + 1);
+                        else load_tile(b[0], base1, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        acc[t & 1] = v16f{};
+#pragma unroll
+                        for (int k = 0; k < NS; ++k) acc[t & 1] = mfma_fp6(wop[k], b[t & 1][k], acc[t & 1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (t > 0) fold(t - 1);
                     }
+                    fold(NT - 1);
+                    base = base1;
                 }
-                auto fold = [&](int t) {
+            } else {
+                int tap = q / ns, k = q - tap * ns;
+                // LDS addresses of the operands of the next step: the 16- and the 8-byte parts of this lane's row of tile 0; the
+                // other tiles lie at fixed distances.
+                const int step16 = rows * (PL * 32), step8 = rows * (PL * 16), plane16 = rows * 32, plane8 = rows * 16;
+                int b16, b8, n16, n8;   // (n: of the next tap's first step)
+                auto set_rows = [&](int tap, int step, int &b16, int &b8) {
+                    const int at = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + h * rows;
+                    b16 = static_cast<int>(lds_address(lds)) + at * 16 + step * step16;
+                    b8 = static_cast<int>(lds_address(lds) + a.part8) + at * 8 + step * step8;
+                };
+                Operand b[NT][PL], wop;
+                auto load_tile = [&](int t) {
+#pragma unroll
+                    for (int plane = 0; plane < PL; ++plane) {
+                        const v4i lo = lds_v4i(b16 + plane * plane16, t * 512);
+                        if constexpr (BYTES) {
+                            b[t][plane] = lo;
+                        } else {
+                            const v2i hi = lds_v2i(b8 + plane * plane8, t * 256);
+                            b[t][plane] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+                        }
+                    }
+                };
+                const Fp6Masks masks;
+                auto expand_weights = [&](const v4i &r, int pair, Operand &o) {
+                    if constexpr (!BYTES) {
+                        int d0, d1, d2;
+                        if (pair == 0) fp6_offset16(masks, r.x, r.y, d0, d1, d2);
+                        else fp6_offset16(masks, r.z, r.w, d0, d1, d2);
+                        asm volatile("" : "+v"(d0), "+v"(d1), "+v"(d2));   // (here, between two matrix instructions)
+                        o[3 * pair] = d0;
+                        o[3 * pair + 1] = d1;
+                        o[3 * pair + 2] = d2;
+                    }
+                };
+
+                Acc acc[NT];              // FOLD: the sums of the tap at work
+                const v4h minus = h ? v4h{} : v4h{-0.125f16, -128.0f16, 0, 0};
+                auto codes_upto = [&](int step, int t) {   // WHOLE_TAPS
+                    return static_cast<int>(s_part[step * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
+                };
+                // A step.  Right after the matrix instructions of a tile the tile's operands of the next step are requested, into the
+                // registers that have just been read; the next step's weights are expanded in between, and their slot of the
+                // ring is filled again.
+                int inside[NT], inside16[NT];   // !FOLD: block exponents: 2^0 (2^4), or for taps outside the image one that leaves nothing
+                auto step = [&](auto STARTS, bool ends) {   // the tap's sums start here; its last step in this share
+                    constexpr bool starts = decltype(STARTS)::value;
+                    b16 = ends ? n16 : b16 + step16;
+                    b8 = ends ? n8 : b8 + step8;
+                    Operand w_next = wop;
+                    v4i now[WP];
+#pragma unroll
+                    for (int i = 0; i < WP; ++i) now[i] = raw[i];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        if constexpr (BYTES) {
+                            Acc c = starts ? Acc{} : acc[t];
+#pragma unroll
+                            for (int i = 0; i < PL; ++i) c = __builtin_amdgcn_mfma_i32_32x32x32_i8(now[i], b[t][i], c, 0, 0, 0);
+                            acc[t] = c;
+                        } else if constexpr (FOLD) {
+                            acc[t] = mfma_fp6(wop, b[t][0], starts && !WHOLE_TAPS ? Acc{} : acc[t]);
+                        } else {
+                            sum[t] = mfma_fp6_scaled(wop, b[t][0], sum[t], inside[t]);
+                            if constexpr (PL == 2) sum[t] = mfma_fp6_scaled(wop, b[t][PL - 1], sum[t], inside16[t]);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        load_tile(t);
+                        if (t == 0) expand_weights(now[0], 0, w_next);
+                        if (t == 1) expand_weights(now[0], 1, w_next);
+                        if (t == (BYTES ? 0 : 2)) {
+                            request();   // (into the slot of the weights that have just been used, or expanded)
+                            take();
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    wop = w_next;
+                };
+                set_rows(tap, k, b16, b8);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) load_tile(t);
+                take();
+                if constexpr (!BYTES) {
+                    wop = v8i{};
+                    expand_weights(raw[0], 0, wop);
+                    expand_weights(raw[0], 1, wop);
+                    request();
+                    take();
+                }
+                for (int to_go = q_end - q; to_go > 0;) {   // taps
+                    const int n = min(ns - k, to_go);
+                    set_rows(min(tap + 1, TAPS - 1), 0, n16, n8);   // (past the last one: not used)
+                    float scale[NT];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        if constexpr (ROW_SCALES) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
+                        if constexpr (WHOLE_TAPS)   // the sums of a tap start with the offset of the steps that this wave will add
+                            acc[t] = __builtin_bit_cast(Acc, minus_eighth_of(minus, codes_upto(k + n - 1, t) - (k ? codes_upto(k - 1, t) : 0)));
+                    }
+                    if constexpr (!FOLD) {
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            inside[t] = (mask[t] >> tap) & 1 ? 127 : 0;
+                            inside16[t] = (mask[t] >> tap) & 1 ? 131 : 0;
+                        }
+                    }
+                    step(std::true_type{}, n == 1);
+#pragma unroll 1
+                    for (int i = 1; i < n; ++i) step(std::false_type{}, i == n - 1);
                     if constexpr (INT_TAPS) {
-                        const uint32_t pix = p0 + px_l + t * 32 + l;
-                        if ((mask[t] >> tap) & 1) {
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            const uint32_t pix = p0 + px_l + t * 32 + l;
+                            if (!((mask[t] >> tap) & 1)) continue;
                             const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32;
-                            const int extra = !BYTES && sl == 0 ? 8 * s_sum[row] : 0;
+                            const int extra = !BYTES && k == 0 ? 8 * s_sum[row] : 0;
                             int *dst = static_cast<int *>(a.y) + (static_cast<uint64_t>(pix) * 9 + tap) * a.n;
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
                                 const int c = c0 + 16 * h + i;
-                                if (c < a.n)
-                                    atomicAdd(dst + c,
-                                              static_cast<int>(acc_of(t)[i] * static_cast<decltype(acc_of(t)[i] + 0)>(UNIT)) - extra);
+                                if (c < a.n) atomicAdd(dst + c, static_cast<int>(acc[t][i] * static_cast<decltype(acc[t][i] + 0)>(UNIT)) - extra);
                             }
                         }
                     } else if constexpr (FOLD) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], static_cast<float>(acc_of(t)[i]), sum[t][i]);
-                        if constexpr (WHOLE_TAPS) tap_acc[t] = minus_eighth_of(minus, codes[t]);
+                        for (int t = 0; t < NT; ++t)
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], static_cast<float>(acc[t][i]), sum[t][i]);
                     }
-                };
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-#pragma unroll
-                    for (int plane = 0; plane < PL; ++plane) {
-                        const int now = t * PL + plane, next = now + 1;
-                        if (next < NT * PL) load_tile(b[next & 1], base, tap, next / PL, next % PL);
-                        else load_tile(b[0], base1, tap1, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if constexpr (BYTES) {
-                            Acc c = plane ? acc_of(t) : Acc{};
-#pragma unroll
-                            for (int k = 0; k < KS; ++k)
-                                c = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop[plane][k], b[now & 1][k], c, 0, 0, 0);
-                            acc_of(t) = c;
-                        } else {
-                            v16f c = WHOLE_TAPS ? acc_of(t) : FOLD ? v16f{} : sum[t];
-#pragma unroll
-                            for (int k = 0; k < KS; ++k)
-                                c = plane ? mfma_fp6_times16(wop[0][k], b[now & 1][k], c) : mfma_fp6(wop[0][k], b[now & 1][k], c);
-                            if constexpr (FOLD) acc_of(t) = c;
-                            else sum[t] = c;
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (t > 0 && plane == 0 && ends) fold(t - 1);
-                    }
+                    to_go -= n;
+                    k = 0;
+                    ++tap;
                 }
-                if (ends) fold(NT - 1);
-                tap = tap1;
-                sl = sl1;
-                base = base1;
+                if constexpr (RING) wait_vmem<0>();   // (nothing arrives in the ring any more)
             }
-            if (s1 < a.slices) break;   // the sums go on with the next chunk (one phase: host)
+            asm volatile("" : : "v"(touched));
+            if (s0 + ns < steps) break;   // the sums go on with the next chunk (one phase: host)
 
             // ---- results of the phase --------------------------------------------------------------------------
             if constexpr (!INT_TAPS) {
@@ -566,15 +763,15 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 }
 
                 const float one_scale = !FOLD && OUT != kOutI32 ? a.sx[0] * a.out_scale : 1.0f;
-                // results of eight sums v of a pixel with correction corr, channels ct .. ct + 7 (in the workgroup)
-                auto scaled = [&](const float (&v)[8], float corr, const float *sw, const float *bias, Out (&res)[8]) {
+                // results of eight sums v of a pixel, channels ct .. ct + 7 (in the workgroup)
+                auto scaled = [&](const float (&v)[8], const float *sw, const float *bias, Out (&res)[8]) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         if constexpr (OUT == kOutI32) {
-                            res[i] = static_cast<int>(v[i] * 64.0f - corr);
+                            res[i] = static_cast<int>(v[i] * UNIT);   // (rounds towards zero)
                         } else {
                             // (scales of up to the largest float: they are not multiplied by the unit before their codes)
-                            const float r = FOLD ? (v[i] - corr) * UNIT : (v[i] * 64.0f - corr) * one_scale;
+                            const float r = FOLD ? v[i] * UNIT : __builtin_rintf(v[i] * UNIT) * one_scale;
                             const float y = fmaf(r, sw[i], bias[i]);
                             if constexpr (OUT == kOutF16) res[i] = __float2half_rn(y);
                             else res[i] = y;
@@ -602,16 +799,11 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     // store the 64 contiguous bytes of a pixel instead of every lane a piece of its own (after an
                     // exchange in the area of the last partner, which nobody else reads)
                     uint8_t *const stage = lds + a.exchange + (kl ? wv ^ 1 : wv) * 8192;
-                    float sw[16], bias[16], corr[NT];
+                    float sw[16], bias[16];
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         sw[i] = OUT != kOutI32 ? s_sw[ct + i] : 0.f;
                         bias[i] = OUT != kOutI32 ? s_bias[ct + i] : 0.f;
-                    }
-#pragma unroll
-                    for (int t = 0; t < NT; ++t) {
-                        const int px = px_l + ((tile0 + t) & (NT - 1)) * 32 + l;
-                        corr[t] = WHOLE_TAPS ? 0.f : s_corr[px];
                     }
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -623,7 +815,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                             float v[8];
 #pragma unroll
                             for (int i = 0; i < 8; ++i) v[i] = sum[t][8 * half + i];
-                            scaled(v, corr[t], sw + 8 * half, bias + 8 * half, res[half]);
+                            scaled(v, sw + 8 * half, bias + 8 * half, res[half]);
                         }
                         if constexpr (OUT == kOutF16) {
 #pragma unroll
@@ -661,7 +853,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         bias[i] = OUT != kOutI32 ? s_bias[ct + 8 * half0 + i] : 0.f;
                     }
                     Out res[8];
-                    scaled(v, WHOLE_TAPS ? 0.f : s_corr[px], sw, bias, res);
+                    scaled(v, sw, bias, res);
                     store8(res, px, c0 + 16 * h + 8 * half0);
                 }
             }
@@ -669,20 +861,17 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             left -= nw >> kl;
             if (left == 0) return;
             shrink();
+            if (RING && a.ring_shared) lds_barrier();   // nobody reads the exchange area any more
             begin_task();
-            load_weights(u / ns, s0 + u % ns);
-#pragma unroll
-            for (int t = 0; t < NT; ++t) sum[t] = v16f{};
         }
 
         // ---- next chunk -----------------------------------------------------------------------------------------
-        s0 = s1;
-        s1 = s0 + a.chunk < a.slices ? s0 + a.chunk : a.slices;
+        s0 += ns;
+        ns = min(a.chunk, steps - s0);
+        begin_fill();
         begin_task();
-        fill_load(p[0], wv < row_items * (s1 - s0) ? wv : 0);
-        load_weights(u / (s1 - s0), s0 + u % (s1 - s0));
-        lds_barrier();   // every wave is done with the resident slices
-        if constexpr (INT_TAPS) {   // per-tap sums are corrected with the code sums of their own slices
+        lds_barrier();   // every wave is done with the resident steps
+        if constexpr (SUMS) {
             for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
             lds_barrier();
         }
@@ -691,13 +880,15 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 
 }  // namespace
 
-// One form's kernels by output type and steps per slice (a file each, so that they compile in parallel).
+// One form's kernels by output type and the last two parameters (a file each, so that they compile in parallel).
 #define HQ_RESIDENT_FORM(NAME, KIND)                                                                            \
-    const void *NAME(int out, int ks) {                                                                         \
-        static const void *const kernels[3][3] = {                                                              \
+    const void *NAME(int out, bool ring, int ns) {                                                              \
+        static const void *const kernels[3][5] = {                                                              \
             HQ_RESIDENT_FORM_OUT(kOutF16, KIND), HQ_RESIDENT_FORM_OUT(kOutF32, KIND), HQ_RESIDENT_FORM_OUT(kOutI32, KIND)}; \
-        return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][ks - 1];                                    \
+        return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][ns ? 1 + ns : ring];                        \
     }
 #define HQ_RESIDENT_FORM_OUT(OUT, KIND)                                                                         \
-    {reinterpret_cast<const void *>(resident_kernel<OUT, KIND, 1>), reinterpret_cast<const void *>(resident_kernel<OUT, KIND, 2>), \
-     reinterpret_cast<const void *>(resident_kernel<OUT, KIND, 3>)}
+    {HQ_RESIDENT_FN(OUT, KIND, false, 0), HQ_RESIDENT_FN(OUT, KIND, true, 0), HQ_RESIDENT_FN(OUT, KIND, false, 1), \
+     HQ_RESIDENT_FN(OUT, KIND, false, 2), HQ_RESIDENT_FN(OUT, KIND, false, 3)}
+#define HQ_RESIDENT_FN(OUT, KIND, RING, NS)                                                                     \
+    reinterpret_cast<const void *>(resident_kernel<OUT, KIND, RING, resident_unrolled(KIND, OUT, NS)>)

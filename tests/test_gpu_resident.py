@@ -256,3 +256,29 @@ def test_width_quant(hq, dtype, w, c, block):
     back = np.einsum("nhbic,ij->nhbjc", u, hb).reshape(x.shape)
     assert (back % block == 0).all()
     check_codes("codes", (back // block).astype(np.int8), q_o, t, 4)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (1, 1, 1, 64, 33),          # every tap but one outside
+    (2, 3, 8, 192, 40),         # shares of a few steps, fewer than the ring holds
+    (1, 46, 46, 960, 72),       # some slices resident at a time, with a ring
+    (1, 6, 200, 960, 40),       # and without room for one
+])
+def test_conv3x3_one_scale_empty_sums(hq, nb, h, w, cin, cout):
+    """Pixels whose window holds only zeros give exactly the bias, also where codes lie just outside the image (the rows above
+    and below, the other end of the neighbouring lines): whatever a tap outside leaves in a sum has to be gone."""
+    rng = np.random.default_rng(h + w + cin)
+    wq = rng.integers(-8, 8, (cout, 9, cin)).astype(np.int8)
+    sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)
+    s1 = torch.tensor([0.37], dtype=torch.float32, device="cuda")
+    xq = np.zeros((nb, h, w, cin), np.int8)
+    for bias in (np.zeros(cout, np.float32), rng.standard_normal(cout).astype(np.float32)):
+        y = host(hq.hq_int_conv2d_static(dev(pack_codes(xq)), s1, dev(pack_codes(wq)), dev(sw), dev(bias), ksize=3, y_dtype=torch.float32))
+        assert np.array_equal(y, np.broadcast_to(bias, y.shape))
+    if w < 4:
+        return
+    xq[:, :, w // 2 + 2:] = rng.integers(-8, 8, xq[:, :, w // 2 + 2:].shape)   # (the left edge's neighbours in memory)
+    acc_o, y_o = oracle.int_conv2d_static(xq, 0.37, wq.reshape(cout, 3, 3, cin), sw, None, stride=1, pad=1)
+    y = host(hq.hq_int_conv2d_static(dev(pack_codes(xq)), s1, dev(pack_codes(wq)), dev(sw), None, ksize=3, y_dtype=torch.float32))
+    assert (y[:, :, : w // 2] == 0).all()
+    check_y("y", y, y_o, rtol=1e-5)   # (fp32: sums are exact, three roundings)
