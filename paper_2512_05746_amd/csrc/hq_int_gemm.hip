@@ -117,6 +117,10 @@ hq_status int_linear(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
     GemmArgs a{xq, x_scale, wq, w_scale, bias, y, static_cast<uint32_t>(m), n, k, 1, 1, 0, 0, 0, 1, sx_static,
                1.0f, bits};
     if (k % 64 != 0) return hq_gemm_launch_anyk(a, 1, y_dtype, static_cast<hipStream_t>(stream));
+    if (bits == 4) {
+        st = hq_linear_fp6_launch(a, 1, y_dtype, static_cast<hipStream_t>(stream));
+        if (st != HQ_ERR_UNSUPPORTED) return st;
+    }
     return launch_gemm(a, 1, y_dtype, static_cast<hipStream_t>(stream));
 }
 
@@ -134,6 +138,8 @@ hq_status int_linear_single(const uint8_t *xq, const float *x_scale, const uint8
     // |W_int H_raw| <= 8 x block: up to block 8 that is two signed base-16 digits ([-136, 119]) and the third
     // plane is zero, so its pass is skipped (the integer output keeps all three sums)
     const int planes = had_block <= 8 && y_dtype != HQ_I32 ? 2 : 3;
+    st = hq_linear_fp6_launch(a, planes, y_dtype, static_cast<hipStream_t>(stream));
+    if (st != HQ_ERR_UNSUPPORTED) return st;
     return launch_gemm(a, planes, y_dtype, static_cast<hipStream_t>(stream));
 }
 
@@ -168,6 +174,10 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
     if (r == 3) {
         if (takes_wave_split(pixels, c_in, c_out, bits)) return hq_conv3x3_wave_launch(a, y_dtype, st_);
         st = hq_resident_launch(a, 0, y_dtype, st_);
+        if (st != HQ_ERR_UNSUPPORTED) return st;
+    }
+    if (r == 1 && bits == 4) {
+        st = hq_linear_fp6_launch(a, 1, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
     return launch_gemm(a, r * s, y_dtype, st_);

@@ -948,6 +948,9 @@ hq_status hq_fill_zero_launch(void *dst, uint64_t ints, hipStream_t stream);
 // (hq_resident.hip); had_block != 0: the activations are digit planes of a transform of that block, at most 32;
 // HQ_ERR_UNSUPPORTED, with nothing launched, if a tile does not fit the LDS
 hq_status hq_resident_launch(const GemmArgs &a, int had_block, hq_dtype y_dtype, hipStream_t stream);
+// linear layers of 4-bit codes, k a multiple of 64, planes of the weights multiplied: 1, or 2 or 3 of three (hq_linear_fp6.hip);
+// HQ_ERR_UNSUPPORTED, with nothing launched, where the tile kernel takes the layer
+hq_status hq_linear_fp6_launch(const GemmArgs &a, int planes, hq_dtype y_dtype, hipStream_t stream);
 // estimated time of a stride-1 3x3 layer on the tile kernel of this file (hq_int_gemm.hip)
 double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had_block);
 // how that kernel cuts a layer of codes (not planes), a static string, or null where it does not take the layer

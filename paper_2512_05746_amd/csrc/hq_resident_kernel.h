@@ -55,6 +55,7 @@
 #pragma once
 #include <type_traits>
 
+#include "hq_buffer.h"
 #include "hq_fp6.h"
 #include "hq_int_gemm_kernel.h"
 
@@ -91,29 +92,6 @@ constexpr int kResSum = 1;      // 3x3, one scale: one sum over all taps
 constexpr int kResPlanes = 2;   // as kResSum, with activations u = d0 + 16 (d1 + 16 d2) in three digit planes, |d1 + 16 d2| <= 16
 constexpr int kResBytes = 3;    // as kResPerTap, with 8-bit codes on the int8 instruction
 
-// Barrier that orders LDS only: __syncthreads() would also wait for the wave's global loads (weights requested
-// ahead) and stores.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// Buffer accesses: uniform base and bound in scalar registers, a 32-bit offset per lane; loads beyond the bound
-// return zeros, stores beyond it are dropped.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, static_cast<int>(bytes), 0x00027000);
-}
-__device__ __forceinline__ v4i buffer_load16(__amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off) {
-    return __builtin_bit_cast(
-        v4i, __builtin_amdgcn_raw_buffer_load_b128(r, static_cast<int>(lane_off), static_cast<int>(uniform_off), 0));
-}
-__device__ __forceinline__ void buffer_store16(const v4i &v, __amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t uniform_off) {
-    typedef unsigned v4u __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, static_cast<int>(lane_off),
-                                           static_cast<int>(uniform_off), 0);
-}
-
 // Direct-to-LDS load of 16 bytes a lane: lane i's land at lds_base + 16 i.  Inline assembly, because the compiler cannot tell which
 // slot of a ring such a load fills and would wait for all of them before every LDS read; the waits (wait_vmem) are placed by
 // hand.  (Its own counted waits stay right: they only wait for more.)
@@ -134,15 +112,6 @@ __host__ __device__ constexpr int resident_unrolled(int kind, int out, int ns) {
 // bytes of a step's weights for 32 channels, a slot of a ring
 __host__ __device__ constexpr int resident_slot_bytes(int kind) { return kind == kResBytes ? 2048 : 1024; }
 constexpr int resident_ring_slots(int) { return 3; }
-
-// LDS reads at an address that is already one of LDS (no base to add)
-typedef int v2i __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ v4i lds_v4i(int address, int offset = 0) {
-    return *reinterpret_cast<const __attribute__((address_space(3))) v4i *>(static_cast<uint32_t>(address) + offset);
-}
-__device__ __forceinline__ v2i lds_v2i(int address, int offset = 0) {
-    return *reinterpret_cast<const __attribute__((address_space(3))) v2i *>(static_cast<uint32_t>(address) + offset);
-}
 
 __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
     return (kind == kResPerTap || kind == kResBytes ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;

@@ -1,0 +1,57 @@
+"""GPU tests: linear layers of 4-bit codes against whole-number sums in fp64."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+# Every tile height (32, 64 and 128 tokens), padded and whole units of steps, 4 and 8 waves, blocks of channels that are not whole,
+# the longest K that fits and one that does not, a large layer of K a multiple of 192; -8 among the codes.  The sums are whole
+# numbers below 2^24: the integer result is equal, fp32 results are a few roundings (the scales, 4; with the planes' weights and
+# sums, 8) from the exact value, fp16 results half an ulp more.
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n", [(1, 64, 1), (33, 64, 40), (31, 128, 8), (130, 320, 333), (1000, 640, 96), (2100, 448, 1000),
+                                   (9000, 704, 640), (70000, 64, 72), (4300, 768, 1160), (40, 6400, 33), (40, 6784, 33),
+                                   (700, 2560, 264), (20, 8192, 40)])
+def test_linear_sums_are_exact(m, k, n):
+    import paper_2512_05746_amd as hq
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + k + n)
+    xq = torch.randint(0, 256, (m, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    wq = torch.randint(0, 256, (n, 3, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    xq[m // 2] = 0x88
+    wq[n // 2] = 0x88
+    wq[0] = 0x77
+    sx = torch.rand((m,), generator=g, device="cuda") + 0.1
+    sw = torch.rand((n,), generator=g, device="cuda") * 1e-4 + 1e-5   # (three planes of 6784 channels stay finite in fp16)
+    bias = torch.randn((n,), generator=g, device="cuda")
+
+    def codes(q):
+        v = torch.stack([q & 15, q >> 4], -1).flatten(-2).double()
+        return torch.where(v > 7, v - 16, v)
+
+    sums = [codes(xq) @ codes(wq[:, p]).T.contiguous() for p in range(3)]
+    w0 = wq[:, 0].contiguous()
+    assert torch.equal(hq.hq_int_linear(xq, sx, w0, sw, None, y_dtype=torch.int32).double(), sums[0])
+    scale = sx.double()[:, None] * sw.double()
+    eps = 2.0 ** -24
+
+    def check(y, exact, size, roundings):
+        limit = roundings * eps * (size + bias.double().abs())
+        if y.dtype == torch.float16:
+            limit = limit + exact.abs() * 2.0 ** -11 + 2.0 ** -25
+        assert ((y.double() - exact).abs() <= limit).all()
+
+    for dtype in (torch.float32, torch.float16):
+        b = bias.to(dtype)
+        exact = sums[0] * scale
+        check(hq.hq_int_linear(xq, sx, w0, sw, b, y_dtype=dtype), exact + b.double(), exact.abs(), 4)
+        exact = sums[0] * sw.double() * sx[0].double()
+        check(hq.hq_int_linear_static(xq, sx[:1], w0, sw, b, y_dtype=dtype), exact + b.double(), exact.abs(), 4)
+        for block, planes in ((8, 2), (64, 3)):
+            norm = 1.0 / block ** 0.5
+            parts = [sums[p] * scale * norm * 16.0 ** p for p in range(planes)]
+            check(hq.hq_int_linear_single(xq, sx, wq, sw, b, block, y_dtype=dtype), sum(parts) + b.double(),
+                  sum(q.abs() for q in parts), 8)
+    y = hq.hq_int_conv2d(xq.view(1, 1, m, k // 2), sx.view(1, 1, m), w0.view(n, 1, k // 2), sw, None, ksize=1, y_dtype=torch.int32)
+    assert torch.equal(y.view(m, n).double(), sums[0])
