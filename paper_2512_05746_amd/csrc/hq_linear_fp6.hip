@@ -394,10 +394,10 @@ Cut choose_cut(int64_t pixels, int n, int k, int planes) {
 
 // HQ_ERR_UNSUPPORTED, with nothing launched: the layer is one for the tile kernel.
 hq_status hq_linear_fp6_launch(const GemmArgs &g, int planes, hq_dtype y_dtype, hipStream_t stream) {
-    const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     if (planes > 1 && y_dtype == HQ_I32) return HQ_ERR_UNSUPPORTED;
     const Cut c = choose_cut(g.pixels, g.n, g.k, planes);
     if (!c.ok) return HQ_ERR_UNSUPPORTED;
+    const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     LinearArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
     a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.sx_static = g.sx_static; a.planes = planes; a.out_scale = g.out_scale;
