@@ -197,8 +197,10 @@ def main():
 
     def instruction(layer, x, static_scale=False):
         """The matrix instruction of a 4-bit layer's integer stage, and its peak."""
-        e2m3 = layer.ksize == 3 and hq.hq_int_conv2d_kernel_name(
-            *x.shape, layer.n_out, static_scale=static_scale).startswith("activation-resident")
+        if layer.ksize == 3:
+            e2m3 = hq.hq_int_conv2d_kernel_name(*x.shape, layer.n_out, static_scale=static_scale).startswith("activation-resident")
+        else:   # (the rule of hq_linear_fp6.hip over these layers)
+            e2m3 = layer.k_in % 192 != 0 or layer.ops >= 2 * 3e9
         return ("e2m3", E2M3_MFMA_PEAK_TOPS) if e2m3 else ("int8", INT8_MFMA_PEAK_TOPS)
 
     def mixed_peak(layers_x, static_scale=False):
@@ -468,7 +470,7 @@ def main():
         "metric": "w4a4_gemm_conv_tops", "value": round(value, 2), "unit": "TOP/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak",
-        "vs_baseline": None, "dtype": "int4 codes, exact integer sums (3x3: E2M3 products; linear, 1x1: int8)", "data": "synthetic",
+        "vs_baseline": None, "dtype": "int4 codes, exact integer sums (3x3 and large linear: E2M3 products; other linear, 1x1: int8)", "data": "synthetic",
         "config": {
             "workload": "configuration 5: LDM-4-shaped UNet layer sweep, batch 16, W4A4, fp16 I/O, "
                         "block-64 Hadamard; 9 layers, act-quant + integer conv/linear each",
