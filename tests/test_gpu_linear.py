@@ -55,3 +55,36 @@ def test_linear_sums_are_exact(m, k, n):
                   sum(q.abs() for q in parts), 8)
     y = hq.hq_int_conv2d(xq.view(1, 1, m, k // 2), sx.view(1, 1, m), w0.view(n, 1, k // 2), sw, None, ksize=1, y_dtype=torch.int32)
     assert torch.equal(y.view(m, n).double(), sums[0])
+
+
+# Weights of more than 2 GiB whose steps are padded: what a padding step multiplies, and adds to the code sums, is zero wherever the
+# channel lies (before, between and behind the places that 2^31 bytes from the start or from the end would reach).
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n,planes", [(40, 2368, 2000000, 1), (64, 2240, 1917500, 1), (64, 960, 1491400, 3)])
+def test_linear_weights_beyond_2gib(m, k, n, planes):
+    import paper_2512_05746_amd as hq
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    wq = torch.randint(0, 256, (n, planes, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    assert wq.numel() > 1 << 31
+    xq = torch.randint(0, 256, (m, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    edge = (1 << 31) // (planes * k // 2)
+    at = torch.cat([torch.arange(200), edge + torch.arange(-100, 100), n - edge + torch.arange(-100, 100),
+                    torch.randint(0, n, (500,)), torch.arange(n - 200, n)]).clamp(0, n - 1).cuda()
+
+    def codes(q):
+        v = torch.stack([q & 15, q >> 4], -1).flatten(-2).double()
+        return torch.where(v > 7, v - 16, v)
+
+    sums = [codes(xq) @ codes(wq[at, p]).T.contiguous() for p in range(planes)]
+    if planes == 1:
+        y = hq.hq_int_linear(xq, None, wq[:, 0], None, None, y_dtype=torch.int32)
+        assert torch.equal(y[:, at].double(), sums[0])
+        return
+    sx = torch.rand((m,), generator=g, device="cuda") + 0.1
+    sw = torch.rand((n,), generator=g, device="cuda") + 0.1
+    y = hq.hq_int_linear_single(xq, sx, wq, sw, None, 64, y_dtype=torch.float32)
+    scale = sx.double()[:, None] * sw[at].double() / 8.0
+    parts = [s * scale * 16.0 ** p for p, s in enumerate(sums)]
+    assert ((y[:, at].double() - sum(parts)).abs() <= 8 * 2.0 ** -24 * sum(q.abs() for q in parts)).all()
