@@ -168,7 +168,7 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
 #pragma unroll
         for (int t = 0; t < NT; ++t) total[t] = v16f{};
     }
-    float weight = 1.0f;   // of the plane
+    float weight = 64.0f;   // of the plane, in units of the accumulators
     int d[6], w_sum = 0;
     auto expand = [&](const v4i &w, int half) {
         if (half == 0) fp6_offset16(masks, w.x, w.y, d[0], d[1], d[2]);
@@ -222,12 +222,11 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
             acc[t] = __builtin_amdgcn_mfma_f32_32x32x8f16(w_part, x_part, acc[t], 0, 0, 0);
         }
         if constexpr (PLANES) {
+            // (the token's scale comes last: times 256 it would overflow for scales from 1.3e36 on)
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const float s = s_sx[t * 32 + l] * weight;
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) total[t][i] = fmaf(s, acc[t][i] * 64.0f, total[t][i]);
-            }
+                for (int i = 0; i < 16; ++i) total[t][i] = fmaf(weight, acc[t][i], total[t][i]);
             weight *= 16.0f;
         }
     }
@@ -261,13 +260,12 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
         Out res[2][8];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const float v = acc[t][i] * 64.0f;
+            float v;
+            if constexpr (PLANES) v = total[t][i];
+            else v = acc[t][i] * 64.0f;
             if constexpr (OUT == kOutI32) res[i >> 3][i & 7] = static_cast<int>(v);
             else {
-                float r;
-                if constexpr (PLANES) r = total[t][i];
-                else r = sx * v;
-                const float y = fmaf(r, sw[i], bias[i]);
+                const float y = fmaf(sx * v, sw[i], bias[i]);
                 if constexpr (OUT == kOutF16) res[i >> 3][i & 7] = __float2half_rn(y);
                 else res[i >> 3][i & 7] = y;
             }

@@ -88,3 +88,29 @@ def test_linear_weights_beyond_2gib(m, k, n, planes):
     scale = sx.double()[:, None] * sw[at].double() / 8.0
     parts = [s * scale * 16.0 ** p for p, s in enumerate(sums)]
     assert ((y[:, at].double() - sum(parts)).abs() <= 8 * 2.0 ** -24 * sum(q.abs() for q in parts)).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n,block", [(40, 128, 40, 8), (130, 640, 96, 64), (4096, 576, 1728, 64)])
+def test_linear_single_of_large_token_scales(m, k, n, block):
+    """Scales of up to the largest float, upper planes that are zero or not: a result is finite where the exact one is (the scale times
+    the sum of a token stays below 3.4e38; two roundings of the planes' sum, three of the scales)."""
+    import paper_2512_05746_amd as hq
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + k + n)
+    xq = torch.zeros((m, k // 2), dtype=torch.uint8, device="cuda")
+    xq[:, k // 4] = 1                                    # one code of 1 a token, so the sums are one weight's digits
+    wq = torch.randint(0, 256, (n, 3, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    wq[: n // 2, 1:] = 0
+    d = wq[:, :, k // 4].double() % 16
+    total = (torch.where(d > 7, d - 16, d) * torch.tensor([1.0, 16.0, 256.0 if block > 8 else 0.0], device="cuda").double()).sum(1)
+    total = total.expand(m, n)
+    sw = (torch.rand((n,), generator=g, device="cuda") + 0.5) * 1e-34
+    for scale in (1.2e36, 1.4e36, 4e37):
+        sx = torch.full((m,), scale, device="cuda")
+        y = hq.hq_int_linear_single(xq, sx, wq, sw, None, block, y_dtype=torch.float32).double()
+        exact = total * sx.double()[:, None] * sw.double() / block ** 0.5
+        fits = (total * scale).abs() < 3.4e38
+        assert fits[:, : n // 2].all()
+        assert ((y - exact).abs() <= 8 * 2.0 ** -24 * exact.abs())[fits].all()
