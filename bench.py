@@ -197,10 +197,9 @@ def main():
 
     def instruction(layer, x, static_scale=False):
         """The matrix instruction of a 4-bit layer's integer stage, and its peak."""
-        if layer.ksize == 3:
-            e2m3 = hq.hq_int_conv2d_kernel_name(*x.shape, layer.n_out, static_scale=static_scale).startswith("activation-resident")
-        else:   # (the rule of hq_linear_fp6.hip over these layers)
-            e2m3 = layer.k_in % 192 != 0 or layer.ops >= 2 * 3e9
+        nb, h, w = x.shape[:3] if layer.kind == "conv" else (1, 1, layer.m)   # (a linear layer is a 1x1 one of as many pixels)
+        name = hq.hq_int_conv2d_kernel_name(nb, h, w, layer.k_in, layer.n_out, ksize=layer.ksize, static_scale=static_scale)
+        e2m3 = name.startswith(("activation-resident", "linear"))
         return ("e2m3", E2M3_MFMA_PEAK_TOPS) if e2m3 else ("int8", INT8_MFMA_PEAK_TOPS)
 
     def mixed_peak(layers_x, static_scale=False):

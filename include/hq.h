@@ -193,7 +193,10 @@ hq_status hq_act_quant_int_linear(const void *x, hq_dtype x_dtype, const uint8_t
  *                       workgroup; with ", slices in turn" before the bracket if only some channel slices are resident
  *                       at a time
  *   "wave-split"        3x3, 192 channels, few tiles: K ranges shared by waves
- *   "tile"              1x1, and 3x3 with image rows too long for the activation tile
+ *   "linear (T tokens, W waves, units of U)"   1x1 at 4 bits (and hq_int_linear of as many tokens as pixels): T = 32, 64 or 128
+ *                       tokens a workgroup, weights U steps of 64 channels ahead
+ *   "tile"              the other 1x1 layers, and 3x3 layers whose image rows are too long for the activation tile or that
+ *                       are estimated to be faster here
  *   "tile (stride 2)"
  *   "small-channel-count"   c_in not a multiple of 64
  *   "unsupported"

@@ -951,6 +951,8 @@ hq_status hq_resident_launch(const GemmArgs &a, int had_block, hq_dtype y_dtype,
 // linear layers of 4-bit codes, k a multiple of 64, planes of the weights multiplied: 1, or 2 or 3 of three (hq_linear_fp6.hip);
 // HQ_ERR_UNSUPPORTED, with nothing launched, where the tile kernel takes the layer
 hq_status hq_linear_fp6_launch(const GemmArgs &a, int planes, hq_dtype y_dtype, hipStream_t stream);
+// The cut of a layer that it takes (one plane), as a name for the diagnostic; nullptr for the others.
+const char *hq_linear_cut_name(int64_t pixels, int n, int k);
 // estimated time of a stride-1 3x3 layer on the tile kernel of this file (hq_int_gemm.hip)
 double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had_block);
 // how that kernel cuts a layer of codes (not planes), a static string, or null where it does not take the layer

@@ -391,6 +391,20 @@ Cut choose_cut(int64_t pixels, int n, int k, int planes) {
 
 }  // namespace
 
+// For the diagnostic: nullptr if the layer is one for the tile kernel.
+const char *hq_linear_cut_name(int64_t pixels, int n, int k) {
+    const Cut c = choose_cut(pixels, n, k, 1);
+    if (!c.ok) return nullptr;
+#define HQ_LINEAR_NAMES(TOKENS, KS) \
+    {"linear (" TOKENS " tokens, 4 waves, units of " KS ")", "linear (" TOKENS " tokens, 8 waves, units of " KS ")"}
+    static const char *const names[3][4][2] = {   // [tokens][kUnits][waves]
+        {HQ_LINEAR_NAMES("32", "8"), HQ_LINEAR_NAMES("32", "5"), HQ_LINEAR_NAMES("32", "4"), HQ_LINEAR_NAMES("32", "3")},
+        {HQ_LINEAR_NAMES("64", "4"), HQ_LINEAR_NAMES("64", "3"), HQ_LINEAR_NAMES("64", "2"), HQ_LINEAR_NAMES("64", "2")},
+        {HQ_LINEAR_NAMES("128", "4"), HQ_LINEAR_NAMES("128", "3"), HQ_LINEAR_NAMES("128", "2"), HQ_LINEAR_NAMES("128", "2")}};
+#undef HQ_LINEAR_NAMES
+    return names[c.nt_log2][c.unit][c.nw == 8];
+}
+
 // HQ_ERR_UNSUPPORTED, with nothing launched: the layer is one for the tile kernel.
 hq_status hq_linear_fp6_launch(const GemmArgs &g, int planes, hq_dtype y_dtype, hipStream_t stream) {
     if (planes > 1 && y_dtype == HQ_I32) return HQ_ERR_UNSUPPORTED;

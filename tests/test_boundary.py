@@ -46,7 +46,11 @@ def test_conv_kernel_choice_is_a_function_of_the_geometry(lib):
         assert name(1, 128, 256, 576, 576, static_scale=static_scale) == "tile"   # it fits, and costs more than it saves
         assert name(1, 256, 128, 384, 384, static_scale=static_scale).startswith("activation-resident")
     assert name(16, 8, 8, 960, 960) == "activation-resident (128 pixels, 8 waves)"
-    assert name(2, 9, 9, 64, 8, ksize=1) == "tile"
+    for static_scale in (False, True):   # 1x1 layers: both sides of the rule that takes them to the linear kernel
+        assert name(2, 9, 9, 64, 8, ksize=1, static_scale=static_scale) == "linear (64 tokens, 4 waves, units of 2)"
+        assert name(8, 32, 32, 384, 1152, ksize=1, static_scale=static_scale) == "linear (128 tokens, 4 waves, units of 3)"
+        assert name(16, 32, 32, 384, 384, ksize=1, static_scale=static_scale) == "tile"   # K a multiple of 192, fewer products
+        assert name(1, 100, 100, 1536, 384, ksize=1, static_scale=static_scale) == "tile"   # K too long for 128 tokens and 8 waves
     assert name(2, 9, 9, 64, 8, stride=2) == "tile (stride 2)"
     assert name(2, 9, 9, 64, 8, ksize=5) == "unsupported"
     assert name(16, 64, 64, 192, 192, bits=8) == "activation-resident (256 pixels, 8 waves)"
