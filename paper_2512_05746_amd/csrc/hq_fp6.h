@@ -31,9 +31,9 @@ constexpr uint32_t fp6_bits(uint32_t field, int a, int b, int c = -1) {
 __device__ __forceinline__ v16f mfma_fp6(const v8i &a, const v8i &b, const v16f &c) {
     return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 0, 0, 0);
 }
-// the same with the products of a lane's column times 2^(exponent - 127)
-__device__ __forceinline__ v16f mfma_fp6_scaled(const v8i &a, const v8i &b, const v16f &c, int exponent) {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, 127, 0, exponent);
+// the same with the products of a lane's row of a times 2^(a_exponent - 127), of its column of b times 2^(b_exponent - 127)
+__device__ __forceinline__ v16f mfma_fp6_scaled(const v8i &a, const v8i &b, const v16f &c, int a_exponent, int b_exponent) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 2, 2, 0, a_exponent, 0, b_exponent);
 }
 
 // Two packed dwords -> three dwords of fields holding code + 8 (0..15, sign bit 0): the offset turns two's

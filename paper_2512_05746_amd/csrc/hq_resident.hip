@@ -192,12 +192,13 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
         const hq_status st = hq_fill_zero_launch(g.y, static_cast<uint64_t>(g.pixels) * 9 * g.n, stream);
         if (st != HQ_OK) return st;
     }
-    const int ns = p.chunk == p.slices ? resident_unrolled(kind, out, g.k / 64) : 0;
+    const int resident = std::min(p.chunk * p.ks, g.k / 64);   // steps
+    const int ns = g.k / 64 % resident ? 0 : resident_unrolled(kind, out, resident);
     const void *fn = kind == kResBytes    ? hq_resident_bytes(out, p.has_ring, ns)
                      : kind == kResPlanes ? hq_resident_planes(out, p.has_ring, ns)
                      : kind == kResSum  ? hq_resident_sum(out, p.has_ring, ns)
                                         : hq_resident_pertap(out, p.has_ring, ns);
-    static std::atomic<uint64_t> allowed[4][3][5];
+    static std::atomic<uint64_t> allowed[4][3][6];
     const hq_status st = allow_lds(fn, allowed[kind][out][ns ? 1 + ns : p.has_ring]);
     if (st != HQ_OK) return st;
     void *args[] = {&a};

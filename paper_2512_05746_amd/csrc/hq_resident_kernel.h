@@ -105,9 +105,12 @@ __device__ __forceinline__ void load_to_ring(const v4i &r, uint32_t lane_off, ui
                  : "s"(lds_base), "v"(lane_off), "s"(r), "s"(uniform_off)
                  : "memory");
 }
-// steps of a tap that a form is built for (0: any number)
+// Steps of a tap that a form is built for (0: any number).  Not for the integer sums of taps, which their stores bound.  Four steps only
+// for sums of codes (us a call, steps in a loop -> unrolled: per-pixel scales 12 x 33 x 33 x 256 16.3 -> 14.5, one scale
+// 2 x 30 x 25 x 256 -> 504 10.2 -> 9.4; the width axis, whose operand planes take twice the registers, 2 x 12 x 40 x 256 11.6 -> 12.2).
 __host__ __device__ constexpr int resident_unrolled(int kind, int out, int ns) {
-    return kind == kResPerTap && out == kOutF16 && ns <= 3 ? ns : 0;
+    const bool int_taps = out == kOutI32 && (kind == kResPerTap || kind == kResBytes);
+    return ns <= (kind == kResPerTap || kind == kResSum ? 4 : 3) && !int_taps ? ns : 0;
 }
 // bytes of a step's weights for 32 channels, a slot of a ring
 __host__ __device__ constexpr int resident_slot_bytes(int kind) { return kind == kResBytes ? 2048 : 1024; }
@@ -128,10 +131,13 @@ __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
 }
 
 // RING: weights pass through a ring in LDS (else, where no room is left for it, straight from memory).
-// NS: 0, or the 1 .. 3 steps of a tap (fp16 results with per-pixel scales, up to 192 channels): a tap is unrolled, with its weights
-// straight from memory and one tap ahead in registers, tile by tile, the folds between the tiles.  A tap so short has a fold for
-// every 4 to 12 matrix instructions, and this order hides them best: us a pass with the quantiser, steps in a loop with a ring -> this:
-// 1 x 62 x 62 x 128 12.3 -> 11.8, 16 x 64 x 64 x 192 (the kernel alone) 24.7 -> 23.4; with more steps the ring wins (below).
+// NS: 0, or the steps of a tap that are resident at a time, 1 .. 4: a tap is unrolled, with its weights straight from memory and one tap
+// ahead in registers, tile by tile, the folds between the tiles.  A tap so short has a fold, new addresses and masks for every 4 to 16
+// matrix instructions, and this order hides them best; with more steps the ring wins (below).  us a call, steps in a loop with a ring
+// -> this:
+//     per-pixel scales  16 x 24 x 53 x 192 13.5 -> 12.7, 3 x 64 x 64 x 384 -> 96 (a slice at a time) 18.5 -> 16.5
+//     one scale         5 x 54 x 54 x 64 10.1 -> 7.9, 24 x 33 x 22 x 192 15.5 -> 12.4, 9 x 32 x 46 x 576 -> 264 (a slice at a time) 35.9 -> 28.0
+//     width axis        4 x 49 x 48 x 192, block 16 14.7 -> 12.4;   8 bits  12 x 23 x 17 x 384 -> 392 (a slice at a time) 20.2 -> 18.2
 template <int OUT, int KIND, bool RING, int NS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
@@ -140,7 +146,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     // planes in memory, operand planes in LDS (BYTES: the two 32-channel halves of a step) and of the weights
     constexpr int IN = KIND == kResPlanes ? 3 : BYTES ? 2 : 1, PL = KIND == kResPlanes || BYTES ? 2 : 1, WP = BYTES ? 2 : 1;
     constexpr int STEP = BYTES ? 64 : 32;   // bytes of a step of 64 codes
-    constexpr int AHEAD = IN == 1 ? 4 : 2;                // items of the fill whose loads are in flight
+    constexpr int PIECES = NS ? NS : 1;                         // steps of an item of the fill
+    constexpr int AHEAD = IN == 1 && NS == 0 ? 4 : 2;           // items of the fill whose loads are in flight
     using Out = typename OutT<OUT>::type;
     using Operand = std::conditional_t<BYTES, v4i, v8i>;
     using Acc = std::conditional_t<BYTES, v16i, v16f>;
@@ -231,11 +238,14 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             advance();
         }
     };
-    v4i raw_tap[NS ? NS : 1];   // NS: weights of the next tap
+    v4i raw_tap[WP][NS ? NS : 1];   // NS: weights of the next tap
     auto take_tap = [&](int tap) {
         const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
 #pragma unroll
-        for (int k = 0; k < NS; ++k) raw_tap[k] = buffer_load16(buf, w_row[0], static_cast<uint32_t>(tap * cb + k * STEP));
+        for (int k = 0; k < NS; ++k)
+#pragma unroll
+            for (int i = 0; i < WP; ++i)
+                raw_tap[i][k] = buffer_load16(buf, w_row[0], static_cast<uint32_t>(tap * cb + (s0 + k) * STEP + i * 32));
     };
     auto begin_task = [&]() {
         const int task = first + (wv >> kl), share = wv & ((1 << kl) - 1);
@@ -274,7 +284,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     };
 
     // ---- activation tile: packed codes -> signed 6-bit fields ------------------------------------------------
-    // Wave items (32 rows, step): lane = (row, lane half), one 16-byte piece each; the code sum of a row's step is that of
+    // Wave items (32 rows, PIECES steps): lane = (row, lane half), a 16-byte piece of each step; the code sum of a row's item is that of
     // two neighbouring lanes.  Neighbouring waves take the steps of the same rows.
     const int row_span = (px_wg + 2 * halo + 31) & ~31;
     const uint32_t last = a.pixels - 1;
@@ -283,72 +293,81 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     const uint32_t plane_bytes = a.pixels * static_cast<uint32_t>(cb);
     const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, BYTES ? plane_bytes : IN * plane_bytes);
     struct Item { int step, row; };
-    int nw_step = 0, nw_row = 0;   // nw items on
+    int nw_step = 0, nw_row = 0, row_steps = 0;   // nw items on; steps of a row, up to a whole item
     auto next = [&](Item &i) {
         i.step += nw_step;
         i.row += nw_row;
-        if (i.step >= ns) {
-            i.step -= ns;
+        if (NS == 0 && i.step >= row_steps) {
+            i.step -= row_steps;
             i.row += 32;
         }
     };
-    auto fill_load = [&](v4i (&p)[IN], const Item &item) {
+    auto fill_load = [&](v4i (&p)[IN][PIECES], const Item &item) {
         if (item.row >= row_span) return;
         // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
         const uint32_t off = (static_cast<uint32_t>(p0) - halo + item.row + f_row) * cb + f_half * 16;
 #pragma unroll
-        for (int i = 0; i < IN; ++i) {
-            if (i < a.in_planes) p[i] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step) * STEP);
-            else p[i] = v4i{0, 0, 0, 0};
-        }
+        for (int i = 0; i < IN; ++i)
+#pragma unroll
+            for (int k = 0; k < PIECES; ++k) {
+                if (i < a.in_planes) p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step + k) * STEP);
+                else p[i][k] = v4i{0, 0, 0, 0};
+            }
     };
-    auto fill_store = [&](const v4i (&p)[IN], const Item &item) {
+    auto fill_store = [&](const v4i (&p)[IN][PIECES], const Item &item) {
         const int row = item.row + f_row;
         int sum = 0;
         if (row < rows - 1) {
-            auto at = [&](int plane) { return ((item.step * PL + plane) * 2 + f_half) * rows + row; };
-            if constexpr (BYTES) {
 #pragma unroll
-                for (int i = 0; i < PL; ++i) *reinterpret_cast<v4i *>(lds + at(i) * 16) = p[i];
-            } else {
-                auto codes = [&](const v4i &v, int s) {
-                    return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s))));
-                };
-                auto put = [&](int plane, const int (&d)[6]) {
-                    *reinterpret_cast<v4i *>(lds + at(plane) * 16) = v4i{d[0], d[1], d[2], d[3]};
-                    *reinterpret_cast<int2 *>(lds + a.part8 + at(plane) * 8) = int2{d[4], d[5]};
-                };
-                int d[6];
-                fp6_signed16(p[0].x, p[0].y, d[0], d[1], d[2]);
-                fp6_signed16(p[0].z, p[0].w, d[3], d[4], d[5]);
-                put(0, d);
-                sum = codes(p[0], 0);
-                if constexpr (KIND == kResPlanes) {
-                    fp6_upper16(p[1].x, p[2].x, p[1].y, p[2].y, d[0], d[1], d[2]);
-                    fp6_upper16(p[1].z, p[2].z, p[1].w, p[2].w, d[3], d[4], d[5]);
-                    put(1, d);
-                    sum += 16 * codes(p[1], 0) + 256 * codes(p[2], 0);
+            for (int k = 0; k < PIECES; ++k) {
+                auto at = [&](int plane) { return (((item.step + k) * PL + plane) * 2 + f_half) * rows + row; };
+                if constexpr (BYTES) {
+#pragma unroll
+                    for (int i = 0; i < PL; ++i) *reinterpret_cast<v4i *>(lds + at(i) * 16) = p[i][k];
+                } else {
+                    auto codes = [&](const v4i &v, int s) {
+                        return sum_codes8(v.x, sum_codes8(v.y, sum_codes8(v.z, sum_codes8(v.w, s))));
+                    };
+                    auto put = [&](int plane, const int (&d)[6]) {
+                        *reinterpret_cast<v4i *>(lds + at(plane) * 16) = v4i{d[0], d[1], d[2], d[3]};
+                        *reinterpret_cast<int2 *>(lds + a.part8 + at(plane) * 8) = int2{d[4], d[5]};
+                    };
+                    int d[6];
+                    fp6_signed16(p[0][k].x, p[0][k].y, d[0], d[1], d[2]);
+                    fp6_signed16(p[0][k].z, p[0][k].w, d[3], d[4], d[5]);
+                    put(0, d);
+                    sum = codes(p[0][k], sum);
+                    if constexpr (KIND == kResPlanes) {
+                        fp6_upper16(p[1][k].x, p[2][k].x, p[1][k].y, p[2][k].y, d[0], d[1], d[2]);
+                        fp6_upper16(p[1][k].z, p[2][k].z, p[1][k].w, p[2][k].w, d[3], d[4], d[5]);
+                        put(1, d);
+                        sum += 16 * codes(p[1][k], 0) + 256 * codes(p[2][k], 0);
+                    }
                 }
             }
         }
         if constexpr (!BYTES) {
             sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
             if (f_half == 0 && row < rows - 1) {
-                if constexpr (WHOLE_TAPS) s_part[item.step * rows + row] = static_cast<short>(sum);
+                if constexpr (WHOLE_TAPS) s_part[item.step / PIECES * rows + row] = static_cast<short>(sum);
                 else atomicAdd(&s_sum[row], sum);
             }
         }
     };
 
     // All first loads are requested before any is waited for (a first use costs a trip to HBM).
-    v4i p[AHEAD][IN];
+    v4i p[AHEAD][IN][PIECES];
     Item load_item{}, store_item{};
     auto begin_fill = [&]() {
-        nw_row = nw / ns * 32;
-        nw_step = nw % ns;
-        load_item = store_item = Item{wv % ns, wv / ns * 32};
+        const int of_rows = ns / PIECES;   // items of 32 rows
+        row_steps = of_rows * PIECES;
+        nw_row = nw / of_rows * 32;
+        nw_step = nw % of_rows * PIECES;
+        load_item = store_item = Item{wv % of_rows * PIECES, wv / of_rows * 32};
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
+#pragma unroll
+            for (int j = 0; j < IN * PIECES; ++j) asm("" : "=v"(p[i][j / PIECES][j % PIECES]));   // (no register holds the old ones meanwhile)
             fill_load(p[i], load_item);
             next(load_item);
         }
@@ -413,41 +432,63 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             }
         }
         lds_barrier();
-        // tables of the pixels: tap masks, scales under the taps, corrections; a lane has one row of the window, four lanes a pixel
-        for (int j = tid; j < 4 * px_wg; j += nt) {
-            const int r = j & 3, i = j >> 2;   // (r == 3: nothing)
-            const uint32_t pix = p0 + i;
-            const uint32_t line = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
-            const int ow = static_cast<int>(pix - line * a.w);
-            const int oh = static_cast<int>(line - hq::div_magic31(line, a.h, a.h_magic, a.h_shift) * a.h);
-            const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
-            int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
-            if (pix >= a.pixels) mask = 0;
-            if (r == 0) s_mask[i] = mask;
-            float corr = 0.f;
+        // tables of the pixels: tap masks, scales under the taps, corrections
+        if constexpr (NS == 0 || KIND == kResPerTap) {   // a lane has one row of the window, four lanes a pixel
+            for (int j = tid; j < 4 * px_wg; j += nt) {
+                const int r = j & 3, i = j >> 2;   // (r == 3: nothing)
+                const uint32_t pix = p0 + i;
+                const uint32_t line = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
+                const int ow = static_cast<int>(pix - line * a.w);
+                const int oh = static_cast<int>(line - hq::div_magic31(line, a.h, a.h_magic, a.h_shift) * a.h);
+                const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
+                int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
+                if (pix >= a.pixels) mask = 0;
+                if (r == 0) s_mask[i] = mask;
+                float corr = 0.f;
 #pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                if (r == 3) break;
-                const int t = 3 * r + s, row = halo + i + (r - 1) * a.w + (s - 1);
-                const bool in = (mask >> t) & 1;
-                if constexpr (ROW_SCALES) {
-                    const float scale = in ? s_rowscale[row] : 0.f;
-                    s_sx[t * px_wg + i] = scale;
-                    if constexpr (SUMS) corr = fmaf(scale * (8.0f / UNIT), static_cast<float>(s_sum[row]), corr);
-                } else if (SUMS && in) {
-                    corr += (8.0f / UNIT) * static_cast<float>(s_sum[row]);
+                for (int s = 0; s < 3; ++s) {
+                    if (r == 3) break;
+                    const int t = 3 * r + s, row = halo + i + (r - 1) * a.w + (s - 1);
+                    const bool in = (mask >> t) & 1;
+                    if constexpr (ROW_SCALES) {
+                        const float scale = in ? s_rowscale[row] : 0.f;
+                        s_sx[t * px_wg + i] = scale;
+                        if constexpr (SUMS) corr = fmaf(scale * (8.0f / UNIT), static_cast<float>(s_sum[row]), corr);
+                    } else if (SUMS && in) {
+                        corr += (8.0f / UNIT) * static_cast<float>(s_sum[row]);
+                    }
                 }
+                corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0xB1, 0xF, 0xF, true));   // lanes 1,0,3,2
+                corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0x4E, 0xF, 0xF, true));   // lanes 2,3,0,1
+                if (r == 0) s_corr[i] = corr;
             }
-            corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0xB1, 0xF, 0xF, true));   // lanes 1,0,3,2
-            corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0x4E, 0xF, 0xF, true));   // lanes 2,3,0,1
-            if (r == 0) s_corr[i] = corr;
+        } else {   // a lane has a pixel: as fast for 128 pixels, faster for 256 (with per-pixel scales of 4-bit codes its registers spill)
+            for (int i = tid; i < px_wg; i += nt) {
+                const uint32_t pix = p0 + i;
+                const uint32_t line = hq::div_magic31(pix, a.w, a.w_magic, a.w_shift);
+                const int ow = static_cast<int>(pix - line * a.w);
+                const int oh = static_cast<int>(line - hq::div_magic31(line, a.h, a.h_magic, a.h_shift) * a.h);
+                const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
+                int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
+                if (pix >= a.pixels) mask = 0;
+                s_mask[i] = mask;
+                float corr = 0.f;
+#pragma unroll
+                for (int t = 0; t < TAPS; ++t) {
+                    const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
+                    const bool in = (mask >> t) & 1;
+                    if constexpr (ROW_SCALES) s_sx[t * px_wg + i] = in ? s_rowscale[row] : 0.f;
+                    else if (SUMS && in) corr += (8.0f / UNIT) * static_cast<float>(s_sum[row]);
+                }
+                if constexpr (SUMS) s_corr[i] = corr;
+            }
         }
-        if constexpr (WHOLE_TAPS) {   // code sums of a step -> of all resident steps up to it
+        if constexpr (WHOLE_TAPS && NS == 0) {   // code sums of a step -> of all resident steps up to it
             for (int i = tid; i < px_wg + 2 * halo; i += nt) {
                 int of = s_part[i];
-                for (int k = 1; k < ns; ++k) {
-                    of += s_part[k * rows + i];
-                    s_part[k * rows + i] = static_cast<short>(of);
+                for (int k = PIECES; k < ns; k += PIECES) {
+                    of += s_part[k / PIECES * rows + i];
+                    s_part[k / PIECES * rows + i] = static_cast<short>(of);
                 }
             }
         }
@@ -474,57 +515,84 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             const int lane_row = px_l + l + halo;
 
             if constexpr (NS > 0) {
-                // While the MFMAs of tile t run, tile t + 1 is on its way from LDS and the sums of tile t - 1 are folded; the next
+                // While the MFMAs of a tile run, the next one is on its way from LDS and the sums of the one before are folded; the next
                 // tap's weights are requested as soon as this one's are expanded.
                 const Fp6Masks masks;
-                const int step16 = rows * 32, step8 = rows * 16;
+                const int step16 = rows * (PL * 32), step8 = rows * (PL * 16), plane16 = rows * 32, plane8 = rows * 16;
                 int tap = q / NS;
                 const int tap_end = q_end / NS;
                 struct Base { int b16, b8; };
+                auto row_shift = [&](int tap) { return (tap / 3 - 1) * a.w + tap % 3 - 1; };
                 auto base_of = [&](int tap) {
-                    const int at = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + h * rows;
+                    const int at = lane_row + row_shift(tap) + h * rows;
                     return Base{static_cast<int>(lds_address(lds)) + at * 16, static_cast<int>(lds_address(lds) + a.part8) + at * 8};
                 };
-                auto load_tile = [&](v8i (&b)[NS], const Base &base, int t) {
+                auto load_tile = [&](Operand (&b)[NS], const Base &base, int t, int plane) {
 #pragma unroll
                     for (int k = 0; k < NS; ++k) {
-                        const v4i lo = lds_v4i(base.b16 + k * step16, t * 512);
-                        const v2i hi = lds_v2i(base.b8 + k * step8, t * 256);
-                        b[k] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+                        const v4i lo = lds_v4i(base.b16 + k * step16 + plane * plane16, t * 512);
+                        if constexpr (BYTES) {
+                            b[k] = lo;
+                        } else {
+                            const v2i hi = lds_v2i(base.b8 + k * step8 + plane * plane8, t * 256);
+                            b[k] = v8i{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, 0, 0};
+                        }
                     }
                 };
+                const v4h minus = h ? v4h{} : v4h{-0.125f16, -128.0f16, 0, 0};
                 Base base = base_of(tap);
-                v8i wop[NS], b[2][NS];
-                load_tile(b[0], base, 0);
+                Operand wop[WP][NS], b[2][NS];
+                load_tile(b[0], base, 0, 0);
                 for (; tap < tap_end; ++tap) {
                     const int tap1 = tap + 1 < tap_end ? tap + 1 : tap;   // (the last one's operands are requested twice)
                     const Base base1 = base_of(tap1);
 #pragma unroll
                     for (int k = 0; k < NS; ++k) {
-                        int d[6];
-                        fp6_offset16(masks, raw_tap[k].x, raw_tap[k].y, d[0], d[1], d[2]);
-                        fp6_offset16(masks, raw_tap[k].z, raw_tap[k].w, d[3], d[4], d[5]);
-                        wop[k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+                        if constexpr (BYTES) {
+#pragma unroll
+                            for (int i = 0; i < WP; ++i) wop[i][k] = raw_tap[i][k];
+                        } else {
+                            int d[6];
+                            fp6_offset16(masks, raw_tap[0][k].x, raw_tap[0][k].y, d[0], d[1], d[2]);
+                            fp6_offset16(masks, raw_tap[0][k].z, raw_tap[0][k].w, d[3], d[4], d[5]);
+                            wop[0][k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
+                        }
                     }
                     take_tap(tap1);
                     float scale[NT];
+                    int codes[NT], inside[NT];   // (as below)
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
-                    v16f acc[2];
+                    for (int t = 0; t < NT; ++t) {
+                        if constexpr (ROW_SCALES) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
+                        if constexpr (WHOLE_TAPS) codes[t] = s_part[lane_row + row_shift(tap) + t * 32];
+                        if constexpr (!FOLD) inside[t] = (mask[t] >> tap) & 1 ? 127 : 0;
+                    }
+                    Acc acc[2];
                     auto fold = [&](int t) {
+                        if constexpr (FOLD) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], acc[t & 1][i], sum[t][i]);
+                            for (int i = 0; i < 16; ++i) sum[t][i] = fmaf(scale[t], static_cast<float>(acc[t & 1][i]), sum[t][i]);
+                        }
                     };
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
-                        if (t + 1 < NT) load_tile(b[(t + 1) & 1], base, t + 1);
-                        else load_tile(b[0], base1, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        acc[t & 1] = v16f{};
+                        if constexpr (WHOLE_TAPS) acc[t & 1] = __builtin_bit_cast(Acc, minus_eighth_of(minus, codes[t]));
+                        else if constexpr (FOLD) acc[t & 1] = Acc{};
 #pragma unroll
-                        for (int k = 0; k < NS; ++k) acc[t & 1] = mfma_fp6(wop[k], b[t & 1][k], acc[t & 1]);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (t > 0) fold(t - 1);
+                        for (int plane = 0; plane < PL; ++plane) {
+                            const int now = t * PL + plane, next = now + 1;
+                            if (next < NT * PL) load_tile(b[next & 1], base, next / PL, next % PL);
+                            else load_tile(b[0], base1, 0, 0);
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int k = 0; k < NS; ++k) {
+                                if constexpr (BYTES) acc[t & 1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wop[plane][k], b[now & 1][k], acc[t & 1], 0, 0, 0);
+                                else if constexpr (FOLD) acc[t & 1] = mfma_fp6(wop[0][k], b[now & 1][k], acc[t & 1]);
+                                else sum[t] = mfma_fp6_scaled(wop[0][k], b[now & 1][k], sum[t], plane ? 131 : 127, inside[t]);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                            if (t > 0 && plane == 0) fold(t - 1);
+                        }
                     }
                     fold(NT - 1);
                     base = base1;
@@ -569,12 +637,12 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 Acc acc[NT];              // FOLD: the sums of the tap at work
                 const v4h minus = h ? v4h{} : v4h{-0.125f16, -128.0f16, 0, 0};
                 auto codes_upto = [&](int step, int t) {   // WHOLE_TAPS
-                    return static_cast<int>(s_part[step * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
+                    return static_cast<int>(s_part[step / PIECES * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
                 };
                 // A step.  Right after the matrix instructions of a tile the tile's operands of the next step are requested, into the
                 // registers that have just been read; the next step's weights are expanded in between, and their slot of the
                 // ring is filled again.
-                int inside[NT], inside16[NT];   // !FOLD: block exponents: 2^0 (2^4), or for taps outside the image one that leaves nothing
+                int inside[NT];   // !FOLD: block exponents: 2^0, or for taps outside the image one that leaves nothing
                 auto step = [&](auto STARTS, bool ends) {   // the tap's sums start here; its last step in this share
                     constexpr bool starts = decltype(STARTS)::value;
                     b16 = ends ? n16 : b16 + step16;
@@ -593,8 +661,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         } else if constexpr (FOLD) {
                             acc[t] = mfma_fp6(wop, b[t][0], starts && !WHOLE_TAPS ? Acc{} : acc[t]);
                         } else {
-                            sum[t] = mfma_fp6_scaled(wop, b[t][0], sum[t], inside[t]);
-                            if constexpr (PL == 2) sum[t] = mfma_fp6_scaled(wop, b[t][PL - 1], sum[t], inside16[t]);
+                            sum[t] = mfma_fp6_scaled(wop, b[t][0], sum[t], 127, inside[t]);
+                            if constexpr (PL == 2) sum[t] = mfma_fp6_scaled(wop, b[t][PL - 1], sum[t], 131, inside[t]);   // (x 2^4)
                         }
                         __builtin_amdgcn_sched_barrier(0);
                         load_tile(t);
@@ -631,10 +699,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     }
                     if constexpr (!FOLD) {
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) {
-                            inside[t] = (mask[t] >> tap) & 1 ? 127 : 0;
-                            inside16[t] = (mask[t] >> tap) & 1 ? 131 : 0;
-                        }
+                        for (int t = 0; t < NT; ++t) inside[t] = (mask[t] >> tap) & 1 ? 127 : 0;
                     }
                     step(std::true_type{}, n == 1);
 #pragma unroll 1
@@ -852,12 +917,12 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 // One form's kernels by output type and the last two parameters (a file each, so that they compile in parallel).
 #define HQ_RESIDENT_FORM(NAME, KIND)                                                                            \
     const void *NAME(int out, bool ring, int ns) {                                                              \
-        static const void *const kernels[3][5] = {                                                              \
+        static const void *const kernels[3][6] = {                                                              \
             HQ_RESIDENT_FORM_OUT(kOutF16, KIND), HQ_RESIDENT_FORM_OUT(kOutF32, KIND), HQ_RESIDENT_FORM_OUT(kOutI32, KIND)}; \
         return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][ns ? 1 + ns : ring];                        \
     }
 #define HQ_RESIDENT_FORM_OUT(OUT, KIND)                                                                         \
     {HQ_RESIDENT_FN(OUT, KIND, false, 0), HQ_RESIDENT_FN(OUT, KIND, true, 0), HQ_RESIDENT_FN(OUT, KIND, false, 1), \
-     HQ_RESIDENT_FN(OUT, KIND, false, 2), HQ_RESIDENT_FN(OUT, KIND, false, 3)}
+     HQ_RESIDENT_FN(OUT, KIND, false, 2), HQ_RESIDENT_FN(OUT, KIND, false, 3), HQ_RESIDENT_FN(OUT, KIND, false, 4)}
 #define HQ_RESIDENT_FN(OUT, KIND, RING, NS)                                                                     \
     reinterpret_cast<const void *>(resident_kernel<OUT, KIND, RING, resident_unrolled(KIND, OUT, NS)>)

@@ -282,3 +282,48 @@ def test_conv3x3_one_scale_empty_sums(hq, nb, h, w, cin, cout):
     y = host(hq.hq_int_conv2d_static(dev(pack_codes(xq)), s1, dev(pack_codes(wq)), dev(sw), None, ksize=3, y_dtype=torch.float32))
     assert (y[:, :, : w // 2] == 0).all()
     check_y("y", y, y_o, rtol=1e-5)   # (fp32: sums are exact, three roundings)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (2, 7, 8, 64, 40), (1, 33, 24, 128, 33), (3, 9, 16, 192, 72), (2, 7, 8, 256, 40),   # taps of one to four steps: unrolled
+    (2, 7, 8, 320, 40),          # five: a loop, the second item of the fill is not whole
+    (7, 24, 40, 192, 200),       # two pixel groups a workgroup, several phases
+    (1, 5, 136, 384, 40),        # three steps resident at a time
+])
+def test_conv3x3_steps_of_a_tap(hq, nb, h, w, cin, cout):
+    """Every form, unrolled and not, with every type of results: integer sums bit for bit, fp32 results to 1e-5 of the largest (the width
+    axis 1e-6, three roundings), fp16 to 1e-3 (one rounding, 4.9e-4)."""
+    rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
+    if w == 136:
+        assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout).endswith("slices in turn)")
+    sx = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
+    sw = rng.uniform(1e-5, 1e-3, cout).astype(np.float32)   # (fp16 results of 8-bit codes stay in range)
+    bias = rng.standard_normal(cout).astype(np.float16)
+    s1 = torch.tensor([0.37], dtype=torch.float32, device="cuda")
+
+    def check(call, x, scale, q_w, acc_o, y_o, rtol, *block):
+        assert np.array_equal(host(call(x, None, q_w, None, None, *block, y_dtype=torch.int32)), acc_o)
+        for ydt, tol in ((torch.float32, rtol), (torch.float16, 1e-3)):
+            check_y("y", host(call(x, scale, q_w, dev(sw), dev(bias).to(ydt), *block, y_dtype=ydt)), y_o, rtol=tol)
+
+    xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
+    xq[0, 0, 0, :], wq[0, :, :, :] = -8, -8
+    x4, w4 = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
+    acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
+    check(hq.hq_int_conv2d, x4, dev(sx), w4, acc_o, y_o, 1e-5)
+    acc_o, y_o = oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1)
+    check(hq.hq_int_conv2d_static, x4, s1, w4, acc_o, y_o, 1e-5)
+    block = 8
+    hb = np.array([[(-1) ** bin(i & j).count("1") for j in range(block)] for i in range(block)])
+    u = np.einsum("nhbic,ij->nhbjc", xq.astype(np.int64).reshape(nb, h, w // block, block, cin), hb).reshape(nb, h, w, cin)
+    d0 = (u + 8) % 16 - 8
+    r1 = (u - d0) // 16
+    d1 = (r1 + 8) % 16 - 8
+    planes = dev(pack_codes(np.stack([d0, d1, (r1 - d1) // 16]).astype(np.int8)))
+    acc_o, y_o = oracle.int_conv2d_width(xq, 0.37, wq, sw, block, bias, stride=1, pad=1)
+    check(hq.hq_int_conv2d_width, planes, s1, w4, acc_o, y_o, 1e-6, block)
+    xq = rng.integers(-128, 128, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-128, 128, (cout, 3, 3, cin)).astype(np.int8)
+    acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
+    check(hq.hq_int_conv2d_i8, dev(xq), dev(sx), dev(wq.reshape(cout, 9, cin)), acc_o, y_o, 1e-5)
