@@ -40,7 +40,7 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     const int ops = ks * (kind >= kResPlanes ? 2 : 1);   // operands of a row, lane half and slice
     const int part8_bytes = kind == kResBytes ? 0 : 16;   // (8-bit codes are 16-byte operands)
     const int slice_bytes = p.rows * ops * (32 + part8_bytes);
-    const int sums = by_slice ? p.rows * 2 * ks : 0;   // (a sum for every step)
+    const int sums = by_slice ? p.rows * 2 : 0;   // (a sum for every three steps)
     int tables = resident_table_bytes(kind, px, p.rows, cb);
     p.chunk = std::min(p.slices, (budget - tables - (overlay ? 0 : area)) / (slice_bytes + sums));
     tables += (p.chunk * sums + 3) & ~3;
@@ -175,7 +175,7 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     a.out_scale = g.out_scale;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
-    a.chunk = p.chunk * p.ks; a.grain = p.ks; a.ring = p.ring; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
+    a.chunk = p.chunk * p.ks; a.ring = p.ring; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
     a.wide = p.wide; a.part8 = p.part8; a.exchange = p.exchange; a.tables = p.tables;
     const int px = 128 << p.xw_log2, blocks = (g.n + 31) / 32;
     const int64_t px_tiles = (static_cast<int64_t>(g.pixels) + px - 1) / px, ch_groups = (blocks + p.cb - 1) / p.cb;

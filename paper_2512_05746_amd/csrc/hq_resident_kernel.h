@@ -72,7 +72,6 @@ struct ResidentArgs {
     float out_scale;     // times the one scale
     uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
     int chunk;                     // steps of 64 channels that are resident at a time
-    int grain;                     // fp32 results: steps of a tap that stay together
     int xw_log2;                   // pixel groups of 128 per workgroup
     int cb;                        // channel blocks of 32 per workgroup
     uint32_t ch_groups, px_tiles;  // workgroups: channel runs x pixel tiles
@@ -146,8 +145,11 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     // planes in memory, operand planes in LDS (BYTES: the two 32-channel halves of a step) and of the weights
     constexpr int IN = KIND == kResPlanes ? 3 : BYTES ? 2 : 1, PL = KIND == kResPlanes || BYTES ? 2 : 1, WP = BYTES ? 2 : 1;
     constexpr int STEP = BYTES ? 64 : 32;   // bytes of a step of 64 codes
-    constexpr int PIECES = NS ? NS : 1;                         // steps of an item of the fill
-    constexpr int AHEAD = IN == 1 && NS == 0 ? 4 : 2;           // items of the fill whose loads are in flight
+    // Steps of an item of the fill, and items whose loads are in flight.  Items of one step have an address, a branch and an atomic sum
+    // for every 16 bytes a lane; us a call, items of one step, four in flight -> of three: one scale 2 x 23 x 23 x 576 13.9 -> 12.8,
+    // per-pixel scales 7 x 12 x 8 x 768 -> 216 17.9 -> 17.0, 8 bits 1 x 16 x 16 x 384 11.3 -> 10.7.  The forms of three planes (2 .. 10 %
+    // slower with three steps), and of 8 bits with a ring (1.5 %), keep to one.
+    constexpr int PIECES = NS ? NS : IN == 1 || (BYTES && !RING) ? 3 : 1, AHEAD = 2;
     using Out = typename OutT<OUT>::type;
     using Operand = std::conditional_t<BYTES, v4i, v8i>;
     using Acc = std::conditional_t<BYTES, v16i, v16f>;
@@ -261,8 +263,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             w_row[j] = row_of(row) + (BYTES ? (lane & 3) ^ ((row >> 2) & 3) : (lane & 1) ^ ((row >> 3) & 1)) * 16;
         }
         if constexpr (!RING) w_row[0] = row_of(l) + h * 16;
-        // (a tap that two waves share is folded twice: fp32 results are cut at every a.grain-th step of a tap only)
-        const int grain = NS ? NS : OUT == kOutF32 ? a.grain : 1, grains = (ns + grain - 1) / grain;
+        // (a tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only)
+        const int grain = NS ? NS : OUT == kOutF32 ? 3 : 1, grains = (ns + grain - 1) / grain;
         auto cut = [&](int of) {
             const int at = of * (TAPS * grains) >> kl, tap = at / grains;
             return tap * ns + (at - tap * grains) * grain;
@@ -310,6 +312,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         for (int i = 0; i < IN; ++i)
 #pragma unroll
             for (int k = 0; k < PIECES; ++k) {
+                if (PIECES > 1 && NS == 0 && item.step + k >= ns) continue;
                 if (i < a.in_planes) p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step + k) * STEP);
                 else p[i][k] = v4i{0, 0, 0, 0};
             }
@@ -320,6 +323,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         if (row < rows - 1) {
 #pragma unroll
             for (int k = 0; k < PIECES; ++k) {
+                if (PIECES > 1 && NS == 0 && item.step + k >= ns) break;
                 auto at = [&](int plane) { return (((item.step + k) * PL + plane) * 2 + f_half) * rows + row; };
                 if constexpr (BYTES) {
 #pragma unroll
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     v4i p[AHEAD][IN][PIECES];
     Item load_item{}, store_item{};
     auto begin_fill = [&]() {
-        const int of_rows = ns / PIECES;   // items of 32 rows
+        const int of_rows = (ns + PIECES - 1) / PIECES;   // items of 32 rows
         row_steps = of_rows * PIECES;
         nw_row = nw / of_rows * 32;
         nw_step = nw % of_rows * PIECES;
@@ -483,7 +487,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 if constexpr (SUMS) s_corr[i] = corr;
             }
         }
-        if constexpr (WHOLE_TAPS && NS == 0) {   // code sums of a step -> of all resident steps up to it
+        if constexpr (WHOLE_TAPS && NS == 0) {   // code sums of three steps -> of all resident steps up to them
             for (int i = tid; i < px_wg + 2 * halo; i += nt) {
                 int of = s_part[i];
                 for (int k = PIECES; k < ns; k += PIECES) {
