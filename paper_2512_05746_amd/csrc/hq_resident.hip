@@ -4,19 +4,19 @@
 
 #include "hq_resident_kernel.h"
 
-const void *hq_resident_pertap(int out, bool ring, int ns);
-const void *hq_resident_sum(int out, bool ring, int ns);
-const void *hq_resident_planes(int out, bool ring, int ns);
-const void *hq_resident_bytes(int out, bool ring, int ns);
+const void *hq_resident_pertap(int out, int form);
+const void *hq_resident_sum(int out, int form);
+const void *hq_resident_planes(int out, int form);
+const void *hq_resident_bytes(int out, int form);
 
 namespace {
 
 constexpr int kLdsPerCu = 163840;
 
 struct Plan {
-    int ks, slices, chunk, nw, xw_log2, cb, rows;
-    uint32_t part8, exchange, ring, ring_stride, tables, lds;
-    bool wide, has_ring, ring_shared, ok;
+    int ks, slices, chunk, nw, xw_log2, cb, rows, ring;   // ring: slots
+    uint32_t part8, exchange, ring_at, ring_stride, tables, lds;
+    bool wide, ring_shared, ok;
 };
 
 // LDS layout of a workgroup of nw waves, 1 << xw_log2 pixel groups and cb channel blocks within `budget` bytes.  by_slice: with a
@@ -54,22 +54,19 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     p.tables = overlay ? std::max(act_end, static_cast<uint32_t>(p.wide ? 2 * area : area)) : act_end + area;
     p.lds = p.tables + tables;
     p.ok = static_cast<int>(p.lds) <= budget + 32 && p.lds <= kLdsPerCu;
-    // The rings of weights: behind the tile (and the exchange area of its own, if it has one) where that leaves room for them, with
-    // the tables behind them; else in the exchange area, which costs a barrier from phase to phase; else (one phase, and a tile that
-    // fills the LDS) there are none.
-    const uint32_t ring_bytes = resident_ring_slots(kind) * resident_slot_bytes(kind), free_at = overlay ? act_end : act_end + area;
-    p.has_ring = true;
-    p.ring = p.exchange;
-    p.ring_stride = 8192;
-    p.ring_shared = !overlay;
-    if (static_cast<int>(free_at + nw * ring_bytes) + tables <= budget) {
-        p.ring = free_at;
-        p.ring_stride = ring_bytes;
-        p.ring_shared = false;
-        p.tables = std::max<uint32_t>(p.tables, free_at + nw * ring_bytes);
+    // The rings of weights: three slots behind the tile (and the exchange area of its own, if it has one) where that leaves room for
+    // them, with the tables behind them; else three in the exchange area, which costs a barrier from phase to phase; else (one phase, and
+    // a tile that fills the LDS) two slots behind the tile, or none.  us a call, weights not in L2, none -> two slots: one scale
+    // 4 x 29 x 29 x 960 34.2 -> 28.4.  Digit planes have 8 matrix instructions a step, which hide a load from L2 (two slots 1 .. 2 % slower).
+    const uint32_t free_at = overlay ? act_end : act_end + area, slot = resident_slot_bytes(kind);
+    auto fits = [&](int slots) { return static_cast<int>(free_at + nw * slots * slot) + tables <= budget; };
+    p.ring = fits(3) || !overlay ? 3 : fits(2) && kind != kResPlanes ? 2 : 0;
+    p.ring_shared = !overlay && !fits(3);
+    p.ring_at = p.ring_shared ? p.exchange : free_at;
+    p.ring_stride = p.ring_shared ? 8192 : p.ring * slot;
+    if (!p.ring_shared) {
+        p.tables = std::max<uint32_t>(p.tables, free_at + nw * p.ring_stride);
         p.lds = p.tables + tables;
-    } else if (overlay) {
-        p.has_ring = false;
     }
     return p;
 }
@@ -116,6 +113,17 @@ Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n, C
     return best;
 }
 
+// Workgroups of four waves are laid out so that two share a CU.  Where there are no more of them than CUs each has all of the LDS to
+// itself: a ring of three slots finds room, and more slices are resident at a time.  us a call with half -> all of it, weights not in L2:
+// 1 x 13 x 13 x 576 (no ring before) 15.3 -> 12.6, 7 x 12 x 8 x 768 -> 216 (slices in turn) 19.2 -> 14.2.
+Plan spread_out(const Plan &p, int kind, bool by_slice, int64_t pixels, int w, int k, int n) {
+    if (!p.ok || p.nw != 4) return p;
+    const int px = 128 << p.xw_log2;
+    const int64_t wgs = (pixels + px - 1) / px * (((n + 31) / 32 + p.cb - 1) / p.cb);
+    if (wgs > hq::compute_units()) return p;
+    return lay_out(kind, by_slice, w, k, n, p.ks, p.nw, p.xw_log2, p.cb, kLdsPerCu);
+}
+
 // The cut, not ok where the tile kernel is estimated to be the faster one by more than the estimates are off.  That is so for
 // images so wide that a tile's rows and those above and below fill the LDS (the tile is expanded again for every 128 channels,
 // or some slices at a time), and for some layers of few channels or of a few more tiles than CUs.  us, resident kernel against
@@ -148,7 +156,8 @@ hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
 }  // namespace
 
 const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, int sx_static) {
-    const Plan p = choose_kernel(kind_of(bits, sx_static), 0, pixels, w, k, n);
+    const int kind = kind_of(bits, sx_static);
+    const Plan p = spread_out(choose_kernel(kind, 0, pixels, w, k, n), kind, false, pixels, w, k, n);
     if (!p.ok) return nullptr;
     static const char *const names[2][2][2] = {   // [pixels][waves][slices resident at a time]
         {{"activation-resident (128 pixels, 4 waves)", "activation-resident (128 pixels, 4 waves, slices in turn)"},
@@ -163,11 +172,13 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     const int kind = had_block ? kResPlanes : kind_of(g.bits, g.sx_static);
     Plan p = choose_kernel(kind, had_block, g.pixels, g.w, g.k, g.n);
-    if (p.ok && kind == kResPerTap && y_dtype == HQ_F32) {
+    const bool by_slice = kind == kResPerTap && y_dtype == HQ_F32;
+    if (p.ok && by_slice) {
         Cost cost{};
         p = choose_plan(kind, true, g.pixels, g.w, g.k, g.n, cost);
     }
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
+    p = spread_out(p, kind, by_slice, g.pixels, g.w, g.k, g.n);
     ResidentArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
     a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.h = g.h; a.w = g.w;
@@ -175,7 +186,7 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     a.out_scale = g.out_scale;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
-    a.chunk = p.chunk * p.ks; a.ring = p.ring; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
+    a.chunk = p.chunk * p.ks; a.ring = p.ring_at; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
     a.wide = p.wide; a.part8 = p.part8; a.exchange = p.exchange; a.tables = p.tables;
     const int px = 128 << p.xw_log2, blocks = (g.n + 31) / 32;
     const int64_t px_tiles = (static_cast<int64_t>(g.pixels) + px - 1) / px, ch_groups = (blocks + p.cb - 1) / p.cb;
@@ -194,12 +205,13 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     }
     const int resident = std::min(p.chunk * p.ks, g.k / 64);   // steps
     const int ns = g.k / 64 % resident ? 0 : resident_unrolled(kind, out, resident);
-    const void *fn = kind == kResBytes    ? hq_resident_bytes(out, p.has_ring, ns)
-                     : kind == kResPlanes ? hq_resident_planes(out, p.has_ring, ns)
-                     : kind == kResSum  ? hq_resident_sum(out, p.has_ring, ns)
-                                        : hq_resident_pertap(out, p.has_ring, ns);
-    static std::atomic<uint64_t> allowed[4][3][6];
-    const hq_status st = allow_lds(fn, allowed[kind][out][ns ? 1 + ns : p.has_ring]);
+    const int form = resident_form(p.ring, ns);
+    const void *fn = kind == kResBytes    ? hq_resident_bytes(out, form)
+                     : kind == kResPlanes ? hq_resident_planes(out, form)
+                     : kind == kResSum  ? hq_resident_sum(out, form)
+                                        : hq_resident_pertap(out, form);
+    static std::atomic<uint64_t> allowed[4][3][7];
+    const hq_status st = allow_lds(fn, allowed[kind][out][form]);
     if (st != HQ_OK) return st;
     void *args[] = {&a};
     if (hipLaunchKernel(fn, dim3(static_cast<unsigned>(tiles)), dim3(64 * p.nw), args, p.lds, stream) != hipSuccess)

@@ -113,7 +113,6 @@ __host__ __device__ constexpr int resident_unrolled(int kind, int out, int ns) {
 }
 // bytes of a step's weights for 32 channels, a slot of a ring
 __host__ __device__ constexpr int resident_slot_bytes(int kind) { return kind == kResBytes ? 2048 : 1024; }
-constexpr int resident_ring_slots(int) { return 3; }
 
 __host__ __device__ constexpr int resident_table_bytes(int kind, int px, int rows, int cb) {
     return (kind == kResPerTap || kind == kResBytes ? 9 : 0) * px * 4 + 2 * px * 4 + 2 * rows * 4 + cb * 256;
@@ -129,7 +128,7 @@ __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
     return __builtin_amdgcn_mfma_f32_32x32x8f16(weights, b, v16f{}, 0, 0, 0);
 }
 
-// RING: weights pass through a ring in LDS (else, where no room is left for it, straight from memory).
+// RING: slots of the ring in LDS through which weights pass, 3 or, where there is less room, 2; 0: straight from memory.
 // NS: 0, or the steps of a tap that are resident at a time, 1 .. 4: a tap is unrolled, with its weights straight from memory and one tap
 // ahead in registers, tile by tile, the folds between the tiles.  A tap so short has a fold, new addresses and masks for every 4 to 16
 // matrix instructions, and this order hides them best; with more steps the ring wins (below).  us a call, steps in a loop with a ring
@@ -137,7 +136,7 @@ __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
 //     per-pixel scales  16 x 24 x 53 x 192 13.5 -> 12.7, 3 x 64 x 64 x 384 -> 96 (a slice at a time) 18.5 -> 16.5
 //     one scale         5 x 54 x 54 x 64 10.1 -> 7.9, 24 x 33 x 22 x 192 15.5 -> 12.4, 9 x 32 x 46 x 576 -> 264 (a slice at a time) 35.9 -> 28.0
 //     width axis        4 x 49 x 48 x 192, block 16 14.7 -> 12.4;   8 bits  12 x 23 x 17 x 384 -> 392 (a slice at a time) 20.2 -> 18.2
-template <int OUT, int KIND, bool RING, int NS>
+template <int OUT, int KIND, int RING, int NS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
     constexpr bool WHOLE_TAPS = KIND == kResPerTap && OUT == kOutF32;   // (see the offset of the weights above)
@@ -147,9 +146,9 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     constexpr int STEP = BYTES ? 64 : 32;   // bytes of a step of 64 codes
     // Steps of an item of the fill, and items whose loads are in flight.  Items of one step have an address, a branch and an atomic sum
     // for every 16 bytes a lane; us a call, items of one step, four in flight -> of three: one scale 2 x 23 x 23 x 576 13.9 -> 12.8,
-    // per-pixel scales 7 x 12 x 8 x 768 -> 216 17.9 -> 17.0, 8 bits 1 x 16 x 16 x 384 11.3 -> 10.7.  The forms of three planes (2 .. 10 %
-    // slower with three steps), and of 8 bits with a ring (1.5 %), keep to one.
-    constexpr int PIECES = NS ? NS : IN == 1 || (BYTES && !RING) ? 3 : 1, AHEAD = 2;
+    // per-pixel scales 7 x 12 x 8 x 768 -> 216 17.9 -> 17.0.  The forms of three planes (2 .. 10 % slower with three steps) and of 8 bits
+    // (eight waves, 2 %) keep to one.
+    constexpr int PIECES = NS ? NS : IN == 1 ? 3 : 1, AHEAD = 2;
     using Out = typename OutT<OUT>::type;
     using Operand = std::conditional_t<BYTES, v4i, v8i>;
     using Acc = std::conditional_t<BYTES, v16i, v16f>;
@@ -199,7 +198,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     // instructions that the KiB feeds.  In rows 8..15 mod 16 (BYTES: 4..7, 8..11, 12..15) the pieces change places, so that
     // the operand reads meet no bank conflict.  Every step requests one (past the share's end its last one again), so the
     // number of requests in flight is always the same.
-    constexpr int R = resident_ring_slots(KIND), SLOT = resident_slot_bytes(KIND), DMAS = SLOT / 1024;
+    constexpr int R = RING, SLOT = resident_slot_bytes(KIND), DMAS = SLOT / 1024;
     const v4i w_buf = buffer_words(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
     const uint32_t ring_at = a.ring + wv * a.ring_stride;   // (uniform)
     const uint32_t ring = lds_address(lds) + ring_at;
@@ -220,14 +219,14 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     };
     v4i raw[WP];             // weights of the next step (BYTES: of this step) as they lie in memory
     auto request = [&]() {   // the next position into its slot
-        if constexpr (RING) {
+        if constexpr (RING > 0) {
 #pragma unroll
             for (int j = 0; j < DMAS; ++j) load_to_ring(w_buf, w_row[j], f_off, ring + slot + j * 1024);
             advance();
         }
     };
     auto take = [&]() {      // raw <- the next slot; R - 1 steps were requested after it
-        if constexpr (RING) {
+        if constexpr (RING > 0) {
             wait_vmem<(R - 1) * DMAS>();
             asm volatile("" ::: "memory");
             slot = slot == (R - 1) * SLOT ? 0 : slot + SLOT;
@@ -262,7 +261,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             const int row = BYTES ? j * 16 + (lane >> 2) : lane >> 1;
             w_row[j] = row_of(row) + (BYTES ? (lane & 3) ^ ((row >> 2) & 3) : (lane & 1) ^ ((row >> 3) & 1)) * 16;
         }
-        if constexpr (!RING) w_row[0] = row_of(l) + h * 16;
+        if constexpr (RING == 0) w_row[0] = row_of(l) + h * 16;
         // (a tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only)
         const int grain = NS ? NS : OUT == kOutF32 ? 3 : 1, grains = (ns + grain - 1) / grain;
         auto cut = [&](int of) {
@@ -276,7 +275,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         f_tap_last = tap * cb + (s0 + ns - 1) * STEP;
         f_last = last_tap * cb + (s0 + q_end - 1 - last_tap * ns) * STEP;
         if constexpr (NS > 0) take_tap(tap);
-        if constexpr (RING) {
+        if constexpr (RING > 0) {
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 slot = i * SLOT;
@@ -414,10 +413,11 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             }
         }
         if (s0 == 0) {
-            // The weights of the workgroup's channels start their way into the L2: from HBM they would take longer than the ring
-            // looks ahead.  A word of every line, which nobody waits for; workgroups that share the channels take an eighth each.
+            // The weights of the workgroup's channels start their way into the L2: from HBM they would take longer than the loop over
+            // steps looks ahead.  A word of every line; workgroups that share the channels take an eighth each.  us a call, weights not in
+            // L2, without -> with, no ring: 1 x 63 x 63 x 768 28.3 -> 25.9.  (8 bits without a ring: 1.5 % slower with it.)
             const uint32_t line = ((px_tile & 7) * nt + tid) * 128u, size = static_cast<uint32_t>(min(blocks * 32, a.n - c_wg)) * (TAPS * cb);
-            if (RING && line < size) touched = *reinterpret_cast<const int *>(a.wq + static_cast<uint32_t>(c_wg) * (TAPS * cb) + line);
+            if (NS == 0 && (RING > 0 || !BYTES) && line < size) touched = *reinterpret_cast<const int *>(a.wq + static_cast<uint32_t>(c_wg) * (TAPS * cb) + line);
             if constexpr (ROW_SCALES) {
                 if (tid < rows) s_rowscale[tid] = t_scale[0];
                 if (tid + nt < rows) s_rowscale[tid + nt] = t_scale[1];
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     k = 0;
                     ++tap;
                 }
-                if constexpr (RING) wait_vmem<0>();   // (nothing arrives in the ring any more)
+                if constexpr (RING > 0) wait_vmem<0>();   // (nothing arrives in the ring any more)
             }
             asm volatile("" : : "v"(touched));
             if (s0 + ns < steps) break;   // the sums go on with the next chunk (one phase: host)
@@ -920,13 +920,15 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 
 // One form's kernels by output type and the last two parameters (a file each, so that they compile in parallel).
 #define HQ_RESIDENT_FORM(NAME, KIND)                                                                            \
-    const void *NAME(int out, bool ring, int ns) {                                                              \
-        static const void *const kernels[3][6] = {                                                              \
+    const void *NAME(int out, int form) {                                                                       \
+        static const void *const kernels[3][7] = {                                                              \
             HQ_RESIDENT_FORM_OUT(kOutF16, KIND), HQ_RESIDENT_FORM_OUT(kOutF32, KIND), HQ_RESIDENT_FORM_OUT(kOutI32, KIND)}; \
-        return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][ns ? 1 + ns : ring];                        \
+        return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][form];                                      \
     }
 #define HQ_RESIDENT_FORM_OUT(OUT, KIND)                                                                         \
-    {HQ_RESIDENT_FN(OUT, KIND, false, 0), HQ_RESIDENT_FN(OUT, KIND, true, 0), HQ_RESIDENT_FN(OUT, KIND, false, 1), \
-     HQ_RESIDENT_FN(OUT, KIND, false, 2), HQ_RESIDENT_FN(OUT, KIND, false, 3), HQ_RESIDENT_FN(OUT, KIND, false, 4)}
+    {HQ_RESIDENT_FN(OUT, KIND, 0, 0), HQ_RESIDENT_FN(OUT, KIND, 0, 1), HQ_RESIDENT_FN(OUT, KIND, 0, 2), HQ_RESIDENT_FN(OUT, KIND, 0, 3), \
+     HQ_RESIDENT_FN(OUT, KIND, 0, 4), HQ_RESIDENT_FN(OUT, KIND, 2, 0), HQ_RESIDENT_FN(OUT, KIND, 3, 0)}
 #define HQ_RESIDENT_FN(OUT, KIND, RING, NS)                                                                     \
     reinterpret_cast<const void *>(resident_kernel<OUT, KIND, RING, resident_unrolled(KIND, OUT, NS)>)
+// form: the steps of an unrolled tap (1 .. 4), else 0 without a ring or 3 more than its slots
+constexpr int resident_form(int ring, int ns) { return ns ? ns : ring ? ring + 3 : 0; }

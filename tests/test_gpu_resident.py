@@ -288,13 +288,18 @@ def test_conv3x3_one_scale_empty_sums(hq, nb, h, w, cin, cout):
     (2, 7, 8, 64, 40), (1, 33, 24, 128, 33), (3, 9, 16, 192, 72), (2, 7, 8, 256, 40),   # taps of one to four steps: unrolled
     (2, 7, 8, 320, 40),          # five: a loop, the second item of the fill is not whole
     (7, 24, 40, 192, 200),       # two pixel groups a workgroup, several phases
-    (1, 5, 136, 384, 40),        # three steps resident at a time
+    (1, 243, 136, 384, 8),       # three steps resident at a time, with per-pixel scales and on the width axis
+    (1, 3, 56, 960, 40),         # one scale: a ring of two slots
+    (1, 3, 88, 448, 40),         # per-pixel scales: a ring of two slots
+    (1, 3, 88, 960, 40),         # and nine steps resident at a time
+    (1, 3, 24, 640, 40),         # 8 bits: a ring of two slots
+    (1, 13, 13, 576, 40),        # few workgroups of four waves: all of the LDS for each
 ])
 def test_conv3x3_steps_of_a_tap(hq, nb, h, w, cin, cout):
     """Every form, unrolled and not, with every type of results: integer sums bit for bit, fp32 results to 1e-5 of the largest (the width
     axis 1e-6, three roundings), fp16 to 1e-3 (one rounding, 4.9e-4)."""
     rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
-    if w == 136:
+    if (w, cin) in ((136, 384), (88, 960)):
         assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout).endswith("slices in turn)")
     sx = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
     sw = rng.uniform(1e-5, 1e-3, cout).astype(np.float32)   # (fp16 results of 8-bit codes stay in range)
@@ -314,7 +319,7 @@ def test_conv3x3_steps_of_a_tap(hq, nb, h, w, cin, cout):
     check(hq.hq_int_conv2d, x4, dev(sx), w4, acc_o, y_o, 1e-5)
     acc_o, y_o = oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1)
     check(hq.hq_int_conv2d_static, x4, s1, w4, acc_o, y_o, 1e-5)
-    block = 8
+    block = 8 if w % 8 == 0 else 1
     hb = np.array([[(-1) ** bin(i & j).count("1") for j in range(block)] for i in range(block)])
     u = np.einsum("nhbic,ij->nhbjc", xq.astype(np.int64).reshape(nb, h, w // block, block, cin), hb).reshape(nb, h, w, cin)
     d0 = (u + 8) % 16 - 8
