@@ -11,10 +11,10 @@ namespace {
 //     even where 128-channel tiles waste nothing: three waves per SIMD hide the latencies of
 //     the chunk loop better than two, which outweighs the extra nibble expansion;
 //   - but where those are more than one round (three per CU) and 128 x 128 tiles are not (two per CU), a second, nearly
-//     empty round costs as much as the larger tile, which reads fewer operand bytes per product.  us per layer with the
-//     quantiser, 64 x 128 -> 128 x 128: 4096 x 576 -> 1984 15.4 -> 14.2, 2048 x 960 -> 3840 18.95 -> 18.4, 16384 x 960 -> 512
-//     27.1 -> 26.2, three weight planes 4096 x 576 -> 1728 24.2 -> 22.3.  Not for short K (4096 x 192 -> 1600 10.25 -> 10.4,
-//     6200 x 384 -> 1280 13.7 -> 13.85): there the results are most of the time and the third workgroup hides them;
+//     empty round costs as much as the larger tile, which reads fewer operand bytes per product.  us a call, 64 x 128 ->
+//     128 x 128: 4096 x 1536 -> 1984 20.6 -> 18.3, 2048 x 2304 -> 3840 26.0 -> 23.3, three weight planes 4096 x 192 -> 1984
+//     11.9 -> 11.1.  Not for short K (6200 x 384 -> 1280 13.7 -> 13.85): there the results are most of the time and the third
+//     workgroup hides them.  (Of one plane, layers of 576 to 1344 channels that would meet the rule go to hq_linear_fp6.hip.)
 //   - otherwise 128 x 128 tiles if there is at least one per CU;
 //   - a layer with fewer tiles takes 64 x 64 tiles at four workgroups per CU.
 enum class Tile { t128x128, t64x128, t64x64 };

@@ -4,17 +4,28 @@ import pytest
 torch = pytest.importorskip("torch")
 
 
-# Every tile height (32, 64 and 128 tokens), padded and whole units of steps, 4 and 8 waves, blocks of channels that are not whole,
-# the longest K that fits and one that does not, a large layer of K a multiple of 192; -8 among the codes.  The sums are whole
-# numbers below 2^24: the integer result is equal, fp32 results are a few roundings (the scales, 4; with the planes' weights and
-# sums, 8) from the exact value, fp16 results half an ulp more.
+# Every cut (tokens / waves / steps of a unit) with and without a padded unit, blocks of channels that are not whole, the longest K
+# that fits and the next, large layers of K a multiple of 192; -8 among the codes.  The sums are whole numbers below 2^24: the integer
+# result is equal, fp32 results are a few roundings (the scales, 4; with the planes' weights and sums, 8) from the exact value, fp16
+# results half an ulp more.  (The planes take the same cuts by their own costs.)
 @pytest.mark.gpu
-@pytest.mark.parametrize("m,k,n", [(1, 64, 1), (33, 64, 40), (31, 128, 8), (130, 320, 333), (1000, 640, 96), (2100, 448, 1000),
-                                   (9000, 704, 640), (70000, 64, 72), (4300, 768, 1160), (40, 6400, 33), (40, 6784, 33),
-                                   (700, 2560, 264), (20, 8192, 40)])
-def test_linear_sums_are_exact(m, k, n):
+@pytest.mark.parametrize("m,k,n,cut", [
+    (1, 64, 1, "64/4/2"), (33, 64, 40, "64/4/2"), (31, 128, 8, "64/4/2"), (130, 320, 333, "32/4/5"), (1000, 640, 96, "32/4/5"),
+    (2100, 448, 1000, "64/8/4"), (9000, 704, 640, "128/8/4"), (70000, 64, 72, "128/4/2"), (4300, 768, 1160, "128/8/4"),
+    (40, 6400, 33, "tile"), (40, 6784, 33, "tile"), (700, 2560, 264, "32/4/8"), (20, 8192, 40, "tile"),
+    (40, 6080, 33, "32/4/8"), (40, 6208, 33, "tile"), (40, 1088, 33, "32/4/3"), (40, 704, 33, "32/4/4"),
+    (40, 256, 33, "32/4/4"), (4487, 128, 130, "32/8/3"), (721, 1344, 5579, "32/8/3"), (4180, 256, 147, "32/8/4"),
+    (4431, 704, 137, "32/8/4"), (4250, 320, 138, "32/8/5"), (4281, 896, 129, "32/8/5"), (4394, 512, 130, "32/8/8"),
+    (4354, 448, 132, "32/8/8"), (2199, 384, 3693, "64/4/3"), (8457, 896, 33, "64/4/3"), (8231, 256, 40, "64/4/4"),
+    (8215, 448, 40, "64/4/4"), (8378, 128, 135, "64/8/2"), (9266, 64, 134, "64/8/2"), (15290, 1344, 146, "64/8/3"),
+    (8432, 320, 134, "64/8/3"), (8663, 256, 130, "64/8/4"), (9179, 128, 262, "128/4/2"), (8649, 320, 266, "128/4/3"),
+    (8710, 256, 288, "128/4/4"), (8984, 448, 261, "128/4/4"), (8508, 1344, 269, "128/4/3"), (10667, 128, 514, "128/8/2"),
+    (12430, 64, 385, "128/8/2"), (7413, 576, 703, "128/8/3"), (11722, 320, 265, "128/8/3")])
+def test_linear_sums_are_exact(m, k, n, cut):
     import paper_2512_05746_amd as hq
 
+    name = "tile" if cut == "tile" else "linear (%s tokens, %s waves, units of %s)" % tuple(cut.split("/"))
+    assert hq.hq_int_conv2d_kernel_name(1, 1, m, k, n, ksize=1) == name
     g = torch.Generator(device="cuda")
     g.manual_seed(m + k + n)
     xq = torch.randint(0, 256, (m, k // 2), dtype=torch.uint8, device="cuda", generator=g)

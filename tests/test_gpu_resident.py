@@ -261,12 +261,17 @@ def test_width_quant(hq, dtype, w, c, block):
 @pytest.mark.parametrize("nb,h,w,cin,cout", [
     (1, 1, 1, 64, 33),          # every tap but one outside
     (2, 3, 8, 192, 40),         # shares of a few steps, fewer than the ring holds
-    (1, 46, 46, 960, 72),       # some slices resident at a time, with a ring
-    (1, 6, 200, 960, 40),       # and without room for one
+    (1, 46, 46, 960, 72),       # all slices resident, no room for a ring of weights
+    (1, 6, 200, 960, 40),       # some slices resident at a time, nor room
+    (1, 3, 32, 960, 40),        # all slices, a ring of two slots
+    (1, 3, 48, 960, 40),        # some at a time, a ring of three slots
+    (1, 3, 56, 960, 40),        # and of two
+    (1, 5, 212, 768, 40),       # three steps at a time, unrolled
 ])
 def test_conv3x3_one_scale_empty_sums(hq, nb, h, w, cin, cout):
     """Pixels whose window holds only zeros give exactly the bias, also where codes lie just outside the image (the rows above
     and below, the other end of the neighbouring lines): whatever a tap outside leaves in a sum has to be gone."""
+    assert hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout, static_scale=True).endswith("in turn)") == (w in (200, 48, 56, 212))
     rng = np.random.default_rng(h + w + cin)
     wq = rng.integers(-8, 8, (cout, 9, cin)).astype(np.int8)
     sw = rng.uniform(0.001, 0.1, cout).astype(np.float32)

@@ -1,5 +1,6 @@
 """Parity of linear layers at the edges of the rule that takes 128 x 128 tiles where 64 x 128 ones need a second round: K (times
-digit planes) of at least 576, more than 768 tiles of 64 x 128 and at most 512 of 128 x 128 (256 CUs)."""
+digit planes) of at least 576, more than 768 tiles of 64 x 128 and at most 512 of 128 x 128 (256 CUs).  Layers of shorter K that would
+meet the rule run on the linear kernel; theirs stay here as a test of that one, and those of 1536 channels test the rule."""
 import numpy as np
 import pytest
 
@@ -23,10 +24,12 @@ def dev(a):
     (4096, 2048, 576),   # 512 large tiles: one round of them
     (4096, 2112, 576),   # 544: small tiles again
     (4096, 1537, 576),   # channels that are no multiple of 64 take large tiles anyway
+    (4096, 1536, 1536), (4096, 1600, 1536), (4033, 1600, 1536), (4096, 2048, 1536), (4096, 2112, 1536),   # the same on the tile kernel
 ])
 def test_linear_one_round(m, n, k):
     """Integer sums bit for bit, fp32 results to 1e-5, fp16 to 1e-3 (one rounding, 4.9e-4)."""
     import paper_2512_05746_amd as hq
+    assert (hq.hq_int_conv2d_kernel_name(1, 1, m, k, n, ksize=1) == "tile") == (k != 576)
     rng = np.random.default_rng(m + n + k)
     xq = rng.integers(-8, 8, (m, k)).astype(np.int8)
     wq = rng.integers(-8, 8, (n, k)).astype(np.int8)
