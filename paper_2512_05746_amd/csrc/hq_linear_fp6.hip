@@ -349,11 +349,11 @@ Cut lay_out(int k, int nt_log2, int nw) {
 // every CU the expansion of tokens, the expansion of weights, the products and the tiles stored.  Fitted to 222 calls of 1 to
 // 131072 tokens, 64 to 4096 channels in, 8 to 5120 out, six cuts each: 12 % rms; the cut it picks is 0.8 % off the best one
 // on average.
-double cut_us(const Cut &c, int64_t pixels, int n, int k, int planes) {
-    const int nt = 1 << c.nt_log2, blocks = (n + 31) / 32, steps = k / 64, cus = hq::compute_units();
+double cut_us(const Cut &c, int pixels, int n, int k, int planes, int cus) {
+    const int nt = 1 << c.nt_log2, blocks = (n + 31) / 32, steps = k / 64;
     const int ks = kUnits[c.nt_log2][c.unit], steps_p = (steps + ks - 1) / ks * ks;
-    const int64_t wgs = (pixels + 32 * nt - 1) / (32 * nt) * ((blocks + c.nw - 1) / c.nw);
-    const double per_cu = static_cast<double>((wgs + cus - 1) / cus);
+    const int64_t wgs = static_cast<int64_t>((pixels + 32u * nt - 1) >> (5 + c.nt_log2)) * ((blocks + c.nw - 1) / c.nw);
+    const double per_cu = ceil(static_cast<double>(wgs) / cus);
     const int waves = planes == 1 || nt == 1 ? 16 : nt == 2 ? 12 : 8;   // (of a CU, by registers)
     const int resident = std::max(1, std::min(kLdsPerCu / c.lds, waves / c.nw));
     const double rounds = ceil(per_cu / resident);
@@ -363,28 +363,35 @@ double cut_us(const Cut &c, int64_t pixels, int n, int k, int planes) {
 }
 
 // Whether this kernel takes the layer, and its cut.  The tile kernel is at its best where K is a multiple of 192 (its stages
-// are 96 bytes of K; other K go by stages of 32).  There it stays the faster one, by up to 15 %, below 3e9 products (1024 x 960
-// -> 960: 5.5 against 6.1 us), for planes of 192 channels, too short for what a plane costs here (16384 tokens -> 576: 15.1
-// against 15.9), and from 1536 channels on, where the tile of 128 tokens no longer fits (6784 x 1536 -> 3840: 56 against 68);
-// above 3e9 this one is (8192 x 384 -> 1152: 11.4 against 12.0 us, 2048 x 960 -> 3840: 13.0 against 14.4, 4096 x 576 -> 1728
-// in three planes: 15.9 against 20.1).  For other K this one is up to 2.5 times faster (64 x 640 -> 640: 4.7 against 7.2 us,
-// 8192 x 640 -> 640: 9.0 against 10.7, 512 x 4096 -> 1024: 14 against 30), save for many rounds of tiles of 32 tokens
-// (9535 x 4096 -> 1920: 188 against 107).
-Cut choose_cut(int64_t pixels, int n, int k, int planes) {
+// are 96 bytes of K; other K go by stages of 32) and n one of 16 (it stores groups of 16 channels whole, others value by value).
+// Where both are so it keeps the layers below 1.5e9 products (1024 x 960 -> 960: 5.5 against 6.1 us) and from 1536 channels on,
+// where the tile of 128 tokens leaves room for four waves only (2924 x 1536 -> 1968: 19.3 against 15.8).  Below 32 channels out one
+// wave of four has work (30454 x 1152 -> 24: 8.8 / 7.1).  Of the rest, layers of 192 and 384 channels come here (8192 x 384 -> 1152 11.4 /
+// 12.0; 105 of 111 are faster by 3 % and more, one is 20 % slower); from 576 on the two estimates decide, which are 10 and 7 % off (77907 x 1344 -> 64
+// 25.8 / 14.8, 23950 x 960 -> 544 26.7 / 19.9, 44867 x 768 -> 576 40.8 / 30.9; 2048 x 960 -> 3840 13.0 / 14.4, 57956 x 1344 -> 296 44.4 / 81.7).
+// For other K this kernel is up to 2.5 times faster (64 x 640 -> 640: 4.7 against 7.2 us, 8192 x 640 -> 640: 9.0 against 10.7,
+// 512 x 4096 -> 1024: 14 against 30), save for many rounds of tiles of 32 tokens (9535 x 4096 -> 1920: 188 against 107).
+Cut choose_cut(int pixels, int n, int k, int planes) {
     Cut best{};
     if (n >= 1 << 21) return best;   // (a tile's results lie within 2 GiB of their first)
     const double products = static_cast<double>(pixels) * n * k * planes;
-    if (k % 192 == 0 && (products < 3e9 || (planes > 1 && k < 384) || !lay_out(k, 2, 8).ok)) return best;
+    const bool tile_k = k % 192 == 0;
+    if (tile_k && (n < 32 || (n % 16 == 0 && products < 1.5e9) || !lay_out(k, 2, 8).ok)) return best;
+    const int cus = hq::compute_units();   // (asks the runtime for the device: once)
     double best_us = HUGE_VAL;
     for (int nt_log2 = 0; nt_log2 < 3; ++nt_log2)
         for (int nw = 4; nw <= 8; nw += 4) {
             const Cut c = lay_out(k, nt_log2, nw);
-            const double us = c.ok ? cut_us(c, pixels, n, k, planes) : HUGE_VAL;
+            const double us = c.ok ? cut_us(c, pixels, n, k, planes, cus) : HUGE_VAL;
             if (us < best_us) { best = c; best_us = us; }
         }
     if (best.ok && best.nt_log2 == 0 && !lay_out(k, 1, 4).ok) {
-        const int64_t wgs = (pixels + 31) / 32 * (((n + 31) / 32 + best.nw - 1) / best.nw);
-        best.ok = wgs <= 2 * hq::compute_units();
+        const int64_t wgs = static_cast<int64_t>((pixels + 31u) / 32) * (((n + 31) / 32 + best.nw - 1) / best.nw);
+        best.ok = wgs <= 2 * cus;
+    }
+    if (tile_k && k >= 576 && best.ok) {
+        const double us = best_us + (n % 8 ? 0.95 * 2e-6 * static_cast<double>(pixels) * n : 0);   // (stored value by value)
+        best.ok = hq_tile_linear_us(pixels, n, k, planes) >= (products < 3e9 ? 1.03 : 0.95) * us;
     }
     return best;
 }
@@ -393,7 +400,8 @@ Cut choose_cut(int64_t pixels, int n, int k, int planes) {
 
 // For the diagnostic: nullptr if the layer is one for the tile kernel.
 const char *hq_linear_cut_name(int64_t pixels, int n, int k) {
-    const Cut c = choose_cut(pixels, n, k, 1);
+    if (pixels >= INT_MAX) return nullptr;   // (refused)
+    const Cut c = choose_cut(static_cast<int>(pixels), n, k, 1);
     if (!c.ok) return nullptr;
 #define HQ_LINEAR_NAMES(TOKENS, KS) \
     {"linear (" TOKENS " tokens, 4 waves, units of " KS ")", "linear (" TOKENS " tokens, 8 waves, units of " KS ")"}
@@ -408,7 +416,7 @@ const char *hq_linear_cut_name(int64_t pixels, int n, int k) {
 // HQ_ERR_UNSUPPORTED, with nothing launched: the layer is one for the tile kernel.
 hq_status hq_linear_fp6_launch(const GemmArgs &g, int planes, hq_dtype y_dtype, hipStream_t stream) {
     if (planes > 1 && y_dtype == HQ_I32) return HQ_ERR_UNSUPPORTED;
-    const Cut c = choose_cut(g.pixels, g.n, g.k, planes);
+    const Cut c = choose_cut(static_cast<int>(g.pixels), g.n, g.k, planes);
     if (!c.ok) return HQ_ERR_UNSUPPORTED;
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     LinearArgs a{};
