@@ -1,7 +1,9 @@
-// Buffer accesses, LDS reads by address and an LDS-only barrier, shared by the kernels on the 6-bit matrix instruction.
+// Buffer accesses, LDS reads by address, an LDS-only barrier and the LDS limit, shared by the kernels on the 6-bit matrix instruction.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <atomic>
 
 #include "hq_int_gemm_kernel.h"
 
@@ -37,6 +39,18 @@ __device__ __forceinline__ v4i lds_v4i(int address, int offset = 0) {
 }
 __device__ __forceinline__ v2i lds_v2i(int address, int offset = 0) {
     return *reinterpret_cast<const __attribute__((address_space(3))) v2i *>(static_cast<uint32_t>(address) + offset);
+}
+
+constexpr int kLdsPerCu = 163840;
+
+// Dynamic LDS beyond the default limit has to be allowed once per kernel and device.
+inline hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return HQ_ERR_LAUNCH;
+    if ((done.load(std::memory_order_acquire) >> dev) & 1) return HQ_OK;
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu) != hipSuccess) return HQ_ERR_LAUNCH;
+    done.fetch_or(1ull << dev, std::memory_order_release);
+    return HQ_OK;
 }
 
 }  // namespace

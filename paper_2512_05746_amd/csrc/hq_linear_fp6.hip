@@ -14,7 +14,8 @@
 // What bounds it (2048 x 960 -> 3840, 13.0 us back to back, the int8 tile kernel 14.4): launch and first loads 2.3 us, the
 // expansion of the tokens 1.3 (issue of vector instructions), products 4.5 (2.8 of matrix instructions, the rest the expansion
 // of the weights beside them), results 1.6 (15.7 MB), from launch to launch 2.  Tiles of 128 tokens halve the weights' loads
-// and expansions against 64 (14.1 us with 64); they keep to 128 registers, so that two workgroups of 8 waves share a CU.
+// and expansions against 64 (14.1 us with 64); they keep to 128 registers, so that two workgroups of 8 waves share a CU where
+// their tokens leave room (up to K = 640).
 #include <limits.h>
 #include <math.h>
 
@@ -27,8 +28,6 @@
 #include "hq_int_gemm_kernel.h"
 
 namespace {
-
-constexpr int kLdsPerCu = 163840;
 
 struct LinearArgs {
     const uint8_t *xq;   // [pixels, k/2]
@@ -292,15 +291,6 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
             store8(res[1], t * 32 + l, c0 + 16 * h + 8);
         }
     }
-}
-
-hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return HQ_ERR_LAUNCH;
-    if ((done.load(std::memory_order_acquire) >> dev) & 1) return HQ_OK;
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu) != hipSuccess) return HQ_ERR_LAUNCH;
-    done.fetch_or(1ull << dev, std::memory_order_release);
-    return HQ_OK;
 }
 
 constexpr int kUnits[3][4] = {{8, 5, 4, 3}, {4, 3, 2, 2}, {4, 3, 2, 2}};   // KS of the tiles of 32, 64 and 128 tokens

@@ -11,8 +11,6 @@ const void *hq_resident_bytes(int out, int form);
 
 namespace {
 
-constexpr int kLdsPerCu = 163840;
-
 struct Plan {
     int ks, slices, chunk, nw, xw_log2, cb, rows, ring;   // ring: slots
     uint32_t part8, exchange, ring_at, ring_stride, tables, lds;
@@ -71,9 +69,9 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     return p;
 }
 
-// Clocks of a workgroup, fitted to time stamps of the kernel on 3x3 layers of 64 to 960 channels (within 15 % of
-// them, and in the measured order of the cuts): start and first loads, filling (rounds of 32-row items over the waves),
-// units (two waves per SIMD share the vector issue), results (each exchange of sums costs two barriers).
+// Clocks of a workgroup, fitted to time stamps of the kernel's form with weights in registers for all layers of 64 to 960 channels
+// (within 15 % of them): start and first loads, filling (rounds of 32-row items over the waves), units (two waves per SIMD share
+// the vector issue), results (each exchange of sums costs two barriers).  The loop with a ring and the unrolled taps take fewer.
 struct Cost { double clocks, rounds; };
 Cost cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
     const int px = 128 << p.xw_log2, blocks = (n + 31) / 32, planes = kind >= kResPlanes ? 2 : 1;
@@ -142,16 +140,6 @@ Plan choose_kernel(int kind, int had_block, int64_t pixels, int w, int k, int n)
 }
 
 int kind_of(int bits, int sx_static) { return bits == 8 ? kResBytes : sx_static ? kResSum : kResPerTap; }
-
-// Dynamic LDS beyond the default limit has to be allowed once per kernel and device.
-hq_status allow_lds(const void *fn, std::atomic<uint64_t> &done) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return HQ_ERR_LAUNCH;
-    if ((done.load(std::memory_order_acquire) >> dev) & 1) return HQ_OK;
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu) != hipSuccess) return HQ_ERR_LAUNCH;
-    done.fetch_or(1ull << dev, std::memory_order_release);
-    return HQ_OK;
-}
 
 }  // namespace
 

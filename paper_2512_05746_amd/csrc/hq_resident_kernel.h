@@ -19,9 +19,9 @@
 // The other half of a launch is what surrounds the loop: start and first loads (2 us), expanding the tile (2 .. 4 us;
 // 24 instructions per 16 codes for the signed form), exchange and results (2 .. 5 us).
 //
-// Measured (3x3, 4-bit, us per pass with the quantiser, weights in L2; kernel with weights in registers -> this one):
-//     per-pixel scales: 8 x 16 x 16 x 960 25.3 -> 24.3, 3 x 45 x 27 x 320 -> 200 14.2 -> 13.8, 3 x 44 x 44 x 576 -> 152 17.2 -> 16.9
-//     one scale:       16 x 32 x 32 x 384 28.5 -> 28.0, 4 x 46 x 46 x 960 -> 488 68.7 -> 66.8
+// Measured (3x3, 4-bit, us a call, weights in L2; kernel with weights in registers for every form -> this one):
+//     per-pixel scales: 8 x 16 x 16 x 960 23.4 -> 21.9, 3 x 45 x 27 x 320 -> 200 11.4 -> 10.8, 3 x 44 x 44 x 576 -> 152 13.3 -> 13.1
+//     one scale:       16 x 32 x 32 x 384 26.2 -> 25.1, 4 x 46 x 46 x 960 -> 488 63.4 -> 60.3
 //
 // Phases.  The tasks (pixel group, channel block) of a workgroup are dealt out to its NW waves in phases: NW at a
 // time, then the remainder in powers of two, the units of a task shared by 2, 4 or 8 waves whose sums meet in
@@ -30,18 +30,18 @@
 // Digit planes (the width-axis form).  The activations are numbers u = d0 + 16 d1 + 256 d2 in three planes of base-16
 // digits; d1 + 16 d2 lies in -16..16 up to transform block 32, which E2M3 still holds, so two operand planes are enough:
 // the fill combines the upper two, and their products are multiplied by 16 by the block exponent of the matrix
-// instruction.  A unit expands its weights once for both planes.  16 x 16 x 16 x 576, block 16: 33.8 us against 76.7 on the
+// instruction.  A unit expands its weights once for both planes.  16 x 16 x 16 x 576, block 16: 28.9 us against 76.7 on the
 // tile kernel, which streams weights and all three planes through LDS.
 //
 // 8-bit codes (the form of 16-byte operands on v_mfma_i32_32x32x32_i8, nothing to expand on either side; the two
 // 32-channel halves of a step take the places of two operand planes, each with weights of its own).  Matrix time is twice
-// that of 4-bit codes and bounds it: 42 clocks an MFMA of 32, at the 1.5 GHz that the chip holds under them.  us per pass with
-// the quantiser, weights in registers and a fold of twice the instructions for every 192 channels -> this form: 16 x 32 x 32 x 384
-// 43.7 -> 39.1, 2 x 24 x 40 x 640 31.3 -> 27.4.
+// that of 4-bit codes and bounds it: 42 clocks an MFMA of 32, at the 1.5 GHz that the chip holds under them.  us a call,
+// weights in registers and a fold of twice the instructions for every 192 channels -> this form: 16 x 32 x 32 x 384 40.3 -> 34.4,
+// 2 x 24 x 40 x 640 25.9 -> 20.1.
 //
 // One scale: taps outside the image must add nothing.  Their products are multiplied by 2^-127 (the block exponent that the matrix
 // instruction takes for every column) instead of reading a row of zeros, which would cost every tile an address of its own
-// in every step (16 x 32 x 32 x 384: 31.2 -> 26.2 us); what they leave, below 1e-35, is rounded away before the sums are scaled.
+// in every step; what they leave, below 1e-35, is rounded away before the sums are scaled.
 //
 // Which layers come here and which stay on the tile kernel: choose_kernel in hq_resident.hip.
 //
@@ -93,7 +93,8 @@ constexpr int kResBytes = 3;    // as kResPerTap, with 8-bit codes on the int8 i
 
 // Direct-to-LDS load of 16 bytes a lane: lane i's land at lds_base + 16 i.  Inline assembly, because the compiler cannot tell which
 // slot of a ring such a load fills and would wait for all of them before every LDS read; the waits (wait_vmem) are placed by
-// hand.  (Its own counted waits stay right: they only wait for more.)
+// hand.  (Its own counted waits stay right: they only wait for more.  m0 is reserved, the compiler sets it before each use of its own
+// and takes no clobber of it.)
 __device__ __forceinline__ v4i buffer_words(const void *p, uint32_t bytes) {   // a buffer as four scalar registers
     const uint64_t at = reinterpret_cast<uint64_t>(p);
     return v4i{static_cast<int>(at), static_cast<int>(at >> 32 & 0xFFFF), static_cast<int>(bytes), 0x00027000};
