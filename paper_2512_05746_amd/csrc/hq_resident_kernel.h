@@ -416,9 +416,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         if (s0 == 0) {
             // The weights of the workgroup's channels start their way into the L2: from HBM they would take longer than the loop over
             // steps looks ahead.  A word of every line; workgroups that share the channels take an eighth each.  us a call, weights not in
-            // L2, without -> with, no ring: 1 x 63 x 63 x 768 28.3 -> 25.9.  (8 bits without a ring: 1.5 % slower with it.)
+            // L2, without -> with, no ring: 1 x 63 x 63 x 768 28.3 -> 25.9.  (Forms of two operand
+            // planes, without a ring: 8 bits 1.5 % slower with it, 16 x 16 x 16 x 576 on the width axis 29.3 -> 29.7.)
             const uint32_t line = ((px_tile & 7) * nt + tid) * 128u, size = static_cast<uint32_t>(min(blocks * 32, a.n - c_wg)) * (TAPS * cb);
-            if (NS == 0 && (RING > 0 || !BYTES) && line < size) touched = *reinterpret_cast<const int *>(a.wq + static_cast<uint32_t>(c_wg) * (TAPS * cb) + line);
+            if (NS == 0 && (RING > 0 || PL == 1) && line < size) touched = *reinterpret_cast<const int *>(a.wq + static_cast<uint32_t>(c_wg) * (TAPS * cb) + line);
             if constexpr (ROW_SCALES) {
                 if (tid < rows) s_rowscale[tid] = t_scale[0];
                 if (tid + nt < rows) s_rowscale[tid + nt] = t_scale[1];
