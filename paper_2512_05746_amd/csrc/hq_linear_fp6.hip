@@ -98,14 +98,17 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
     const uint32_t w_lane = static_cast<uint32_t>(co < a.n ? co : a.n - 1) * a.row_bytes + h * 16;
     const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * a.row_bytes);
     int ld_step = 0, ld_plane = 0;   // of the next weights to load
+    uint32_t ld_at = 0;              // and where they are in the row
     auto load_weights = [&](v4i &raw) {
         // Padding steps, and what follows the last: zeros, from beyond the tensor, which ends at 2^32 - 32 at most.  (The uniform
         // offset stays within the tensor: the bound that the lanes' offsets are held against is what it leaves of the size.)
         const bool real = ld_step < steps && ld_plane < a.planes;
-        raw = buffer_load16(w_buf, w_lane | (real ? 0u : 0xFFFFFFE0u), real ? static_cast<uint32_t>(ld_plane * cb + ld_step * 32) : 0u);
+        raw = buffer_load16(w_buf, w_lane | (real ? 0u : 0xFFFFFFE0u), real ? ld_at : 0u);
+        ld_at += 32;
         if (++ld_step == steps_p) {
             ld_step = 0;
             ++ld_plane;
+            ld_at = static_cast<uint32_t>(ld_plane * cb);
         }
     };
     v4i raw[KS];
