@@ -21,9 +21,8 @@ namespace {
 //   - a layer with fewer tiles takes 64 x 64 tiles at four workgroups per CU.
 enum class Tile { t128x128, t64x128, t64x64 };
 
-Tile choose_tile(int64_t pixels, int n, int k, int bits, int taps) {
+Tile choose_tile(int64_t pixels, int n, int k, int bits, int taps, int64_t cus) {
     if ((bits == 8 ? k : k / 2) % 96 != 0) return Tile::t128x128;
-    const int64_t cus = hq::compute_units();
     const int64_t pix128 = (pixels + 127) / 128, tiles64 = pix128 * ((n + 63) / 64), tiles128 = pix128 * ((n + 127) / 128);
     if (bits == 4 && taps <= 3 && taps * k >= 576 && tiles64 > 3 * cus && tiles128 <= 2 * cus) return Tile::t128x128;
     if (n % 64 == 0 && pix128 * (n / 64) >= 2 * cus) return Tile::t64x128;
@@ -31,7 +30,7 @@ Tile choose_tile(int64_t pixels, int n, int k, int bits, int taps) {
 }
 
 hq_status launch_gemm(const GemmArgs &a, int taps, hq_dtype y_dtype, hipStream_t stream) {
-    switch (choose_tile(a.pixels, a.n, a.k, a.bits, taps)) {
+    switch (choose_tile(a.pixels, a.n, a.k, a.bits, taps, hq::compute_units())) {
         case Tile::t128x128: return hq_gemm_launch_128x128(a, taps, y_dtype, stream);
         case Tile::t64x128: return hq_gemm_launch_64x128(a, taps, y_dtype, stream);
         default: return hq_gemm_launch_64x64(a, taps, y_dtype, stream);
@@ -53,12 +52,13 @@ double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had
     constexpr Costs bytes{5.1, 0.24, {5.67, 1.67}, {0, 2.00}, {0, 4.40}, {1.66, 0.71}};
     constexpr Costs planes{6.4, 0.51, {11.6, 1.31}, {0, 3.44}, {4.00, 7.00}, {3.30, 1.22}};
     const Costs &c = had_block ? planes : bits == 8 ? bytes : sx_static ? one_sum : per_tap;
-    const Tile tile = choose_tile(pixels, n, k, bits, 9);
+    const int cus = hq::compute_units();   // (asks the runtime for the device)
+    const Tile tile = choose_tile(pixels, n, k, bits, 9, cus);
     const int pt = tile == Tile::t64x64 ? 64 : 128, ct = tile == Tile::t128x128 ? 128 : 64;
     const int per_round = tile == Tile::t64x64 ? 4 : tile == Tile::t64x128 ? 3 : 2;   // (workgroups of a CU)
     const int64_t total = (pixels + pt - 1) / pt * ((n + ct - 1) / ct);
     if (static_cast<double>(total) * ((bits == 8 ? k : k / 2) / 32) * (had_block ? 27 : 9) > 0x7fffffff) return HUGE_VAL;   // (refused)
-    const double tiles = static_cast<double>(total) / hq::compute_units();
+    const double tiles = static_cast<double>(total) / cus;
     const double rounds = ceil(tiles / per_round), used = (rounds - 1) * per_round + ceil(tiles - (rounds - 1) * per_round);
     const auto &cost = (bits == 8 ? k : k / 2) % 96 != 0 ? c.short_chunks
                        : tile == Tile::t64x128           ? c.t64x128
@@ -74,11 +74,11 @@ double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had
 // The same for linear layers whose K is a multiple of 192: start, results (per MB of fp16; beyond what the caches take they cost more),
 // and for every 64 channels of a plane what a round of a CU's tiles and each of its tiles cost.  Fitted to 790 layers of 64 to
 // 131072 tokens, 1.5e9 to 6e10 products, one and three planes: 7 % rms.
-double hq_tile_linear_us(int64_t pixels, int n, int k, int planes) {
-    const Tile tile = choose_tile(pixels, n, k, 4, planes);
+double hq_tile_linear_us(int64_t pixels, int n, int k, int planes, int cus) {
+    const Tile tile = choose_tile(pixels, n, k, 4, planes, cus);
     const int pt = tile == Tile::t64x64 ? 64 : 128, ct = tile == Tile::t128x128 ? 128 : 64;
     const int per_round = tile == Tile::t64x64 ? 4 : tile == Tile::t64x128 ? 3 : 2;   // (workgroups of a CU)
-    const double tiles = static_cast<double>((pixels + pt - 1) / pt * ((n + ct - 1) / ct)) / hq::compute_units();
+    const double tiles = static_cast<double>((pixels + pt - 1) / pt * ((n + ct - 1) / ct)) / cus;
     const double rounds = ceil(tiles / per_round), used = (rounds - 1) * per_round + ceil(tiles - (rounds - 1) * per_round);
     const double result_mb = static_cast<double>(pixels) * n * 2e-6, steps = k / 64 * planes;
     const double start = 3.46 + result_mb * (n % 16 ? 1.76 : 0.153) + std::max(0.0, result_mb - 64) * 0.015;

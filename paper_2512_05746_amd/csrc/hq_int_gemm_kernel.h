@@ -956,6 +956,6 @@ const char *hq_linear_cut_name(int64_t pixels, int n, int k);
 // estimated time of a stride-1 3x3 layer on the tile kernel of this file (hq_int_gemm.hip)
 double hq_tile_us(int64_t pixels, int n, int k, int bits, int sx_static, int had_block);
 // and of a linear layer of 4-bit codes whose K is a multiple of 192, planes of its weights multiplied
-double hq_tile_linear_us(int64_t pixels, int n, int k, int planes);
+double hq_tile_linear_us(int64_t pixels, int n, int k, int planes, int cus);
 // how that kernel cuts a layer of codes (not planes), a static string, or null where it does not take the layer
 const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, int sx_static);

@@ -384,7 +384,7 @@ Cut choose_cut(int pixels, int n, int k, int planes) {
     }
     if (tile_k && k >= 576 && best.ok) {
         const double us = best_us + (n % 8 ? 0.95 * 2e-6 * static_cast<double>(pixels) * n : 0);   // (stored value by value)
-        best.ok = hq_tile_linear_us(pixels, n, k, planes) >= (products < 3e9 ? 1.03 : 0.95) * us;
+        best.ok = hq_tile_linear_us(pixels, n, k, planes, cus) >= (products < 3e9 ? 1.03 : 0.95) * us;
     }
     return best;
 }
