@@ -359,8 +359,9 @@ double cut_us(const Cut &c, int pixels, int n, int k, int planes, int cus) {
 // are 96 bytes of K; other K go by stages of 32) and n one of 16 (it stores groups of 16 channels whole, others value by value).
 // Where both are so it keeps the layers below 1.5e9 products (1024 x 960 -> 960: 5.5 against 6.1 us) and from 1536 channels on,
 // where the tile of 128 tokens leaves room for four waves only (2924 x 1536 -> 1968: 19.3 against 15.8).  Below 32 channels out one
-// wave of four has work (30454 x 1152 -> 24: 8.8 / 7.1).  Of the rest, layers of 192 and 384 channels come here (8192 x 384 -> 1152 11.4 /
-// 12.0; 105 of 111 are faster by 3 % and more, one is 20 % slower); from 576 on the two estimates decide, which are 10 and 7 % off (77907 x 1344 -> 64
+// wave of four has work (30454 x 1152 -> 24: 8.8 / 7.1).  Of the rest, layers of 192 and 384 channels of one plane come here (8192 x 384 ->
+// 1152 11.4 / 12.0; 105 of 111 are faster by 3 % and more, one is 20 % slower); from 576 on, and for digit planes, the two estimates
+// decide, which are 10 and 7 % off, so it has to be 8 % ahead for small layers and not 5 % behind for large ones (77907 x 1344 -> 64
 // 25.8 / 14.8, 23950 x 960 -> 544 26.7 / 19.9, 44867 x 768 -> 576 40.8 / 30.9; 2048 x 960 -> 3840 13.0 / 14.4, 57956 x 1344 -> 296 44.4 / 81.7).
 // For other K this kernel is up to 2.5 times faster (64 x 640 -> 640: 4.7 against 7.2 us, 8192 x 640 -> 640: 9.0 against 10.7,
 // 512 x 4096 -> 1024: 14 against 30), save for many rounds of tiles of 32 tokens (9535 x 4096 -> 1920: 188 against 107).
@@ -382,9 +383,9 @@ Cut choose_cut(int pixels, int n, int k, int planes) {
         const int64_t wgs = static_cast<int64_t>((pixels + 31u) / 32) * (((n + 31) / 32 + best.nw - 1) / best.nw);
         best.ok = wgs <= 2 * cus;
     }
-    if (tile_k && k >= 576 && best.ok) {
+    if (tile_k && (k >= 576 || planes > 1) && best.ok) {
         const double us = best_us + (n % 8 ? 0.95 * 2e-6 * static_cast<double>(pixels) * n : 0);   // (stored value by value)
-        best.ok = hq_tile_linear_us(pixels, n, k, planes, cus) >= (products < 3e9 ? 1.03 : 0.95) * us;
+        best.ok = hq_tile_linear_us(pixels, n, k, planes, cus) >= (products < 3e9 || k < 384 ? 1.08 : 0.95) * us;
     }
     return best;
 }
