@@ -174,25 +174,29 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     a.out_scale = g.out_scale;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
-    a.chunk = p.chunk * p.ks; a.ring = p.ring_at; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
+    const int steps = g.k / 64, resident = std::min(p.chunk * p.ks, steps), last = steps % resident ? steps % resident : resident;
+    a.chunk = resident;
+    a.inverses = inverse_of(resident) | inverse_of((resident + 2) / 3) << 16;
+    a.inverses_last = inverse_of(last) | inverse_of((last + 2) / 3) << 16;
+    a.waves = p.nw;
+    a.ring = p.ring_at; a.ring_stride = p.ring_stride; a.ring_shared = p.ring_shared; a.xw_log2 = p.xw_log2; a.cb = p.cb; a.rows = p.rows;
     a.wide = p.wide; a.part8 = p.part8; a.exchange = p.exchange; a.tables = p.tables;
     const int px = 128 << p.xw_log2, blocks = (g.n + 31) / 32;
     const int64_t px_tiles = (static_cast<int64_t>(g.pixels) + px - 1) / px, ch_groups = (blocks + p.cb - 1) / p.cb;
     const int64_t tiles = px_tiles * ch_groups;
     if (tiles > 0x7fffffff) return HQ_ERR_SHAPE;
-    a.px_tiles = static_cast<uint32_t>(px_tiles);
-    a.ch_groups = static_cast<uint32_t>(ch_groups);
+    a.tiles = static_cast<uint32_t>(tiles);
     // the larger operand is the one that an XCD's run of tiles shares
     a.ch_major = static_cast<int64_t>(g.n) * 9 > static_cast<int64_t>(g.pixels);
-    const hq::Magic31 md = hq::magic31(a.ch_major ? a.px_tiles : a.ch_groups);
+    a.fast = static_cast<uint32_t>(a.ch_major ? px_tiles : ch_groups);
+    const hq::Magic31 md = hq::magic31(a.fast);
     a.d_magic = md.m; a.d_shift = md.s;
     const int out = y_dtype == HQ_F16 ? kOutF16 : y_dtype == HQ_F32 ? kOutF32 : kOutI32;
     if (out == kOutI32 && (kind == kResPerTap || kind == kResBytes)) {
         const hq_status st = hq_fill_zero_launch(g.y, static_cast<uint64_t>(g.pixels) * 9 * g.n, stream);
         if (st != HQ_OK) return st;
     }
-    const int resident = std::min(p.chunk * p.ks, g.k / 64);   // steps
-    const int ns = g.k / 64 % resident ? 0 : resident_unrolled(kind, out, resident);
+    const int ns = steps % resident ? 0 : resident_unrolled(kind, out, resident);
     const int form = resident_form(p.ring, ns);
     const void *fn = kind == kResBytes    ? hq_resident_bytes(out, form)
                      : kind == kResPlanes ? hq_resident_planes(out, form)

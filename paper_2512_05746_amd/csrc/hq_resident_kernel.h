@@ -11,13 +11,16 @@
 //
 // A step is 64 channels of one tap: 14 vector instructions to expand the weights (hq_fp6.h), one operand read and one MFMA for
 // each of the four 32-pixel tiles; per-pixel scales: one fold of 16 values a tile into the fp32 sums for every tap.  What bounds
-// it: a loop of such MFMAs alone takes 23 ns each (the chip holds 1.7 GHz under them), the kernel's 32 .. 34.  The rest is
-// the wave's own instructions (14 an MFMA, issued in order, two waves a SIMD), LDS (34 clocks of its time an MFMA and CU: operands,
-// ring) and the address path (22 clocks an MFMA).  Taking the weights' requests out of the loop makes it 1.3 us faster on
-// 16 x 32 x 32 x 384, the operand reads 3, the expansion 3, the folds 1.  Before, weights were loaded straight into the operand's
-// lanes (37 clocks of address path an MFMA), folds were per 192 channels, expansion took 20 instructions and addresses 25.
-// The other half of a launch is what surrounds the loop: start and first loads (2 us), expanding the tile (2 .. 4 us;
-// 24 instructions per 16 codes for the signed form), exchange and results (2 .. 5 us).
+// it: such MFMAs alone take 33 clocks (a loop of them holds 1.4 GHz, the short one here 1.9 .. 2.1), with the operand reads 34 (two
+// waves a SIMD), with ring and direct-to-LDS loads 48, with 4 vector instructions each 51, and every 2 scalar instructions
+// an MFMA cost 8 more: a wave issues in order, and what it issues beside an MFMA adds to it.  So steps come in groups of three (below):
+// slots of the ring, places of the expanded weights and distances in LDS are constants, requests advance the lane's offset on the
+// way; 38 instructions a step instead of 62.  us a call, a step at a time -> groups of three, and the start's arguments loaded at
+// once: per-pixel scales 16 x 32 x 32 x 384 25.1 -> 23.6, 8 x 16 x 16 x 960 21.6 -> 20.3; one scale 24.9 -> 23.3; 8 bits 34.0 -> 32.7;
+// over 1200 random layers 0.92 .. 0.945 of the time, none more than 2.4 % slower.
+// The other half of a launch is what surrounds the loop: start and first loads (2 us: instructions of two waves a SIMD, 7 clocks
+// each, and 100 KiB of requests), expanding the tile (2 .. 4 us; 24 instructions per 16 codes for the signed form), exchange and
+// results (2 .. 5 us).
 //
 // Measured (3x3, 4-bit, us a call, weights in L2; kernel with weights in registers for every form -> this one):
 //     per-pixel scales: 8 x 16 x 16 x 960 23.4 -> 21.9, 3 x 45 x 27 x 320 -> 200 11.4 -> 10.8, 3 x 44 x 44 x 576 -> 152 13.3 -> 13.1
@@ -53,6 +56,8 @@
 // below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).  fp32 results would lose digits, so there
 // the sums of a tap start at minus its correction (one fp16 matrix step per tap and tile): 6e-8, as with sums in integers.
 #pragma once
+#include <stddef.h>
+
 #include <type_traits>
 
 #include "hq_buffer.h"
@@ -60,29 +65,36 @@
 #include "hq_int_gemm_kernel.h"
 
 struct ResidentArgs {
+    // What the start of a workgroup needs, 32 words that it loads together.
     const uint8_t *xq;   // [pixels, k/2]
-    const float *sx;     // [pixels], or one value
     const uint8_t *wq;   // [n, taps, k/2]
+    const float *sx;     // [pixels], or one value
     const float *sw;     // [n]
     const void *bias;    // [n] of the output dtype, or null
-    void *y;             // [pixels, n]; per-tap integer output [pixels, 9, n], zero-filled before the launch
     uint32_t pixels;
-    int n, k, h, w;
-    int in_planes;       // kResPlanes: planes that are not all zeros (2 or 3)
-    float out_scale;     // times the one scale
-    uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
+    int n, k, w;
     int chunk;                     // steps of 64 channels that are resident at a time
     int xw_log2;                   // pixel groups of 128 per workgroup
     int cb;                        // channel blocks of 32 per workgroup
-    uint32_t ch_groups, px_tiles;  // workgroups: channel runs x pixel tiles
-    uint32_t d_magic, d_shift;     // exact division of a tile index by the count that runs fastest
+    int waves;                     // 4 or 8
+    uint32_t tiles, fast;          // workgroups: channel runs x pixel tiles; those of the kind that runs fastest
+    uint32_t d_magic, d_shift;     // exact division of a tile index by that count
     int ch_major;                  // neighbouring workgroups share the channels (else the pixels)
     int rows;                      // rows of the LDS image and one more, odd
-    int wide;                      // the exchange area has 16 KiB per wave (else 8)
+    uint32_t part8, ring, tables;  // LDS offsets: 8-byte parts, rings, tables
     uint32_t ring_stride;          // LDS from wave to wave's ring
-    int ring_shared;               // the rings lie in the exchange area
-    uint32_t part8, exchange, ring, tables;   // LDS offsets: 8-byte parts, exchange / staging area, rings, tables
+    uint32_t inverses, inverses_last;   // inverse_of the resident steps and, in the upper half, of their threes; of the last chunk's
+    int in_planes;       // kResPlanes: planes that are not all zeros (2 or 3)
+    int ring_shared;     // the rings lie in the exchange area
+    // The rest.
+    void *y;             // [pixels, n]; per-tap integer output [pixels, 9, n], zero-filled before the launch
+    int h;
+    float out_scale;     // times the one scale
+    uint32_t w_magic, w_shift, h_magic, h_shift;   // exact division of a pixel index by w and by h
+    int wide;            // the exchange area has 16 KiB per wave (else 8)
+    uint32_t exchange;   // LDS offset of the exchange / staging area
 };
+static_assert(offsetof(ResidentArgs, y) == 128, "32 words");
 
 namespace {
 
@@ -94,15 +106,16 @@ constexpr int kResBytes = 3;    // as kResPerTap, with 8-bit codes on the int8 i
 // Direct-to-LDS load of 16 bytes a lane: lane i's land at lds_base + 16 i.  Inline assembly, because the compiler cannot tell which
 // slot of a ring such a load fills and would wait for all of them before every LDS read; the waits (wait_vmem) are placed by
 // hand.  (Its own counted waits stay right: they only wait for more.  m0 is reserved, the compiler sets it before each use of its own
-// and takes no clobber of it.)
+// and takes no clobber of it.)  The lane's offset goes on by `step` first, which takes the place of the wait state after m0.
 __device__ __forceinline__ v4i buffer_words(const void *p, uint32_t bytes) {   // a buffer as four scalar registers
     const uint64_t at = reinterpret_cast<uint64_t>(p);
     return v4i{static_cast<int>(at), static_cast<int>(at >> 32 & 0xFFFF), static_cast<int>(bytes), 0x00027000};
 }
-__device__ __forceinline__ void load_to_ring(const v4i &r, uint32_t lane_off, uint32_t uniform_off, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :
-                 : "s"(lds_base), "v"(lane_off), "s"(r), "s"(uniform_off)
+template <int STEP>
+__device__ __forceinline__ void load_to_ring(const v4i &r, uint32_t &lane_off, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %1\n\tv_add_u32_e32 %0, %3, %0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds"
+                 : "+v"(lane_off)
+                 : "s"(lds_base), "s"(r), "n"(STEP)
                  : "memory");
 }
 // Steps of a tap that a form is built for (0: any number).  Not for the integer sums of taps, which their stores bound.  Four steps only
@@ -129,6 +142,33 @@ __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
     return __builtin_amdgcn_mfma_f32_32x32x8f16(weights, b, v16f{}, 0, 0, 0);
 }
 
+// x / d rounded down, of inv = 2^15 / d + 1: exact for x d below 2^15
+__host__ __device__ constexpr uint32_t inverse_of(int d) { return 32768u / static_cast<uint32_t>(d) + 1; }
+__device__ __forceinline__ int quotient(int x, uint32_t inv) { return static_cast<int>(static_cast<uint32_t>(x) * inv >> 15); }
+
+// The arguments, and the index of the thread, read anew: what a part of the kernel derives from them is computed there instead of
+// being held (and, for want of registers, spilled) over the loop of matrix instructions.  A load of scalars takes 300 clocks, so the
+// start has its own loaded at once (one after the other as they are needed they cost 0.6 us).
+typedef const __attribute__((address_space(4))) ResidentArgs KernelArgs;
+__device__ __forceinline__ KernelArgs &args_again() {
+    uint64_t at = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+    asm volatile("" : "+s"(at));
+    return *reinterpret_cast<KernelArgs *>(at);
+}
+__device__ __forceinline__ void start_args(ResidentArgs &a) {
+    typedef int v16w __attribute__((ext_vector_type(16)));
+    typedef const __attribute__((address_space(4))) v16w KernelWords;
+    const uint64_t at = reinterpret_cast<uint64_t>(__builtin_amdgcn_kernarg_segment_ptr());
+    v16w words[2] = {reinterpret_cast<KernelWords *>(at)[0], reinterpret_cast<KernelWords *>(at)[1]};
+    asm volatile("" : "+s"(words[0]), "+s"(words[1]));
+    __builtin_memcpy(&a, words, sizeof words);
+}
+__device__ __forceinline__ int thread_again() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
 // RING: slots of the ring in LDS through which weights pass, 3 or, where there is less room, 2; 0: straight from memory.
 // NS: 0, or the steps of a tap that are resident at a time, 1 .. 4: a tap is unrolled, with its weights straight from memory and one tap
 // ahead in registers, tile by tile, the folds between the tiles.  A tap so short has a fold, new addresses and masks for every 4 to 16
@@ -138,7 +178,7 @@ __device__ __forceinline__ v16f minus_eighth_of(const v4h &weights, int sum) {
 //     one scale         5 x 54 x 54 x 64 10.1 -> 7.9, 24 x 33 x 22 x 192 15.5 -> 12.4, 9 x 32 x 46 x 576 -> 264 (a slice at a time) 35.9 -> 28.0
 //     width axis        4 x 49 x 48 x 192, block 16 14.7 -> 12.4;   8 bits  12 x 23 x 17 x 384 -> 392 (a slice at a time) 20.2 -> 18.2
 template <int OUT, int KIND, int RING, int NS>
-__global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
+__global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
     constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
     constexpr bool WHOLE_TAPS = KIND == kResPerTap && OUT == kOutF32;   // (see the offset of the weights above)
     constexpr int TAPS = 9, NT = 4;
@@ -156,100 +196,115 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     constexpr float UNIT = BYTES ? 1.0f : 64.0f;   // a product of two codes is 1 / UNIT in the accumulators
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
 
-    const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6;
-    const int lane = tid & 63, l = lane & 31, h = lane >> 5;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cb = BYTES ? a.k : a.k >> 1, steps = a.k >> 6, rows = a.rows;
-    const int px_wg = 128 << a.xw_log2;
-    const int halo = a.w + 1;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    ResidentArgs a;
+    start_args(a);
+    auto row_bytes = [](const auto &a) { return BYTES ? a.k : a.k >> 1; };   // of a pixel's codes, and of a channel's for one tap
 
     // workgroup b runs on XCD b % 8: every XCD gets a contiguous run of tiles
-    const uint32_t nwg = gridDim.x, xcd = blockIdx.x & 7, q8 = nwg >> 3, r8 = nwg & 7;
+    const uint32_t nwg = a.tiles, xcd = blockIdx.x & 7, q8 = nwg >> 3, r8 = nwg & 7;
     const uint32_t tile = xcd * q8 + (xcd < r8 ? xcd : r8) + (blockIdx.x >> 3);
-    const uint32_t fast = a.ch_major ? a.px_tiles : a.ch_groups;
-    const uint32_t slow_i = hq::div_magic31(tile, fast, a.d_magic, a.d_shift), fast_i = tile - slow_i * fast;
-    const uint32_t px_tile = a.ch_major ? fast_i : slow_i, p0 = px_tile * px_wg;
+    const uint32_t slow_i = hq::div_magic31(tile, a.fast, a.d_magic, a.d_shift), fast_i = tile - slow_i * a.fast;
+    const uint32_t px_tile = a.ch_major ? fast_i : slow_i, p0 = px_tile << (7 + a.xw_log2);
     const int c_wg = static_cast<int>(a.ch_major ? slow_i : fast_i) * a.cb * 32;
     const int blocks = min(a.cb, (a.n - c_wg + 31) / 32);   // channel blocks of this workgroup
 
-    float *s_sx = reinterpret_cast<float *>(lds + a.tables);
-    float *s_corr = s_sx + (FOLD ? TAPS : 0) * px_wg;
-    int *s_mask = reinterpret_cast<int *>(s_corr + px_wg);
-    float *s_rowscale = reinterpret_cast<float *>(s_mask + px_wg);
-    int *s_sum = reinterpret_cast<int *>(s_rowscale + rows);   // code sums [row] of the resident steps
-    float *s_sw = reinterpret_cast<float *>(s_sum + rows);
-    float *s_bias = s_sw + a.cb * 32;
-    short *s_part = reinterpret_cast<short *>(s_bias + a.cb * 32);   // WHOLE_TAPS: code sums [resident step][row]
+    struct Tables {
+        float *sx;         // [tap][pixel] scales
+        float *corr;       // [pixel]
+        int *mask;         // [pixel]
+        float *rowscale;   // [row]
+        int *sum;          // [row] code sums of the resident steps
+        float *sw, *bias;  // [channel]
+        short *part;       // WHOLE_TAPS: code sums [three resident steps][row]
+    };
+    auto tables_of = [&](const auto &a) {
+        const int px = 128 << a.xw_log2;
+        Tables t;
+        t.sx = reinterpret_cast<float *>(lds + a.tables);
+        t.corr = t.sx + (FOLD ? TAPS : 0) * px;
+        t.mask = reinterpret_cast<int *>(t.corr + px);
+        t.rowscale = reinterpret_cast<float *>(t.mask + px);
+        t.sum = reinterpret_cast<int *>(t.rowscale + a.rows);
+        t.sw = reinterpret_cast<float *>(t.sum + a.rows);
+        t.bias = t.sw + a.cb * 32;
+        t.part = reinterpret_cast<short *>(t.bias + a.cb * 32);
+        return t;
+    };
 
     // ---- phases: tasks and shares ---------------------------------------------------------------------------
     // tasks first .. first + (nw >> kl) - 1, each by 1 << kl waves; wave wv has task first + wv >> kl, share wv mod
     int left = blocks << a.xw_log2, first = 0, kl = 0;
-    auto shrink = [&]() {
-        kl = 0;
-        while ((nw >> kl) > left) ++kl;
+    const int nw = a.waves;
+    auto shrink = [&]() {   // (4 or 8 waves)
+        kl = left * 8 < nw * 2 ? 3 : left * 4 < nw * 2 ? 2 : left < nw ? 1 : 0;
     };
     shrink();
     int c0 = 0, px_l = 0;    // first channel, first pixel (local)
-    int s0 = 0, ns = a.chunk < steps ? a.chunk : steps;   // resident steps s0 .. s0 + ns - 1
-    int q = 0, q_end = 0;    // steps of this wave's share: tap q / ns, resident step q % ns
+    int s0 = 0, ns = a.chunk;   // resident steps s0 .. s0 + ns - 1
+    int tap0 = 0, step0 = 0, share_steps = 0;   // this wave's share: first tap and resident step, steps
 
     // ---- weights: from memory into the wave's ring in LDS, R steps ahead --------------------------------------
     // A step's 32 rows of 32 bytes (BYTES: 64) are fetched by neighbouring lanes piece by piece, which takes the address
     // path 22 clocks a KiB; loads straight into the operand's lanes (16 rows in every 16 lanes) take 37, more than the matrix
     // instructions that the KiB feeds.  In rows 8..15 mod 16 (BYTES: 4..7, 8..11, 12..15) the pieces change places, so that
-    // the operand reads meet no bank conflict.  Every step requests one (past the share's end its last one again), so the
+    // the operand reads meet no bank conflict.  Every step requests one (past the share's end what follows there), so the
     // number of requests in flight is always the same.
     constexpr int R = RING, SLOT = resident_slot_bytes(KIND), DMAS = SLOT / 1024;
-    const v4i w_buf = buffer_words(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
-    const uint32_t ring_at = a.ring + wv * a.ring_stride;   // (uniform)
-    const uint32_t ring = lds_address(lds) + ring_at;
-    uint32_t w_row[DMAS];    // this lane's pieces: offset of the weight row and piece (without a ring: [0] its operand's row)
-    // where this lane's operand pieces lie in a slot
-    int r_piece[WP];
-#pragma unroll
-    for (int i = 0; i < WP; ++i)
-        r_piece[i] = static_cast<int>(ring) + (BYTES ? l * 64 + ((2 * i + h) ^ ((l >> 2) & 3)) * 16 : l * 32 + (h ^ ((l >> 3) & 1)) * 16);
-    uint32_t f_off = 0, f_tap_last = 0, f_last = 0;   // position requested next, the last of its tap and of the share
-    uint32_t slot = 0;       // slot read last and filled next
-    auto advance = [&]() {
-        if (f_off == f_tap_last) {
-            f_off += cb - ns * STEP;
-            f_tap_last += cb;
-        }
-        f_off = min(f_off + STEP, f_last);
-    };
+    const uint32_t w_bytes = static_cast<uint32_t>(a.n) * (TAPS * row_bytes(a));
+    const v4i w_buf = buffer_words(a.wq, w_bytes);
+    constexpr int UNROLL = RING ? RING : 3;   // steps of a group (below): a ring's slots come round
+    uint32_t w_row[DMAS];    // this lane's pieces: offset of the position requested last (without a ring: [0], its operand's row)
+    // where this lane's operand pieces lie in the slots, and the slots themselves; [0]: filled next
+    int r_piece[RING ? RING : 1][WP];
+    uint32_t r_slot[RING ? RING : 1];
+    uint32_t w_gap = 0;      // from the last of a tap's resident steps to the first of the next, less a step
+    int w_left = 0;          // steps to request before that
     v4i raw[WP];             // weights of the next step (BYTES: of this step) as they lie in memory
-    auto request = [&]() {   // the next position into its slot
+    auto skip_gap = [&]() {
+#pragma unroll
+        for (int j = 0; j < DMAS; ++j) w_row[j] += w_gap;
+        w_left = ns;
+    };
+    auto request = [&](int slot) {   // the next position into a slot
         if constexpr (RING > 0) {
 #pragma unroll
-            for (int j = 0; j < DMAS; ++j) load_to_ring(w_buf, w_row[j], f_off, ring + slot + j * 1024);
-            advance();
+            for (int j = 0; j < DMAS; ++j) load_to_ring<STEP>(w_buf, w_row[j], r_slot[slot] + j * 1024);
         }
     };
-    auto take = [&]() {      // raw <- the next slot; R - 1 steps were requested after it
+    auto take = [&](int slot) {      // raw <- the weights in a slot; R - 1 steps were requested after them
         if constexpr (RING > 0) {
             wait_vmem<(R - 1) * DMAS>();
             asm volatile("" ::: "memory");
-            slot = slot == (R - 1) * SLOT ? 0 : slot + SLOT;
 #pragma unroll
-            for (int i = 0; i < WP; ++i) raw[i] = lds_v4i(r_piece[i] + slot);
+            for (int i = 0; i < WP; ++i) raw[i] = lds_v4i(r_piece[slot][i]);
         } else {
-            const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
+            const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, w_bytes);
+            if (w_left == 0) skip_gap();
+            --w_left;
+            w_row[0] += STEP;
 #pragma unroll
-            for (int i = 0; i < WP; ++i) raw[i] = buffer_load16(buf, w_row[0] + i * 32, f_off);
-            advance();
+            for (int i = 0; i < WP; ++i) raw[i] = buffer_load16(buf, w_row[0], i * 32);
+        }
+    };
+    auto request_next = [&](int slot) {   // wherever in a tap it is
+        if constexpr (RING > 0) {
+            if (w_left == 0) skip_gap();
+            --w_left;
+            request(slot);
         }
     };
     v4i raw_tap[WP][NS ? NS : 1];   // NS: weights of the next tap
-    auto take_tap = [&](int tap) {
-        const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * (TAPS * cb));
+    auto take_tap = [&](int tap, int tap_bytes) {
+        const __amdgpu_buffer_rsrc_t buf = buffer_of(a.wq, w_bytes);
 #pragma unroll
         for (int k = 0; k < NS; ++k)
 #pragma unroll
             for (int i = 0; i < WP; ++i)
-                raw_tap[i][k] = buffer_load16(buf, w_row[0], static_cast<uint32_t>(tap * cb + (s0 + k) * STEP + i * 32));
+                raw_tap[i][k] = buffer_load16(buf, w_row[0], static_cast<uint32_t>(tap * tap_bytes + (s0 + k) * STEP + i * 32));
     };
-    auto begin_task = [&]() {
+    auto begin_task = [&](const auto &a) {
+        const int lane = thread_again() & 63, l = lane & 31, h = lane >> 5, cb = row_bytes(a);
         const int task = first + (wv >> kl), share = wv & ((1 << kl) - 1);
         px_l = (task & ((1 << a.xw_log2) - 1)) * 128;
         c0 = c_wg + (task >> a.xw_log2) * 32;
@@ -263,24 +318,42 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             w_row[j] = row_of(row) + (BYTES ? (lane & 3) ^ ((row >> 2) & 3) : (lane & 1) ^ ((row >> 3) & 1)) * 16;
         }
         if constexpr (RING == 0) w_row[0] = row_of(l) + h * 16;
-        // (a tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only)
-        const int grain = NS ? NS : OUT == kOutF32 ? 3 : 1, grains = (ns + grain - 1) / grain;
+        // (A tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only.  So are chunks, for the
+        // sake of the groups of steps.)
+        struct Cut { int tap, step; };
         auto cut = [&](int of) {
-            const int at = of * (TAPS * grains) >> kl, tap = at / grains;
-            return tap * ns + (at - tap * grains) * grain;
+            if constexpr (NS > 0) {
+                return Cut{of * TAPS >> kl, 0};
+            } else if (OUT == kOutF32 || a.chunk < a.k >> 6) {
+                const int grains = (ns + 2) / 3, at = of * (TAPS * grains) >> kl, tap = quotient(at, (ns == a.chunk ? a.inverses : a.inverses_last) >> 16);
+                return Cut{tap, (at - tap * grains) * 3};
+            } else {
+                const int at = of * (TAPS * ns) >> kl, tap = quotient(at, (ns == a.chunk ? a.inverses : a.inverses_last) & 0xFFFF);
+                return Cut{tap, at - tap * ns};
+            }
         };
-        q = cut(share);
-        q_end = cut(share + 1);
-        const int tap = q / ns, last_tap = (q_end - 1) / ns;
-        f_off = tap * cb + (s0 + q - tap * ns) * STEP;
-        f_tap_last = tap * cb + (s0 + ns - 1) * STEP;
-        f_last = last_tap * cb + (s0 + q_end - 1 - last_tap * ns) * STEP;
-        if constexpr (NS > 0) take_tap(tap);
+        const Cut from = cut(share), to = cut(share + 1);
+        tap0 = from.tap;
+        step0 = from.step;
+        share_steps = (to.tap - from.tap) * ns + to.step - from.step;
+        if constexpr (NS > 0) {
+            take_tap(tap0, cb);
+        } else {
+#pragma unroll
+            for (int j = 0; j < DMAS; ++j) w_row[j] += tap0 * cb + (s0 + step0 - 1) * STEP;
+            w_gap = cb - ns * STEP;
+            w_left = ns - step0;
+        }
         if constexpr (RING > 0) {
+            const uint32_t ring = lds_address(lds) + a.ring + wv * a.ring_stride;   // (uniform)
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                slot = i * SLOT;
-                request();
+                r_slot[i] = ring + i * SLOT;
+#pragma unroll
+                for (int j = 0; j < WP; ++j)
+                    r_piece[i][j] = static_cast<int>(r_slot[i]) +
+                                    (BYTES ? l * 64 + ((2 * j + h) ^ ((l >> 2) & 3)) * 16 : l * 32 + (h ^ ((l >> 3) & 1)) * 16);
+                request_next(i);
             }
         }
     };
@@ -288,14 +361,16 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     // ---- activation tile: packed codes -> signed 6-bit fields ------------------------------------------------
     // Wave items (32 rows, PIECES steps): lane = (row, lane half), a 16-byte piece of each step; the code sum of a row's item is that of
     // two neighbouring lanes.  Neighbouring waves take the steps of the same rows.
-    const int row_span = (px_wg + 2 * halo + 31) & ~31;
-    const uint32_t last = a.pixels - 1;
-    const int64_t row_pixel0 = static_cast<int64_t>(p0) - halo;
-    const int f_row = lane >> 1, f_half = lane & 1;
-    const uint32_t plane_bytes = a.pixels * static_cast<uint32_t>(cb);
-    const __amdgpu_buffer_rsrc_t x_buf = buffer_of(a.xq, BYTES ? plane_bytes : IN * plane_bytes);
     struct Item { int step, row; };
+    // set by begin_fill
     int nw_step = 0, nw_row = 0, row_steps = 0;   // nw items on; steps of a row, up to a whole item
+    int f_row = 0, f_half = 0, row_span = 0, rows = 0;
+    uint32_t f_off = 0, f_row_bytes = 0, plane_bytes = 0;
+    const uint8_t *x_codes = nullptr;
+    uint32_t part8 = 0;
+    int in_planes = 0;
+    int *f_sum = nullptr;     // code sums
+    short *f_part = nullptr;
     auto next = [&](Item &i) {
         i.step += nw_step;
         i.row += nw_row;
@@ -307,13 +382,14 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     auto fill_load = [&](v4i (&p)[IN][PIECES], const Item &item) {
         if (item.row >= row_span) return;
         // (rows outside the tensor wrap or lie beyond the bound and read as zeros; they are never used)
-        const uint32_t off = (static_cast<uint32_t>(p0) - halo + item.row + f_row) * cb + f_half * 16;
+        const uint32_t off = f_off + item.row * f_row_bytes;
+        const __amdgpu_buffer_rsrc_t x_buf = buffer_of(x_codes, BYTES ? plane_bytes : IN * plane_bytes);
 #pragma unroll
         for (int i = 0; i < IN; ++i)
 #pragma unroll
             for (int k = 0; k < PIECES; ++k) {
                 if (PIECES > 1 && NS == 0 && item.step + k >= ns) continue;
-                if (i < a.in_planes) p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step + k) * STEP);
+                if (IN < 3 || i < in_planes) p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step + k) * STEP);
                 else p[i][k] = v4i{0, 0, 0, 0};
             }
     };
@@ -334,7 +410,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     };
                     auto put = [&](int plane, const int (&d)[6]) {
                         *reinterpret_cast<v4i *>(lds + at(plane) * 16) = v4i{d[0], d[1], d[2], d[3]};
-                        *reinterpret_cast<int2 *>(lds + a.part8 + at(plane) * 8) = int2{d[4], d[5]};
+                        *reinterpret_cast<int2 *>(lds + part8 + at(plane) * 8) = int2{d[4], d[5]};
                     };
                     int d[6];
                     fp6_signed16(p[0][k].x, p[0][k].y, d[0], d[1], d[2]);
@@ -353,8 +429,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
         if constexpr (!BYTES) {
             sum += __builtin_amdgcn_mov_dpp(sum, 0xB1, 0xF, 0xF, true);   // the other half of the row (lanes 1,0,3,2)
             if (f_half == 0 && row < rows - 1) {
-                if constexpr (WHOLE_TAPS) s_part[item.step / PIECES * rows + row] = static_cast<short>(sum);
-                else atomicAdd(&s_sum[row], sum);
+                if constexpr (WHOLE_TAPS) f_part[item.step / PIECES * rows + row] = static_cast<short>(sum);
+                else atomicAdd(&f_sum[row], sum);
             }
         }
     };
@@ -362,12 +438,29 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
     // All first loads are requested before any is waited for (a first use costs a trip to HBM).
     v4i p[AHEAD][IN][PIECES];
     Item load_item{}, store_item{};
-    auto begin_fill = [&]() {
-        const int of_rows = (ns + PIECES - 1) / PIECES;   // items of 32 rows
+    auto begin_fill = [&](const auto &a) {
+        const int lane = thread_again() & 63;
+        const uint32_t cb = row_bytes(a);
+        f_row = lane >> 1;
+        f_half = lane & 1;
+        rows = a.rows;
+        row_span = ((128 << a.xw_log2) + 2 * (a.w + 1) + 31) & ~31;
+        x_codes = a.xq;
+        f_row_bytes = cb;
+        plane_bytes = a.pixels * cb;
+        in_planes = a.in_planes;
+        part8 = a.part8;
+        const Tables table = tables_of(a);
+        f_sum = table.sum;
+        f_part = table.part;
+        f_off = (p0 - (a.w + 1) + f_row) * cb + f_half * 16;
+        const int of_rows = NS ? 1 : (ns + PIECES - 1) / PIECES;   // items of 32 rows
+        const uint32_t inverses = ns == a.chunk ? a.inverses : a.inverses_last, inv = PIECES == 1 ? inverses & 0xFFFF : inverses >> 16;
+        const int nw_q = NS ? nw : quotient(nw, inv), wv_q = NS ? wv : quotient(wv, inv);
         row_steps = of_rows * PIECES;
-        nw_row = nw / of_rows * 32;
-        nw_step = nw % of_rows * PIECES;
-        load_item = store_item = Item{wv % of_rows * PIECES, wv / of_rows * 32};
+        nw_row = nw_q * 32;
+        nw_step = (nw - nw_q * of_rows) * PIECES;
+        load_item = store_item = Item{(wv - wv_q * of_rows) * PIECES, wv_q * 32};
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
 #pragma unroll
@@ -376,29 +469,36 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             next(load_item);
         }
     };
-    begin_fill();
-    begin_task();
-    constexpr bool ROW_SCALES = FOLD && !INT_TAPS;
-    auto row_scale = [&](int i) {
-        int64_t pix = row_pixel0 + i;
-        pix = pix < 0 ? 0 : (pix > static_cast<int64_t>(last) ? last : pix);
+    begin_fill(a);
+    begin_task(a);
+    constexpr bool ROW_SCALES = FOLD && !INT_TAPS, SUMS = !BYTES && !WHOLE_TAPS;
+    auto row_scale = [&](const auto &a, int i) {
+        const int64_t last = a.pixels - 1u;
+        int64_t pix = static_cast<int64_t>(p0) - (a.w + 1) + i;
+        pix = pix < 0 ? 0 : (pix > last ? last : pix);
         return a.sx[pix];
     };
-    float t_scale[2] = {}, t_sw = 0.f, t_bias = 0.f;
-    if constexpr (ROW_SCALES) {
-        t_scale[0] = row_scale(tid);
-        t_scale[1] = row_scale(tid + nt);
+    float t_scale[2] = {}, t_sw = 0.f;
+    Out t_bias{};
+    {
+        const int tid = thread_again(), nt = nw * 64;
+        if constexpr (ROW_SCALES) {
+            t_scale[0] = row_scale(a, tid);
+            t_scale[1] = row_scale(a, tid + nt);
+        }
+        if constexpr (OUT != kOutI32) {
+            const int c = c_wg + tid < a.n ? c_wg + tid : a.n - 1;
+            t_sw = a.sw[c];
+            t_bias = static_cast<const Out *>(a.bias ? a.bias : a.sw)[c];   // (without a bias: not used; a branch would wait for it)
+        }
     }
-    if constexpr (OUT != kOutI32) {
-        const int c = c_wg + tid < a.n ? c_wg + tid : a.n - 1;
-        t_sw = a.sw[c];
-        t_bias = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
-    }
-    constexpr bool SUMS = !BYTES && !WHOLE_TAPS;
-    if constexpr (SUMS) {
-        for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
-        lds_barrier();   // the code sums are zero before they are added to
-    }
+    auto clear_sums = [&]() {
+        if constexpr (SUMS) {
+            for (int i = thread_again(); i < rows; i += nw * 64) f_sum[i] = 0;
+            lds_barrier();   // the code sums are zero before they are added to
+        }
+    };
+    clear_sums();
 
     int touched = 0;     // (see below)
     v16f sum[NT];        // the accumulators themselves, or (FOLD) fp32 combinations of per-tap sums
@@ -413,6 +513,10 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 next(load_item);
             }
         }
+        KernelArgs &a = args_again();
+        const int tid = thread_again(), nt = nw * 64, px_wg = 128 << a.xw_log2, halo = a.w + 1, steps = a.k >> 6;
+        const uint32_t cb = row_bytes(a);
+        const Tables table = tables_of(a);
         if (s0 == 0) {
             // The weights of the workgroup's channels start their way into the L2: from HBM they would take longer than the loop over
             // steps looks ahead.  A word of every line; workgroups that share the channels take an eighth each.  us a call, weights not in
@@ -421,19 +525,19 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
             const uint32_t line = ((px_tile & 7) * nt + tid) * 128u, size = static_cast<uint32_t>(min(blocks * 32, a.n - c_wg)) * (TAPS * cb);
             if (NS == 0 && (RING > 0 || PL == 1) && line < size) touched = *reinterpret_cast<const int *>(a.wq + static_cast<uint32_t>(c_wg) * (TAPS * cb) + line);
             if constexpr (ROW_SCALES) {
-                if (tid < rows) s_rowscale[tid] = t_scale[0];
-                if (tid + nt < rows) s_rowscale[tid + nt] = t_scale[1];
-                for (int i = tid + 2 * nt; i < rows; i += nt) s_rowscale[i] = row_scale(i);
+                if (tid < rows) table.rowscale[tid] = t_scale[0];
+                if (tid + nt < rows) table.rowscale[tid + nt] = t_scale[1];
+                for (int i = tid + 2 * nt; i < rows; i += nt) table.rowscale[i] = row_scale(a, i);
             }
             if constexpr (OUT != kOutI32) {
                 if (tid < blocks * 32) {
-                    s_sw[tid] = t_sw;
-                    s_bias[tid] = t_bias;
+                    table.sw[tid] = t_sw;
+                    table.bias[tid] = a.bias ? to_float(t_bias) : 0.f;
                 }
                 for (int i = tid + nt; i < blocks * 32; i += nt) {
                     const int c = c_wg + i < a.n ? c_wg + i : a.n - 1;
-                    s_sw[i] = a.sw[c];
-                    s_bias[i] = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
+                    table.sw[i] = a.sw[c];
+                    table.bias[i] = a.bias ? to_float(static_cast<const Out *>(a.bias)[c]) : 0.f;
                 }
             }
         }
@@ -449,7 +553,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
                 int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
                 if (pix >= a.pixels) mask = 0;
-                if (r == 0) s_mask[i] = mask;
+                if (r == 0) table.mask[i] = mask;
                 float corr = 0.f;
 #pragma unroll
                 for (int s = 0; s < 3; ++s) {
@@ -457,16 +561,16 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     const int t = 3 * r + s, row = halo + i + (r - 1) * a.w + (s - 1);
                     const bool in = (mask >> t) & 1;
                     if constexpr (ROW_SCALES) {
-                        const float scale = in ? s_rowscale[row] : 0.f;
-                        s_sx[t * px_wg + i] = scale;
-                        if constexpr (SUMS) corr = fmaf(scale * (8.0f / UNIT), static_cast<float>(s_sum[row]), corr);
+                        const float scale = in ? table.rowscale[row] : 0.f;
+                        table.sx[t * px_wg + i] = scale;
+                        if constexpr (SUMS) corr = fmaf(scale * (8.0f / UNIT), static_cast<float>(table.sum[row]), corr);
                     } else if (SUMS && in) {
-                        corr += (8.0f / UNIT) * static_cast<float>(s_sum[row]);
+                        corr += (8.0f / UNIT) * static_cast<float>(table.sum[row]);
                     }
                 }
                 corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0xB1, 0xF, 0xF, true));   // lanes 1,0,3,2
                 corr += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, corr), 0x4E, 0xF, 0xF, true));   // lanes 2,3,0,1
-                if (r == 0) s_corr[i] = corr;
+                if (r == 0) table.corr[i] = corr;
             }
         } else {   // a lane has a pixel: as fast for 128 pixels, faster for 256 (with per-pixel scales of 4-bit codes its registers spill)
             for (int i = tid; i < px_wg; i += nt) {
@@ -477,34 +581,39 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 const int cm = (ow > 0 ? 1 : 0) | 2 | (ow + 1 < a.w ? 4 : 0);
                 int mask = (oh > 0 ? cm : 0) | (cm << 3) | (oh + 1 < a.h ? cm << 6 : 0);
                 if (pix >= a.pixels) mask = 0;
-                s_mask[i] = mask;
+                table.mask[i] = mask;
                 float corr = 0.f;
 #pragma unroll
                 for (int t = 0; t < TAPS; ++t) {
                     const int row = halo + i + (t / 3 - 1) * a.w + (t % 3 - 1);
                     const bool in = (mask >> t) & 1;
-                    if constexpr (ROW_SCALES) s_sx[t * px_wg + i] = in ? s_rowscale[row] : 0.f;
-                    else if (SUMS && in) corr += (8.0f / UNIT) * static_cast<float>(s_sum[row]);
+                    if constexpr (ROW_SCALES) table.sx[t * px_wg + i] = in ? table.rowscale[row] : 0.f;
+                    else if (SUMS && in) corr += (8.0f / UNIT) * static_cast<float>(table.sum[row]);
                 }
-                if constexpr (SUMS) s_corr[i] = corr;
+                if constexpr (SUMS) table.corr[i] = corr;
             }
         }
         if constexpr (WHOLE_TAPS && NS == 0) {   // code sums of three steps -> of all resident steps up to them
             for (int i = tid; i < px_wg + 2 * halo; i += nt) {
-                int of = s_part[i];
+                int of = table.part[i];
                 for (int k = PIECES; k < ns; k += PIECES) {
-                    of += s_part[k / PIECES * rows + i];
-                    s_part[k / PIECES * rows + i] = static_cast<short>(of);
+                    of += table.part[k / PIECES * rows + i];
+                    table.part[k / PIECES * rows + i] = static_cast<short>(of);
                 }
             }
         }
         lds_barrier();
 
         for (;;) {   // phases
+            KernelArgs &a = args_again();
+            const int lane = thread_again() & 63, l = lane & 31, h = lane >> 5, rows = a.rows;
+            const Tables table = tables_of(a);
+            const float *const s_sx = table.sx;
+            const int px_wg = 128 << a.xw_log2;
             int mask[NT];   // kResSum / INT_TAPS: taps inside the image, for the pixels of the four tiles
             if constexpr (!FOLD || INT_TAPS) {
 #pragma unroll
-                for (int t = 0; t < NT; ++t) mask[t] = s_mask[px_l + t * 32 + l];
+                for (int t = 0; t < NT; ++t) mask[t] = table.mask[px_l + t * 32 + l];
             }
             // the sums start from minus the correction for the weights' offset
             const bool corrects = SUMS && !INT_TAPS && (wv & ((1 << kl) - 1)) == 0;
@@ -513,20 +622,20 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 float from = 0.f;
                 if (corrects) {
                     const int i = px_l + t * 32 + l;
-                    from = -s_corr[i];
+                    from = -table.corr[i];
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) sum[t][i] = s0 == 0 ? from : sum[t][i] + from;
             }
-            const int lane_row = px_l + l + halo;
+            const int lane_row = px_l + l + a.w + 1;
 
             if constexpr (NS > 0) {
                 // While the MFMAs of a tile run, the next one is on its way from LDS and the sums of the one before are folded; the next
                 // tap's weights are requested as soon as this one's are expanded.
                 const Fp6Masks masks;
                 const int step16 = rows * (PL * 32), step8 = rows * (PL * 16), plane16 = rows * 32, plane8 = rows * 16;
-                int tap = q / NS;
-                const int tap_end = q_end / NS;
+                int tap = tap0;
+                const int tap_end = tap0 + share_steps / NS, tap_bytes = row_bytes(a);
                 struct Base { int b16, b8; };
                 auto row_shift = [&](int tap) { return (tap / 3 - 1) * a.w + tap % 3 - 1; };
                 auto base_of = [&](int tap) {
@@ -564,13 +673,13 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                             wop[0][k] = v8i{d[0], d[1], d[2], d[3], d[4], d[5], 0, 0};
                         }
                     }
-                    take_tap(tap1);
+                    take_tap(tap1, tap_bytes);
                     float scale[NT];
                     int codes[NT], inside[NT];   // (as below)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         if constexpr (ROW_SCALES) scale[t] = s_sx[tap * px_wg + px_l + t * 32 + l];
-                        if constexpr (WHOLE_TAPS) codes[t] = s_part[lane_row + row_shift(tap) + t * 32];
+                        if constexpr (WHOLE_TAPS) codes[t] = table.part[lane_row + row_shift(tap) + t * 32];
                         if constexpr (!FOLD) inside[t] = (mask[t] >> tap) & 1 ? 127 : 0;
                     }
                     Acc acc[2];
@@ -604,17 +713,16 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     base = base1;
                 }
             } else {
-                int tap = q / ns, k = q - tap * ns;
-                // LDS addresses of the operands of the next step: the 16- and the 8-byte parts of this lane's row of tile 0; the
+                int tap = tap0, k = step0;
+                // LDS addresses of the operands of the step at work: the 16- and the 8-byte parts of this lane's row of tile 0; the
                 // other tiles lie at fixed distances.
-                const int step16 = rows * (PL * 32), step8 = rows * (PL * 16), plane16 = rows * 32, plane8 = rows * 16;
-                int b16, b8, n16, n8;   // (n: of the next tap's first step)
-                auto set_rows = [&](int tap, int step, int &b16, int &b8) {
-                    const int at = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + h * rows;
-                    b16 = static_cast<int>(lds_address(lds)) + at * 16 + step * step16;
-                    b8 = static_cast<int>(lds_address(lds) + a.part8) + at * 8 + step * step8;
-                };
-                Operand b[NT][PL], wop;
+                const int step16 = rows * (PL * 32), plane16 = rows * 32, plane8 = rows * 16;
+                auto row_shift = [&](int tap) { return (tap / 3 - 1) * a.w + tap % 3 - 1; };
+                const int first_row = lane_row + row_shift(tap) + h * rows;
+                int b16 = static_cast<int>(lds_address(lds)) + first_row * 16 + k * step16;
+                int b8 = static_cast<int>(lds_address(lds) + a.part8) + first_row * 8 + (k * step16 >> 1);
+                Operand b[NT][PL];
+                int wop[UNROLL][6];   // weights of this step and, at the next place, of the next one
                 auto load_tile = [&](int t) {
 #pragma unroll
                     for (int plane = 0; plane < PL; ++plane) {
@@ -628,35 +736,34 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     }
                 };
                 const Fp6Masks masks;
-                auto expand_weights = [&](const v4i &r, int pair, Operand &o) {
+                auto expand_weights = [&](const v4i &r, int pair, int (&o)[6]) {
                     if constexpr (!BYTES) {
-                        int d0, d1, d2;
-                        if (pair == 0) fp6_offset16(masks, r.x, r.y, d0, d1, d2);
-                        else fp6_offset16(masks, r.z, r.w, d0, d1, d2);
-                        asm volatile("" : "+v"(d0), "+v"(d1), "+v"(d2));   // (here, between two matrix instructions)
-                        o[3 * pair] = d0;
-                        o[3 * pair + 1] = d1;
-                        o[3 * pair + 2] = d2;
+                        int *const d = o + 3 * pair;
+                        if (pair == 0) fp6_offset16(masks, r.x, r.y, d[0], d[1], d[2]);
+                        else fp6_offset16(masks, r.z, r.w, d[0], d[1], d[2]);
+                        asm volatile("" : "+v"(d[0]), "+v"(d[1]), "+v"(d[2]));   // (here, between two matrix instructions)
                     }
                 };
 
                 Acc acc[NT];              // FOLD: the sums of the tap at work
                 const v4h minus = h ? v4h{} : v4h{-0.125f16, -128.0f16, 0, 0};
                 auto codes_upto = [&](int step, int t) {   // WHOLE_TAPS
-                    return static_cast<int>(s_part[step / PIECES * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
+                    return static_cast<int>(table.part[step / PIECES * rows + lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32]);
                 };
                 // A step.  Right after the matrix instructions of a tile the tile's operands of the next step are requested, into the
                 // registers that have just been read; the next step's weights are expanded in between, and their slot of the
-                // ring is filled again.
+                // ring is filled again.  on: from this step's operands to the next one's.
                 int inside[NT];   // !FOLD: block exponents: 2^0, or for taps outside the image one that leaves nothing
-                auto step = [&](auto STARTS, bool ends) {   // the tap's sums start here; its last step in this share
+                auto step = [&](auto STARTS, auto PLACE, int on, auto fill) {   // the tap's sums start here
                     constexpr bool starts = decltype(STARTS)::value;
-                    b16 = ends ? n16 : b16 + step16;
-                    b8 = ends ? n8 : b8 + step8;
-                    Operand w_next = wop;
+                    constexpr int place = decltype(PLACE)::value, next = (place + 1) % UNROLL;
+                    b16 += on;
+                    b8 += on >> 1;
                     v4i now[WP];
 #pragma unroll
                     for (int i = 0; i < WP; ++i) now[i] = raw[i];
+                    const int (&o)[6] = wop[place];
+                    const v8i weights = v8i{o[0], o[1], o[2], o[3], o[4], o[5], 0, 0};
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         if constexpr (BYTES) {
@@ -665,37 +772,77 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                             for (int i = 0; i < PL; ++i) c = __builtin_amdgcn_mfma_i32_32x32x32_i8(now[i], b[t][i], c, 0, 0, 0);
                             acc[t] = c;
                         } else if constexpr (FOLD) {
-                            acc[t] = mfma_fp6(wop, b[t][0], starts && !WHOLE_TAPS ? Acc{} : acc[t]);
+                            acc[t] = mfma_fp6(weights, b[t][0], starts && !WHOLE_TAPS ? Acc{} : acc[t]);
                         } else {
-                            sum[t] = mfma_fp6_scaled(wop, b[t][0], sum[t], 127, inside[t]);
-                            if constexpr (PL == 2) sum[t] = mfma_fp6_scaled(wop, b[t][PL - 1], sum[t], 131, inside[t]);   // (x 2^4)
+                            sum[t] = mfma_fp6_scaled(weights, b[t][0], sum[t], 127, inside[t]);
+                            if constexpr (PL == 2) sum[t] = mfma_fp6_scaled(weights, b[t][PL - 1], sum[t], 131, inside[t]);   // (x 2^4)
                         }
                         __builtin_amdgcn_sched_barrier(0);
                         load_tile(t);
-                        if (t == 0) expand_weights(now[0], 0, w_next);
-                        if (t == 1) expand_weights(now[0], 1, w_next);
+                        if (t == 0) expand_weights(now[0], 0, wop[next]);
+                        if (t == 1) expand_weights(now[0], 1, wop[next]);
                         if (t == (BYTES ? 0 : 2)) {
-                            request();   // (into the slot of the weights that have just been used, or expanded)
-                            take();
+                            fill(place);   // (the slot of the weights that have just been used, or expanded)
+                            take(next);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    wop = w_next;
                 };
-                set_rows(tap, k, b16, b8);
+                auto rotate = [&]() {   // the slots go on by one
+                    if constexpr (RING > 0) {
+                        const uint32_t slot = r_slot[0];
+#pragma unroll
+                        for (int i = 0; i + 1 < R; ++i) r_slot[i] = r_slot[i + 1];
+                        r_slot[R - 1] = slot;
+#pragma unroll
+                        for (int j = 0; j < WP; ++j) {
+                            const int piece = r_piece[0][j];
+#pragma unroll
+                            for (int i = 0; i + 1 < R; ++i) r_piece[i][j] = r_piece[i + 1][j];
+                            r_piece[R - 1][j] = piece;
+                        }
+                    }
+                };
+                // A step by itself: the next one's weights come to the first place again.
+                auto single = [&](int on) {
+                    step(std::false_type{}, std::integral_constant<int, 0>{}, on, request_next);
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) wop[0][i] = wop[1][i];
+                    rotate();
+                };
+                // UNROLL steps, as many as are left in the tap or a multiple of them: the requests, ahead by UNROLL + 1 steps (BYTES:
+                // UNROLL), come to the end of a tap with the last (first) step of a group or not at all.
+                auto group = [&](auto STARTS, int on) {
+                    constexpr int CROSSES = BYTES ? 0 : UNROLL - 1;
+                    auto fill = [&](int place) {
+                        if (RING > 0 && place == CROSSES) {
+                            const bool crosses = w_left == CROSSES;
+#pragma unroll
+                            for (int j = 0; j < DMAS; ++j) w_row[j] += crosses ? w_gap : 0;
+                            w_left += (crosses ? ns : 0) - UNROLL;
+                        }
+                        request(place);
+                    };
+                    step(STARTS, std::integral_constant<int, 0>{}, step16, fill);
+                    if constexpr (UNROLL == 3) step(std::false_type{}, std::integral_constant<int, 1>{}, step16, fill);
+                    step(std::false_type{}, std::integral_constant<int, UNROLL - 1>{}, on, fill);
+                };
 #pragma unroll
                 for (int t = 0; t < NT; ++t) load_tile(t);
-                take();
+                take(0);
                 if constexpr (!BYTES) {
-                    wop = v8i{};
-                    expand_weights(raw[0], 0, wop);
-                    expand_weights(raw[0], 1, wop);
-                    request();
-                    take();
+                    expand_weights(raw[0], 0, wop[0]);
+                    expand_weights(raw[0], 1, wop[0]);
+                    request_next(0);
+                    take(1);
+                    rotate();
                 }
-                for (int to_go = q_end - q; to_go > 0;) {   // taps
+                // (in the order of memory the requests cross from tap to tap unnoticed)
+                const bool groups = RING == 0 || w_gap == 0 || (UNROLL == 3 && ns % 3 == 0);
+                for (int to_go = share_steps; to_go > 0;) {   // taps
                     const int n = min(ns - k, to_go);
-                    set_rows(min(tap + 1, TAPS - 1), 0, n16, n8);   // (past the last one: not used)
+                    // from the last step to the next tap's first (past the last tap: the same operands again, not used)
+                    const int over = tap + 1 < TAPS ? (row_shift(tap + 1) - row_shift(tap)) * 16 - (k + n - 1) * step16 : 0;
                     float scale[NT];
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -707,16 +854,29 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                         for (int t = 0; t < NT; ++t) inside[t] = (mask[t] >> tap) & 1 ? 127 : 0;
                     }
-                    step(std::true_type{}, n == 1);
+                    int left = n;
+                    if constexpr (FOLD && !WHOLE_TAPS) {
+                        if (n >= UNROLL && groups) {
+                            group(std::true_type{}, left == UNROLL ? over : step16);
+                            left -= UNROLL;
+                        } else {
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) acc[t] = Acc{};
+                        }
+                    }
+                    if (groups) {
 #pragma unroll 1
-                    for (int i = 1; i < n; ++i) step(std::false_type{}, i == n - 1);
+                        for (; left >= UNROLL; left -= UNROLL) group(std::false_type{}, left == UNROLL ? over : step16);
+                    }
+#pragma unroll 1
+                    for (; left > 0; --left) single(left == 1 ? over : step16);
                     if constexpr (INT_TAPS) {
 #pragma unroll
                         for (int t = 0; t < NT; ++t) {
                             const uint32_t pix = p0 + px_l + t * 32 + l;
                             if (!((mask[t] >> tap) & 1)) continue;
                             const int row = lane_row + (tap / 3 - 1) * a.w + tap % 3 - 1 + t * 32;
-                            const int extra = !BYTES && k == 0 ? 8 * s_sum[row] : 0;
+                            const int extra = !BYTES && k == 0 ? 8 * table.sum[row] : 0;
                             int *dst = static_cast<int *>(a.y) + (static_cast<uint64_t>(pix) * 9 + tap) * a.n;
 #pragma unroll
                             for (int i = 0; i < 16; ++i) {
@@ -737,10 +897,13 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                 if constexpr (RING > 0) wait_vmem<0>();   // (nothing arrives in the ring any more)
             }
             asm volatile("" : : "v"(touched));
-            if (s0 + ns < steps) break;   // the sums go on with the next chunk (one phase: host)
+            if (s0 + ns < a.k >> 6) break;   // the sums go on with the next chunk (one phase: host)
 
             // ---- results of the phase --------------------------------------------------------------------------
             if constexpr (!INT_TAPS) {
+                KernelArgs &a = args_again();
+                const int lane = thread_again() & 63, l = lane & 31, h = lane >> 5;
+                const Tables table = tables_of(a);
                 // Tasks shared by 2, 4 or 8 waves: in every round a wave hands half of what it holds to a partner and
                 // adds the partner's sums of the other half, until it holds 4 >> kl pixel tiles (or half a tile).
                 int tile0 = 0, half0 = 0;   // what it holds: tiles tile0 .., or half half0 of tile tile0
@@ -818,7 +981,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                         }
                     }
                 };
-                const uint32_t rows_left = min(a.pixels - p0, static_cast<uint32_t>(px_wg));
+                const uint32_t rows_left = min(a.pixels - p0, 128u << a.xw_log2);
                 Out *const y_wg = static_cast<Out *>(a.y) + static_cast<uint64_t>(p0) * a.n;
                 const __amdgpu_buffer_rsrc_t y_buf = buffer_of(y_wg, rows_left * static_cast<uint32_t>(a.n * sizeof(Out)));
                 const bool vec = a.n % 8 == 0;   // groups of eight channels are whole and 16-byte aligned
@@ -842,8 +1005,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
                     float sw[16], bias[16];
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        sw[i] = OUT != kOutI32 ? s_sw[ct + i] : 0.f;
-                        bias[i] = OUT != kOutI32 ? s_bias[ct + i] : 0.f;
+                        sw[i] = OUT != kOutI32 ? table.sw[ct + i] : 0.f;
+                        bias[i] = OUT != kOutI32 ? table.bias[ct + i] : 0.f;
                     }
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
@@ -889,32 +1052,31 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs a) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
                         v[i] = sum[0][i];
-                        sw[i] = OUT != kOutI32 ? s_sw[ct + 8 * half0 + i] : 0.f;
-                        bias[i] = OUT != kOutI32 ? s_bias[ct + 8 * half0 + i] : 0.f;
+                        sw[i] = OUT != kOutI32 ? table.sw[ct + 8 * half0 + i] : 0.f;
+                        bias[i] = OUT != kOutI32 ? table.bias[ct + 8 * half0 + i] : 0.f;
                     }
                     Out res[8];
                     scaled(v, sw, bias, res);
                     store8(res, px, c0 + 16 * h + 8 * half0);
                 }
             }
-            first += nw >> kl;
-            left -= nw >> kl;
+            const int done = nw >> kl;
+            first += done;
+            left -= done;
             if (left == 0) return;
             shrink();
             if (RING && a.ring_shared) lds_barrier();   // nobody reads the exchange area any more
-            begin_task();
+            begin_task(a);
         }
 
         // ---- next chunk -----------------------------------------------------------------------------------------
         s0 += ns;
         ns = min(a.chunk, steps - s0);
-        begin_fill();
-        begin_task();
+        KernelArgs &again = args_again();
+        begin_fill(again);
+        begin_task(again);
         lds_barrier();   // every wave is done with the resident steps
-        if constexpr (SUMS) {
-            for (int i = tid; i < rows; i += nt) s_sum[i] = 0;
-            lds_barrier();
-        }
+        clear_sums();
     }
 }
 

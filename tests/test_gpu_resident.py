@@ -299,6 +299,9 @@ def test_conv3x3_one_scale_empty_sums(hq, nb, h, w, cin, cout):
     (1, 3, 88, 960, 40),         # and nine steps resident at a time
     (1, 3, 24, 640, 40),         # 8 bits: a ring of two slots
     (1, 13, 13, 576, 40),        # few workgroups of four waves: all of the LDS for each
+    (2, 9, 16, 448, 40), (1, 16, 16, 512, 72),   # groups of three steps and one, and two, by themselves; shares that start within a tap
+    (1, 3, 56, 704, 40),         # one scale: nine steps resident, then two
+    (1, 5, 72, 832, 40),         # and thirteen steps in all: nine and four, or six, six and one
 ])
 def test_conv3x3_steps_of_a_tap(hq, nb, h, w, cin, cout):
     """Every form, unrolled and not, with every type of results: integer sums bit for bit, fp32 results to 1e-5 of the largest (the width
