@@ -20,7 +20,21 @@ __device__ __forceinline__ uint32_t pack8_magic(const float *v, float inv) {
     return (w - kMagicSum) ^ 0x88888888u;
 }
 
-// The same with the clamp of a given scale: v is limited to [lo, hi] = [qmin / inv, qmax / inv]
+// Sixteen values as bytes, value i in byte i.
+__device__ __forceinline__ uint4 bytes16_magic(const float *v, float inv) {
+    uint32_t w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        uint32_t m[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = __float_as_uint(__builtin_fmaf(v[4 * j + i], inv, 12582912.0f));   // 1.5 * 2^23
+        const uint32_t lo = __builtin_amdgcn_perm(m[1], m[0], 0x0C0C0400), hi = __builtin_amdgcn_perm(m[3], m[2], 0x04000C0C);
+        w[j] = lo | hi;
+    }
+    return uint4{w[0], w[1], w[2], w[3]};
+}
+
+// pack8_magic with the clamp of a given scale: v is limited to [lo, hi] = [qmin / inv, qmax / inv]
 // first (rounding is monotonic and the limits are integers, so clamp and round commute).
 __device__ __forceinline__ uint32_t pack8_magic_clamped(const float *v, float inv, float lo, float hi) {
     float c[8];

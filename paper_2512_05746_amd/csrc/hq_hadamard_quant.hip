@@ -269,13 +269,17 @@ __global__ __launch_bounds__(kThreads) void rowquant_large(const T *__restrict__
 // float's bit pattern.  Eight such patterns are merged by w = (w << 4) + m; the known
 // constant contributed by the upper bits is subtracted and the offset removed by
 // xor 0x88888888, which yields the eight two's-complement nibbles.
-// STATIC: the scale is given (one for the tensor): no abs-max, clamp active, no scale output;
-// `given` points to it.  NBLK: 64-channel blocks per row.  Four waves (token groups) per workgroup.
-template <int NBLK, bool STATIC>
+// kStatic: the scale is given (one for the tensor): no abs-max, clamp active, no scale output;
+// `given` points to it.  kBytes: one code a byte, 16 bytes a lane and block (codes of up to 8 bits; the low byte of the pattern of
+// fma(v, qmax / amax, 1.5 * 2^23) is the code itself).  16 x 32 x 32 x 384, 8 bits: 8.5 us as a butterfly.
+// NBLK: 64-channel blocks per row.  Four waves (token groups) per workgroup.
+enum Mode { kNibbles, kStatic, kBytes };
+template <int NBLK, int MODE>
 __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__restrict__ x, int64_t m, float qmax,
                                                            uint8_t *__restrict__ xq, float *__restrict__ scale,
                                                            const float *__restrict__ given) {
     constexpr int K = 64 * NBLK;
+    constexpr bool STATIC = MODE == kStatic, BYTES = MODE == kBytes;
     constexpr bool KEEP = STATIC || NBLK <= 4;   // transformed values stay in registers
     const int lane = threadIdx.x & 63;
     const int tok = lane & 15, q = lane >> 4;
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
             for (int r = 0; r < 4; ++r) v[4 * ct + r] = acc[r];
         }
     };
-    uint8_t *dst = xq + token * (K / 2) + 8 * q;
+    uint8_t *dst = BYTES ? xq + token * K + 16 * q : xq + token * (K / 2) + 8 * q;
 
     if constexpr (STATIC) {
         const float inv = 0.125f / given[0];
@@ -344,145 +348,158 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
         for (int blk = 0; blk < NBLK; ++blk) {
             float (&vb)[16] = v[KEEP ? blk : 0];
             if constexpr (!KEEP) transform(blk, vb);
-            uint2 w;
-            w.x = pack8_magic(vb, inv);
-            w.y = pack8_magic(vb + 8, inv);
-            if (live) *reinterpret_cast<uint2 *>(dst + 32 * blk) = w;
+            if constexpr (BYTES) {
+                const uint4 w = bytes16_magic(vb, inv);
+                if (live) *reinterpret_cast<uint4 *>(dst + 64 * blk) = w;
+            } else {
+                uint2 w;
+                w.x = pack8_magic(vb, inv);
+                w.y = pack8_magic(vb + 8, inv);
+                if (live) *reinterpret_cast<uint2 *>(dst + 32 * blk) = w;
+            }
         }
     }
 }
 
 // The same for tensors with too few tokens to fill the chip with one wave per 16 tokens: a
-// workgroup has one wave per 64-channel block of the row and handles groups of 16 tokens; wave b
-// transforms block b.  The abs-max of a token then needs every wave: they exchange their maxima
-// through LDS (one barrier per group, two sets of slots).  Workgroups are persistent and fetch
-// the next group's pieces before they work on the current one.
-template <bool STATIC>
+// workgroup handles groups of 16 tokens, with one wave for every NB 64-channel blocks of the row.  The abs-max of a
+// token then needs every wave: they exchange their maxima through LDS (one barrier per group, two sets
+// of slots).  Workgroups are persistent and fetch the next group's pieces before they work on the current one.
+template <int MODE, int NB>
 __global__ __launch_bounds__(64 * kMaxBlocks) void hadamard64_quant_split_f16(const __half *__restrict__ x, int64_t m,
                                                                         int k, float qmax,
                                                                         uint8_t *__restrict__ xq,
                                                                         float *__restrict__ scale,
                                                                         const float *__restrict__ given) {
+    constexpr bool STATIC = MODE == kStatic, BYTES = MODE == kBytes;
     __shared__ float s_amax[2][kMaxBlocks][16];
     const int lane = threadIdx.x & 63;
-    const int blk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // 64-channel block of this wave
-    const int nblk = k >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const int tok = lane & 15, q = lane >> 4;
 
-    // "A" operands: tile ct (4 tiles of 16 rows) x K half h.  Row i of tile ct is channel
-    // c = 16 (i / 4) + 4 ct + i % 4, so lane (token, q) ends up with channels 16 q + 4 ct + r.
-    // Sign of H[c][kk] = parity of popcount(c & kk), kk = 32 h + 8 q' + e with q' = this lane's
-    // K slice: the bits of e (0..2) and of 32 h + 8 q' (3..5) do not overlap, so the sign is
-    // (pattern over e from c & 7) xor (one bit from c & (32 h + 8 q')).
-    v8h hmat[4][2];
-    hadamard64_operands(lane, hmat);
-
     const int64_t groups = (m + 15) >> 4;
-    auto fetch = [&](int64_t grp, v8h (&b)[2]) {
+    auto fetch = [&](int64_t grp, v8h (&b)[NB][2]) {
         int64_t token = grp * 16 + tok;
         token = token < m ? token : m - 1;
-        const __half *src = x + token * k + 64 * blk + 8 * q;
-        b[0] = *reinterpret_cast<const v8h *>(src);
-        b[1] = *reinterpret_cast<const v8h *>(src + 32);
+        const __half *src = x + token * k + 64 * NB * wave + 8 * q;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            b[i][0] = *reinterpret_cast<const v8h *>(src + 64 * i);
+            b[i][1] = *reinterpret_cast<const v8h *>(src + 64 * i + 32);
+        }
     };
 
-    v8h b[2], bn[2];
+    v8h b[NB][2], bn[NB][2];
     int64_t grp = blockIdx.x;
     if (grp < groups) fetch(grp, b);
+    v8h hmat[4][2];
+    hadamard64_operands(lane, hmat);   // (while the first pieces are on their way)
     int set = 0;
     for (; grp < groups; grp += gridDim.x, set ^= 1) {
         const int64_t next = grp + gridDim.x;
         if (next < groups) fetch(next, bn);
 
-        float v[16];
+        float v[NB][16];
         float amax = 0.f;
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-            v4f acc = {0.f, 0.f, 0.f, 0.f};
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(hmat[ct][0], b[0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(hmat[ct][1], b[1], acc, 0, 0, 0);
+        for (int i = 0; i < NB; ++i) {
+            hadamard64_transform(hmat, b[i], v[i]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                v[4 * ct + r] = acc[r];
-                amax = fmaxf(amax, fabsf(acc[r]));
-            }
+            for (int r = 0; r < 16; ++r) amax = fmaxf(amax, fabsf(v[i][r]));
         }
         const int64_t token = grp * 16 + tok;
+        float inv, lo = 0.f, hi = 0.f;
         if constexpr (STATIC) {
-            if (token < m) {
-                const float inv = 0.125f / given[0];   // the sums are 8 x the orthonormal transform
-                const float lo = (-qmax - 1.0f) / inv, hi = qmax / inv;
-                uint2 w;
-                w.x = pack8_magic_clamped(v, inv, lo, hi);
-                w.y = pack8_magic_clamped(v + 8, inv, lo, hi);
-                *reinterpret_cast<uint2 *>(xq + token * (k >> 1) + 32 * blk + 8 * q) = w;
-            }
+            inv = 0.125f / given[0];   // the sums are 8 x the orthonormal transform
+            lo = (-qmax - 1.0f) / inv;
+            hi = qmax / inv;
         } else {
-            // the token's other three K slices of this block, then its other blocks
+            // the token's other three K slices of these blocks, then its other blocks
             amax = fmaxf(amax, __shfl_xor(amax, 16));
             amax = fmaxf(amax, __shfl_xor(amax, 32));
-            if (nblk > 1) {
-                if (q == 0) s_amax[set][blk][tok] = amax;
+            if (waves > 1) {
+                if (q == 0) s_amax[set][wave][tok] = amax;
                 __syncthreads();
-                for (int w = 0; w < nblk; ++w) amax = fmaxf(amax, s_amax[set][w][tok]);
+#pragma unroll
+                for (int w = 0; w < kMaxBlocks; w += 4)
+                    if (w < waves) amax = fmaxf(amax, s_amax[set][w + q < waves ? w + q : w][tok]);
+                amax = fmaxf(amax, __shfl_xor(amax, 16));
+                amax = fmaxf(amax, __shfl_xor(amax, 32));
             }
-            if (token < m) {
-                const float inv = amax > 0.f ? qmax / amax : 0.f;
-                if (blk == 0 && q == 0) scale[token] = amax > 0.f ? (amax * 0.125f) / qmax : 1.0f;
-                uint2 w;
-                w.x = pack8_magic(v, inv);
-                w.y = pack8_magic(v + 8, inv);
-                *reinterpret_cast<uint2 *>(xq + token * (k >> 1) + 32 * blk + 8 * q) = w;
+            inv = amax > 0.f ? qmax / amax : 0.f;
+            if (wave == 0 && q == 0 && token < m) scale[token] = amax > 0.f ? (amax * 0.125f) / qmax : 1.0f;
+        }
+        if (token < m) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int64_t at = token * k + 64 * (NB * wave + i) + 16 * q;
+                if constexpr (BYTES) {
+                    *reinterpret_cast<uint4 *>(xq + at) = bytes16_magic(v[i], inv);
+                } else {
+                    uint2 w;
+                    w.x = STATIC ? pack8_magic_clamped(v[i], inv, lo, hi) : pack8_magic(v[i], inv);
+                    w.y = STATIC ? pack8_magic_clamped(v[i] + 8, inv, lo, hi) : pack8_magic(v[i] + 8, inv);
+                    *reinterpret_cast<uint2 *>(xq + (at >> 1)) = w;
+                }
             }
         }
-        b[0] = bn[0];
-        b[1] = bn[1];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            b[i][0] = bn[i][0];
+            b[i][1] = bn[i][1];
+        }
     }
 }
 
-hq_status launch_hadamard64_split(const __half *x, int64_t m, int k, int bits, uint8_t *xq, float *scale,
-                            const float *given, hipStream_t stream) {
+template <int NB>
+hq_status launch_hadamard64_split(const __half *x, int64_t m, int k, float qmax, bool bytes, uint8_t *xq, float *scale,
+                                  const float *given, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
-    const float qmax = static_cast<float>((1 << (bits - 1)) - 1);
-    const int nblk = k / 64;
+    const int waves = k / 64 / NB;
     const int64_t groups = (m + 15) / 16;
     // resident workgroups: 32 waves per CU at the register use of this kernel
-    const int64_t cap = static_cast<int64_t>(hq::compute_units()) * (32 / nblk > 0 ? 32 / nblk : 1);
+    const int64_t cap = static_cast<int64_t>(hq::compute_units()) * (32 / waves);
     const int64_t rounds = (groups + cap - 1) / cap;          // groups per workgroup
     const int64_t grid = (groups + rounds - 1) / rounds;      // the same number for (almost) all of them
-    if (given)
-        hipLaunchKernelGGL(hadamard64_quant_split_f16<true>, dim3(static_cast<unsigned>(grid)), dim3(64 * nblk), 0,
-                           stream, x, m, k, qmax, xq, scale, given);
-    else
-        hipLaunchKernelGGL(hadamard64_quant_split_f16<false>, dim3(static_cast<unsigned>(grid)), dim3(64 * nblk), 0,
-                           stream, x, m, k, qmax, xq, scale, given);
+    const auto kernel = given   ? hadamard64_quant_split_f16<kStatic, NB>
+                        : bytes ? hadamard64_quant_split_f16<kBytes, NB>
+                                : hadamard64_quant_split_f16<kNibbles, NB>;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)), dim3(64 * waves), 0, stream, x, m, k, qmax, xq, scale, given);
     return check.status();
 }
 
 template <int NBLK>
-void launch_hadamard64_blocks(const __half *x, int64_t m, float qmax, uint8_t *xq, float *scale,
+void launch_hadamard64_blocks(const __half *x, int64_t m, float qmax, bool bytes, uint8_t *xq, float *scale,
                               const float *given, unsigned grid, hipStream_t stream) {
-    if (given)
-        hipLaunchKernelGGL((hadamard64_quant_f16<NBLK, true>), dim3(grid), dim3(256), 0, stream, x, m, qmax, xq,
-                           scale, given);
-    else
-        hipLaunchKernelGGL((hadamard64_quant_f16<NBLK, false>), dim3(grid), dim3(256), 0, stream, x, m, qmax, xq,
-                           scale, given);
+    const auto kernel = given   ? hadamard64_quant_f16<NBLK, kStatic>
+                        : bytes ? hadamard64_quant_f16<NBLK, kBytes>
+                                : hadamard64_quant_f16<NBLK, kNibbles>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, x, m, qmax, xq, scale, given);
 }
 
-hq_status launch_hadamard64(const __half *x, int64_t m, int k, int bits, uint8_t *xq, float *scale,
+// bytes: one code per byte (never with a given scale)
+hq_status launch_hadamard64(const __half *x, int64_t m, int k, int bits, bool bytes, uint8_t *xq, float *scale,
                             const float *given, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
+    const float qmax = static_cast<float>((1 << (bits - 1)) - 1);
     // one wave per 16 tokens needs about two waves per SIMD to hide the latency of its loads
     if ((m + 15) / 16 < 8 * static_cast<int64_t>(hq::compute_units()))
-        return launch_hadamard64_split(x, m, k, bits, xq, scale, given, stream);
-    const float qmax = static_cast<float>((1 << (bits - 1)) - 1);
+    {
+        // Blocks a wave: one, so that few tokens still make many waves; from 16 waves per CU on two or three, because starting more
+        // waves takes longer than what they overlap (a given scale has no barrier and gains nothing).  us, one -> two (three):
+        // 16384 x 384 6.4 -> 5.7, 8 bits 7.0 -> 6.3, 20000 x 960, 8 bits 17.9 -> (15.4); 8192 x 384 4.2 -> 4.2, 256 x 256 2.3 -> 2.4.
+        const int nblk = k / 64;
+        const bool fill = !given && (m + 15) / 16 * nblk > 16 * static_cast<int64_t>(hq::compute_units());
+        if (fill && nblk % 2 == 0) return launch_hadamard64_split<2>(x, m, k, qmax, bytes, xq, scale, given, stream);
+        if (fill && nblk % 3 == 0) return launch_hadamard64_split<3>(x, m, k, qmax, bytes, xq, scale, given, stream);
+        return launch_hadamard64_split<1>(x, m, k, qmax, bytes, xq, scale, given, stream);
+    }
     const int64_t wgs = ((m + 15) / 16 + 3) / 4;   // 16 tokens per wave, four waves per workgroup
     if (wgs > 0x7fffffffLL) return HQ_ERR_SHAPE;
     const unsigned grid = static_cast<unsigned>(wgs);
     switch (k / 64) {
 #define HQ_BLOCKS_CASE(N) \
-    case N: launch_hadamard64_blocks<N>(x, m, qmax, xq, scale, given, grid, stream); break;
+    case N: launch_hadamard64_blocks<N>(x, m, qmax, bytes, xq, scale, given, grid, stream); break;
         HQ_BLOCKS_CASE(1) HQ_BLOCKS_CASE(2) HQ_BLOCKS_CASE(3) HQ_BLOCKS_CASE(4)
         HQ_BLOCKS_CASE(5) HQ_BLOCKS_CASE(6) HQ_BLOCKS_CASE(7) HQ_BLOCKS_CASE(8)
         HQ_BLOCKS_CASE(9) HQ_BLOCKS_CASE(10) HQ_BLOCKS_CASE(11) HQ_BLOCKS_CASE(12)
@@ -571,8 +588,9 @@ hq_status act_hadamard_quant(const void *x, hq_dtype x_dtype, int64_t m, int k, 
                              bool bytes, uint8_t *xq, float *x_scale, const float *given, void *stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t *out = reinterpret_cast<uint32_t *>(xq);
-    if (x_dtype == HQ_F16 && had_block == 64 && k <= 64 * kMaxBlocks && a_bits != 8 && !bytes)
-        return launch_hadamard64(static_cast<const __half *>(x), m, k, a_bits, xq, x_scale, given, s);
+    const bool byte_codes = bytes || a_bits == 8;
+    if (x_dtype == HQ_F16 && had_block == 64 && k <= 64 * kMaxBlocks && !(byte_codes && given))
+        return launch_hadamard64(static_cast<const __half *>(x), m, k, a_bits, byte_codes, xq, x_scale, given, s);
     if (x_dtype == HQ_F16)
         return dispatch_block(static_cast<const __half *>(x), m, k, had_block, a_bits, bytes, out, x_scale, given, s);
     return dispatch_block(static_cast<const float *>(x), m, k, had_block, a_bits, bytes, out, x_scale, given, s);
