@@ -95,25 +95,19 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
         }
     }
     const int co = c0 + tile_row_to_channel(l);
-    const uint32_t w_lane = static_cast<uint32_t>(co < a.n ? co : a.n - 1) * a.row_bytes + h * 16;
-    const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.wq, static_cast<uint32_t>(a.n) * a.row_bytes);
-    int ld_step = 0, ld_plane = 0;   // of the next weights to load
-    uint32_t ld_at = 0;              // and where they are in the row
-    auto load_weights = [&](v4i &raw) {
-        // Padding steps, and what follows the last: zeros, from beyond the tensor, which ends at 2^32 - 32 at most.  (The uniform
-        // offset stays within the tensor: the bound that the lanes' offsets are held against is what it leaves of the size.)
-        const bool real = ld_step < steps && ld_plane < a.planes;
-        raw = buffer_load16(w_buf, w_lane | (real ? 0u : 0xFFFFFFE0u), real ? ld_at : 0u);
-        ld_at += 32;
-        if (++ld_step == steps_p) {
-            ld_step = 0;
-            ++ld_plane;
-            ld_at = static_cast<uint32_t>(ld_plane * cb);
-        }
+    const uint32_t w_lane = static_cast<uint32_t>(co < a.n ? co : a.n - 1) * a.row_bytes + h * 16, w_bytes = static_cast<uint32_t>(a.n) * a.row_bytes;
+    const __amdgpu_buffer_rsrc_t w_buf = buffer_of(a.wq, w_bytes);
+    uint32_t w_at = 0;   // of the next weights to load, in the row
+    // The steps that pad the last unit, and what follows the last plane, read zeros, from the end of the tensor on: the uniform offset
+    // is what the bound that the lanes' offsets are held against is less by, so it must not exceed the size.
+    const int pad = steps_p - steps;
+    auto load_weights = [&](v4i &raw, int k, bool last_unit) {
+        raw = buffer_load16(w_buf, w_lane, last_unit && k >= KS - pad ? w_bytes : min(w_at, w_bytes));
+        w_at += 32;
     };
     v4i raw[KS];
 #pragma unroll
-    for (int k = 0; k < KS; ++k) load_weights(raw[k]);
+    for (int k = 0; k < KS; ++k) load_weights(raw[k], k, a.units == 1);
     if (tid < PX) s_sum[tid] = 0;
     for (int i = tid; i < (steps_p - steps) * 2 * PX; i += nt) {   // padding steps
         const int at = steps * 2 * PX + i;
@@ -180,7 +174,13 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
     expand(raw[0], 1);
     auto add_codes = [](const v4i &w, int sum) { return sum_codes8(w.x, sum_codes8(w.y, sum_codes8(w.z, sum_codes8(w.w, sum)))); };
     int w_first = add_codes(raw[0], 0);   // of the coming unit's first step
-    load_weights(raw[0]);
+    // (a unit's first step is expanded, and its place loaded again, with the last step of the unit before)
+    int planes_left = PLANES ? a.planes : 1;   // to load
+    auto load_first = [&](int unit) {
+        if (unit == 0) w_at = --planes_left == 0 ? w_bytes : w_at - pad * 32;   // (the next plane follows the real steps)
+        load_weights(raw[0], 0, false);
+    };
+    load_first(a.units == 1 ? 0 : 1);
     for (int plane = 0; plane < (PLANES ? a.planes : 1); ++plane) {
         w_sum = 0;
 #pragma unroll
@@ -206,9 +206,13 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
                     if (t == (NT > 1)) {
                         expand(next, 1);
                         const int sum = add_codes(next, k + 1 < KS ? w_sum : 0);
-                        if (k + 1 < KS) w_sum = sum;
-                        else w_first = sum;
-                        load_weights(next);
+                        if (k + 1 < KS) {
+                            w_sum = sum;
+                            load_weights(next, k + 1, u1 == a.units - 1);
+                        } else {
+                            w_first = sum;
+                            load_first(u1 + 1 < a.units ? u1 + 1 : 0);
+                        }
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
