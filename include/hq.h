@@ -198,7 +198,7 @@ hq_status hq_act_quant_int_linear(const void *x, hq_dtype x_dtype, const uint8_t
  *   "tile"              the other 1x1 layers, and 3x3 layers whose image rows are too long for the activation tile or that
  *                       are estimated to be faster here
  *   "tile (stride 2)"
- *   "small-channel-count"   c_in not a multiple of 64
+ *   "small-channel-count"   c_in not a multiple of 64 (whichever kernel it goes to)
  *   "unsupported"
  * It depends on the geometry only, never on y_dtype, but that fp32 results with per-pixel scales need more room on chip: their
  * tile may be another one, and at the longest image rows that fit they run "tile".

@@ -136,11 +136,11 @@ hq_status int_linear(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
     if (!fits_32bit(m, 1, n, 1, bits == 8 ? 2 * k : k)) return HQ_ERR_UNSUPPORTED;
     GemmArgs a{xq, x_scale, wq, w_scale, bias, y, static_cast<uint32_t>(m), n, k, 1, 1, 0, 0, 0, 1, sx_static,
                1.0f, bits};
-    if (k % 64 != 0) return hq_gemm_launch_anyk(a, 1, y_dtype, static_cast<hipStream_t>(stream));
     if (bits == 4) {
         st = hq_linear_fp6_launch(a, 1, y_dtype, static_cast<hipStream_t>(stream));
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
+    if (k % 64 != 0) return hq_gemm_launch_anyk(a, 1, y_dtype, static_cast<hipStream_t>(stream));
     return launch_gemm(a, 1, y_dtype, static_cast<hipStream_t>(stream));
 }
 
@@ -190,7 +190,6 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
         a.pixels = static_cast<uint32_t>(static_cast<int64_t>(nb) * a.h_out * a.w_out);
         return hq_gemm_launch_64x64(a, 9, y_dtype, st_);
     }
-    if (c_in % 64 != 0) return hq_gemm_launch_anyk(a, r * s, y_dtype, st_);
     if (r == 3) {
         if (takes_wave_split(pixels, c_in, c_out, bits)) return hq_conv3x3_wave_launch(a, y_dtype, st_);
         st = hq_resident_launch(a, 0, y_dtype, st_);
@@ -200,6 +199,7 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
         st = hq_linear_fp6_launch(a, 1, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
+    if (c_in % 64 != 0) return hq_gemm_launch_anyk(a, r * s, y_dtype, st_);
     return launch_gemm(a, r * s, y_dtype, st_);
 }
 

@@ -2,8 +2,10 @@
 // 64 (Method, "Matrix Multiplication": a layer with fewer input channels than the transform's
 // order keeps H = I, e.g. the convolution on a 4- or 8-channel latent; such layers are small).
 //
-// The large kernels fetch 64-code chunks with 16-byte direct-to-LDS loads and so need rows that
-// are whole chunks.  Here a workgroup of four waves owns a 64-pixel x 64-channel tile (one 32 x 32
+// Only what the 6-bit kernels refuse comes here: linear layers of less than 64 channels and 2^20 products, tokens or image rows too
+// long for the LDS.
+//
+// A workgroup of four waves owns a 64-pixel x 64-channel tile (one 32 x 32
 // MFMA tile per wave) and walks K in chunks of 32 codes: 128 threads fetch one row's chunk each
 // with four guarded dword loads (a dword past the end of the row is taken as zero codes, which
 // is what pads K up to a multiple of 32; K is a multiple of 8, so validity is per dword), expand

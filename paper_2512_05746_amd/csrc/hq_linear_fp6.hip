@@ -8,6 +8,9 @@
 //     sum (x + 8)(w + 8) = sum x w + 8 (sum x + 8 K) + 8 sum w;
 // the code sums are taken with dot products on the way, and one small fp16 matrix step per tile subtracts them, exactly.
 //
+// K that is no multiple of 64 (but of 8): the last step is filled up with activation codes of zero, on the way into LDS; what the
+// weights' loads find beyond the end of a row then does not matter, since the correction counts it as well.
+//
 // Digit planes of the weights (the Single scheme: [n, 3, k/2], planes weighing 1, 16, 256): one such product for every plane, folded
 // into fp32 sums, the tokens expanded once for all.
 //
@@ -60,7 +63,7 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
     const int tid = threadIdx.x, nt = blockDim.x, nw = nt >> 6;
     const int lane = tid & 63, l = lane & 31, h = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cb = a.k >> 1, steps = a.k >> 6, steps_p = a.units * KS;
+    const int cb = a.k >> 1, steps = (a.k + 63) >> 6, steps_p = a.units * KS;
     const int part8 = steps_p * STEP16;
     int *s_sum = reinterpret_cast<int *>(lds + operand_bytes(PX, steps_p));
     float *s_sx = reinterpret_cast<float *>(s_sum + PX);
@@ -129,6 +132,14 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
         f_sum = sum_codes8(p.x, sum_codes8(p.y, sum_codes8(p.z, sum_codes8(p.w, f_sum))));
     };
     for (int step = f_step0; step < steps; step += AHEAD * f_stride) {
+        if (a.k & 63) {   // the last step is not whole: the rest are codes of zero (here, once for all loads: 2 % less than at every step)
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i)
+                if (step + i * f_stride == steps - 1) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) p[i][e] = f_half * 4 + e < (a.k & 63) >> 3 ? p[i][e] : 0;
+                }
+        }
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
             if (step + i * f_stride >= steps) break;
@@ -222,7 +233,7 @@ __global__ __launch_bounds__(512, !PLANES || NT == 1 ? 4 : NT == 2 ? 3 : 2) void
         const v4h w_part = {half_of(w_sum & 1023), half_of(w_sum >> 10), 1.0f16, 1024.0f16};
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const int s_x = s_sum[t * 32 + l] + 8 * a.k;
+            const int s_x = s_sum[t * 32 + l] + 8 * 64 * steps;
             const _Float16 of_x = h ? 0.0f16 : -0.125f16;
             const v4h x_part = {-0.125f16, -128.0f16, half_of(s_x & 1023) * of_x, half_of(s_x >> 10) * of_x};
             acc[t] = __builtin_amdgcn_mfma_f32_32x32x8f16(w_part, x_part, acc[t], 0, 0, 0);
@@ -335,9 +346,9 @@ int choose_unit(int steps, int nt_log2) {
 }
 
 Cut lay_out(int k, int nt_log2, int nw) {
-    Cut c{nt_log2, choose_unit(k / 64, nt_log2), nw, 0, false};
+    Cut c{nt_log2, choose_unit((k + 63) / 64, nt_log2), nw, 0, false};
     const int ks = kUnits[nt_log2][c.unit], px = 32 << nt_log2;
-    c.lds = operand_bytes(px, (k / 64 + ks - 1) / ks * ks) + table_bytes(px, nw);
+    c.lds = operand_bytes(px, ((k + 63) / 64 + ks - 1) / ks * ks) + table_bytes(px, nw);
     c.ok = c.lds <= kLdsPerCu;
     return c;
 }
@@ -347,7 +358,7 @@ Cut lay_out(int k, int nt_log2, int nw) {
 // 131072 tokens, 64 to 4096 channels in, 8 to 5120 out, six cuts each: 12 % rms; the cut it picks is 0.8 % off the best one
 // on average.
 double cut_us(const Cut &c, int pixels, int n, int k, int planes, int cus) {
-    const int nt = 1 << c.nt_log2, blocks = (n + 31) / 32, steps = k / 64;
+    const int nt = 1 << c.nt_log2, blocks = (n + 31) / 32, steps = (k + 63) / 64;
     const int ks = kUnits[c.nt_log2][c.unit], steps_p = (steps + ks - 1) / ks * ks;
     const int64_t wgs = static_cast<int64_t>((pixels + 32u * nt - 1) >> (5 + c.nt_log2)) * ((blocks + c.nw - 1) / c.nw);
     const double per_cu = ceil(static_cast<double>(wgs) / cus);
@@ -367,6 +378,8 @@ double cut_us(const Cut &c, int pixels, int n, int k, int planes, int cus) {
 // 1152 11.4 / 12.0; 105 of 111 are faster by 3 % and more, one is 20 % slower); from 576 on, and for digit planes, the two estimates
 // decide, which are 10 and 7 % off, so it has to be 8 % ahead for small layers and not 5 % behind for large ones (77907 x 1344 -> 64
 // 25.8 / 14.8, 23950 x 960 -> 544 26.7 / 19.9, 44867 x 768 -> 576 40.8 / 30.9; 2048 x 960 -> 3840 13.0 / 14.4, 57956 x 1344 -> 296 44.4 / 81.7).
+// K that are no multiple of 64 go to the kernel of hq_int_gemm_anyk.hip only below one step and 2^20 products (27 x 40 -> 24 4.0 / 4.5;
+// 2209 x 24 -> 88 6.1 / 4.2, 4096 x 200 -> 400 11.2 / 5.1, 8192 x 920 -> 1152 120 / 20; 200 random layers 0.66 of the time).
 // For other K this kernel is up to 2.5 times faster (64 x 640 -> 640: 4.7 against 7.2 us, 8192 x 640 -> 640: 9.0 against 10.7,
 // 512 x 4096 -> 1024: 14 against 30), save for many rounds of tiles of 32 tokens (9535 x 4096 -> 1920: 188 against 107).
 Cut choose_cut(int pixels, int n, int k, int planes) {
@@ -374,6 +387,7 @@ Cut choose_cut(int pixels, int n, int k, int planes) {
     if (n >= 1 << 21) return best;   // (a tile's results lie within 2 GiB of their first)
     const double products = static_cast<double>(pixels) * n * k * planes;
     const bool tile_k = k % 192 == 0;
+    if (k % 64 && k < 64 && products < 1 << 20) return best;
     if (tile_k && (n < 32 || (n % 16 == 0 && products < 1.5e9) || !lay_out(k, 2, 8).ok)) return best;
     const int cus = hq::compute_units();   // (asks the runtime for the device: once)
     double best_us = HUGE_VAL;
@@ -422,7 +436,7 @@ hq_status hq_linear_fp6_launch(const GemmArgs &g, int planes, hq_dtype y_dtype, 
     a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.sx_static = g.sx_static; a.planes = planes; a.out_scale = g.out_scale;
     a.row_bytes = static_cast<uint32_t>(g.k / 2) * (planes > 1 ? 3 : 1);
     const int ks = kUnits[c.nt_log2][c.unit];
-    a.units = (g.k / 64 + ks - 1) / ks;
+    a.units = ((g.k + 63) / 64 + ks - 1) / ks;
     const int px = 32 << c.nt_log2;
     const int64_t px_tiles = (static_cast<int64_t>(g.pixels) + px - 1) / px, ch_groups = ((g.n + 31) / 32 + c.nw - 1) / c.nw;
     if (px_tiles * ch_groups > 0x7fffffff) return HQ_ERR_UNSUPPORTED;

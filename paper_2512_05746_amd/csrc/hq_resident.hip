@@ -23,7 +23,7 @@ Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int x
     const int blocks = (n + 31) / 32;
     Plan p{};
     p.ks = ks;
-    p.slices = (k / 64 + ks - 1) / ks;
+    p.slices = ((k + 63) / 64 + ks - 1) / ks;
     p.nw = nw;
     p.xw_log2 = xw_log2;
     p.cb = cb;
@@ -95,7 +95,7 @@ Cost cost_of(const Plan &p, int kind, int64_t pixels, int n, int cus) {
 
 // The best cut, not ok if none fits the LDS.
 Plan choose_plan(int kind, bool by_slice, int64_t pixels, int w, int k, int n, Cost &cost) {
-    const int steps = k / 64, cus = hq::compute_units();
+    const int steps = (k + 63) / 64, cus = hq::compute_units();
     const int ks = steps % 3 == 0 || steps > 4 ? 3 : steps == 1 ? 1 : 2;
     Plan best{};
     if (n >= 1 << 21) return best;   // (a tile's results lie within 2 GiB of their first)
@@ -130,7 +130,7 @@ Plan spread_out(const Plan &p, int kind, bool by_slice, int64_t pixels, int w, i
 Plan choose_kernel(int kind, int had_block, int64_t pixels, int w, int k, int n) {
     Cost cost{};
     Plan p = choose_plan(kind, false, pixels, w, k, n, cost);
-    if (!p.ok) return p;
+    if (!p.ok || k % 64) return p;   // (the tile kernel takes whole steps only)
     struct Us { double kclock, chunk; };   // of a thousand clocks, and of making a set of slices resident
     constexpr Us us[4] = {{0.42, 1.6}, {0.42, 1.6}, {0.34, 2.2}, {0.42, 1.3}};   // by kind; fitted as hq_tile_us, 7 .. 11 % rms
     const int chunks = (p.slices + p.chunk - 1) / p.chunk;
@@ -174,7 +174,7 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     a.out_scale = g.out_scale;
     const hq::Magic31 mw = hq::magic31(static_cast<uint32_t>(g.w)), mh = hq::magic31(static_cast<uint32_t>(g.h));
     a.w_magic = mw.m; a.w_shift = mw.s; a.h_magic = mh.m; a.h_shift = mh.s;
-    const int steps = g.k / 64, resident = std::min(p.chunk * p.ks, steps), last = steps % resident ? steps % resident : resident;
+    const int steps = (g.k + 63) / 64, resident = std::min(p.chunk * p.ks, steps), last = steps % resident ? steps % resident : resident;
     a.chunk = resident;
     a.inverses = inverse_of(resident) | inverse_of((resident + 2) / 3) << 16;
     a.inverses_last = inverse_of(last) | inverse_of((last + 2) / 3) << 16;

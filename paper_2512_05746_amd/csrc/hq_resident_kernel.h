@@ -46,6 +46,10 @@
 // instruction takes for every column) instead of reading a row of zeros, which would cost every tile an address of its own
 // in every step; what they leave, below 1e-35, is rounded away before the sums are scaled.
 //
+// Channel counts that are no multiple of 64 (but of 8): the last step of a tap is filled up with activation codes of zero, whatever
+// the weights' loads find beyond the tap.  us a call, the kernel of hq_int_gemm_anyk.hip -> this one: 2 x 32 x 32 x 200 32.7 -> 9.2,
+// 4 x 32 x 32 x 328 58.9 -> 13.2; 150 random layers of 8 to 952 channels 0.43 of the time, none slower.
+//
 // Which layers come here and which stay on the tile kernel: choose_kernel in hq_resident.hip.
 //
 // Weights carry an offset of 8 (hq_fp6.h; not those of 8 bits): a sum exceeds the wanted one by 8 x (sum of the activation
@@ -318,13 +322,13 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
             w_row[j] = row_of(row) + (BYTES ? (lane & 3) ^ ((row >> 2) & 3) : (lane & 1) ^ ((row >> 3) & 1)) * 16;
         }
         if constexpr (RING == 0) w_row[0] = row_of(l) + h * 16;
-        // (A tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only.  So are chunks, for the
-        // sake of the groups of steps.)
+        // (A tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only.  So are chunks and
+        // taps whose last step is not whole, for the sake of the groups of steps.)
         struct Cut { int tap, step; };
         auto cut = [&](int of) {
             if constexpr (NS > 0) {
                 return Cut{of * TAPS >> kl, 0};
-            } else if (OUT == kOutF32 || a.chunk < a.k >> 6) {
+            } else if (OUT == kOutF32 || cb != ns * STEP) {
                 const int grains = (ns + 2) / 3, at = of * (TAPS * grains) >> kl, tap = quotient(at, (ns == a.chunk ? a.inverses : a.inverses_last) >> 16);
                 return Cut{tap, (at - tap * grains) * 3};
             } else {
@@ -368,6 +372,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
     uint32_t f_off = 0, f_row_bytes = 0, plane_bytes = 0;
     const uint8_t *x_codes = nullptr;
     uint32_t part8 = 0;
+    int tail = 0, tail_step = 0;   // packed dwords of the last step if it is not whole, and which it is
     int in_planes = 0;
     int *f_sum = nullptr;     // code sums
     short *f_part = nullptr;
@@ -392,6 +397,17 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
                 if (IN < 3 || i < in_planes) p[i][k] = buffer_load16(x_buf, off, i * (BYTES ? 32u : plane_bytes) + (s0 + item.step + k) * STEP);
                 else p[i][k] = v4i{0, 0, 0, 0};
             }
+    };
+    auto cut_tail = [&](v4i (&p)[IN][PIECES], const Item &item) {   // the rest are codes of zero
+        if constexpr (IN == 1) {
+            if (tail == 0) return;   // (one branch an item: 2 % less than at every step)
+#pragma unroll
+            for (int k = 0; k < PIECES; ++k)
+                if (item.step + k == tail_step) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) p[0][k][e] = f_half * 4 + e < tail ? p[0][k][e] : 0;
+                }
+        }
     };
     auto fill_store = [&](const v4i (&p)[IN][PIECES], const Item &item) {
         const int row = item.row + f_row;
@@ -450,6 +466,8 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
         plane_bytes = a.pixels * cb;
         in_planes = a.in_planes;
         part8 = a.part8;
+        tail = (a.k & 63) >> 3;
+        tail_step = (a.k >> 6) - s0;
         const Tables table = tables_of(a);
         f_sum = table.sum;
         f_part = table.part;
@@ -507,6 +525,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) {
                 if (store_item.row >= row_span) break;
+                cut_tail(p[i], store_item);
                 fill_store(p[i], store_item);
                 next(store_item);
                 fill_load(p[i], load_item);
@@ -514,7 +533,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
             }
         }
         KernelArgs &a = args_again();
-        const int tid = thread_again(), nt = nw * 64, px_wg = 128 << a.xw_log2, halo = a.w + 1, steps = a.k >> 6;
+        const int tid = thread_again(), nt = nw * 64, px_wg = 128 << a.xw_log2, halo = a.w + 1;
         const uint32_t cb = row_bytes(a);
         const Tables table = tables_of(a);
         if (s0 == 0) {
@@ -897,7 +916,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
                 if constexpr (RING > 0) wait_vmem<0>();   // (nothing arrives in the ring any more)
             }
             asm volatile("" : : "v"(touched));
-            if (s0 + ns < a.k >> 6) break;   // the sums go on with the next chunk (one phase: host)
+            if (s0 + ns < (a.k + 63) >> 6) break;   // the sums go on with the next chunk (one phase: host)
 
             // ---- results of the phase --------------------------------------------------------------------------
             if constexpr (!INT_TAPS) {
@@ -1071,7 +1090,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
 
         // ---- next chunk -----------------------------------------------------------------------------------------
         s0 += ns;
-        ns = min(a.chunk, steps - s0);
+        ns = min(a.chunk, ((a.k + 63) >> 6) - s0);
         KernelArgs &again = args_again();
         begin_fill(again);
         begin_task(again);

@@ -125,3 +125,38 @@ def test_linear_single_of_large_token_scales(m, k, n, block):
         fits = (total * scale).abs() < 3.4e38
         assert fits[:, : n // 2].all()
         assert ((y - exact).abs() <= 8 * 2.0 ** -24 * exact.abs())[fits].all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,k,n", [
+    (1, 8, 1), (27, 40, 24),          # the kernel for few channels
+    (1, 72, 1), (70, 120, 33),        # one packed dword in the last step, seven; loads that reach beyond the tensor
+    (3000, 56, 440), (2100, 200, 96), (500, 952, 264), (9000, 328, 640), (40, 6392, 33), (40, 8200, 33)])
+def test_linear_k_no_multiple_of_64(m, k, n):
+    """As above.  The codes that follow a row in memory are extreme, so that what a load finds there would show."""
+    import paper_2512_05746_amd as hq
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(m + k + n)
+    xq = torch.randint(0, 256, (m, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    wq = torch.randint(0, 256, (n, k // 2), dtype=torch.uint8, device="cuda", generator=g)
+    xq[:, :4], wq[:, :4] = 0x88, 0x88
+    sx = torch.rand((m,), generator=g, device="cuda") + 0.1
+    sw = torch.rand((n,), generator=g, device="cuda") * 1e-4 + 1e-5
+    bias = torch.randn((n,), generator=g, device="cuda")
+
+    def codes(q):
+        v = torch.stack([q & 15, q >> 4], -1).flatten(-2).double()
+        return torch.where(v > 7, v - 16, v)
+
+    acc = codes(xq) @ codes(wq).T.contiguous()
+    assert torch.equal(hq.hq_int_linear(xq, sx, wq, sw, None, y_dtype=torch.int32).double(), acc)
+    for scale, call in ((sx, hq.hq_int_linear), (sx[:1], hq.hq_int_linear_static)):
+        exact = acc * scale.double()[:, None] * sw.double()
+        for dtype in (torch.float32, torch.float16):
+            limit = 4 * 2.0 ** -24 * (exact.abs() + bias.double().abs())
+            want = exact + bias.to(dtype).double()
+            if dtype == torch.float16:
+                limit = limit + want.abs() * 2.0 ** -11 + 2.0 ** -25
+            y = call(xq, scale, wq, sw, bias.to(dtype), y_dtype=dtype)
+            assert ((y.double() - want).abs() <= limit).all()

@@ -340,3 +340,31 @@ def test_conv3x3_steps_of_a_tap(hq, nb, h, w, cin, cout):
     wq = rng.integers(-128, 128, (cout, 3, 3, cin)).astype(np.int8)
     acc_o, y_o = oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)
     check(hq.hq_int_conv2d_i8, dev(xq), dev(sx), dev(wq.reshape(cout, 9, cin)), acc_o, y_o, 1e-5)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (1, 1, 1, 8, 1),             # one packed dword a tap; the loads of the last tap reach beyond the tensor
+    (2, 9, 8, 72, 40), (1, 12, 24, 184, 33),   # two and three steps a tap, unrolled; seven packed dwords in the last
+    (3, 9, 16, 248, 72),         # four, unrolled for codes
+    (2, 16, 16, 328, 200),       # six steps: shares begin within a tap
+    (1, 33, 24, 456, 40), (2, 8, 8, 952, 96),  # eight and fifteen
+    (1, 3, 88, 952, 40),         # some resident at a time
+    (1, 4, 300, 200, 40),        # rows too long: the kernel for few channels
+])
+def test_conv3x3_channels_no_multiple_of_64(hq, nb, h, w, cin, cout):
+    """As test_conv3x3_steps_of_a_tap.  Weights of -8 follow the end of every row, so that what a load finds there would show."""
+    rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
+    xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
+    wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
+    wq[..., :8], xq[..., :8] = -8, 7
+    sx = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
+    sw = rng.uniform(1e-5, 1e-3, cout).astype(np.float32)
+    bias = rng.standard_normal(cout).astype(np.float16)
+    x4, w4 = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
+    s1 = torch.tensor([0.37], dtype=torch.float32, device="cuda")
+    for call, scale, (acc_o, y_o) in (
+            (hq.hq_int_conv2d, dev(sx), oracle.int_conv2d(xq, sx, wq, sw, bias, stride=1, pad=1)),
+            (hq.hq_int_conv2d_static, s1, oracle.int_conv2d_static(xq, 0.37, wq, sw, bias, stride=1, pad=1))):
+        assert np.array_equal(host(call(x4, None, w4, None, None, ksize=3, y_dtype=torch.int32)), acc_o)
+        for ydt, tol in ((torch.float32, 1e-5), (torch.float16, 1e-3)):
+            check_y("y", host(call(x4, scale, w4, dev(sw), dev(bias).to(ydt), ksize=3, y_dtype=ydt)), y_o, rtol=tol)
