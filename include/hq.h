@@ -111,8 +111,8 @@ hq_status hq_act_hadamard_quant(const void *x, hq_dtype x_dtype, int64_t m, int 
  *   y[i, j]   = acc[i, j] * x_scale[i] * w_scale[j] + bias[j]   (fp32, cast to y_dtype)
  *
  *   xq [m, k/2], x_scale [m], wq [n, k/2], w_scale [n]; bias [n] of y_dtype or
- *   NULL; k a multiple of 8 (multiples of 64 take the fast kernels; any other multiple of 8, e.g.
- *   the few channels of a layer that keeps H = I, takes a small general kernel), k < 131072; y [m, n].
+ *   NULL; k a multiple of 8 (the last of its 64-code steps is filled up with zeros; the smallest layers of the few channels
+ *   that keep H = I take a small general kernel), k < 131072; y [m, n].
  *   y_dtype == HQ_I32 writes acc itself (bias and scales ignored; they may be NULL).
  */
 hq_status hq_int_linear(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
@@ -136,7 +136,7 @@ hq_status hq_int_linear(const uint8_t *xq, const float *x_scale, const uint8_t *
  *   Built: R = S in {1, 3}, stride 1, pad (R-1)/2 (h_out = h, w_out = w), and the
  *   downsampling form R = S = 3, stride 2, pad 1 (h_out = (h-1)/2 + 1,
  *   w_out = (w-1)/2 + 1); anything else returns HQ_ERR_UNSUPPORTED.
- *   c_in a multiple of 8 at stride 1 (multiples of 64 take the fast kernels), a multiple of 64 at stride 2.
+ *   c_in a multiple of 8 at stride 1, a multiple of 64 at stride 2.
  *   y_dtype == HQ_I32 writes the per-tap accumulators [nb, h_out, w_out, R*S, c_out].
  */
 hq_status hq_int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
