@@ -5,6 +5,7 @@
 #include "hq_resident_kernel.h"
 
 const void *hq_resident_pertap(int out, int form);
+const void *hq_resident_wholetaps(int out, int form);
 const void *hq_resident_sum(int out, int form);
 const void *hq_resident_planes(int out, int form);
 const void *hq_resident_bytes(int out, int form);
@@ -18,7 +19,7 @@ struct Plan {
 };
 
 // LDS layout of a workgroup of nw waves, 1 << xw_log2 pixel groups and cb channel blocks within `budget` bytes.  by_slice: with a
-// table of 16-bit code sums by row and step behind the others (fp32 results of per-pixel scales).
+// table of 16-bit code sums by row and three steps behind the others (kResWholeTaps).
 Plan lay_out(int kind, bool by_slice, int w, int k, int n, int ks, int nw, int xw_log2, int cb, int budget) {
     const int blocks = (n + 31) / 32;
     Plan p{};
@@ -139,13 +140,23 @@ Plan choose_kernel(int kind, int had_block, int64_t pixels, int w, int k, int n)
     return p;
 }
 
+// As launched.  by_slice: another cut of the same layers (they need more room), so that which kernel runs does not depend on the results.
+Plan plan_of(int kind, bool by_slice, int had_block, int64_t pixels, int w, int k, int n) {
+    Plan p = choose_kernel(kind, had_block, pixels, w, k, n);
+    if (p.ok && by_slice) {
+        Cost cost{};
+        p = choose_plan(kind, true, pixels, w, k, n, cost);
+    }
+    return spread_out(p, kind, by_slice, pixels, w, k, n);
+}
+
 int kind_of(int bits, int sx_static) { return bits == 8 ? kResBytes : sx_static ? kResSum : kResPerTap; }
 
 }  // namespace
 
 const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, int sx_static) {
     const int kind = kind_of(bits, sx_static);
-    const Plan p = spread_out(choose_kernel(kind, 0, pixels, w, k, n), kind, false, pixels, w, k, n);
+    const Plan p = plan_of(kind, kind == kResPerTap && k % 64, 0, pixels, w, k, n);
     if (!p.ok) return nullptr;
     static const char *const names[2][2][2] = {   // [pixels][waves][slices resident at a time]
         {{"activation-resident (128 pixels, 4 waves)", "activation-resident (128 pixels, 4 waves, slices in turn)"},
@@ -159,14 +170,11 @@ const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, 
 hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     const int kind = had_block ? kResPlanes : kind_of(g.bits, g.sx_static);
-    Plan p = choose_kernel(kind, had_block, g.pixels, g.w, g.k, g.n);
-    const bool by_slice = kind == kResPerTap && y_dtype == HQ_F32;
-    if (p.ok && by_slice) {
-        Cost cost{};
-        p = choose_plan(kind, true, g.pixels, g.w, g.k, g.n, cost);
-    }
+    // fp16 results of ragged channels: as exact as those of the kernel for few channels, which takes the layers that do not fit.
+    // us a call, kResPerTap -> kResWholeTaps: 2 x 32 x 32 x 200 9.2 -> 9.4, 4 x 32 x 32 x 328 12.9 -> 14.0, 2 x 24 x 24 x 952 17.9 -> 18.5.
+    const bool whole_taps = kind == kResPerTap && (y_dtype == HQ_F32 || (y_dtype == HQ_F16 && g.k % 64));
+    const Plan p = plan_of(kind, whole_taps, had_block, g.pixels, g.w, g.k, g.n);
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
-    p = spread_out(p, kind, by_slice, g.pixels, g.w, g.k, g.n);
     ResidentArgs a{};
     a.xq = g.xq; a.sx = g.sx; a.wq = g.wq; a.sw = g.sw; a.bias = g.bias; a.y = g.y;
     a.pixels = g.pixels; a.n = g.n; a.k = g.k; a.h = g.h; a.w = g.w;
@@ -200,10 +208,11 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     const int form = resident_form(p.ring, ns);
     const void *fn = kind == kResBytes    ? hq_resident_bytes(out, form)
                      : kind == kResPlanes ? hq_resident_planes(out, form)
-                     : kind == kResSum  ? hq_resident_sum(out, form)
-                                        : hq_resident_pertap(out, form);
-    static std::atomic<uint64_t> allowed[4][3][7];
-    const hq_status st = allow_lds(fn, allowed[kind][out][form]);
+                     : kind == kResSum    ? hq_resident_sum(out, form)
+                     : whole_taps         ? hq_resident_wholetaps(out, form)
+                                          : hq_resident_pertap(out, form);
+    static std::atomic<uint64_t> allowed[5][3][7];
+    const hq_status st = allow_lds(fn, allowed[whole_taps ? kResWholeTaps : kind][out][form]);
     if (st != HQ_OK) return st;
     void *args[] = {&a};
     if (hipLaunchKernel(fn, dim3(static_cast<unsigned>(tiles)), dim3(64 * p.nw), args, p.lds, stream) != hipSuccess)

@@ -58,7 +58,9 @@
 // With per-pixel scales the fp32 sums start from minus the correction and then hold it in part, which costs digits: the 2-norm
 // error is 2e-7 .. 3e-7 where code sums are small, up to 1.5e-5 where the codes of a pixel have one sign (64 .. 960 channels),
 // below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).  fp32 results would lose digits, so there
-// the sums of a tap start at minus its correction (one fp16 matrix step per tap and tile): 6e-8, as with sums in integers.
+// the sums of a tap start at minus its correction (one fp16 matrix step per tap and tile): 6e-8, as with sums in integers.  So do
+// they for fp16 results of channel counts that are no multiple of 64: 0.02 % of these differ from the exact result rounded once, as
+// with sums in integers, against 0.3 % (8 to 952 channels).
 #pragma once
 #include <stddef.h>
 
@@ -106,6 +108,7 @@ constexpr int kResPerTap = 0;   // 3x3, per-pixel scales: one sum per tap, combi
 constexpr int kResSum = 1;      // 3x3, one scale: one sum over all taps
 constexpr int kResPlanes = 2;   // as kResSum, with activations u = d0 + 16 (d1 + 16 d2) in three digit planes, |d1 + 16 d2| <= 16
 constexpr int kResBytes = 3;    // as kResPerTap, with 8-bit codes on the int8 instruction
+constexpr int kResWholeTaps = 4;   // as kResPerTap, with sums of taps that start at minus their correction (fp32 results; fp16 ones of ragged channels)
 
 // Direct-to-LDS load of 16 bytes a lane: lane i's land at lds_base + 16 i.  Inline assembly, because the compiler cannot tell which
 // slot of a ring such a load fills and would wait for all of them before every LDS read; the waits (wait_vmem) are placed by
@@ -127,7 +130,7 @@ __device__ __forceinline__ void load_to_ring(const v4i &r, uint32_t &lane_off, u
 // 2 x 30 x 25 x 256 -> 504 10.2 -> 9.4; the width axis, whose operand planes take twice the registers, 2 x 12 x 40 x 256 11.6 -> 12.2).
 __host__ __device__ constexpr int resident_unrolled(int kind, int out, int ns) {
     const bool int_taps = out == kOutI32 && (kind == kResPerTap || kind == kResBytes);
-    return ns <= (kind == kResPerTap || kind == kResSum ? 4 : 3) && !int_taps ? ns : 0;
+    return ns <= (kind == kResPlanes || kind == kResBytes ? 3 : 4) && !int_taps ? ns : 0;
 }
 // bytes of a step's weights for 32 channels, a slot of a ring
 __host__ __device__ constexpr int resident_slot_bytes(int kind) { return kind == kResBytes ? 2048 : 1024; }
@@ -183,8 +186,8 @@ __device__ __forceinline__ int thread_again() {
 //     width axis        4 x 49 x 48 x 192, block 16 14.7 -> 12.4;   8 bits  12 x 23 x 17 x 384 -> 392 (a slice at a time) 20.2 -> 18.2
 template <int OUT, int KIND, int RING, int NS>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
-    constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
-    constexpr bool WHOLE_TAPS = KIND == kResPerTap && OUT == kOutF32;   // (see the offset of the weights above)
+    constexpr bool WHOLE_TAPS = KIND == kResWholeTaps;   // (see the offset of the weights above)
+    constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || WHOLE_TAPS || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
     constexpr int TAPS = 9, NT = 4;
     // planes in memory, operand planes in LDS (BYTES: the two 32-channel halves of a step) and of the weights
     constexpr int IN = KIND == kResPlanes ? 3 : BYTES ? 2 : 1, PL = KIND == kResPlanes || BYTES ? 2 : 1, WP = BYTES ? 2 : 1;
@@ -322,7 +325,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
             w_row[j] = row_of(row) + (BYTES ? (lane & 3) ^ ((row >> 2) & 3) : (lane & 1) ^ ((row >> 3) & 1)) * 16;
         }
         if constexpr (RING == 0) w_row[0] = row_of(l) + h * 16;
-        // (A tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only.  So are chunks and
+        // (A tap that two waves share is folded twice: fp32 results are cut at every third step of a tap only, where WHOLE_TAPS has code sums.  So are chunks and
         // taps whose last step is not whole, for the sake of the groups of steps.)
         struct Cut { int tap, step; };
         auto cut = [&](int of) {
@@ -562,7 +565,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
         }
         lds_barrier();
         // tables of the pixels: tap masks, scales under the taps, corrections
-        if constexpr (NS == 0 || KIND == kResPerTap) {   // a lane has one row of the window, four lanes a pixel
+        if constexpr (NS == 0 || KIND == kResPerTap || WHOLE_TAPS) {   // a lane has one row of the window, four lanes a pixel
             for (int j = tid; j < 4 * px_wg; j += nt) {
                 const int r = j & 3, i = j >> 2;   // (r == 3: nothing)
                 const uint32_t pix = p0 + i;
@@ -1101,13 +1104,14 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
 
 }  // namespace
 
-// One form's kernels by output type and the last two parameters (a file each, so that they compile in parallel).
-#define HQ_RESIDENT_FORM(NAME, KIND)                                                                            \
+// One form's kernels by output type and the last two parameters (a file each, so that they compile in parallel); F16, F32, I32: those
+// output types' rows, HQ_RESIDENT_FORM_OUT or HQ_RESIDENT_NONE.
+#define HQ_RESIDENT_FORM(NAME, KIND, F16, F32, I32)                                                             \
     const void *NAME(int out, int form) {                                                                       \
-        static const void *const kernels[3][7] = {                                                              \
-            HQ_RESIDENT_FORM_OUT(kOutF16, KIND), HQ_RESIDENT_FORM_OUT(kOutF32, KIND), HQ_RESIDENT_FORM_OUT(kOutI32, KIND)}; \
+        static const void *const kernels[3][7] = {F16(kOutF16, KIND), F32(kOutF32, KIND), I32(kOutI32, KIND)};  \
         return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][form];                                      \
     }
+#define HQ_RESIDENT_NONE(OUT, KIND) {}
 #define HQ_RESIDENT_FORM_OUT(OUT, KIND)                                                                         \
     {HQ_RESIDENT_FN(OUT, KIND, 0, 0), HQ_RESIDENT_FN(OUT, KIND, 0, 1), HQ_RESIDENT_FN(OUT, KIND, 0, 2), HQ_RESIDENT_FN(OUT, KIND, 0, 3), \
      HQ_RESIDENT_FN(OUT, KIND, 0, 4), HQ_RESIDENT_FN(OUT, KIND, 2, 0), HQ_RESIDENT_FN(OUT, KIND, 3, 0)}

@@ -368,3 +368,29 @@ def test_conv3x3_channels_no_multiple_of_64(hq, nb, h, w, cin, cout):
         assert np.array_equal(host(call(x4, None, w4, None, None, ksize=3, y_dtype=torch.int32)), acc_o)
         for ydt, tol in ((torch.float32, 1e-5), (torch.float16, 1e-3)):
             check_y("y", host(call(x4, scale, w4, dev(sw), dev(bias).to(ydt), ksize=3, y_dtype=ydt)), y_o, rtol=tol)
+
+
+@pytest.mark.parametrize("nb,h,w,cin,cout", [
+    (1, 1, 1, 8, 2), (2, 9, 8, 72, 40), (1, 12, 24, 184, 34), (3, 9, 16, 248, 72), (2, 16, 16, 328, 200), (2, 8, 8, 952, 96),
+    (1, 3, 88, 952, 40)])
+def test_conv3x3_channels_no_multiple_of_64_rounded_once(hq, nb, h, w, cin, cout):
+    """Per-pixel scales, fp16 and fp32 results: no further from the exact result than the sums of taps in integers, combined in fp32, are,
+    that is 32 roundings (a fold or two a tap, 7 sums of waves, the scales) of at most the sum of the terms' magnitudes, and one to the
+    type of the result.  Codes of one sign, and weights whose sum is zero over constant codes: the terms of half of the channels are
+    zero in half of the images' rows, and so is the result, whatever offset the weights carry on the way."""
+    rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
+    xq = rng.integers(0, 8, (nb, h, w, cin)).astype(np.int8)
+    xq[:, : (h + 1) // 2] = 7
+    wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
+    wq[::2] = np.tile([7, -7], cin // 2)
+    sx = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
+    sw = rng.uniform(0.1, 1.0, cout).astype(np.float32)
+    acc, _ = oracle.int_conv2d(xq, sx, wq, sw, None, stride=1, pad=1)
+    padded = np.pad(sx.astype(np.float64), ((0, 0), (1, 1), (1, 1)))
+    under = np.stack([padded[:, t // 3:t // 3 + h, t % 3:t % 3 + w] for t in range(9)], axis=-1)   # [nb, h, w, tap]
+    terms = acc * under[..., None] * sw.astype(np.float64)
+    want, limit = terms.sum(axis=3), 32 * 2.0 ** -24 * np.abs(terms).sum(axis=3)
+    x4, w4 = dev(pack_codes(xq)), dev(pack_codes(wq.reshape(cout, 9, cin)))
+    for dtype, half_ulp, least in ((torch.float32, 2.0 ** -24, 0.0), (torch.float16, 2.0 ** -11, 2.0 ** -25)):
+        y = host(hq.hq_int_conv2d(x4, dev(sx), w4, dev(sw), None, ksize=3, y_dtype=dtype)).astype(np.float64)
+        assert (np.abs(y - want) <= limit + half_ulp * np.abs(want) + least * (want != 0)).all()
