@@ -307,7 +307,6 @@ extern "C" const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in,
     if (r == 3 && s == 3 && stride == 2 && pad == 1) return c_in % 64 == 0 ? "tile (stride 2)" : "unsupported";
     if (r != s || (r != 1 && r != 3) || stride != 1 || pad != (r - 1) / 2) return "unsupported";
     if (c_in % 8 != 0 || (bits == 8 && c_in % 64 != 0)) return "unsupported";
-    if (c_in % 64 != 0) return "small-channel-count";
     if (r == 3) {   // (from here on as in int_conv2d)
         const int64_t pixels = static_cast<int64_t>(nb) * h * w;
         if (takes_wave_split(pixels, c_in, c_out, bits)) return "wave-split";
@@ -315,5 +314,5 @@ extern "C" const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in,
     }
     if (r == 1 && bits == 4)
         if (const char *cut = hq_linear_cut_name(static_cast<int64_t>(nb) * h * w, c_out, c_in)) return cut;
-    return "tile";
+    return c_in % 64 != 0 ? "small-channel-count" : "tile";
 }

@@ -61,8 +61,16 @@ def test_conv_kernel_choice_is_a_function_of_the_geometry(lib):
     assert name(1, 16, 16, 192, 100, bits=8).startswith("activation-resident")
     assert name(4, 8, 1500, 192, 192, bits=8) == "tile"
     assert name(16, 64, 64, 192, 192, ksize=1, bits=8) == "tile"
-    assert name(2, 32, 32, 8, 320) == "small-channel-count"
-    assert name(2, 32, 32, 200, 64, ksize=1) == "small-channel-count"
+    for static_scale in (False, True):   # channel counts that are no multiple of 64: the same kernels, and one for what they refuse
+        assert name(2, 32, 32, 8, 320, static_scale=static_scale) == "activation-resident (128 pixels, 4 waves)"
+        assert name(1, 4, 300, 200, 40, static_scale=static_scale) == "activation-resident (128 pixels, 8 waves)"
+        assert name(1, 3, 88, 952, 40, static_scale=static_scale) == "activation-resident (128 pixels, 8 waves, slices in turn)"
+        assert name(1, 2, 1500, 200, 40, static_scale=static_scale) == "small-channel-count"   # no activation tile holds such a row
+        assert name(2, 32, 32, 200, 64, ksize=1, static_scale=static_scale).startswith("linear (")
+        assert name(1, 3, 9, 40, 24, ksize=1, static_scale=static_scale) == "small-channel-count"   # less than 64 channels and 2^20 products
+        assert name(8, 64, 64, 40, 24, ksize=1, static_scale=static_scale).startswith("linear (")
+        assert name(1, 5, 8, 6136, 33, ksize=1, static_scale=static_scale).startswith("linear (")
+        assert name(1, 5, 8, 6392, 33, ksize=1, static_scale=static_scale) == "small-channel-count"   # no room for 32 pixels
     assert name(2, 32, 32, 12, 64) == "unsupported"
     assert name(2, 32, 32, 72, 64, bits=8) == "unsupported"
 

@@ -796,7 +796,8 @@ def test_channel_counts_that_are_not_multiples_of_64(hq, k):
         sxc = rng.uniform(0.01, 1.0, (nb, h, w)).astype(np.float32)
         swc = rng.uniform(0.001, 0.1, cout).astype(np.float32)
         bc = rng.standard_normal(cout).astype(np.float32)
-        assert hq.hq_int_conv2d_kernel_name(nb, h, w, k, cout, ksize=ks) == "small-channel-count"
+        kernel = hq.hq_int_conv2d_kernel_name(nb, h, w, k, cout, ksize=ks)
+        assert kernel.startswith("activation-resident (" if ks == 3 else "linear (" if k > 64 else "small-channel-count")
         xc_d, wc_d = dev(pack_codes(xc)), dev(pack_codes(wc.reshape(cout, ks * ks, k)))
         acc_o, y_o = oracle.int_conv2d(xc, sxc, wc, swc, bc, stride=1, pad=(ks - 1) // 2)
         acc_g = host(hq.hq_int_conv2d(xc_d, None, wc_d, None, None, ksize=ks, y_dtype=torch.int32))
