@@ -2,8 +2,8 @@
 // 64 (Method, "Matrix Multiplication": a layer with fewer input channels than the transform's
 // order keeps H = I, e.g. the convolution on a 4- or 8-channel latent; such layers are small).
 //
-// Only what the 6-bit kernels refuse comes here: linear layers of less than 64 channels and 2^20 products, tokens or image rows too
-// long for the LDS.
+// Only what the 6-bit kernels refuse comes here: linear layers of less than 64 channels and 2^20 products, or of which 32 tokens do
+// not fit the LDS (more than 6136 channels), and image rows too long for it.
 //
 // A workgroup of four waves owns a 64-pixel x 64-channel tile (one 32 x 32
 // MFMA tile per wave) and walks K in chunks of 32 codes: 128 threads fetch one row's chunk each
