@@ -305,17 +305,6 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
     // (pattern over e from c & 7) xor (one bit from c & (32 h + 8 q')).
     v8h hmat[4][2];
     hadamard64_operands(lane, hmat);
-    // the 16 sums of this lane for one block: 8 x the orthonormal transform
-    auto transform = [&](int blk, float (&v)[16]) {
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-            v4f acc = {0.f, 0.f, 0.f, 0.f};
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(hmat[ct][0], b[blk][0], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(hmat[ct][1], b[blk][1], acc, 0, 0, 0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[4 * ct + r] = acc[r];
-        }
-    };
     uint8_t *dst = BYTES ? xq + token * K + 16 * q : xq + token * (K / 2) + 8 * q;
 
     if constexpr (STATIC) {
@@ -324,7 +313,7 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
 #pragma unroll
         for (int blk = 0; blk < NBLK; ++blk) {
             float v[16];
-            transform(blk, v);
+            hadamard64_transform(hmat, b[blk], v);
             uint2 w;
             w.x = pack8_magic_clamped(v, inv, lo, hi);
             w.y = pack8_magic_clamped(v + 8, inv, lo, hi);
@@ -336,7 +325,7 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
 #pragma unroll
         for (int blk = 0; blk < NBLK; ++blk) {
             float (&vb)[16] = v[KEEP ? blk : 0];
-            transform(blk, vb);
+            hadamard64_transform(hmat, b[blk], vb);
 #pragma unroll
             for (int r = 0; r < 16; ++r) amax = fmaxf(amax, fabsf(vb[r]));
         }
@@ -347,7 +336,7 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
 #pragma unroll
         for (int blk = 0; blk < NBLK; ++blk) {
             float (&vb)[16] = v[KEEP ? blk : 0];
-            if constexpr (!KEEP) transform(blk, vb);
+            if constexpr (!KEEP) hadamard64_transform(hmat, b[blk], vb);
             if constexpr (BYTES) {
                 const uint4 w = bytes16_magic(vb, inv);
                 if (live) *reinterpret_cast<uint4 *>(dst + 64 * blk) = w;
@@ -364,9 +353,13 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
 // The same for tensors with too few tokens to fill the chip with one wave per 16 tokens: a
 // workgroup handles groups of 16 tokens, with one wave for every NB 64-channel blocks of the row.  The abs-max of a
 // token then needs every wave: they exchange their maxima through LDS (one barrier per group, two sets
-// of slots).  Workgroups are persistent and fetch the next group's pieces before they work on the current one.
-template <int MODE, int NB>
-__global__ __launch_bounds__(64 * kMaxBlocks) void hadamard64_quant_split_f16(const __half *__restrict__ x, int64_t m,
+// of slots).  Workgroups may take several groups, and fetch the next one's pieces before they work on the current one.
+// QUARTERS: the four lanes of a token read a quarter of the maxima each, for two exchanges more.  us without -> with, where a
+// workgroup has several groups: 12000 x 832 9.71 -> 9.50, 32000 x 448 9.29 -> 9.03; one group: 256 x 64 2.39 -> 2.67, 8192 x 512
+// 3.85 -> 4.11, 20000 x 320 5.07 -> 5.14; two blocks a wave 20000 x 896 10.6 -> 10.4; three (129 registers, so a wave less a SIMD)
+// 20000 x 960 11.5 -> 14.0.
+template <int MODE, int NB, bool QUARTERS>
+__global__ __launch_bounds__(64 * (kMaxBlocks / NB)) void hadamard64_quant_split_f16(const __half *__restrict__ x, int64_t m,
                                                                         int k, float qmax,
                                                                         uint8_t *__restrict__ xq,
                                                                         float *__restrict__ scale,
@@ -389,11 +382,13 @@ __global__ __launch_bounds__(64 * kMaxBlocks) void hadamard64_quant_split_f16(co
         }
     };
 
-    v8h b[NB][2], bn[NB][2];
+    // Two or three blocks a wave: the operands while the first pieces are on their way (16384 x 384 4.36 -> 4.22 us).  One: before that
+    // (10912 x 384 4.32 -> 4.22, 8192 x 128 2.91 -> 2.84; 256 x 256 2.73 -> 2.77, 8 bits 2.70 -> 2.77).
+    v8h b[NB][2], bn[NB][2], hmat[4][2];
+    if constexpr (NB == 1) hadamard64_operands(lane, hmat);
     int64_t grp = blockIdx.x;
     if (grp < groups) fetch(grp, b);
-    v8h hmat[4][2];
-    hadamard64_operands(lane, hmat);   // (while the first pieces are on their way)
+    if constexpr (NB > 1) hadamard64_operands(lane, hmat);
     int set = 0;
     for (; grp < groups; grp += gridDim.x, set ^= 1) {
         const int64_t next = grp + gridDim.x;
@@ -420,16 +415,21 @@ __global__ __launch_bounds__(64 * kMaxBlocks) void hadamard64_quant_split_f16(co
             if (waves > 1) {
                 if (q == 0) s_amax[set][wave][tok] = amax;
                 __syncthreads();
+                if constexpr (QUARTERS) {
 #pragma unroll
-                for (int w = 0; w < kMaxBlocks; w += 4)
-                    if (w < waves) amax = fmaxf(amax, s_amax[set][w + q < waves ? w + q : w][tok]);
-                amax = fmaxf(amax, __shfl_xor(amax, 16));
-                amax = fmaxf(amax, __shfl_xor(amax, 32));
+                    for (int w = 0; w < kMaxBlocks; w += 4)
+                        if (w < waves) amax = fmaxf(amax, s_amax[set][w + q < waves ? w + q : w][tok]);
+                    amax = fmaxf(amax, __shfl_xor(amax, 16));
+                    amax = fmaxf(amax, __shfl_xor(amax, 32));
+                } else {
+                    for (int w = 0; w < waves; ++w) amax = fmaxf(amax, s_amax[set][w][tok]);
+                }
             }
             inv = amax > 0.f ? qmax / amax : 0.f;
-            if (wave == 0 && q == 0 && token < m) scale[token] = amax > 0.f ? (amax * 0.125f) / qmax : 1.0f;
         }
         if (token < m) {
+            if constexpr (!STATIC)
+                if (wave == 0 && q == 0) scale[token] = amax > 0.f ? (amax * 0.125f) / qmax : 1.0f;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 const int64_t at = token * k + 64 * (NB * wave + i) + 16 * q;
@@ -455,15 +455,27 @@ template <int NB>
 hq_status launch_hadamard64_split(const __half *x, int64_t m, int k, float qmax, bool bytes, uint8_t *xq, float *scale,
                                   const float *given, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
-    const int waves = k / 64 / NB;
+    const int waves = k / 64 / NB, cus = hq::compute_units();
     const int64_t groups = (m + 15) / 16;
-    // resident workgroups: 32 waves per CU at the register use of this kernel
-    const int64_t cap = static_cast<int64_t>(hq::compute_units()) * (32 / waves);
-    const int64_t rounds = (groups + cap - 1) / cap;          // groups per workgroup
-    const int64_t grid = (groups + rounds - 1) / rounds;      // the same number for (almost) all of them
-    const auto kernel = given   ? hadamard64_quant_split_f16<kStatic, NB>
-                        : bytes ? hadamard64_quant_split_f16<kBytes, NB>
-                                : hadamard64_quant_split_f16<kNibbles, NB>;
+    int64_t rounds = 1;   // groups of a workgroup, the same number for (almost) all of them
+    if (NB == 1) {
+        // Registers hold 24 waves a CU.  Workgroups for 32 (where that is more, the last ones start as others end) lose to those for 24
+        // where 24 are a whole number of workgroups, and win where they are not: 12000 x 832 9.5 against 7.6 us, 20000 x 320 5.1 against 5.4.
+        const int64_t cap = static_cast<int64_t>(cus) * (32 / waves);
+        rounds = (groups + cap - 1) / cap;
+    } else if (waves >= 5 && groups > static_cast<int64_t>(cus) * (16 / waves)) {
+        // Registers hold 16 waves a CU, two or three workgroups of 5 to 8.  Two with several groups each if that keeps 9 of 10 busy, else a
+        // workgroup for every group.  us, two a CU against one for every group: 16384 x 640 6.8 / 7.9, 32000 x 960 15.6 / 17.1; uneven
+        // 12000 x 896 8.0 / 6.7, 20000 x 960 11.7 / 11.5.  Of fewer waves, more of which share a CU, the latter (32000 x 512 9.5 / 8.5).
+        const int64_t even = (groups + 2 * cus - 1) / (2 * cus);
+        if (10 * groups >= 9 * even * 2 * cus) rounds = even;
+    }
+    const int64_t grid = (groups + rounds - 1) / rounds;
+    auto kernel = bytes ? hadamard64_quant_split_f16<kBytes, NB, NB == 2> : hadamard64_quant_split_f16<kNibbles, NB, NB == 2>;
+    if constexpr (NB == 1) {
+        if (given) kernel = hadamard64_quant_split_f16<kStatic, 1, false>;
+        else if (rounds > 1) kernel = bytes ? hadamard64_quant_split_f16<kBytes, 1, true> : hadamard64_quant_split_f16<kNibbles, 1, true>;
+    }
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)), dim3(64 * waves), 0, stream, x, m, k, qmax, xq, scale, given);
     return check.status();
 }
@@ -483,15 +495,15 @@ hq_status launch_hadamard64(const __half *x, int64_t m, int k, int bits, bool by
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     const float qmax = static_cast<float>((1 << (bits - 1)) - 1);
     // one wave per 16 tokens needs about two waves per SIMD to hide the latency of its loads
-    if ((m + 15) / 16 < 8 * static_cast<int64_t>(hq::compute_units()))
-    {
+    if ((m + 15) / 16 < 8 * static_cast<int64_t>(hq::compute_units())) {
         // Blocks a wave: one, so that few tokens still make many waves; from 16 waves per CU on two or three, because starting more
-        // waves takes longer than what they overlap (a given scale has no barrier and gains nothing).  us, one -> two (three):
-        // 16384 x 384 6.4 -> 5.7, 8 bits 7.0 -> 6.3, 20000 x 960, 8 bits 17.9 -> (15.4); 8192 x 384 4.2 -> 4.2, 256 x 256 2.3 -> 2.4.
+        // waves takes longer than what they overlap (a given scale has no barrier and gains nothing).  us, one -> two -> three:
+        // 4 bits 12000 x 384 4.4 -> 3.8 -> 3.9, 16384 x 384 5.2 -> 4.2 -> 4.3, 16384 x 768 7.9 -> 8.0 -> 6.8, 32000 x 768 12.9 -> 13.3 -> 12.3,
+        // 20000 x 1024 15.3 -> 12.4, 20000 x 960 15.2 -> - -> 11.5; below the line 2048 x 256 2.8 -> 2.9 (but 6000 x 384 3.7 -> 3.3).
         const int nblk = k / 64;
         const bool fill = !given && (m + 15) / 16 * nblk > 16 * static_cast<int64_t>(hq::compute_units());
+        if (fill && nblk % 3 == 0 && nblk != 6) return launch_hadamard64_split<3>(x, m, k, qmax, bytes, xq, scale, given, stream);
         if (fill && nblk % 2 == 0) return launch_hadamard64_split<2>(x, m, k, qmax, bytes, xq, scale, given, stream);
-        if (fill && nblk % 3 == 0) return launch_hadamard64_split<3>(x, m, k, qmax, bytes, xq, scale, given, stream);
         return launch_hadamard64_split<1>(x, m, k, qmax, bytes, xq, scale, given, stream);
     }
     const int64_t wgs = ((m + 15) / 16 + 3) / 4;   // 16 tokens per wave, four waves per workgroup

@@ -12,8 +12,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,k", [
     (1, 64), (17, 128), (33, 1024), (40, 960),   # few tokens: a wave for every block of the row
-    (10913, 384), (10945, 384),                  # around 16 waves a CU: one block a wave, two
+    (10912, 384), (10945, 384),                  # around 16 waves a CU of 256: one block a wave, two
     (7265, 576), (7300, 576),                    # one, three
+    (12001, 832), (31993, 1024), (31993, 960),   # several groups a workgroup: one, two, three blocks a wave
+    (19993, 1024), (19993, 960),                 # (too uneven for that: one group)
     (32753, 64), (32770, 320),                   # around 8 groups of 16 tokens a CU: a wave for whole tokens, its last one ragged
 ])
 @pytest.mark.parametrize("bits,one_per_byte", [(8, True), (3, True), (4, False)])
@@ -26,7 +28,7 @@ def test_hadamard64_quant(m, k, bits, one_per_byte):
     x_d = torch.from_numpy(x).cuda()
     xq, sx = (hq.hq_act_hadamard_quant_i8 if one_per_byte and bits != 8 else hq.hq_act_hadamard_quant)(x_d, 64, bits)
     torch.cuda.synchronize()
-    rows = np.unique(np.concatenate([np.arange(min(m, 200)), np.arange(max(0, m - 200), m), [m // 2]]))   # (the oracle multiplies densely)
+    rows = np.unique(np.concatenate([np.arange(min(m, 200)), np.arange(max(0, m - 200), m), np.arange(m // 2, min(m, m // 2 + 200))]))   # (the oracle multiplies densely)
     codes = xq.cpu().numpy()[rows]
     codes_o, s_o, t = oracle.act_hadamard_quant(x[rows], 64, bits)
     check_codes("codes", codes if one_per_byte else unpack_codes(codes), codes_o, t, bits)
