@@ -15,8 +15,10 @@ MARSHAL = os.path.join(PKG, "_marshal.so")
 MARSHAL_SOURCE = os.path.join(CSRC, "marshal.cpp")
 SOURCES = ["hq_hadamard_quant.hip", "hq_int_gemm.hip", "hq_int_gemm_128x128.hip",
            "hq_int_gemm_64x128.hip", "hq_int_gemm_64x64.hip", "hq_conv3x3_wave.hip", "hq_conv3x3_fused.hip",
-           "hq_resident.hip", "hq_resident_pertap.hip", "hq_resident_wholetaps.hip", "hq_resident_sum.hip", "hq_resident_planes.hip",
-           "hq_resident_bytes.hip", "hq_linear_fp6.hip", "hq_linear_fused.hip", "hq_int_gemm_anyk.hip",
+           "hq_resident.hip", "hq_resident_pertap.hip", "hq_resident_wholetaps.hip",
+           "hq_resident_wholetaps_ragged.hip", "hq_resident_sum.hip", "hq_resident_sum_ragged.hip",
+           "hq_resident_planes.hip", "hq_resident_bytes.hip", "hq_linear_fp6.hip", "hq_linear_fused.hip",
+           "hq_int_gemm_anyk.hip",
            "hq_single_weights.hip", "hq_width_quant.hip"]
 HEADERS = ["hq_common.h", "hq_int_gemm_kernel.h", "hq_hadamard_mfma.h", "hq_conv3x3_res_kernel.h",
            "hq_resident_kernel.h", "hq_fp6.h", "hq_buffer.h"]

@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void rowquant_large(const T *__restrict__
 // xor 0x88888888, which yields the eight two's-complement nibbles.
 // kStatic: the scale is given (one for the tensor): no abs-max, clamp active, no scale output;
 // `given` points to it.  kBytes: one code a byte, 16 bytes a lane and block (codes of up to 8 bits; the low byte of the pattern of
-// fma(v, qmax / amax, 1.5 * 2^23) is the code itself).  16 x 32 x 32 x 384, 8 bits: 8.5 us as a butterfly.
+// fma(v, qmax / amax, 1.5 * 2^23) is the code itself).  16384 x 384, 8 bits, in a graph: 4.8 us, 7.1 as a butterfly.
 // NBLK: 64-channel blocks per row.  Four waves (token groups) per workgroup.
 enum Mode { kNibbles, kStatic, kBytes };
 template <int NBLK, int MODE>
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
 // QUARTERS: the four lanes of a token read a quarter of the maxima each, for two exchanges more.  us without -> with, where a
 // workgroup has several groups: 12000 x 832 9.71 -> 9.50, 32000 x 448 9.29 -> 9.03; one group: 256 x 64 2.39 -> 2.67, 8192 x 512
 // 3.85 -> 4.11, 20000 x 320 5.07 -> 5.14; two blocks a wave 20000 x 896 10.6 -> 10.4; three (129 registers, so a wave less a SIMD)
-// 20000 x 960 11.5 -> 14.0.
+// 20000 x 960 12.4 -> 14.0.
 template <int MODE, int NB, bool QUARTERS>
 __global__ __launch_bounds__(64 * (kMaxBlocks / NB)) void hadamard64_quant_split_f16(const __half *__restrict__ x, int64_t m,
                                                                         int k, float qmax,

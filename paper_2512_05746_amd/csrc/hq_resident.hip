@@ -5,10 +5,12 @@
 #include "hq_resident_kernel.h"
 
 const void *hq_resident_pertap(int out, int form);
-const void *hq_resident_wholetaps(int out, int form);
 const void *hq_resident_sum(int out, int form);
 const void *hq_resident_planes(int out, int form);
 const void *hq_resident_bytes(int out, int form);
+const void *hq_resident_wholetaps(int out, int form);
+const void *hq_resident_sum_ragged(int out, int form);
+const void *hq_resident_wholetaps_ragged(int out, int form);
 
 namespace {
 
@@ -206,13 +208,14 @@ hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype,
     }
     const int ns = steps % resident ? 0 : resident_unrolled(kind, out, resident);
     const int form = resident_form(p.ring, ns);
-    const void *fn = kind == kResBytes    ? hq_resident_bytes(out, form)
-                     : kind == kResPlanes ? hq_resident_planes(out, form)
-                     : kind == kResSum    ? hq_resident_sum(out, form)
-                     : whole_taps         ? hq_resident_wholetaps(out, form)
-                                          : hq_resident_pertap(out, form);
-    static std::atomic<uint64_t> allowed[5][3][7];
-    const hq_status st = allow_lds(fn, allowed[whole_taps ? kResWholeTaps : kind][out][form]);
+    using Form = const void *(int out, int form);
+    static Form *const forms[7] = {hq_resident_pertap,    hq_resident_sum,        hq_resident_planes,          hq_resident_bytes,
+                                   hq_resident_wholetaps, hq_resident_sum_ragged, hq_resident_wholetaps_ragged};   // (by kind first)
+    const bool ragged = g.k % 64 != 0;
+    const int of = whole_taps ? (ragged ? 6 : kResWholeTaps) : kind == kResSum && ragged ? 5 : kind;
+    const void *fn = forms[of](out, form);
+    static std::atomic<uint64_t> allowed[7][3][7];
+    const hq_status st = allow_lds(fn, allowed[of][out][form]);
     if (st != HQ_OK) return st;
     void *args[] = {&a};
     if (hipLaunchKernel(fn, dim3(static_cast<unsigned>(tiles)), dim3(64 * p.nw), args, p.lds, stream) != hipSuccess)

@@ -184,7 +184,10 @@ __device__ __forceinline__ int thread_again() {
 //     per-pixel scales  16 x 24 x 53 x 192 13.5 -> 12.7, 3 x 64 x 64 x 384 -> 96 (a slice at a time) 18.5 -> 16.5
 //     one scale         5 x 54 x 54 x 64 10.1 -> 7.9, 24 x 33 x 22 x 192 15.5 -> 12.4, 9 x 32 x 46 x 576 -> 264 (a slice at a time) 35.9 -> 28.0
 //     width axis        4 x 49 x 48 x 192, block 16 14.7 -> 12.4;   8 bits  12 x 23 x 17 x 384 -> 392 (a slice at a time) 20.2 -> 18.2
-template <int OUT, int KIND, int RING, int NS>
+// TAIL: channel counts that are no multiple of 64 too.  A form of its own, because the branches cost layers of whole steps 1 to 2 %, up to
+// 4 (2 x 24 x 40 x 640 14.8 -> 15.4 us, one scale 1 x 6 x 200 x 960 -> 40 23.8 -> 24.6), and a loop of its own in the same kernel costs the sums of
+// codes 2; not for the integer sums of taps, which their stores bound.
+template <int OUT, int KIND, int RING, int NS, bool TAIL>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
     constexpr bool WHOLE_TAPS = KIND == kResWholeTaps;   // (see the offset of the weights above)
     constexpr bool BYTES = KIND == kResBytes, FOLD = KIND == kResPerTap || WHOLE_TAPS || BYTES, INT_TAPS = OUT == kOutI32 && FOLD;
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
     uint32_t f_off = 0, f_row_bytes = 0, plane_bytes = 0;
     const uint8_t *x_codes = nullptr;
     uint32_t part8 = 0;
-    int tail = 0, tail_step = 0;   // packed dwords of the last step if it is not whole, and which it is
+    int tail = 0, tail_step = 0;   // TAIL: packed dwords of the last step if it is not whole, and which it is
     int in_planes = 0;
     int *f_sum = nullptr;     // code sums
     short *f_part = nullptr;
@@ -402,8 +405,7 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
             }
     };
     auto cut_tail = [&](v4i (&p)[IN][PIECES], const Item &item) {   // the rest are codes of zero
-        if constexpr (IN == 1) {
-            if (tail == 0) return;   // (one branch an item: 2 % less than at every step)
+        if constexpr (TAIL) {   // (if the last step is whole, the one after it, which is in no item)
 #pragma unroll
             for (int k = 0; k < PIECES; ++k)
                 if (item.step + k == tail_step) {
@@ -1104,18 +1106,21 @@ __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
 
 }  // namespace
 
-// One form's kernels by output type and the last two parameters (a file each, so that they compile in parallel); F16, F32, I32: those
-// output types' rows, HQ_RESIDENT_FORM_OUT or HQ_RESIDENT_NONE.
+// One form's kernels by output type and weights' way (a file each, so that they compile in parallel); F16, F32, I32: those
+// output types' rows, HQ_RESIDENT_WHOLE (of steps), HQ_RESIDENT_TAIL or HQ_RESIDENT_NONE.
 #define HQ_RESIDENT_FORM(NAME, KIND, F16, F32, I32)                                                             \
     const void *NAME(int out, int form) {                                                                       \
         static const void *const kernels[3][7] = {F16(kOutF16, KIND), F32(kOutF32, KIND), I32(kOutI32, KIND)};  \
         return kernels[out == kOutF16 ? 0 : out == kOutF32 ? 1 : 2][form];                                      \
     }
 #define HQ_RESIDENT_NONE(OUT, KIND) {}
-#define HQ_RESIDENT_FORM_OUT(OUT, KIND)                                                                         \
-    {HQ_RESIDENT_FN(OUT, KIND, 0, 0), HQ_RESIDENT_FN(OUT, KIND, 0, 1), HQ_RESIDENT_FN(OUT, KIND, 0, 2), HQ_RESIDENT_FN(OUT, KIND, 0, 3), \
-     HQ_RESIDENT_FN(OUT, KIND, 0, 4), HQ_RESIDENT_FN(OUT, KIND, 2, 0), HQ_RESIDENT_FN(OUT, KIND, 3, 0)}
-#define HQ_RESIDENT_FN(OUT, KIND, RING, NS)                                                                     \
-    reinterpret_cast<const void *>(resident_kernel<OUT, KIND, RING, resident_unrolled(KIND, OUT, NS)>)
+#define HQ_RESIDENT_WHOLE(OUT, KIND) HQ_RESIDENT_ROW(OUT, KIND, false)
+#define HQ_RESIDENT_TAIL(OUT, KIND) HQ_RESIDENT_ROW(OUT, KIND, true)
+#define HQ_RESIDENT_ROW(OUT, KIND, TAIL)                                                                        \
+    {HQ_RESIDENT_FN(OUT, KIND, 0, 0, TAIL), HQ_RESIDENT_FN(OUT, KIND, 0, 1, TAIL), HQ_RESIDENT_FN(OUT, KIND, 0, 2, TAIL), \
+     HQ_RESIDENT_FN(OUT, KIND, 0, 3, TAIL), HQ_RESIDENT_FN(OUT, KIND, 0, 4, TAIL), HQ_RESIDENT_FN(OUT, KIND, 2, 0, TAIL), \
+     HQ_RESIDENT_FN(OUT, KIND, 3, 0, TAIL)}
+#define HQ_RESIDENT_FN(OUT, KIND, RING, NS, TAIL)                                                               \
+    reinterpret_cast<const void *>(resident_kernel<OUT, KIND, RING, resident_unrolled(KIND, OUT, NS), TAIL>)
 // form: the steps of an unrolled tap (1 .. 4), else 0 without a ring or 3 more than its slots
 constexpr int resident_form(int ring, int ns) { return ns ? ns : ring ? ring + 3 : 0; }
