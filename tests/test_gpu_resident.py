@@ -349,10 +349,14 @@ def test_conv3x3_steps_of_a_tap(hq, nb, h, w, cin, cout):
     (2, 16, 16, 328, 200),       # six steps: shares begin within a tap
     (1, 33, 24, 456, 40), (2, 8, 8, 952, 96),  # eight and fifteen
     (1, 3, 88, 952, 40),         # some resident at a time
-    (1, 4, 300, 200, 40),        # rows too long: the kernel for few channels
+    (1, 4, 300, 200, 40),        # the tile takes nearly all of the LDS
+    (1, 2, 1500, 200, 40),       # rows too long: the kernel for few channels
 ])
 def test_conv3x3_channels_no_multiple_of_64(hq, nb, h, w, cin, cout):
     """As test_conv3x3_steps_of_a_tap.  Weights of -8 follow the end of every row, so that what a load finds there would show."""
+    for static_scale in (False, True):
+        kernel = hq.hq_int_conv2d_kernel_name(nb, h, w, cin, cout, static_scale=static_scale)
+        assert kernel == "small-channel-count" if w == 1500 else kernel.startswith("activation-resident (")
     rng = np.random.default_rng(nb * 1000 + h * 100 + w + cin + cout)
     xq = rng.integers(-8, 8, (nb, h, w, cin)).astype(np.int8)
     wq = rng.integers(-8, 8, (cout, 3, 3, cin)).astype(np.int8)
