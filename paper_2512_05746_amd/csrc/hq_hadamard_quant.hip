@@ -354,17 +354,16 @@ __global__ __launch_bounds__(256) void hadamard64_quant_f16(const __half *__rest
 // workgroup handles groups of 16 tokens, with one wave for every NB 64-channel blocks of the row.  The abs-max of a
 // token then needs every wave: they exchange their maxima through LDS (one barrier per group, two sets
 // of slots).  Workgroups may take several groups, and fetch the next one's pieces before they work on the current one.
-// QUARTERS: the four lanes of a token read a quarter of the maxima each, for two exchanges more.  us without -> with, where a
-// workgroup has several groups: 12000 x 832 9.71 -> 9.50, 32000 x 448 9.29 -> 9.03; one group: 256 x 64 2.39 -> 2.67, 8192 x 512
-// 3.85 -> 4.11, 20000 x 320 5.07 -> 5.14; two blocks a wave 20000 x 896 10.6 -> 10.4; three (129 registers, so a wave less a SIMD)
-// 20000 x 960 12.4 -> 14.0.
-template <int MODE, int NB, bool QUARTERS>
+// The four lanes of a token read a quarter of the other waves' maxima each, for two exchanges more: us, whole -> quarters, inputs from
+// HBM: 8192 x 384 4.37 -> 4.30, 20000 x 448 8.95 -> 8.66, 12000 x 832 11.8 -> 11.6; 4096 x 512 3.73 -> 3.79.  Not three blocks a wave, which
+// would hold 129 registers and so one wave less a SIMD (20000 x 960 14.2 -> 17.1).
+template <int MODE, int NB>
 __global__ __launch_bounds__(64 * (kMaxBlocks / NB)) void hadamard64_quant_split_f16(const __half *__restrict__ x, int64_t m,
                                                                         int k, float qmax,
                                                                         uint8_t *__restrict__ xq,
                                                                         float *__restrict__ scale,
                                                                         const float *__restrict__ given) {
-    constexpr bool STATIC = MODE == kStatic, BYTES = MODE == kBytes;
+    constexpr bool STATIC = MODE == kStatic, BYTES = MODE == kBytes, QUARTERS = NB < 3;
     __shared__ float s_amax[2][kMaxBlocks][16];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
@@ -382,13 +381,10 @@ __global__ __launch_bounds__(64 * (kMaxBlocks / NB)) void hadamard64_quant_split
         }
     };
 
-    // Two or three blocks a wave: the operands while the first pieces are on their way (16384 x 384 4.36 -> 4.22 us).  One: before that
-    // (10912 x 384 4.32 -> 4.22, 8192 x 128 2.91 -> 2.84; 256 x 256 2.73 -> 2.77, 8 bits 2.70 -> 2.77).
     v8h b[NB][2], bn[NB][2], hmat[4][2];
-    if constexpr (NB == 1) hadamard64_operands(lane, hmat);
     int64_t grp = blockIdx.x;
     if (grp < groups) fetch(grp, b);
-    if constexpr (NB > 1) hadamard64_operands(lane, hmat);
+    hadamard64_operands(lane, hmat);   // (while the first pieces are on their way)
     int set = 0;
     for (; grp < groups; grp += gridDim.x, set ^= 1) {
         const int64_t next = grp + gridDim.x;
@@ -426,10 +422,9 @@ __global__ __launch_bounds__(64 * (kMaxBlocks / NB)) void hadamard64_quant_split
                 }
             }
             inv = amax > 0.f ? qmax / amax : 0.f;
+            if (wave == 0 && q == 0 && token < m) scale[token] = amax > 0.f ? (amax * 0.125f) / qmax : 1.0f;
         }
         if (token < m) {
-            if constexpr (!STATIC)
-                if (wave == 0 && q == 0) scale[token] = amax > 0.f ? (amax * 0.125f) / qmax : 1.0f;
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 const int64_t at = token * k + 64 * (NB * wave + i) + 16 * q;
@@ -460,22 +455,20 @@ hq_status launch_hadamard64_split(const __half *x, int64_t m, int k, float qmax,
     int64_t rounds = 1;   // groups of a workgroup, the same number for (almost) all of them
     if (NB == 1) {
         // Registers hold 24 waves a CU.  Workgroups for 32 (where that is more, the last ones start as others end) lose to those for 24
-        // where 24 are a whole number of workgroups, and win where they are not: 12000 x 832 9.5 against 7.6 us, 20000 x 320 5.1 against 5.4.
+        // where 24 are a whole number of workgroups, and win where they are not: 12000 x 832 11.8 against 10.0 us, 20000 x 320 6.6 against 7.2.
         const int64_t cap = static_cast<int64_t>(cus) * (32 / waves);
         rounds = (groups + cap - 1) / cap;
     } else if (waves >= 5 && groups > static_cast<int64_t>(cus) * (16 / waves)) {
         // Registers hold 16 waves a CU, two or three workgroups of 5 to 8.  Two with several groups each if that keeps 9 of 10 busy, else a
-        // workgroup for every group.  us, two a CU against one for every group: 16384 x 640 6.8 / 7.9, 32000 x 960 15.6 / 17.1; uneven
-        // 12000 x 896 8.0 / 6.7, 20000 x 960 11.7 / 11.5.  Of fewer waves, more of which share a CU, the latter (32000 x 512 9.5 / 8.5).
+        // workgroup for every group.  us, two a CU against one for every group: 16384 x 640 9.1 / 10.1, 32000 x 960 19.7 / 20.8; uneven
+        // 12000 x 896 10.0 / 9.2, 20000 x 960 14.7 / 14.2.  Of fewer waves, more of which share a CU, the latter (32000 x 512 12.5 / 11.0).
         const int64_t even = (groups + 2 * cus - 1) / (2 * cus);
         if (10 * groups >= 9 * even * 2 * cus) rounds = even;
     }
     const int64_t grid = (groups + rounds - 1) / rounds;
-    auto kernel = bytes ? hadamard64_quant_split_f16<kBytes, NB, NB == 2> : hadamard64_quant_split_f16<kNibbles, NB, NB == 2>;
-    if constexpr (NB == 1) {
-        if (given) kernel = hadamard64_quant_split_f16<kStatic, 1, false>;
-        else if (rounds > 1) kernel = bytes ? hadamard64_quant_split_f16<kBytes, 1, true> : hadamard64_quant_split_f16<kNibbles, 1, true>;
-    }
+    auto kernel = bytes ? hadamard64_quant_split_f16<kBytes, NB> : hadamard64_quant_split_f16<kNibbles, NB>;
+    if constexpr (NB == 1)
+        if (given) kernel = hadamard64_quant_split_f16<kStatic, 1>;
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(grid)), dim3(64 * waves), 0, stream, x, m, k, qmax, xq, scale, given);
     return check.status();
 }
@@ -498,8 +491,8 @@ hq_status launch_hadamard64(const __half *x, int64_t m, int k, int bits, bool by
     if ((m + 15) / 16 < 8 * static_cast<int64_t>(hq::compute_units())) {
         // Blocks a wave: one, so that few tokens still make many waves; from 16 waves per CU on two or three, because starting more
         // waves takes longer than what they overlap (a given scale has no barrier and gains nothing).  us, one -> two -> three:
-        // 4 bits 12000 x 384 4.4 -> 3.8 -> 3.9, 16384 x 384 5.2 -> 4.2 -> 4.3, 16384 x 768 7.9 -> 8.0 -> 6.8, 32000 x 768 12.9 -> 13.3 -> 12.3,
-        // 20000 x 1024 15.3 -> 12.4, 20000 x 960 15.2 -> - -> 11.5; below the line 2048 x 256 2.8 -> 2.9 (but 6000 x 384 3.7 -> 3.3).
+        // 16384 x 384 6.5 -> 5.8 -> 5.9, 16384 x 768 10.7 -> 10.4 -> 9.6, 32000 x 768 17.8 -> 16.4 -> 16.0, 16384 x 1024 14.9 -> 12.6, 20000 x 960
+        // 18.1 -> - -> 14.2; about the line 12000 x 384 (18 waves) 5.0 -> 5.0 -> 5.1, 8192 x 384 (12) 4.3 -> 4.2 -> 4.3.  (Inputs from HBM, as all here.)
         const int nblk = k / 64;
         const bool fill = !given && (m + 15) / 16 * nblk > 16 * static_cast<int64_t>(hq::compute_units());
         if (fill && nblk % 3 == 0 && nblk != 6) return launch_hadamard64_split<3>(x, m, k, qmax, bytes, xq, scale, given, stream);
