@@ -593,8 +593,11 @@ hq_status act_hadamard_quant(const void *x, hq_dtype x_dtype, int64_t m, int k, 
                              bool bytes, uint8_t *xq, float *x_scale, const float *given, void *stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t *out = reinterpret_cast<uint32_t *>(xq);
+    // Bytes of few long rows stay with the butterfly, which has a row's maximum sooner.  us, 8 bits, matrix cores against it: 16 x 1024 3.2 / 2.3,
+    // 256 x 960 3.5 / 2.7, 1024 x 768 3.4 / 3.1; beyond the line 2048 x 768 3.9 / 3.9, 2048 x 384 2.9 / 3.1; 1024 x 256 2.6 / 2.6; 64 x 64 1.9 / 2.1.
     const bool byte_codes = bytes || a_bits == 8;
-    if (x_dtype == HQ_F16 && had_block == 64 && k <= 64 * kMaxBlocks && !(byte_codes && given))
+    const bool few = k >= 256 && 128 * m <= static_cast<int64_t>(hq::compute_units()) * k;
+    if (x_dtype == HQ_F16 && had_block == 64 && k <= 64 * kMaxBlocks && !(byte_codes && (given || few)))
         return launch_hadamard64(static_cast<const __half *>(x), m, k, a_bits, byte_codes, xq, x_scale, given, s);
     if (x_dtype == HQ_F16)
         return dispatch_block(static_cast<const __half *>(x), m, k, had_block, a_bits, bytes, out, x_scale, given, s);

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("m,k", [
     (1, 64), (17, 128), (33, 1024), (40, 960),   # few tokens: a wave for every block of the row
+    (512, 256), (513, 256), (1920, 960), (1921, 960),   # about the line below which bytes stay with the butterfly
     (10912, 384), (10945, 384),                  # around 16 waves a CU of 256: one block a wave, two
     (7265, 576), (7300, 576),                    # one, three
     (12001, 832), (31993, 1024), (31993, 960),   # several groups a workgroup: one, two, three blocks a wave
