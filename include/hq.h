@@ -199,11 +199,13 @@ hq_status hq_act_quant_int_linear(const void *x, hq_dtype x_dtype, const uint8_t
  *                       are estimated to be faster here
  *   "tile (stride 2)"
  *   "small-channel-count"   what of c_in that are no multiple of 64 the kernels above refuse: image rows too long for the activation
- *                       tile, 1x1 layers of less than 64 channels and 2^20 products, or of channels too many for the chip
+ *                       tile, 1x1 layers of less than 64 channels and 2^20 products, of channels too many for the chip, or of up to 8
+ *                       channels out at more than 16384 pixels
  *   "unsupported"
  * It depends on the geometry only, never on y_dtype, but that fp32 results with per-pixel scales need more room on chip: their
- * tile may be another one, and at the longest image rows that fit they run "tile".  (c_in no multiple of 64: the name is that of fp32
- * and fp16 results; integer sums need less room, and at such rows run on the activation tile where it says "small-channel-count".)
+ * tile may be another one, and at the longest image rows that fit they run "tile".  c_in no multiple of 64: the name is that of fp16
+ * results; integer sums of taps, and results of 32 bits where few channels are in and c_out is no multiple of 8, run
+ * "small-channel-count" where that is estimated to be faster.
  */
 const char *hq_int_conv2d_kernel_name(int nb, int h, int w, int c_in, int c_out, int r, int s,
                                       int stride, int pad, int static_scale, int bits);

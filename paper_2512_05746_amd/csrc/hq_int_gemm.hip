@@ -123,6 +123,18 @@ bool takes_wave_split(int64_t pixels, int c_in, int c_out, int bits) {
     return bits == 4 && c_in == 192 && ((pixels + 63) / 64) * ((c_out + 63) / 64) * 4 <= 5 * hq::compute_units();
 }
 
+// Layers of ragged channels that the kernel for few channels finishes sooner: results of 32 bits where groups of eight channels are not
+// whole, which the 6-bit kernels store one by one.  us, resident / few channels, 64 x 64 pixels: 8 -> 626 fp32 25 / 19, one int32 sum 23 / 17,
+// 24 -> 626 25 / 20 and 23 / 18, 40 -> 626 25 / 23 and 23 / 21, 72 -> 626 27 / 27 and 24 / 25, 8 -> 20 11.0 / 10.7; 8 x 8 pixels 8 -> 59 11.0 / 11.7.
+bool few_channels_conv3x3(int64_t pixels, int c_in, int c_out, hq_dtype y_dtype) {
+    return c_in % 64 != 0 && y_dtype != HQ_F16 && c_out % 8 != 0 && c_out >= 32 && pixels > 128 && c_in < (y_dtype == HQ_I32 ? 64 : 40);
+}
+// Linear layers, int32 sums: 30000 x 8 -> 627 94 / 60, 8000 x 120 -> 627 32 / 22, 2000 x 40 -> 201 6.4 / 5.7; for fewer results to a channel the
+// products count: 2000 x 200 -> 201 6.7 / 7.4, 500 x 120 -> 41 4.4 / 5.0.
+bool few_channels_linear(int64_t m, int k, int n, hq_dtype y_dtype) {
+    return k % 64 != 0 && y_dtype == HQ_I32 && n % 8 != 0 && k < 256 && m * n > static_cast<int64_t>(k) * 4340;
+}
+
 }  // namespace
 
 namespace {
@@ -136,7 +148,7 @@ hq_status int_linear(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
     if (!fits_32bit(m, 1, n, 1, bits == 8 ? 2 * k : k)) return HQ_ERR_UNSUPPORTED;
     GemmArgs a{xq, x_scale, wq, w_scale, bias, y, static_cast<uint32_t>(m), n, k, 1, 1, 0, 0, 0, 1, sx_static,
                1.0f, bits};
-    if (bits == 4) {
+    if (bits == 4 && !few_channels_linear(m, k, n, y_dtype)) {
         st = hq_linear_fp6_launch(a, 1, y_dtype, static_cast<hipStream_t>(stream));
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
@@ -190,12 +202,12 @@ hq_status int_conv2d(const uint8_t *xq, const float *x_scale, const uint8_t *wq,
         a.pixels = static_cast<uint32_t>(static_cast<int64_t>(nb) * a.h_out * a.w_out);
         return hq_gemm_launch_64x64(a, 9, y_dtype, st_);
     }
-    if (r == 3) {
+    if (r == 3 && !few_channels_conv3x3(pixels, c_in, c_out, y_dtype)) {
         if (takes_wave_split(pixels, c_in, c_out, bits)) return hq_conv3x3_wave_launch(a, y_dtype, st_);
         st = hq_resident_launch(a, 0, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }
-    if (r == 1 && bits == 4) {
+    if (r == 1 && bits == 4 && !few_channels_linear(pixels, c_in, c_out, y_dtype)) {
         st = hq_linear_fp6_launch(a, 1, y_dtype, st_);
         if (st != HQ_ERR_UNSUPPORTED) return st;
     }

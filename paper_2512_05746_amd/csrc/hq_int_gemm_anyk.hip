@@ -2,8 +2,9 @@
 // 64 (Method, "Matrix Multiplication": a layer with fewer input channels than the transform's
 // order keeps H = I, e.g. the convolution on a 4- or 8-channel latent; such layers are small).
 //
-// Only what the 6-bit kernels refuse comes here: linear layers of less than 64 channels and 2^20 products, or of which 32 tokens do
-// not fit the LDS (more than 6136 channels), and image rows too long for it.
+// Only what the 6-bit kernels do not take comes here: linear layers of less than 64 channels and 2^20 products, or of which 32 tokens do
+// not fit the LDS (more than 6136 channels), image rows too long for it, integer sums of taps, and layers of few channels bound by
+// results that those kernels store one by one (few_channels_conv3x3, few_channels_linear, choose_cut in hq_linear_fp6.hip).
 //
 // A workgroup of four waves owns a 64-pixel x 64-channel tile (one 32 x 32
 // MFMA tile per wave) and walks K in chunks of 32 codes: 128 threads fetch one row's chunk each

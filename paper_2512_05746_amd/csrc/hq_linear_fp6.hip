@@ -379,8 +379,9 @@ double cut_us(const Cut &c, int pixels, int n, int k, int planes, int cus) {
 // decide, which are 10 and 7 % off, so it has to be 8 % ahead for small layers and not 5 % behind for large ones (77907 x 1344 -> 64
 // 25.8 / 14.8, 23950 x 960 -> 544 26.7 / 19.9, 44867 x 768 -> 576 40.8 / 30.9; 2048 x 960 -> 3840 13.0 / 14.4, 57956 x 1344 -> 296 44.4 / 81.7).
 // K that are no multiple of 64 go to the kernel of hq_int_gemm_anyk.hip only below one step and 2^20 products (27 x 40 -> 24 4.0 / 4.5;
-// 2209 x 24 -> 88 6.1 / 4.2, 4096 x 200 -> 400 11.2 / 5.1, 8192 x 920 -> 1152 120 / 20; 200 random layers 0.66 of the time), and
-// where 32 tokens do not fit the LDS.
+// 2209 x 24 -> 88 6.1 / 4.2, 4096 x 200 -> 400 11.2 / 5.1, 8192 x 920 -> 1152 120 / 20; 200 random layers 0.66 of the time), for many tokens
+// and one group of eight channels out, of which the waves for the others have nothing to do (30000 x 40 -> 6 4.7 / 5.9, 30000 x 200 -> 6
+// 6.2 / 6.7; 8000 x 40 -> 6 4.6 / 4.8), and where 32 tokens do not fit the LDS.
 // For other K this kernel is up to 2.5 times faster (64 x 640 -> 640: 4.7 against 7.2 us, 8192 x 640 -> 640: 9.0 against 10.7,
 // 512 x 4096 -> 1024: 14 against 30), save for many rounds of tiles of 32 tokens (9535 x 4096 -> 1920: 188 against 107 of the tile
 // kernel; K of 4088 does not go there, 852 us on the kernel of hq_int_gemm_anyk.hip, so the rule is for multiples of 64 only: 213 here).
@@ -389,7 +390,7 @@ Cut choose_cut(int pixels, int n, int k, int planes) {
     if (n >= 1 << 21) return best;   // (a tile's results lie within 2 GiB of their first)
     const double products = static_cast<double>(pixels) * n * k * planes;
     const bool tile_k = k % 192 == 0;
-    if (k % 64 && k < 64 && products < 1 << 20) return best;
+    if (k % 64 && ((k < 64 && products < 1 << 20) || (n <= 8 && pixels > 16384 && k < 256))) return best;
     if (tile_k && (n < 32 || (n % 16 == 0 && products < 1.5e9) || !lay_out(k, 2, 8).ok)) return best;
     const int cus = hq::compute_units();   // (asks the runtime for the device: once)
     double best_us = HUGE_VAL;

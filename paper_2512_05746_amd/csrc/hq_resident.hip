@@ -168,13 +168,16 @@ const char *hq_resident_cut_name(int64_t pixels, int w, int k, int n, int bits, 
     return names[p.xw_log2][p.nw == 8][p.chunk < p.slices];
 }
 
-// HQ_ERR_UNSUPPORTED, with nothing launched: the layer is one for the tile kernel.
+// HQ_ERR_UNSUPPORTED, with nothing launched: the layer is one for the tile kernel, or for the one of few channels.
 hq_status hq_resident_launch(const GemmArgs &g, int had_block, hq_dtype y_dtype, hipStream_t stream) {
     const hq::LaunchCheck check;   // samples the thread's error state before anything is launched
     const int kind = had_block ? kResPlanes : kind_of(g.bits, g.sx_static);
     // fp16 results of ragged channels: as exact as those of the kernel for few channels, which takes the layers that do not fit.
     // us a call, kResPerTap -> kResWholeTaps: 2 x 32 x 32 x 200 9.2 -> 9.4, 4 x 32 x 32 x 328 12.9 -> 14.0, 2 x 24 x 24 x 952 17.9 -> 18.5.
     const bool whole_taps = kind == kResPerTap && (y_dtype == HQ_F32 || (y_dtype == HQ_F16 && g.k % 64));
+    // Integer sums of taps are added to an output that is cleared first.  Those of ragged channels have no form: us, with one / the kernel for
+    // few channels: 2 x 32 x 32 x 72 -> 320 254 / 32, 3 x 20 x 92 x 56 -> 33 111 / 17, 2 x 32 x 32 x 952 -> 320 399 / 162 (1 x 8 x 8 x 952 -> 64 39 / 123).
+    if (kind == kResPerTap && y_dtype == HQ_I32 && g.k % 64) return HQ_ERR_UNSUPPORTED;
     const Plan p = plan_of(kind, whole_taps, had_block, g.pixels, g.w, g.k, g.n);
     if (!p.ok) return HQ_ERR_UNSUPPORTED;
     ResidentArgs a{};

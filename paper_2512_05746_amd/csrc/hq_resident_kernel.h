@@ -186,7 +186,7 @@ __device__ __forceinline__ int thread_again() {
 //     width axis        4 x 49 x 48 x 192, block 16 14.7 -> 12.4;   8 bits  12 x 23 x 17 x 384 -> 392 (a slice at a time) 20.2 -> 18.2
 // TAIL: channel counts that are no multiple of 64 too.  A form of its own, because the branches cost layers of whole steps 1 to 2 %, up to
 // 4 (2 x 24 x 40 x 640 14.8 -> 15.4 us, one scale 1 x 6 x 200 x 960 -> 40 23.8 -> 24.6), and a loop of its own in the same kernel costs the sums of
-// codes 2; not for the integer sums of taps, which their stores bound.
+// codes 2.
 template <int OUT, int KIND, int RING, int NS, bool TAIL>
 __global__ __launch_bounds__(512, 2) void resident_kernel(ResidentArgs) {
     constexpr bool WHOLE_TAPS = KIND == kResWholeTaps;   // (see the offset of the weights above)

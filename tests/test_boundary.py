@@ -69,6 +69,8 @@ def test_conv_kernel_choice_is_a_function_of_the_geometry(lib):
         assert name(2, 32, 32, 200, 64, ksize=1, static_scale=static_scale).startswith("linear (")
         assert name(1, 3, 9, 40, 24, ksize=1, static_scale=static_scale) == "small-channel-count"   # less than 64 channels and 2^20 products
         assert name(8, 64, 64, 40, 24, ksize=1, static_scale=static_scale).startswith("linear (")
+        assert name(1, 128, 129, 40, 8, ksize=1, static_scale=static_scale) == "small-channel-count"   # one group of channels out
+        assert name(1, 128, 129, 40, 9, ksize=1, static_scale=static_scale).startswith("linear (")
         assert name(1, 5, 8, 6136, 33, ksize=1, static_scale=static_scale).startswith("linear (")
         assert name(1, 1, 9535, 4088, 1920, ksize=1, static_scale=static_scale).startswith("linear (32 tokens")   # many rounds
         assert name(1, 1, 9535, 4096, 1920, ksize=1, static_scale=static_scale) == "tile"   # (where the tile kernel is the faster one)

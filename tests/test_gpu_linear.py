@@ -132,6 +132,8 @@ def test_linear_single_of_large_token_scales(m, k, n, block):
     (1, 8, 1), (27, 40, 24),          # the kernel for few channels
     (1, 72, 1), (70, 120, 33),        # one packed dword in the last step, seven; loads that reach beyond the tensor
     (3000, 56, 440), (2100, 200, 96), (500, 952, 264), (9000, 328, 640),
+    (3000, 56, 441), (2000, 104, 627),   # (int32 sums: the kernel for few channels)
+    (20000, 40, 6), (16384, 40, 6),      # one group of channels out: that kernel, and not
     (2081, 4088, 1920),               # many rounds of tiles of 32 tokens
     (40, 6136, 33), (40, 6152, 33),   # the longest K of which 32 tokens fit the LDS; the kernel for few channels again
     (40, 6392, 33), (40, 8200, 33)])
@@ -140,7 +142,7 @@ def test_linear_k_no_multiple_of_64(m, k, n):
     import paper_2512_05746_amd as hq
 
     kernel = hq.hq_int_conv2d_kernel_name(1, 1, m, k, n, ksize=1)
-    assert kernel == "small-channel-count" if k > 6136 or (m, k) in ((1, 8), (27, 40)) else kernel.startswith("linear (")
+    assert kernel == "small-channel-count" if k > 6136 or (m, k) in ((1, 8), (27, 40), (20000, 40)) else kernel.startswith("linear (")
     g = torch.Generator(device="cuda")
     g.manual_seed(m + k + n)
     xq = torch.randint(0, 256, (m, k // 2), dtype=torch.uint8, device="cuda", generator=g)
