@@ -22,7 +22,7 @@
 // each, and 100 KiB of requests), expanding the tile (2 .. 4 us; 24 instructions per 16 codes for the signed form), exchange and
 // results (2 .. 5 us).
 //
-// Measured (3x3, 4-bit, us a call, weights in L2; kernel with weights in registers for every form -> this one):
+// Before the steps came in groups (3x3, 4-bit, us a call, weights in L2; weights in registers for every form -> through the ring):
 //     per-pixel scales: 8 x 16 x 16 x 960 23.4 -> 21.9, 3 x 45 x 27 x 320 -> 200 11.4 -> 10.8, 3 x 44 x 44 x 576 -> 152 13.3 -> 13.1
 //     one scale:       16 x 32 x 32 x 384 26.2 -> 25.1, 4 x 46 x 46 x 960 -> 488 63.4 -> 60.3
 //
@@ -39,16 +39,16 @@
 // 8-bit codes (the form of 16-byte operands on v_mfma_i32_32x32x32_i8, nothing to expand on either side; the two
 // 32-channel halves of a step take the places of two operand planes, each with weights of its own).  Matrix time is twice
 // that of 4-bit codes and bounds it: 42 clocks an MFMA of 32, at the 1.5 GHz that the chip holds under them.  us a call,
-// weights in registers and a fold of twice the instructions for every 192 channels -> this form: 16 x 32 x 32 x 384 40.3 -> 34.4,
-// 2 x 24 x 40 x 640 25.9 -> 20.1.
+// weights in registers and a fold of twice the instructions for every 192 channels -> this form, before the steps came in groups:
+// 16 x 32 x 32 x 384 40.3 -> 34.4, 2 x 24 x 40 x 640 25.9 -> 20.1.
 //
 // One scale: taps outside the image must add nothing.  Their products are multiplied by 2^-127 (the block exponent that the matrix
 // instruction takes for every column) instead of reading a row of zeros, which would cost every tile an address of its own
 // in every step; what they leave, below 1e-35, is rounded away before the sums are scaled.
 //
 // Channel counts that are no multiple of 64 (but of 8): the last step of a tap is filled up with activation codes of zero, whatever
-// the weights' loads find beyond the tap.  us a call, the kernel of hq_int_gemm_anyk.hip -> this one: 2 x 32 x 32 x 200 32.7 -> 9.2,
-// 4 x 32 x 32 x 328 58.9 -> 13.2; 150 random layers of 8 to 952 channels 0.43 of the time, none slower.
+// the weights' loads find beyond the tap.  us a call, the kernel of hq_int_gemm_anyk.hip -> this one: 2 x 32 x 32 x 200 31.7 -> 9.4,
+// 4 x 32 x 32 x 328 50.6 -> 14.0.  It keeps layers that it writes sooner (few_channels_conv3x3 in hq_int_gemm.hip) and the integer sums of taps.
 //
 // Which layers come here and which stay on the tile kernel: choose_kernel in hq_resident.hip.
 //
@@ -60,7 +60,7 @@
 // below the 2.07e-4 of rounding to fp16 (seen there: nothing in six digits, or 0.2 %).  fp32 results would lose digits, so there
 // the sums of a tap start at minus its correction (one fp16 matrix step per tap and tile): 6e-8, as with sums in integers.  So do
 // they for fp16 results of channel counts that are no multiple of 64: 0.02 % of these differ from the exact result rounded once, as
-// with sums in integers, against 0.3 % (8 to 952 channels).
+// with sums in integers, against 0.1 .. 0.4 % (8 to 952 channels).
 #pragma once
 #include <stddef.h>
 
